@@ -155,7 +155,7 @@ template <int M, int DMA>
 __device__ __forceinline__ void run_subtree(const Ctx &c, const View<uint32_t, 1, BT_THREADS> &v,
                                             const BatchLane<uint32_t, DMA> &st, uint32_t list,
                                             Sub<uint32_t> &u) {
-    level<uint32_t, M, false, 1, BT_THREADS, DMA>(c, v, st, list, 0u, u);
+    level<uint32_t, M, false, DMA>(c, v, st, list, 0u, u);
 }
 
 __device__ __forceinline__ unsigned long long wave_min(unsigned long long x) {
@@ -322,9 +322,9 @@ __global__ __launch_bounds__(BT_THREADS) void batch_wide_kernel(const tgo_task *
             Sub<TT> u;
             sub_init(u);
             switch (m) {
-                case 1: level<TT, 1, false, 1, BT_THREADS, DMA>(c, v, st, list, 0u, u); break;
-                case 2: level<TT, 2, false, 1, BT_THREADS, DMA>(c, v, st, list, 0u, u); break;
-                default: level<TT, 3, false, 1, BT_THREADS, DMA>(c, v, st, list, 0u, u); break;
+                case 1: level<TT, 1, false, DMA>(c, v, st, list, 0u, u); break;
+                case 2: level<TT, 2, false, DMA>(c, v, st, list, 0u, u); break;
+                default: level<TT, 3, false, DMA>(c, v, st, list, 0u, u); break;
             }
             const uint64_t r0 = (uint64_t)sb * fact_c(m);
             // the lane meets its subtrees in increasing rank: strict comparisons keep the lowest rank

@@ -53,10 +53,11 @@ struct Ctx {
 
 // Level with L positions left (position n - L is being chosen).  list holds
 // the remaining tasks in increasing order, one per nibble.  LaneT is the
-// simulation state (Lane: event form, CLane: chain form).
-template <typename TT, int L, bool STORE, int TS, int QS, int DMA, typename LaneT>
-__device__ __forceinline__ void level(const Ctx &c, const View<TT, TS, QS> &v, const LaneT &s,
-                                      uint32_t list, uint32_t l, Sub<TT> &u) {
+// simulation state (Lane: event form, CLane: chain form, or a lane under a
+// start rule) and ViewT its tables and queue.
+template <typename TT, int L, bool STORE, int DMA, typename LaneT, typename ViewT>
+__device__ __forceinline__ void level(const Ctx &c, const ViewT &v, const LaneT &s, uint32_t list, uint32_t l,
+                                      Sub<TT> &u) {
     const int j = c.n - L;
     auto child = [&](int ci) {
         const uint32_t x = (list >> (4 * ci)) & 15u;
@@ -68,7 +69,7 @@ __device__ __forceinline__ void level(const Ctx &c, const View<TT, TS, QS> &v, c
         } else {
             const uint32_t lo = list & ((1u << (4 * ci)) - 1u);
             const uint32_t hi = (list >> (4 * ci + 4)) << (4 * ci);
-            level<TT, L - 1, STORE, TS, QS, DMA>(c, v, s2, lo | hi, l2, u);
+            level<TT, L - 1, STORE, DMA>(c, v, s2, lo | hi, l2, u);
         }
     };
     // the three innermost levels are unrolled (each child's state is then
@@ -84,9 +85,8 @@ __device__ __forceinline__ void level(const Ctx &c, const View<TT, TS, QS> &v, c
 
 // Decode the prefix of subtree s (positions 0 .. n-M-1 of rank s*M!) and
 // simulate its windows.  Returns the remaining tasks, ascending, one per nibble.
-template <int DMA, typename LaneT, typename TT, int TS, int QS>
-__device__ __forceinline__ uint64_t prefix(LaneT &st, uint32_t s, int n, int m,
-                                           const View<TT, TS, QS> &v, const Rates &r) {
+template <int DMA, typename LaneT, typename ViewT>
+__device__ __forceinline__ uint64_t prefix(LaneT &st, uint32_t s, int n, int m, const ViewT &v, const Rates &r) {
     uint64_t list = 0;
     for (int i = n - 1; i >= 0; --i) list = (list << 4) | (uint64_t)i;
     lane_reset(st);
@@ -128,9 +128,9 @@ __constant__ constexpr Binom BINOM{};
 // their prefixes, which makes their DtH work alike.  Decodes s', simulates the
 // prefix windows and returns the remaining tasks (ascending, one per nibble);
 // *lex receives the subtree's lexicographic index (its first rank / m!).
-template <int DMA, typename LaneT, typename TT, int TS, int QS>
-__device__ __forceinline__ uint64_t prefix_by_set(LaneT &st, uint32_t sp, int n, int m,
-                                                  const View<TT, TS, QS> &v, const Rates &r, uint32_t *lex) {
+template <int DMA, typename LaneT, typename ViewT>
+__device__ __forceinline__ uint64_t prefix_by_set(LaneT &st, uint32_t sp, int n, int m, const ViewT &v,
+                                                  const Rates &r, uint32_t *lex) {
     lane_reset(st);
     const int plen = n - m;
     uint32_t pf = 1;  // plen! < 2^32: n!/m! = C(n, plen) * plen! fits 32 bits

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "../../include/tgo.h"
+#include "enum_dev.h"
 #include "model_dev.h"
 
 namespace tgo {
@@ -20,6 +21,34 @@ __device__ inline int classify_group(const tgo_task *t, int n, const Rates &r) {
         mx = qd > mx ? qd : mx;
         sum += (qh + r.p_h - 1) / r.p_h + (uint64_t)k + (qd + r.p_d - 1) / r.p_d;
     }
+    const uint64_t lim32 = 1ull << 31;
+    return (mx < lim32 && sum + time_bound_slack(n) < lim32) ? 0 : 1;
+}
+
+// The group's status as classify_group computes it, with one lane per task
+// (the per-task terms are combined by wave reductions; same result).
+__device__ inline int classify_group_wave(const tgo_task *t, int n, const Rates &r, int lane) {
+    const uint64_t q = 1ull << r.q_log2;
+    int bad = 0;
+    uint64_t mx = 0, sum = 0;
+    if (lane < n) {
+        const int64_t h = t[lane].htd_ns, k = t[lane].kern_ns, d = t[lane].dth_ns;
+        const int64_t lim = int64_t(1) << 40;
+        if (h < 0 || k < 0 || d < 0 || h >= lim || k >= lim || d >= lim) {
+            bad = 1;
+        } else {
+            const uint64_t qh = q * (uint64_t)h, qd = q * (uint64_t)d;
+            mx = qh > qd ? qh : qd;
+            sum = (qh + r.p_h - 1) / r.p_h + (uint64_t)k + (qd + r.p_d - 1) / r.p_d;
+        }
+    }
+    for (int m = 32; m >= 1; m >>= 1) {
+        bad |= __shfl_xor(bad, m);
+        const uint64_t mx2 = shfl_xor64(mx, m);
+        mx = mx2 > mx ? mx2 : mx;
+        sum += shfl_xor64(sum, m);
+    }
+    if (bad) return TGO_ERANGE;
     const uint64_t lim32 = 1ull << 31;
     return (mx < lim32 && sum + time_bound_slack(n) < lim32) ? 0 : 1;
 }

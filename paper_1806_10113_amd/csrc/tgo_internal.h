@@ -31,6 +31,10 @@ int make_rates(const tgo_model *m, Rates *r);
 // may overlap; calls on one stream are ordered by the stream.
 int workspace(size_t bytes, void **ptr, hipStream_t st);
 
+// Blocks of `threads` threads that fit on the device at once for a kernel and
+// its dynamic LDS.
+uint32_t resident_blocks(const void *kern, int threads, size_t shm);
+
 constexpr uint64_t factorial(int n) { return n <= 1 ? 1ull : (uint64_t)n * factorial(n - 1); }
 
 // Device-side validity of a task table: 0 (32-bit time path), 1 (64-bit path)
