@@ -17,30 +17,30 @@
 //     every DtH, on one queue), with the Section 4.2.1 overlap rates.
 // With every kernel holding the whole capacity this is the one-queue model.
 //
-// Kernel ends no longer follow one chain, so the window formulation of the
-// other paths does not apply; each lane steps the events of one ordering
-// (64-bit time): at each instant every finished command retires, then every
-// ready head starts and the kernel dispatcher takes what fits, until nothing
-// changes; time then advances to the earliest completion.
+// The enumeration and Algorithm 1 run the window formulation (rule_dev.h,
+// RULE_CONCURRENT): transfers do not feel how kernels are dispatched, and the
+// end of a kernel is fixed once its HtD has ended.  tgo_evaluate_cke steps the
+// events of each given ordering (64-bit time): at each instant every finished
+// command retires, then every ready head starts and the kernel dispatcher
+// takes what fits, until nothing changes; time then advances to the earliest
+// completion.
 #include <hip/hip_runtime.h>
 
-#include "enum_dev.h"
+#include "enum_kernel.h"
 #include "heur_dev.h"
+#include "rule_dev.h"
 #include "tables_dev.h"
 #include "tgo_internal.h"
 
 namespace tgo {
 
 constexpr int CK_THREADS = 256;
-constexpr uint32_t CK_MAX_BLOCKS = 8192;
 constexpr int32_t CK_MAX_CAPACITY = 1 << 30;
 
 struct CTab {
     int64_t h[MAXN], k[MAXN], d[MAXN];
     int32_t u[MAXN];
 };
-
-__device__ __forceinline__ uint32_t ck_nib(uint64_t v, int i) { return (uint32_t)(v >> (4 * i)) & 15u; }
 
 // Block-wide load of the task table; 0, TGO_ERANGE (a duration outside
 // [0, 2^40)) or TGO_EINVAL (a unit count outside 1..cap).
@@ -65,15 +65,10 @@ __device__ int ctab_load(const tgo_task *__restrict__ tasks, const int32_t *__re
     return (f & 1) ? TGO_ERANGE : (f & 2) ? TGO_EINVAL : 0;
 }
 
-struct CkeOut {
-    int64_t T;           // end of the last command
-    int64_t th, tk, td;  // ends of the last position's HtD, K and DtH
-};
-
-// One ordering (seq: task at position j in nibble j, n positions).  kend:
+// T of one ordering (seq: task at position j in nibble j, n positions).  kend:
 // this lane's kernel end times by position (stride kst).
 template <bool ONE>
-__device__ CkeOut cke_sim(uint64_t seq, int n, const CTab &tb, int cap, const Rates &r, int64_t *kend, int kst) {
+__device__ int64_t cke_sim(uint64_t seq, int n, const CTab &tb, int cap, const Rates &r, int64_t *kend, int kst) {
     const int64_t q = int64_t(1) << r.q_log2;
     int64_t t = 0;
     int hc = 0, dc = 0, xo = 0;  // next queue entry: HtD, DtH (two engines); transfer queue (one)
@@ -82,7 +77,6 @@ __device__ CkeOut cke_sim(uint64_t seq, int n, const CTab &tb, int cap, const Ra
     int64_t uh = 0, ud = 0;
     int kc = 0, held = 0;
     uint32_t krun = 0, kdone = 0;
-    CkeOut o = {0, 0, 0, 0};
     for (;;) {
         bool changed = true;
         while (changed) {
@@ -90,12 +84,10 @@ __device__ CkeOut cke_sim(uint64_t seq, int n, const CTab &tb, int cap, const Ra
             if (hrun && uh == 0) {
                 hrun = false;
                 ++hdone;
-                if (hpos == n - 1) o.th = t;
                 changed = true;
             }
             if (drun && ud == 0) {
                 drun = false;
-                if (dpos == n - 1) o.td = t;
                 changed = true;
             }
             for (uint32_t m = krun; m; m &= m - 1) {
@@ -103,21 +95,20 @@ __device__ CkeOut cke_sim(uint64_t seq, int n, const CTab &tb, int cap, const Ra
                 if (kend[p * kst] == t) {
                     krun &= ~(1u << p);
                     kdone |= 1u << p;
-                    held -= tb.u[ck_nib(seq, p)];
-                    if (p == n - 1) o.tk = t;
+                    held -= tb.u[nibble(seq, p)];
                     changed = true;
                 }
             }
             if constexpr (!ONE) {
                 if (!hrun && hc < n) {
                     hpos = hc++;
-                    uh = q * tb.h[ck_nib(seq, hpos)];
+                    uh = q * tb.h[nibble(seq, hpos)];
                     hrun = true;
                     changed = true;
                 }
                 if (!drun && dc < n && ((kdone >> dc) & 1u)) {
                     dpos = dc++;
-                    ud = q * tb.d[ck_nib(seq, dpos)];
+                    ud = q * tb.d[nibble(seq, dpos)];
                     drun = true;
                     changed = true;
                 }
@@ -125,21 +116,21 @@ __device__ CkeOut cke_sim(uint64_t seq, int n, const CTab &tb, int cap, const Ra
                 if (!hrun && !drun) {
                     if (xo < n) {
                         hpos = xo++;
-                        uh = q * tb.h[ck_nib(seq, hpos)];
+                        uh = q * tb.h[nibble(seq, hpos)];
                         hrun = true;
                         changed = true;
                     } else if (xo < 2 * n && ((kdone >> (xo - n)) & 1u)) {
                         dpos = xo - n;
                         ++xo;
-                        ud = q * tb.d[ck_nib(seq, dpos)];
+                        ud = q * tb.d[nibble(seq, dpos)];
                         drun = true;
                         changed = true;
                     }
                 }
             }
             // in-order dispatch of the kernels whose HtD has ended and that fit
-            while (kc < n && kc < hdone && held + tb.u[ck_nib(seq, kc)] <= cap) {
-                const uint32_t x = ck_nib(seq, kc);
+            while (kc < n && kc < hdone && held + tb.u[nibble(seq, kc)] <= cap) {
+                const uint32_t x = nibble(seq, kc);
                 kend[kc * kst] = t + tb.k[x];
                 krun |= 1u << kc;
                 held += tb.u[x];
@@ -163,80 +154,154 @@ __device__ CkeOut cke_sim(uint64_t seq, int n, const CTab &tb, int cap, const Ra
         if (drun) ud = ed == dt ? 0 : ud - rd * dt;
         t += dt;
     }
-    o.T = t;
-    return o;
+    return t;
 }
 
-// rank (lexicographic) -> task at each position, one per nibble
-__device__ __forceinline__ uint64_t ck_unrank(int n, uint64_t rk) {
-    uint64_t list = 0;
-    for (int i = n - 1; i >= 0; --i) list = (list << 4) | (uint64_t)i;
-    uint64_t f = fact_c(n - 1), seq = 0;
-    for (int i = 0; i < n; ++i) {
-        const uint64_t c = f ? rk / f : 0;
-        rk -= c * f;
-        if (n - 1 - i > 0) f /= (uint64_t)(n - 1 - i);
-        seq |= ((list >> (4 * c)) & 15u) << (4 * i);
-        const uint64_t lo = list & ((1ull << (4 * c)) - 1ull);
-        const uint64_t hi = (list >> (4 * c + 4)) << (4 * c);
-        list = lo | hi;
+// Concurrent kernels under the enumeration kernel (enum_kernel.h).  Bound by
+// VALU issue over divergent window loops, like the plain enumeration, plus the
+// scan of running kernels where a kernel does not fit at once.  As a lane per
+// ordering stepping all of its events in 64-bit time, n = 12 took 123.5 ms
+// (479M orderings); with shared prefixes, windows and 32-bit time 4.6 ms.
+struct CkeRule {
+    struct Args {
+        const int32_t *units;
+        int32_t cap;
+    };
+    template <typename TT>
+    using View = RView<TT, 1, EX_THREADS, RULE_CONCURRENT>;
+    template <typename TT, int DMA>
+    using Lane = RLane<TT, RULE_CONCURRENT>;
+    // 6 waves per SIMD (80 VGPRs; some saved walk state spills): 4.15 / 4.22 /
+    // 4.49 ms on three n = 12 groups, against 4.32 / 4.53 / 4.77 at 5 waves,
+    // 4.24 / 4.12 / 4.43 at 7 and 4.89 / 4.87 / 5.09 at 8
+    template <typename TT, int DMA>
+    static constexpr int min_waves() { return sizeof(TT) == 4 ? 6 : 1; }
+    static constexpr bool queue(bool) { return true; }
+    static __host__ __device__ constexpr size_t lds_bytes(int) { return sizeof(int32_t) * MAXN; }
+    template <typename ViewT>
+    static __device__ __forceinline__ void load(ViewT &v, unsigned char *lds, const Args &a, int n, uint64_t *seq) {
+        int32_t *u = reinterpret_cast<int32_t *>(lds);
+        if ((int)threadIdx.x < n) u[threadIdx.x] = a.units[threadIdx.x];
+        v.units = u;
+        v.cap = a.cap;
+        v.seq = seq;
     }
-    return seq;
+};
+
+// Time path of the group (as classify_group), or TGO_ERANGE / TGO_EINVAL (a
+// unit count outside 1..cap); clears the accumulator.
+__device__ __forceinline__ int cke_status_wave(const tgo_task *tasks, const int32_t *units, int n, int cap,
+                                               const Rates &r, int lane) {
+    const int m = classify_group_wave(tasks, n, r, lane);
+    const int32_t u = lane < n ? units[lane] : 1;
+    const bool bad = __any(u < 1 || u > cap);
+    return m < 0 ? m : bad ? TGO_EINVAL : m;
+}
+__global__ __launch_bounds__(64) void cke_prepare_kernel(const tgo_task *__restrict__ tasks,
+                                                         const int32_t *__restrict__ units, int n, int cap, Rates r,
+                                                         int *mode, ExAcc *acc) {
+    const int m = cke_status_wave(tasks, units, n, cap, r, threadIdx.x);
+    if (threadIdx.x == 0) {
+        *mode = m;
+        exacc_init(acc);
+    }
 }
 
-template <bool ONE, bool STORE>
-__global__ __launch_bounds__(CK_THREADS) void cke_enum_kernel(const tgo_task *__restrict__ tasks,
-                                                             const int32_t *__restrict__ units, int n, int cap,
-                                                             Rates r, uint32_t count, int64_t *out,
-                                                             Partial *partials) {
-    __shared__ CTab tb;
-    __shared__ int flag;
-    __shared__ int64_t kq[MAXN * CK_THREADS];
-    const int st = ctab_load(tasks, units, n, cap, tb, &flag);
-    if (st != 0) {
+// Block 0 writes the enumeration's part of the summary, the first wave of
+// block 1 Algorithm 1 (Section 5.1) with `update` simulating the ordered set
+// under the same rule.
+template <int DMA>
+__global__ __launch_bounds__(EX_FIN_THREADS) void cke_finalize_kernel(
+    const Partial *__restrict__ parts, int nparts, int n, uint64_t count, const ExAcc *__restrict__ acc,
+    const int *__restrict__ modep, const tgo_task *__restrict__ tasks, const int32_t *__restrict__ units, int cap,
+    Rates r, tgo_summary *out) {
+    using TT = uint64_t;
+    const int mode = *modep;
+    if (blockIdx.x == 0) {
+        finalize_block(parts, nparts, n, count, acc, mode, out);
+        return;
+    }
+    if (threadIdx.x >= 64) return;
+    if (mode < 0) {
         if (threadIdx.x == 0) {
-            Partial p = {};
-            p.status = st;
-            partials[blockIdx.x] = p;
+            put_order(out->heur, 0, 0);
+            out->heur_ns = mode;
         }
         return;
     }
-    Partial p;
-    p.min_t = ~0ull; p.min_r = ~0ull; p.max_t = 0; p.max_r = ~0ull;
-    p.sum_lo = 0; p.sum_hi = 0; p.fp = 0; p.status = 0; p.pad = 0;
-    const uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t rk = blockIdx.x * blockDim.x + threadIdx.x; rk < count; rk += stride) {
-        const uint64_t T = (uint64_t)cke_sim<ONE>(ck_unrank(n, rk), n, tb, cap, r, kq + threadIdx.x, CK_THREADS).T;
-        if constexpr (STORE) out[rk] = (int64_t)T;
-        if (T < p.min_t) { p.min_t = T; p.min_r = rk; }
-        if (T + 1 > p.max_t) { p.max_t = T + 1; p.max_r = rk; }
-        add128(p.sum_lo, p.sum_hi, T, 0);
-        p.fp += (2ull * rk + 1ull) * T;
+    __shared__ Quad<TT> Ht[MAXN];
+    __shared__ DRec<TT> Dt[MAXN];
+    __shared__ Slot<TT> Qs[MAXN];
+    __shared__ int32_t us[MAXN];
+    if ((int)threadIdx.x < n) {
+        table_entry<TT>(tasks[threadIdx.x], r, &Ht[threadIdx.x], &Dt[threadIdx.x]);
+        us[threadIdx.x] = units[threadIdx.x];
     }
-    for (int m = 32; m >= 1; m >>= 1) {
-        const uint64_t mt = shfl_xor64(p.min_t, m), mr = shfl_xor64(p.min_r, m);
-        const uint64_t xt = shfl_xor64(p.max_t, m), xr = shfl_xor64(p.max_r, m);
-        const uint64_t sl = shfl_xor64(p.sum_lo, m), sh = shfl_xor64(p.sum_hi, m);
-        const uint64_t f = shfl_xor64(p.fp, m);
-        merge_min(p.min_t, p.min_r, mt, mr);
-        merge_max(p.max_t, p.max_r, xt, xr);
-        add128(p.sum_lo, p.sum_hi, sl, sh);
-        p.fp += f;
-    }
-    __shared__ Partial wsum[CK_THREADS / 64];
-    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x / 64] = p;
-    __syncthreads();
+    wave_lds_sync();
+    uint64_t seq = 0;
+    RView<TT, 1, 1, RULE_CONCURRENT> v;
+    v.H = Ht;
+    v.D = Dt;
+    v.Q = Qs;
+    v.units = us;
+    v.cap = cap;
+    v.seq = &seq;
+    using LaneT = RLane<TT, RULE_CONCURRENT>;
+    uint64_t ord;
+    const int64_t T = heuristic_wave<DMA, LaneT>(
+        n, v, r,
+        [&r](const LaneT &s) {
+            Fit3 u;
+            u.th = (int64_t)s.t;
+            u.tk = (int64_t)s.ke;
+            u.td = (int64_t)tail<DMA>(s, r);
+            return u;
+        },
+        &ord);
     if (threadIdx.x == 0) {
-        Partial o = wsum[0];
-        for (int i = 1; i < CK_THREADS / 64; ++i) {
-            merge_min(o.min_t, o.min_r, wsum[i].min_t, wsum[i].min_r);
-            merge_max(o.max_t, o.max_r, wsum[i].max_t, wsum[i].max_r);
-            add128(o.sum_lo, o.sum_hi, wsum[i].sum_lo, wsum[i].sum_hi);
-            o.fp += wsum[i].fp;
-        }
-        o.status = 0;
-        o.pad = 0;
-        partials[blockIdx.x] = o;
+        put_order(out->heur, ord, n);
+        out->heur_ns = T;
+    }
+}
+
+template <int M, bool STORE, int DMA>
+static int launch_cke(hipStream_t st, const tgo_task *t, const int32_t *units, int n, int cap, const Rates &r,
+                      int64_t *out, tgo_summary *d_out) {
+    const void *k32 = reinterpret_cast<const void *>(&enum_kernel<CkeRule, uint32_t, M, STORE, DMA>);
+    const uint32_t n_sub = (uint32_t)(factorial(n) / factorial(M));
+    uint32_t blocks = 0;
+    EnumScratch sc;
+    int rc = enum_grid(k32, enum_shm_bytes<CkeRule, uint32_t>(n, DMA == DMA_ONE), n_sub, 0, ExScratch{}, st, &blocks,
+                       &sc);
+    if (rc) return rc;
+    hipLaunchKernelGGL(cke_prepare_kernel, dim3(1), dim3(64), 0, st, t, units, n, cap, r, sc.mode, sc.acc);
+    rc = enum_launch<CkeRule, M, STORE, DMA>(st, t, n, r, CkeRule::Args{units, cap}, n_sub, out, blocks, sc);
+    if (rc) return rc;
+    hipLaunchKernelGGL(cke_finalize_kernel<DMA>, dim3(2), dim3(EX_FIN_THREADS), 0, st, sc.parts, (int)blocks, n,
+                       factorial(n), sc.acc, sc.mode, t, units, cap, r, d_out);
+    TGO_HIP(hipGetLastError());
+    return TGO_OK;
+}
+
+// Positions walked depth first per lane (TGO_CKE_M, 1..5, overrides it): at
+// n = 12, 14.9 / 7.6 / 4.9 / 4.1 ms with 2 / 3 / 4 / 5.
+static int choose_cke_m(int n) {
+    if (const char *e = std::getenv("TGO_CKE_M")) {
+        const int m = std::atoi(e);
+        if (m >= 1 && m <= 5 && m <= n) return m;
+    }
+    return rule_depth(n, 5);
+}
+
+template <bool STORE, int DMA>
+static int launch_cke_m(hipStream_t st, const tgo_task *t, const int32_t *units, int n, int cap, const Rates &r,
+                        int64_t *out, tgo_summary *d_out) {
+    switch (choose_cke_m(n)) {
+        case 1: return launch_cke<1, STORE, DMA>(st, t, units, n, cap, r, out, d_out);
+        case 2: return launch_cke<2, STORE, DMA>(st, t, units, n, cap, r, out, d_out);
+        case 3: return launch_cke<3, STORE, DMA>(st, t, units, n, cap, r, out, d_out);
+        case 4: return launch_cke<4, STORE, DMA>(st, t, units, n, cap, r, out, d_out);
+        default: return launch_cke<5, STORE, DMA>(st, t, units, n, cap, r, out, d_out);
     }
 }
 
@@ -267,75 +332,7 @@ __global__ __launch_bounds__(CK_THREADS) void cke_evaluate_kernel(const tgo_task
         out[i] = TGO_EINVAL;
         return;
     }
-    out[i] = cke_sim<ONE>(seq, n, tb, cap, r, kq + threadIdx.x, CK_THREADS).T;
-}
-
-// Algorithm 1 (Section 5.1) with `update` simulating the ordered set under
-// the same rule; one thread.  Writes heur / heur_ns of the summary.
-template <bool ONE>
-__global__ __launch_bounds__(64) void cke_heuristic_kernel(const tgo_task *__restrict__ tasks,
-                                                           const int32_t *__restrict__ units, int n, int cap,
-                                                           Rates r, tgo_summary *out) {
-    __shared__ CTab tb;
-    __shared__ int flag;
-    __shared__ int64_t kq[MAXN];
-    const int st = ctab_load(tasks, units, n, cap, tb, &flag);
-    if (threadIdx.x != 0) return;
-    if (st != 0) {
-        out->heur_ns = st;
-        return;
-    }
-    auto update = [&](uint64_t seq, int len) {
-        const CkeOut o = cke_sim<ONE>(seq, len, tb, cap, r, kq, 1);
-        Fit3 u;
-        u.th = o.th;
-        u.tk = o.tk;
-        u.td = o.td;
-        return u;
-    };
-    uint64_t seq = 0;
-    uint32_t rt = (1u << n) - 1u;
-    int first = 0;
-    for (int x = 1; x < n; ++x) {
-        const int64_t kh = tb.k[x] - tb.h[x], bkh = tb.k[first] - tb.h[first];
-        if (kh > bkh || (kh == bkh && tb.d[x] > tb.d[first])) first = x;
-    }
-    seq = (uint64_t)first;
-    rt &= ~(1u << first);
-    int pos = 1;
-    while (__popc(rt) > 2) {
-        const Fit3 u = update(seq, pos);
-        int best = -1;
-        int64_t bf = 0;
-        for (int c = 0; c < n; ++c) {
-            if (!((rt >> c) & 1u)) continue;
-            const int64_t f = fit(tb.h[c], tb.k[c], u);
-            if (best < 0 || f < bf) { best = c; bf = f; }
-        }
-        seq |= (uint64_t)best << (4 * pos);
-        ++pos;
-        rt &= ~(1u << best);
-    }
-    if (__popc(rt) == 2) {
-        const int a = __ffs(rt) - 1, b = 31 - __clz(rt);
-        const Fit3 u = update(seq, pos);
-        int bx = -1, by = -1;
-        int64_t bs = 0, bdy = 0;
-        for (int o = 0; o < 2; ++o) {
-            const int x = o == 0 ? a : b, y = o == 0 ? b : a;
-            const int64_t s1 = fit(tb.h[x], tb.k[x], u);
-            const Fit3 w = update(seq | ((uint64_t)x << (4 * pos)), pos + 1);
-            const int64_t sc = s1 + fit(tb.h[y], tb.k[y], w) + tb.d[y];
-            if (bx < 0 || sc < bs || (sc == bs && tb.d[y] < bdy)) { bx = x; by = y; bs = sc; bdy = tb.d[y]; }
-        }
-        seq |= ((uint64_t)bx << (4 * pos)) | ((uint64_t)by << (4 * (pos + 1)));
-        pos += 2;
-    } else if (__popc(rt) == 1) {
-        seq |= (uint64_t)(__ffs(rt) - 1) << (4 * pos);
-        ++pos;
-    }
-    for (int j = 0; j < 16; ++j) out->heur[j] = j < n ? (uint8_t)ck_nib(seq, j) : (uint8_t)0xff;
-    out->heur_ns = cke_sim<ONE>(seq, n, tb, cap, r, kq, 1).T;
+    out[i] = cke_sim<ONE>(seq, n, tb, cap, r, kq + threadIdx.x, CK_THREADS);
 }
 
 static int check_cke(const tgo_model *model, Rates *r, int n, int max_n, int32_t cap) {
@@ -359,40 +356,11 @@ int tgo_exhaustive_cke(const tgo_model *model, const tgo_task *d_tasks, const in
     if (rc) return rc;
     if (!d_tasks || !d_units || !d_summary) return fail(TGO_EINVAL, "NULL buffer");
     hipStream_t st = (hipStream_t)stream;
-    const uint64_t count = factorial(n);
-    const uint64_t want = (count + CK_THREADS - 1) / CK_THREADS;
-    const uint32_t blocks = (uint32_t)(want < CK_MAX_BLOCKS ? want : CK_MAX_BLOCKS);
-    Partial *parts = nullptr;
-    rc = workspace(sizeof(Partial) * blocks, (void **)&parts, st);
-    if (rc) return rc;
-    const uint32_t c32 = (uint32_t)count;
-    const bool one = r.one_dma != 0;
-    if (one) {
-        if (d_per_order)
-            hipLaunchKernelGGL((cke_enum_kernel<true, true>), dim3(blocks), dim3(CK_THREADS), 0, st, d_tasks, d_units,
-                               n, capacity, r, c32, d_per_order, parts);
-        else
-            hipLaunchKernelGGL((cke_enum_kernel<true, false>), dim3(blocks), dim3(CK_THREADS), 0, st, d_tasks,
-                               d_units, n, capacity, r, c32, nullptr, parts);
-    } else {
-        if (d_per_order)
-            hipLaunchKernelGGL((cke_enum_kernel<false, true>), dim3(blocks), dim3(CK_THREADS), 0, st, d_tasks,
-                               d_units, n, capacity, r, c32, d_per_order, parts);
-        else
-            hipLaunchKernelGGL((cke_enum_kernel<false, false>), dim3(blocks), dim3(CK_THREADS), 0, st, d_tasks,
-                               d_units, n, capacity, r, c32, nullptr, parts);
-    }
-    TGO_HIP(hipGetLastError());
-    rc = launch_summary_finalize(parts, (int)blocks, n, 1, count, count, d_summary, st);
-    if (rc) return rc;
-    if (one)
-        hipLaunchKernelGGL(cke_heuristic_kernel<true>, dim3(1), dim3(64), 0, st, d_tasks, d_units, n, capacity, r,
-                           d_summary);
-    else
-        hipLaunchKernelGGL(cke_heuristic_kernel<false>, dim3(1), dim3(64), 0, st, d_tasks, d_units, n, capacity, r,
-                           d_summary);
-    TGO_HIP(hipGetLastError());
-    return TGO_OK;
+    if (r.one_dma)
+        return d_per_order ? launch_cke_m<true, DMA_ONE>(st, d_tasks, d_units, n, capacity, r, d_per_order, d_summary)
+                           : launch_cke_m<false, DMA_ONE>(st, d_tasks, d_units, n, capacity, r, nullptr, d_summary);
+    return d_per_order ? launch_cke_m<true, DMA_TWO>(st, d_tasks, d_units, n, capacity, r, d_per_order, d_summary)
+                       : launch_cke_m<false, DMA_TWO>(st, d_tasks, d_units, n, capacity, r, nullptr, d_summary);
 }
 
 int tgo_evaluate_cke(const tgo_model *model, const tgo_task *d_tasks, const int32_t *d_units, int n,
