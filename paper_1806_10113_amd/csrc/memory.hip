@@ -2,52 +2,32 @@
 // simulators are described in mem_dev.h): every ordering, T of given
 // orderings, and Algorithm 1 with its update step under the limit.
 //
-// Enumeration.  Lexicographic ranks put the orderings that share their first
-// n - M positions in one block of M! consecutive ranks.  One lane owns such a
-// block: it places the prefix once, then walks the last M positions depth
-// first in ascending task order (which is rank order), keeping the state
-// after each placed position and extending a copy of it for every choice of
-// the next one.  With two DMA engines a placed position's state is the
-// instant its HtD ends, so only the events after that instant are stepped
-// again per extension; with one DMA engine the state is the chain's running
-// ends and the open sub-group.  Work per ordering is then mostly the last
-// position's events instead of all 3n of them.
-//
-// The 32-bit instantiation runs when every instant and work amount of the
-// group fits 31 bits (the same bound as the single-group enumeration); the
-// 64-bit twin runs otherwise; each block of the other one returns at once.
+// The enumeration and Algorithm 1 run the window formulation: with two DMA
+// engines a window whose HtD may have to wait for the DtHs that free its
+// memory (rule_dev.h, RULE_MEMORY), with one the closed-form chain of
+// sub-groups.  Whether a set of tasks fits together does not depend on times,
+// so it is looked up in a table of 2^n bits made once per call.
+// tgo_evaluate_mem steps the events of each given ordering (mem_dev.h).
 #include <hip/hip_runtime.h>
 
 #include <cstdlib>
 #include <type_traits>
 
-#include "enum_dev.h"
+#include "enum_kernel.h"
 #include "heur_dev.h"
 #include "mem_dev.h"
+#include "rule_dev.h"
 #include "tables_dev.h"
 #include "tgo_internal.h"
 
 namespace tgo {
 
-constexpr int MEM_THREADS = 256;
-// Blocks per launch at most: about 8 rounds of the resident blocks with two
-// engines (2,048 at 8 waves per SIMD), where subtrees vary most in cost
-// (n = 12: 16,384 blocks 10.4 / 14.9 / 16.2 ms at capacity 100 / 60 / 40 %
-// against 10.7 / 15.6 / 16.9 ms with 8,192); with one engine 8,192 (16,384
-// was 4-6 % slower, 4,096 the same).
-constexpr int MEM_MAX_BLOCKS_TWO = 16384;
-constexpr int MEM_MAX_BLOCKS_ONE = 8192;
+constexpr int MEM_THREADS = 256;  // tgo_evaluate_mem
 
-__constant__ uint32_t MEM_FACT[13] = {1u,      1u,       2u,        6u,         24u,        120u,     720u,
-                                      5040u,   40320u,   362880u,   3628800u,   39916800u,  479001600u};
-
-// Task tables of the block (n <= 16 threads fill them).  Returns the block's
-// status: 0 (this instantiation runs), 1 (the other width runs), or a
-// negative TGO_E* code.
-template <typename TT>
+// Task tables of the block (n <= 16 threads fill them), 64-bit time.  Returns
+// the block's status: 0 or a negative TGO_E* code.
 __device__ __forceinline__ int mem_tables(const tgo_task *__restrict__ tasks, const int64_t *__restrict__ mem,
-                                          int n, uint64_t cap, const Rates &r, MemTab<TT> &tb, int *flag) {
-    constexpr int MODE = sizeof(TT) == 4 ? 0 : 1;
+                                          int n, uint64_t cap, const Rates &r, MemTab<uint64_t> &tb, int *flag) {
     if (threadIdx.x == 0) *flag = classify_group(tasks, n, r);
     __syncthreads();
     if ((int)threadIdx.x < n) {
@@ -55,244 +35,208 @@ __device__ __forceinline__ int mem_tables(const tgo_task *__restrict__ tasks, co
         const int64_t m = mem[threadIdx.x];
         if (m < 0 || (uint64_t)m > cap) atomicMin(flag, (int)TGO_EINVAL);
         const uint64_t q = 1ull << r.q_log2;
-        tb.h[threadIdx.x] = (TT)t.htd_ns;
-        tb.k[threadIdx.x] = (TT)t.kern_ns;
-        tb.d[threadIdx.x] = (TT)t.dth_ns;
-        tb.qh[threadIdx.x] = (TT)(q * (uint64_t)t.htd_ns);
-        tb.qd[threadIdx.x] = (TT)(q * (uint64_t)t.dth_ns);
+        tb.h[threadIdx.x] = (uint64_t)t.htd_ns;
+        tb.k[threadIdx.x] = (uint64_t)t.kern_ns;
+        tb.d[threadIdx.x] = (uint64_t)t.dth_ns;
+        tb.qh[threadIdx.x] = q * (uint64_t)t.htd_ns;
+        tb.qd[threadIdx.x] = q * (uint64_t)t.dth_ns;
         tb.m[threadIdx.x] = (uint64_t)m;
     }
     __syncthreads();
     const int f = *flag;
-    return f < 0 ? f : (f == MODE ? 0 : 1);
+    return f < 0 ? f : 0;
 }
 
+// One DMA engine: the closed-form chain of sub-groups (mem_dev.h, Chain) with
+// the open sub-group's buffers as a set of tasks.
 template <typename TT>
-__device__ __forceinline__ void mem_push(GSim<TT> &s, uint32_t x, const MemTab<TT> &tb, uint64_t cap,
-                                         const Rates &r, const KQ<TT> &kq) {
-    gsim_push(s, x, tb, cap, r, kq);
-}
-template <typename TT>
-__device__ __forceinline__ void mem_push(Chain<TT> &c, uint32_t x, const MemTab<TT> &tb, uint64_t cap,
-                                         const Rates &, const KQ<TT> &) {
-    chain_push(c, x, tb, cap);
-}
-template <typename TT>
-__device__ __forceinline__ TT mem_finish(GSim<TT> &s, const MemTab<TT> &tb, const Rates &r, const KQ<TT> &kq) {
-    return gsim_finish(s, tb, r, kq);
-}
-template <typename TT>
-__device__ __forceinline__ TT mem_finish(Chain<TT> &c, const MemTab<TT> &tb, const Rates &, const KQ<TT> &) {
-    return chain_finish(c, tb);
-}
-
-// Per-lane reduction over the lane's ranks, visited in increasing order.
-struct MAcc {
-    uint64_t min_t, min_r, max_t1, max_r, sum_lo, sum_hi, fp, rank;
+struct MChain {
+    using ST = typename Signed<TT>::type;
+    TT x;          // end of the open sub-group's last HtD (none open: of the last DtH)
+    TT kp;         // end of the last kernel
+    ST emax;       // open sub-group: max of (K_p end - its DtH time before p)
+    TT dsum;       // open sub-group: its DtH time so far
+    uint32_t set;  // open sub-group: its tasks
 };
-
-template <bool STORE>
-__device__ __forceinline__ void mem_leaf(MAcc &a, uint64_t T, int64_t *out) {
-    const uint64_t rk = a.rank++;
-    if constexpr (STORE) out[rk] = (int64_t)T;
-    if (T < a.min_t) { a.min_t = T; a.min_r = rk; }
-    if (T + 1 > a.max_t1) { a.max_t1 = T + 1; a.max_r = rk; }
-    add128(a.sum_lo, a.sum_hi, T, 0);
-    a.fp += (2 * rk + 1) * T;
+template <typename TT>
+__device__ __forceinline__ void lane_reset(MChain<TT> &s) {
+    using ST = typename Signed<TT>::type;
+    s.x = s.kp = s.dsum = 0;
+    s.emax = (ST)(((TT)1) << (8 * sizeof(TT) - 1));  // most negative
+    s.set = 0;
+}
+template <int DMA, typename TT>
+__device__ __forceinline__ TT tail(const MChain<TT> &s, const Rates &) {
+    using ST = typename Signed<TT>::type;
+    const ST e = (ST)s.x > s.emax ? (ST)s.x : s.emax;
+    return (TT)(e + (ST)s.dsum);
+}
+template <int DMA, bool PUT = true, typename TT, typename ViewT>
+__device__ __forceinline__ void window(MChain<TT> &s, int, uint32_t x, const ViewT &v, const Rates &r) {
+    using ST = typename Signed<TT>::type;
+    const Quad<TT> tx = v.task(x);
+    uint32_t set = s.set | (1u << x);
+    // x alone fits, so the first task of a sub-group never closes one
+    const bool close = !((v.fits[set >> 5] >> (set & 31u)) & 1u);
+    s.x = (close ? tail<DMA>(s, r) : s.x) + tx.h;
+    s.set = close ? 1u << x : set;
+    s.kp = tmax(s.x, s.kp) + tx.k;
+    const TT before = close ? TT(0) : s.dsum;
+    const ST e = (ST)s.kp - (ST)before;
+    s.emax = close ? e : (e > s.emax ? e : s.emax);
+    s.dsum = before + tx.d;
 }
 
-// Depth-first walk of the last D positions over the tasks in `rem`
-// (ascending task index = lexicographic rank order).
-template <int D, bool STORE, typename S, typename TT>
-__device__ __forceinline__ void mem_dfs(const S &s, uint32_t rem, const MemTab<TT> &tb, uint64_t cap,
-                                        const Rates &r, const KQ<TT> &kq, MAcc &a, int64_t *out) {
-    uint32_t m = rem;
-    for (int i = 0; i < D; ++i) {
-        const uint32_t x = (uint32_t)(__ffs(m) - 1);
-        m &= m - 1;
-        S c = s;
-        mem_push(c, x, tb, cap, r, kq);
-        if constexpr (D == 1) {
-            mem_leaf<STORE>(a, (uint64_t)mem_finish(c, tb, r, kq), out);
-        } else {
-            mem_dfs<D - 1, STORE>(c, rem & ~(1u << x), tb, cap, r, kq, a, out);
+// The device-memory limit under the enumeration kernel (enum_kernel.h).  Bound
+// by VALU issue over divergent window loops.  Two engines, n = 12, capacity
+// 40 %: 18.9 ms when every transfer event was stepped (footprints summed in
+// 64 bits at each), 4.2 ms with windows and the set table; one engine 1.2 -> 1.0 ms.
+struct MemRule {
+    struct Args {
+        const uint32_t *fits;  // bit s: the tasks of set s fit together
+    };
+    template <typename TT>
+    using View = RView<TT, 1, EX_THREADS, RULE_MEMORY>;
+    template <typename TT, int DMA>
+    using Lane = std::conditional_t<DMA == DMA_TWO, RLane<TT, RULE_MEMORY>, MChain<TT>>;
+    // 5 waves per SIMD (96 VGPRs): two engines, n = 12, capacity 40 %, three
+    // groups: 3.93 / 4.02 / 4.39 ms against 4.18 / 4.17 / 4.52 at 7 waves and
+    // 4.70 / 4.77 / 5.09 at 8; one engine 1.01 / 0.96 / 0.94 ms at 5 and 7.
+    // (At 6 waves hipcc's spilling of the five-level walk gave wrong times:
+    // the n = 11 test against the oracle caught it.)
+    template <typename TT, int DMA>
+    static constexpr int min_waves() { return sizeof(TT) == 4 ? 5 : 1; }
+    static constexpr bool queue(bool one_dma) { return !one_dma; }
+    static __host__ __device__ constexpr int words(int n) { return n <= 5 ? 4 : 1 << (n - 5); }
+    static __host__ __device__ constexpr size_t lds_bytes(int n) { return sizeof(uint32_t) * words(n); }
+    template <typename ViewT>
+    static __device__ __forceinline__ void load(ViewT &v, unsigned char *lds, const Args &a, int n, uint64_t *seq) {
+        uint32_t *f = reinterpret_cast<uint32_t *>(lds);
+        if ((int)threadIdx.x < words(n)) f[threadIdx.x] = a.fits[threadIdx.x];
+        v.fits = f;
+        v.seq = seq;
+    }
+};
+static_assert(MemRule::words(TGO_MAX_MEM_N) <= EX_THREADS, "one word of the set table per thread");
+
+// Time path of the group (as classify_group) or TGO_EINVAL (a footprint
+// outside [0, cap]); clears the accumulator and fills the set table (a set
+// fits if its footprints sum to at most cap; cap <= 2^62, so a partial sum
+// that still fits plus one footprint cannot overflow).
+constexpr int MEM_PREP_THREADS = 1024;
+__global__ __launch_bounds__(MEM_PREP_THREADS) void mem_prepare_kernel(const tgo_task *__restrict__ tasks,
+                                                                       const int64_t *__restrict__ mem, int n,
+                                                                       uint64_t cap, Rates r, int *mode, ExAcc *acc,
+                                                                       uint32_t *fits) {
+    __shared__ uint64_t ms[MAXN];
+    const int lane = threadIdx.x & 63;
+    if (threadIdx.x < 64) {
+        const int c = classify_group_wave(tasks, n, r, lane);
+        const int64_t m = lane < n ? mem[lane] : 0;
+        const bool bad = __any(m < 0 || (uint64_t)m > cap);
+        if (lane == 0) {
+            *mode = c < 0 ? c : bad ? TGO_EINVAL : c;
+            exacc_init(acc);
         }
+        // a footprint that fits nowhere is an error (above); the sums stay defined
+        if (lane < n) ms[lane] = (m < 0 || (uint64_t)m > cap) ? cap : (uint64_t)m;
+    }
+    __syncthreads();
+    const uint32_t sets = 32u * (uint32_t)MemRule::words(n);
+    for (uint32_t s = threadIdx.x; s < sets; s += MEM_PREP_THREADS) {
+        uint64_t sum = 0;
+        bool ok = true;
+        for (int i = 0; i < n; ++i)
+            if ((s >> i) & 1u) {
+                sum += ok ? ms[i] : 0;
+                ok = ok && sum <= cap;
+            }
+        const unsigned long long b = __ballot(ok);
+        if ((lane & 31) == 0) fits[s >> 5] = (uint32_t)(b >> (lane & 32));
     }
 }
 
-// 32-bit time path: VGPRs capped for 8 waves per SIMD with two DMA engines
-// (64 VGPRs; the per-lane queue is 12 KB per block, so 8 blocks fit per CU)
-// and 6 with one.  The compiler spills some saved walk state to scratch,
-// which the extra waves more than pay for: at n = 12, capacity 100 / 60 /
-// 40 / 25 % of the footprint, 12.4 / 18.2 / 19.9 / 19.9 ms uncapped (90
-// VGPRs, 5 waves), 11.1 / 16.0 / 17.4 / 17.5 ms at 7 waves, 10.8 / 15.6 /
-// 16.9 / 16.9 ms at 8; one engine 1.20-1.24 -> 1.16-1.22 ms.
-template <typename TT, bool ONE>
-constexpr int mem_min_waves() { return sizeof(TT) == 4 ? (ONE ? 6 : 8) : 1; }
-
-template <typename TT, bool ONE, bool STORE, int M>
-__global__ __launch_bounds__(MEM_THREADS) __attribute__((amdgpu_waves_per_eu(mem_min_waves<TT, ONE>()))) void mem_enum_kernel(const tgo_task *__restrict__ tasks,
-                                                               const int64_t *__restrict__ mem, int n,
-                                                               uint64_t cap, Rates r, uint32_t n_sub,
-                                                               int64_t *out, Partial *partials) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ MemTab<TT> tb;
-    __shared__ int flag;
-    const int st = mem_tables<TT>(tasks, mem, n, cap, r, tb, &flag);
-    if (st < 0) {
-        if (sizeof(TT) == 4 && threadIdx.x == 0) {
-            Partial p = {};
-            p.status = st;
-            partials[blockIdx.x] = p;
+// Block 0 writes the enumeration's part of the summary, the first wave of
+// block 1 Algorithm 1 with `update` simulating the ordered set under the limit.
+template <int DMA>
+__global__ __launch_bounds__(EX_FIN_THREADS) void mem_finalize_kernel(
+    const Partial *__restrict__ parts, int nparts, int n, uint64_t count, const ExAcc *__restrict__ acc,
+    const int *__restrict__ modep, const tgo_task *__restrict__ tasks, const uint32_t *__restrict__ fits, Rates r,
+    tgo_summary *out) {
+    using TT = uint64_t;
+    const int mode = *modep;
+    if (blockIdx.x == 0) {
+        finalize_block(parts, nparts, n, count, acc, mode, out);
+        return;
+    }
+    if (threadIdx.x >= 64) return;
+    if (mode < 0) {
+        if (threadIdx.x == 0) {
+            put_order(out->heur, 0, 0);
+            out->heur_ns = mode;
         }
         return;
     }
-    if (st != 0) return;
-    using S = typename std::conditional<ONE, Chain<TT>, GSim<TT>>::type;
-    // two engines: the lane's kernel-end queue, n slots (none with one engine)
-    const KQ<TT> kq{reinterpret_cast<TT *>(smem) + threadIdx.x, MEM_THREADS};
-    MAcc a;
-    a.min_t = ~0ull; a.min_r = ~0ull; a.max_t1 = 0; a.max_r = ~0ull;
-    a.sum_lo = 0; a.sum_hi = 0; a.fp = 0; a.rank = 0;
-    const uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t sub = blockIdx.x * blockDim.x + threadIdx.x; sub < n_sub; sub += stride) {
-        S s;
-        if constexpr (ONE) chain_init(s);
-        else gsim_init(s);
-        // prefix: position i takes digit c of the factorial base (radix n - i)
-        uint64_t list = 0;
-        for (int i = n - 1; i >= 0; --i) list = (list << 4) | (uint64_t)i;
-        uint32_t rest = sub;
-        for (int i = 0; i < n - M; ++i) {
-            const uint32_t block = MEM_FACT[n - 1 - i] / MEM_FACT[M];
-            const uint32_t c = rest / block;
-            rest -= c * block;
-            const uint32_t x = (uint32_t)(list >> (4 * c)) & 15u;
-            const uint64_t lo = list & ((1ull << (4 * c)) - 1ull);
-            list = lo | ((list >> (4 * c + 4)) << (4 * c));
-            mem_push(s, x, tb, cap, r, kq);
-        }
-        uint32_t remset = 0;
-        for (int i = 0; i < M; ++i) remset |= 1u << ((list >> (4 * i)) & 15u);
-        a.rank = (uint64_t)sub * MEM_FACT[M];
-        mem_dfs<M, STORE>(s, remset, tb, cap, r, kq, a, out);
+    __shared__ Quad<TT> Ht[MAXN];
+    __shared__ DRec<TT> Dt[MAXN];
+    __shared__ Slot<TT> Qs[MAXN];
+    if ((int)threadIdx.x < n) table_entry<TT>(tasks[threadIdx.x], r, &Ht[threadIdx.x], &Dt[threadIdx.x]);
+    wave_lds_sync();
+    uint64_t seq = 0;
+    RView<TT, 1, 1, RULE_MEMORY> v;
+    v.H = Ht;
+    v.D = Dt;
+    v.Q = Qs;
+    v.fits = fits;
+    v.seq = &seq;
+    uint64_t ord;
+    int64_t T;
+    if constexpr (DMA == DMA_TWO) {
+        using LaneT = RLane<TT, RULE_MEMORY>;
+        T = heuristic_wave<DMA, LaneT>(
+            n, v, r,
+            [&r](const LaneT &s) {
+                Fit3 u;
+                u.th = (int64_t)s.t;
+                u.tk = (int64_t)s.ke;
+                u.td = (int64_t)tail<DMA>(s, r);
+                return u;
+            },
+            &ord);
+    } else {
+        using LaneT = MChain<TT>;
+        T = heuristic_wave<DMA, LaneT>(
+            n, v, r,
+            [&r](const LaneT &s) {
+                Fit3 u;
+                u.th = (int64_t)s.x;
+                u.tk = (int64_t)s.kp;
+                u.td = (int64_t)tail<DMA>(s, r);
+                return u;
+            },
+            &ord);
     }
-    Partial p;
-    p.min_t = a.min_t; p.min_r = a.min_r; p.max_t = a.max_t1; p.max_r = a.max_r;
-    p.sum_lo = a.sum_lo; p.sum_hi = a.sum_hi; p.fp = a.fp; p.status = 0; p.pad = 0;
-    for (int o = 32; o >= 1; o >>= 1) {
-        const uint64_t mt = shfl_xor64(p.min_t, o), mr = shfl_xor64(p.min_r, o);
-        const uint64_t xt = shfl_xor64(p.max_t, o), xr = shfl_xor64(p.max_r, o);
-        const uint64_t sl = shfl_xor64(p.sum_lo, o), sh = shfl_xor64(p.sum_hi, o);
-        const uint64_t f = shfl_xor64(p.fp, o);
-        merge_min(p.min_t, p.min_r, mt, mr);
-        merge_max(p.max_t, p.max_r, xt, xr);
-        add128(p.sum_lo, p.sum_hi, sl, sh);
-        p.fp += f;
-    }
-    __shared__ Partial wsum[MEM_THREADS / 64];
-    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x / 64] = p;
-    __syncthreads();
     if (threadIdx.x == 0) {
-        Partial o = wsum[0];
-        for (int i = 1; i < MEM_THREADS / 64; ++i) {
-            merge_min(o.min_t, o.min_r, wsum[i].min_t, wsum[i].min_r);
-            merge_max(o.max_t, o.max_r, wsum[i].max_t, wsum[i].max_r);
-            add128(o.sum_lo, o.sum_hi, wsum[i].sum_lo, wsum[i].sum_hi);
-            o.fp += wsum[i].fp;
-        }
-        o.status = 0;
-        o.pad = 0;
-        partials[blockIdx.x] = o;
+        put_order(out->heur, ord, n);
+        out->heur_ns = T;
     }
 }
 
-// Simulate the group launched in ord[0..len) alone: (end of its last HtD,
-// kernel, DtH) -- Algorithm 1's update -- in 64-bit time.
+// T of the group launched in ord[0..len), in 64-bit time.
 template <bool ONE>
-__device__ Fit3 mem_update(const uint8_t *ord, int len, const MemTab<uint64_t> &tb, uint64_t cap,
-                           const Rates &r, const KQ<uint64_t> &kq) {
-    Fit3 u;
+__device__ int64_t mem_time(const uint8_t *ord, int len, const MemTab<uint64_t> &tb, uint64_t cap, const Rates &r,
+                            const KQ<uint64_t> &kq) {
     if constexpr (ONE) {
         Chain<uint64_t> c;
         chain_init(c);
         for (int i = 0; i < len; ++i) chain_push(c, ord[i], tb, cap);
-        u.th = (int64_t)c.x;
-        u.tk = (int64_t)c.kp;
-        u.td = (int64_t)chain_finish(c, tb);
+        return (int64_t)chain_finish(c, tb);
     } else {
         GSim<uint64_t> s;
         gsim_init(s);
         for (int i = 0; i < len; ++i) gsim_push(s, ord[i], tb, cap, r, kq);
-        u.th = (int64_t)s.t;
-        u.tk = (int64_t)s.kp;
-        u.td = (int64_t)gsim_finish(s, tb, r, kq);
+        return (int64_t)gsim_finish(s, tb, r, kq);
     }
-    return u;
-}
-
-// Algorithm 1 under the limit (one thread): the selection rules of the
-// unconstrained heuristic (heur_dev.h), every update simulated under it.
-template <bool ONE>
-__global__ __launch_bounds__(64) void mem_heuristic_kernel(const tgo_task *__restrict__ tasks,
-                                                           const int64_t *__restrict__ mem, int n, uint64_t cap,
-                                                           Rates r, tgo_summary *out) {
-    __shared__ MemTab<uint64_t> tb;
-    __shared__ int flag;
-    __shared__ uint64_t kqs[MAXN];
-    const KQ<uint64_t> kq{kqs, 1};
-    const int st = mem_tables<uint64_t>(tasks, mem, n, cap, r, tb, &flag);
-    if (threadIdx.x != 0) return;
-    if (st < 0) {
-        out->heur_ns = st;
-        return;
-    }
-    uint8_t ord[MAXN];
-    uint32_t rt = (1u << n) - 1u;
-    int first = 0;
-    for (int x = 1; x < n; ++x) {
-        const int64_t kh = (int64_t)tb.k[x] - (int64_t)tb.h[x];
-        const int64_t bkh = (int64_t)tb.k[first] - (int64_t)tb.h[first];
-        if (kh > bkh || (kh == bkh && tb.d[x] > tb.d[first])) first = x;
-    }
-    ord[0] = (uint8_t)first;
-    rt &= ~(1u << first);
-    int pos = 1;
-    while (__popc(rt) > 2) {
-        const Fit3 u = mem_update<ONE>(ord, pos, tb, cap, r, kq);
-        int best = -1;
-        int64_t bf = 0;
-        for (int c = 0; c < n; ++c) {
-            if (!((rt >> c) & 1u)) continue;
-            const int64_t f = fit((int64_t)tb.h[c], (int64_t)tb.k[c], u);
-            if (best < 0 || f < bf) { best = c; bf = f; }
-        }
-        ord[pos++] = (uint8_t)best;
-        rt &= ~(1u << best);
-    }
-    if (__popc(rt) == 2) {
-        const int a = __ffs(rt) - 1, b = 31 - __clz(rt);
-        const Fit3 u = mem_update<ONE>(ord, pos, tb, cap, r, kq);
-        int bx = -1, by = -1;
-        int64_t bs = 0, bdy = 0;
-        for (int o = 0; o < 2; ++o) {
-            const int x = o == 0 ? a : b, y = o == 0 ? b : a;
-            ord[pos] = (uint8_t)x;
-            const Fit3 w = mem_update<ONE>(ord, pos + 1, tb, cap, r, kq);
-            const int64_t dy = (int64_t)tb.d[y];
-            const int64_t sc = fit((int64_t)tb.h[x], (int64_t)tb.k[x], u) +
-                               fit((int64_t)tb.h[y], (int64_t)tb.k[y], w) + dy;
-            if (bx < 0 || sc < bs || (sc == bs && dy < bdy)) { bx = x; by = y; bs = sc; bdy = dy; }
-        }
-        ord[pos] = (uint8_t)bx;
-        ord[pos + 1] = (uint8_t)by;
-        pos += 2;
-    } else if (__popc(rt) == 1) {
-        ord[pos++] = (uint8_t)(__ffs(rt) - 1);
-    }
-    const Fit3 f = mem_update<ONE>(ord, n, tb, cap, r, kq);
-    for (int j = 0; j < 16; ++j) out->heur[j] = j < n ? ord[j] : (uint8_t)0xff;
-    out->heur_ns = f.td;
 }
 
 // T of given orderings (rows of n bytes) under the limit; one lane per row,
@@ -307,7 +251,7 @@ __global__ __launch_bounds__(MEM_THREADS) void mem_evaluate_kernel(const tgo_tas
     __shared__ int flag;
     __shared__ uint64_t kqs[MAXN * MEM_THREADS];
     const KQ<uint64_t> kq{kqs + threadIdx.x, MEM_THREADS};
-    const int st = mem_tables<uint64_t>(tasks, mem, n, cap, r, tb, &flag);
+    const int st = mem_tables(tasks, mem, n, cap, r, tb, &flag);
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= m) return;
     if (st < 0) {
@@ -325,75 +269,60 @@ __global__ __launch_bounds__(MEM_THREADS) void mem_evaluate_kernel(const tgo_tas
         seen |= 1u << x;
         ord[j] = x;
     }
-    out[i] = mem_update<ONE>(ord, n, tb, cap, r, kq).td;
+    out[i] = mem_time<ONE>(ord, n, tb, cap, r, kq);
 }
 
-template <typename TT, bool ONE, bool STORE>
-static void launch_enum_width(int M, dim3 grid, hipStream_t st, const tgo_task *t, const int64_t *mem, int n,
-                              uint64_t cap, const Rates &r, uint32_t n_sub, int64_t *out, Partial *parts) {
-    const size_t shm = ONE ? 0 : sizeof(TT) * MEM_THREADS * (size_t)n;
-#define TGO_MEM_ENUM(MM)                                                                                         \
-    hipLaunchKernelGGL((mem_enum_kernel<TT, ONE, STORE, MM>), grid, dim3(MEM_THREADS), shm, st, t, mem, n, cap, \
-                       r, n_sub, out, parts)
-    switch (M) {
-        case 1: TGO_MEM_ENUM(1); break;
-        case 2: TGO_MEM_ENUM(2); break;
-        case 3: TGO_MEM_ENUM(3); break;
-        case 4: TGO_MEM_ENUM(4); break;
-        default: TGO_MEM_ENUM(5); break;
-    }
-#undef TGO_MEM_ENUM
+template <int M, bool STORE, int DMA>
+static int launch_mem(hipStream_t st, const tgo_task *t, const int64_t *mem, int n, uint64_t cap, const Rates &r,
+                      int64_t *out, tgo_summary *d_out) {
+    const void *k32 = reinterpret_cast<const void *>(&enum_kernel<MemRule, uint32_t, M, STORE, DMA>);
+    const uint32_t n_sub = (uint32_t)(factorial(n) / factorial(M));
+    uint32_t blocks = 0;
+    EnumScratch sc;
+    int rc = enum_grid(k32, enum_shm_bytes<MemRule, uint32_t>(n, DMA == DMA_ONE), n_sub, MemRule::lds_bytes(n),
+                       ExScratch{}, st, &blocks, &sc);
+    if (rc) return rc;
+    uint32_t *fits = reinterpret_cast<uint32_t *>(sc.extra);
+    hipLaunchKernelGGL(mem_prepare_kernel, dim3(1), dim3(MEM_PREP_THREADS), 0, st, t, mem, n, cap, r, sc.mode, sc.acc,
+                       fits);
+    rc = enum_launch<MemRule, M, STORE, DMA>(st, t, n, r, MemRule::Args{fits}, n_sub, out, blocks, sc);
+    if (rc) return rc;
+    hipLaunchKernelGGL(mem_finalize_kernel<DMA>, dim3(2), dim3(EX_FIN_THREADS), 0, st, sc.parts, (int)blocks, n,
+                       factorial(n), sc.acc, sc.mode, t, fits, r, d_out);
+    TGO_HIP(hipGetLastError());
+    return TGO_OK;
 }
 
-template <bool ONE, bool STORE>
-static void launch_enum(int M, dim3 grid, hipStream_t st, const tgo_task *t, const int64_t *mem, int n,
-                        uint64_t cap, const Rates &r, uint32_t n_sub, int64_t *out, Partial *parts) {
-    launch_enum_width<uint32_t, ONE, STORE>(M, grid, st, t, mem, n, cap, r, n_sub, out, parts);
-    launch_enum_width<uint64_t, ONE, STORE>(M, grid, st, t, mem, n, cap, r, n_sub, out, parts);
-}
-
-// Positions walked depth first per lane, or n if smaller: 4 with two DMA
-// engines (12.4 vs 14.9 ms at n = 12: one more wave per SIMD), 5 with one
-// (a few per cent faster); TGO_MEM_M overrides it for tuning experiments
-// (1..5).
-static int choose_mem_m(int n, bool one_dma) {
-    int m = one_dma ? 5 : 4;
+// Positions walked depth first per lane (TGO_MEM_M, 1..5, overrides it): two
+// engines, n = 12: 4.63 / 3.93 ms with 4 / 5, one engine 1.33 / 1.01 ms.
+static int choose_mem_m(int n) {
     if (const char *e = std::getenv("TGO_MEM_M")) {
-        const int v = std::atoi(e);
-        if (v >= 1 && v <= 5) m = v;
+        const int m = std::atoi(e);
+        if (m >= 1 && m <= 5 && m <= n) return m;
     }
-    return m < n ? m : n;
+    return rule_depth(n, 5);
+}
+
+template <bool STORE, int DMA>
+static int launch_mem_m(hipStream_t st, const tgo_task *t, const int64_t *mem, int n, uint64_t cap, const Rates &r,
+                        int64_t *out, tgo_summary *d_out) {
+    switch (choose_mem_m(n)) {
+        case 1: return launch_mem<1, STORE, DMA>(st, t, mem, n, cap, r, out, d_out);
+        case 2: return launch_mem<2, STORE, DMA>(st, t, mem, n, cap, r, out, d_out);
+        case 3: return launch_mem<3, STORE, DMA>(st, t, mem, n, cap, r, out, d_out);
+        case 4: return launch_mem<4, STORE, DMA>(st, t, mem, n, cap, r, out, d_out);
+        default: return launch_mem<5, STORE, DMA>(st, t, mem, n, cap, r, out, d_out);
+    }
 }
 
 int launch_memory(const Rates &r, const tgo_task *d_tasks, const int64_t *d_mem, int n, int64_t cap,
                   int64_t *d_per_order, tgo_summary *d_out, hipStream_t st) {
-    const int M = choose_mem_m(n, r.one_dma != 0);
-    const uint64_t count = factorial(n);
-    const uint32_t n_sub = (uint32_t)(count / factorial(M));
-    const uint64_t want = ((uint64_t)n_sub + MEM_THREADS - 1) / MEM_THREADS;
-    const uint64_t most = r.one_dma ? MEM_MAX_BLOCKS_ONE : MEM_MAX_BLOCKS_TWO;
-    const uint32_t blocks = (uint32_t)(want < most ? want : most);
-    Partial *parts = nullptr;
-    int rc = workspace(sizeof(Partial) * blocks, (void **)&parts, st);
-    if (rc) return rc;
     const uint64_t c = (uint64_t)cap;
-    const dim3 g(blocks);
-    if (r.one_dma) {
-        if (d_per_order) launch_enum<true, true>(M, g, st, d_tasks, d_mem, n, c, r, n_sub, d_per_order, parts);
-        else launch_enum<true, false>(M, g, st, d_tasks, d_mem, n, c, r, n_sub, nullptr, parts);
-    } else {
-        if (d_per_order) launch_enum<false, true>(M, g, st, d_tasks, d_mem, n, c, r, n_sub, d_per_order, parts);
-        else launch_enum<false, false>(M, g, st, d_tasks, d_mem, n, c, r, n_sub, nullptr, parts);
-    }
-    TGO_HIP(hipGetLastError());
-    rc = launch_summary_finalize(parts, (int)blocks, n, 1, count, count, d_out, st);
-    if (rc) return rc;
     if (r.one_dma)
-        hipLaunchKernelGGL(mem_heuristic_kernel<true>, dim3(1), dim3(64), 0, st, d_tasks, d_mem, n, c, r, d_out);
-    else
-        hipLaunchKernelGGL(mem_heuristic_kernel<false>, dim3(1), dim3(64), 0, st, d_tasks, d_mem, n, c, r, d_out);
-    TGO_HIP(hipGetLastError());
-    return TGO_OK;
+        return d_per_order ? launch_mem_m<true, DMA_ONE>(st, d_tasks, d_mem, n, c, r, d_per_order, d_out)
+                           : launch_mem_m<false, DMA_ONE>(st, d_tasks, d_mem, n, c, r, nullptr, d_out);
+    return d_per_order ? launch_mem_m<true, DMA_TWO>(st, d_tasks, d_mem, n, c, r, d_per_order, d_out)
+                       : launch_mem_m<false, DMA_TWO>(st, d_tasks, d_mem, n, c, r, nullptr, d_out);
 }
 
 int launch_memory_evaluate(const Rates &r, const tgo_task *d_tasks, const int64_t *d_mem, int n, int64_t cap,
