@@ -162,11 +162,13 @@ __device__ int64_t cke_sim(uint64_t seq, int n, const CTab &tb, int cap, const R
 // scan of running kernels where a kernel does not fit at once.  As a lane per
 // ordering stepping all of its events in 64-bit time, n = 12 took 123.5 ms
 // (479M orderings); with shared prefixes, windows and 32-bit time 4.6 ms.
-struct CkeRule {
+struct CkeRule : SetMajorPrefix {
     struct Args {
         const int32_t *units;
         int32_t cap;
+        tgo_summary *out;  // the heuristic's fields
     };
+    static constexpr bool SIDE = true;
     template <typename TT>
     using View = RView<TT, 1, EX_THREADS, RULE_CONCURRENT>;
     template <typename TT, int DMA>
@@ -186,10 +188,18 @@ struct CkeRule {
         v.cap = a.cap;
         v.seq = seq;
     }
+    // Algorithm 1 (Section 5.1) with `update` simulating the ordered set under
+    // the same rule.
+    template <typename TT, int DMA, typename ViewT>
+    static __device__ __forceinline__ void side(const ViewT &v, int n, const Rates &r, const Args &a) {
+        uint64_t ord;
+        const int64_t T = heuristic_wave<DMA, Lane<TT, DMA>>((1u << n) - 1u, v, r, &ord);
+        put_heuristic(a.out, ord, n, T);
+    }
 };
 
 // Time path of the group (as classify_group), or TGO_ERANGE / TGO_EINVAL (a
-// unit count outside 1..cap); clears the accumulator.
+// unit count outside 1..cap); clears the accumulators.
 __device__ __forceinline__ int cke_status_wave(const tgo_task *tasks, const int32_t *units, int n, int cap,
                                                const Rates &r, int lane) {
     const int m = classify_group_wave(tasks, n, r, lane);
@@ -201,67 +211,8 @@ __global__ __launch_bounds__(64) void cke_prepare_kernel(const tgo_task *__restr
                                                          const int32_t *__restrict__ units, int n, int cap, Rates r,
                                                          int *mode, ExAcc *acc) {
     const int m = cke_status_wave(tasks, units, n, cap, r, threadIdx.x);
-    if (threadIdx.x == 0) {
-        *mode = m;
-        exacc_init(acc);
-    }
-}
-
-// Block 0 writes the enumeration's part of the summary, the first wave of
-// block 1 Algorithm 1 (Section 5.1) with `update` simulating the ordered set
-// under the same rule.
-template <int DMA>
-__global__ __launch_bounds__(EX_FIN_THREADS) void cke_finalize_kernel(
-    const Partial *__restrict__ parts, int nparts, int n, uint64_t count, const ExAcc *__restrict__ acc,
-    const int *__restrict__ modep, const tgo_task *__restrict__ tasks, const int32_t *__restrict__ units, int cap,
-    Rates r, tgo_summary *out) {
-    using TT = uint64_t;
-    const int mode = *modep;
-    if (blockIdx.x == 0) {
-        finalize_block(parts, nparts, n, count, acc, mode, out);
-        return;
-    }
-    if (threadIdx.x >= 64) return;
-    if (mode < 0) {
-        if (threadIdx.x == 0) {
-            put_order(out->heur, 0, 0);
-            out->heur_ns = mode;
-        }
-        return;
-    }
-    __shared__ Quad<TT> Ht[MAXN];
-    __shared__ DRec<TT> Dt[MAXN];
-    __shared__ Slot<TT> Qs[MAXN];
-    __shared__ int32_t us[MAXN];
-    if ((int)threadIdx.x < n) {
-        table_entry<TT>(tasks[threadIdx.x], r, &Ht[threadIdx.x], &Dt[threadIdx.x]);
-        us[threadIdx.x] = units[threadIdx.x];
-    }
-    wave_lds_sync();
-    uint64_t seq = 0;
-    RView<TT, 1, 1, RULE_CONCURRENT> v;
-    v.H = Ht;
-    v.D = Dt;
-    v.Q = Qs;
-    v.units = us;
-    v.cap = cap;
-    v.seq = &seq;
-    using LaneT = RLane<TT, RULE_CONCURRENT>;
-    uint64_t ord;
-    const int64_t T = heuristic_wave<DMA, LaneT>(
-        n, v, r,
-        [&r](const LaneT &s) {
-            Fit3 u;
-            u.th = (int64_t)s.t;
-            u.tk = (int64_t)s.ke;
-            u.td = (int64_t)tail<DMA>(s, r);
-            return u;
-        },
-        &ord);
-    if (threadIdx.x == 0) {
-        put_order(out->heur, ord, n);
-        out->heur_ns = T;
-    }
+    if (threadIdx.x == 0) *mode = m;
+    exacc_init(acc, threadIdx.x);
 }
 
 template <int M, bool STORE, int DMA>
@@ -275,10 +226,10 @@ static int launch_cke(hipStream_t st, const tgo_task *t, const int32_t *units, i
                        &sc);
     if (rc) return rc;
     hipLaunchKernelGGL(cke_prepare_kernel, dim3(1), dim3(64), 0, st, t, units, n, cap, r, sc.mode, sc.acc);
-    rc = enum_launch<CkeRule, M, STORE, DMA>(st, t, n, r, CkeRule::Args{units, cap}, n_sub, out, blocks, sc);
+    rc = enum_launch<CkeRule, M, STORE, DMA>(st, t, n, r, CkeRule::Args{units, cap, d_out}, n_sub, out, blocks, sc);
     if (rc) return rc;
-    hipLaunchKernelGGL(cke_finalize_kernel<DMA>, dim3(2), dim3(EX_FIN_THREADS), 0, st, sc.parts, (int)blocks, n,
-                       factorial(n), sc.acc, sc.mode, t, units, cap, r, d_out);
+    hipLaunchKernelGGL(rule_finalize, dim3(1), dim3(EX_FIN_THREADS), 0, st, sc.parts, (int)blocks, n, factorial(n),
+                       sc.acc, sc.mode, d_out);
     TGO_HIP(hipGetLastError());
     return TGO_OK;
 }

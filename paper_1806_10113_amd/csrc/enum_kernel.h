@@ -2,9 +2,10 @@
 // of one group), its reduction and its launch.
 //
 // A Rule says which model the lanes simulate: the lane state and its window
-// and tail functions (BaseRule: the temporal model alone; the memory limit
-// and concurrent kernels bring their own, rule_dev.h), the tables the block
-// keeps in LDS beside the tasks', and the registers the 32-bit kernel may use.
+// and tail functions (BaseRule: the temporal model alone; the memory limit,
+// concurrent kernels and dependent tasks bring their own, rule_dev.h), how a
+// subtree's prefix is placed, the tables the block keeps in LDS beside the
+// tasks', and the registers the 32-bit kernel may use.
 //
 // Each lane walks subtrees (see enum_dev.h), striding over the grid in the
 // set-major order of prefix_by_set; every merge prefers the lower rank on
@@ -96,23 +97,31 @@ __device__ inline Partial block_reduce(Partial p, Partial *wsum) {
     return o;
 }
 
-// Whole-group accumulator of the 32-bit time path, folded into by every
+// Whole-group accumulators of the 32-bit time path, folded into by every
 // block with 64-bit atomics.  There T < 2^31 and a rank < 13! < 2^33, so
 // (T << 33) | rank orders by time and then by rank: the smallest key is the
 // best ordering with the lowest rank, and with the rank complemented the
 // largest key is the worst ordering with the lowest rank.  The sum over all
 // orderings stays below 13! * 2^31 < 2^64; the fingerprint wraps.
-struct ExAcc {
+// Device-scope atomics on one address are served one after another (about
+// 15 ns each here), so blocks spread over EX_ACCS accumulators, a cache line
+// each, and the finalize merges them.
+struct alignas(128) ExAcc {
     unsigned long long minkey, maxkey, sum, fp;
 };
+constexpr int EX_ACCS = 64;
 constexpr uint64_t EX_RANK_MASK = (1ull << 33) - 1;
 
-__device__ __forceinline__ void exacc_init(ExAcc *acc) {
-    acc->minkey = ~0ull;
-    acc->maxkey = 0;
-    acc->sum = 0;
-    acc->fp = 0;
+// One lane per accumulator.
+__device__ __forceinline__ void exacc_init(ExAcc *acc, int lane) {
+    ExAcc a;
+    a.minkey = ~0ull;
+    a.maxkey = 0;
+    a.sum = 0;
+    a.fp = 0;
+    acc[lane] = a;
 }
+static_assert(EX_ACCS == 64, "one wave initialises and merges the accumulators");
 
 // Dynamic LDS of the enumeration kernel: the task tables (n entries each),
 // the rule's own tables, then the per-lane queue, n - 1 slots (the last
@@ -130,11 +139,21 @@ inline size_t enum_shm_bytes(int n, bool one_dma) {
     return enum_tables_bytes<Rule, TT>(n) + (q > red ? q : red);
 }
 
+// Subtrees of one group in set-major order.
+struct SetMajorPrefix {
+    template <int DMA, typename LaneT, typename ViewT, typename ArgsT>
+    static __device__ __forceinline__ uint64_t prefix(LaneT &st, uint32_t s, int n, int m, ViewT &v, const Rates &r,
+                                                      const ArgsT &, uint32_t *lex) {
+        return prefix_by_set<DMA>(st, s, n, m, v, r, lex);
+    }
+};
+
 // The temporal model alone.  32-bit time path: at most 72 VGPRs so that 7
 // waves fit per SIMD (with the n - 1 slot queue, 7 blocks also fit in LDS at
 // n = 12).
-struct BaseRule {
+struct BaseRule : SetMajorPrefix {
     struct Args {};
+    static constexpr bool SIDE = false;
     template <typename TT>
     using View = tgo::View<TT, 1, EX_THREADS>;
     // two DMA engines: the chain form; one engine: windows without DtH events
@@ -172,6 +191,15 @@ void enum_kernel(const tgo_task *__restrict__ tasks, int n, Rates r, typename Ru
     uint64_t seq = 0;  // task at each placed position, one per nibble (rules that ask for it)
     Rule::load(v, smem + (size_t)n * (sizeof(Quad<TT>) + sizeof(DRec<TT>)), args, n, &seq);
     __syncthreads();
+    // the rule's heuristic runs on one wave of block 0, beside the enumeration
+    // (its latency is that of a small group's whole enumeration)
+    if constexpr (Rule::SIDE) {
+        if (blockIdx.x == 0) {
+            if (threadIdx.x < 64) Rule::template side<TT, DMA>(v, n, r, args);
+            return;
+        }
+    }
+    const uint32_t blocks = gridDim.x - (Rule::SIDE ? 1u : 0u), block = blockIdx.x - (Rule::SIDE ? 1u : 0u);
     Ctx c;
     c.n = n;
     c.r = r;
@@ -179,12 +207,12 @@ void enum_kernel(const tgo_task *__restrict__ tasks, int n, Rates r, typename Ru
 
     Acc<TT> a;
     acc_init(a);
-    const uint32_t stride = gridDim.x * blockDim.x;
+    const uint32_t stride = blocks * blockDim.x;
     using LaneT = typename Rule::template Lane<TT, DMA>;
-    for (uint32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < n_sub; s += stride) {
+    for (uint32_t s = block * blockDim.x + threadIdx.x; s < n_sub; s += stride) {
         LaneT st;
         uint32_t lex;
-        const uint64_t list = prefix_by_set<DMA>(st, s, n, M, v, r, &lex);
+        const uint64_t list = Rule::template prefix<DMA>(st, s, n, M, v, r, args, &lex);
         const uint64_t r0 = (uint64_t)lex * factorial(M);
         if constexpr (STORE) c.out_sub = out + r0;
         Sub<TT> u;
@@ -209,12 +237,13 @@ void enum_kernel(const tgo_task *__restrict__ tasks, int n, Rates r, typename Ru
     if (threadIdx.x == 0) {
         if constexpr (sizeof(TT) == 4) {
             // every block owns at least one subtree, so o holds an ordering
+            acc += block % EX_ACCS;
             atomicMin(&acc->minkey, (unsigned long long)((o.min_t << 33) | o.min_r));
             atomicMax(&acc->maxkey, (unsigned long long)(((o.max_t - 1) << 33) | (EX_RANK_MASK - o.max_r)));
             atomicAdd(&acc->sum, (unsigned long long)o.sum_lo);
             atomicAdd(&acc->fp, (unsigned long long)o.fp);
         } else {
-            partials[blockIdx.x] = o;
+            partials[block] = o;
         }
     }
 }
@@ -268,7 +297,9 @@ static_assert(offsetof(tgo_summary, best) % 8 == 0 && offsetof(tgo_summary, wors
 
 // The fields of *out that the enumeration fills, from its reduced result
 // (thread 0 the numbers and the best ordering, thread 64 the worst).
-__device__ inline void write_summary(const Partial &o, int status, int n, uint64_t count, tgo_summary *out) {
+template <typename Decode>
+__device__ __forceinline__ void write_summary(const Partial &o, int status, int n, uint64_t count, Decode decode,
+                                              tgo_summary *out) {
     if (threadIdx.x == 0) {
         out->n = n;
         out->status = status;
@@ -291,18 +322,20 @@ __device__ inline void write_summary(const Partial &o, int status, int n, uint64
             }
         }
         out->mean_ns = mean;
-        put_order(out->best, status ? 0 : unrank_nibbles(n, o.min_r), status ? 0 : n);
+        put_order(out->best, status ? 0 : decode(o.min_r), status ? 0 : n);
     } else if (threadIdx.x == 64) {
-        put_order(out->worst, status ? 0 : unrank_nibbles(n, o.max_r), status ? 0 : n);
+        put_order(out->worst, status ? 0 : decode(o.max_r), status ? 0 : n);
     }
 }
 
 constexpr int EX_FIN_THREADS = 1024;
 
-// One block: the group's result from the accumulator (32-bit path: nothing
-// to reduce) or from the block partials (64-bit path).
-__device__ inline void finalize_block(const Partial *__restrict__ parts, int nparts, int n, uint64_t count,
-                                      const ExAcc *__restrict__ acc, int mode, tgo_summary *out) {
+// One block: the group's result from the accumulators (32-bit path) or from the block partials (64-bit path).  decode(rank) gives an
+// ordering, one task per nibble.
+template <typename Decode>
+__device__ __forceinline__ void finalize_block(const Partial *__restrict__ parts, int nparts, int n, uint64_t count,
+                                               const ExAcc *__restrict__ acc, int mode, Decode decode,
+                                               tgo_summary *out) {
     __shared__ Partial red[EX_FIN_THREADS / 64];
     Partial p;
     p.min_t = ~0ull; p.min_r = ~0ull; p.max_t = 0; p.max_r = ~0ull;
@@ -330,15 +363,50 @@ __device__ inline void finalize_block(const Partial *__restrict__ parts, int npa
         __syncthreads();
         p = red[0];
     } else if (mode == 0) {
-        p.min_t = acc->minkey >> 33;
-        p.min_r = acc->minkey & EX_RANK_MASK;
-        p.max_t = (acc->maxkey >> 33) + 1;
-        p.max_r = EX_RANK_MASK - (acc->maxkey & EX_RANK_MASK);
-        p.sum_lo = acc->sum;
+        // every wave merges the accumulators (waves 0 and 1 use the result)
+        if (threadIdx.x >= 128) return;
+        const ExAcc mine = acc[threadIdx.x & 63];
+        uint64_t mn = mine.minkey, mx = mine.maxkey, sum = mine.sum, fp = mine.fp;
+        for (int m = 32; m >= 1; m >>= 1) {
+            const uint64_t a = shfl_xor64(mn, m), b = shfl_xor64(mx, m);
+            mn = a < mn ? a : mn;
+            mx = b > mx ? b : mx;
+            sum += shfl_xor64(sum, m);
+            fp += shfl_xor64(fp, m);
+        }
+        p.min_t = mn >> 33;
+        p.min_r = mn & EX_RANK_MASK;
+        p.max_t = (mx >> 33) + 1;
+        p.max_r = EX_RANK_MASK - (mx & EX_RANK_MASK);
+        p.sum_lo = sum;
         p.sum_hi = 0;
-        p.fp = acc->fp;
+        p.fp = fp;
     }
-    write_summary(p, mode < 0 ? mode : 0, n, count, out);
+    write_summary(p, mode < 0 ? mode : 0, n, count, decode, out);
+}
+__device__ __forceinline__ void finalize_block(const Partial *__restrict__ parts, int nparts, int n, uint64_t count,
+                                               const ExAcc *__restrict__ acc, int mode, tgo_summary *out) {
+    finalize_block(parts, nparts, n, count, acc, mode, [n](uint64_t rk) { return unrank_nibbles(n, rk); }, out);
+}
+
+// The summary's heuristic ordering and its total time (one lane writes).
+__device__ __forceinline__ void put_heuristic(tgo_summary *out, uint64_t ord, int n, int64_t T) {
+    if (threadIdx.x == 0) {
+        put_order(out->heur, ord, n);
+        out->heur_ns = T;
+    }
+}
+
+// The finalize of a search under a rule; the heuristic's fields are the side
+// block's unless the group is in error.
+static __global__ __launch_bounds__(EX_FIN_THREADS) void rule_finalize(const Partial *__restrict__ parts, int nparts,
+                                                                       int n, uint64_t count,
+                                                                       const ExAcc *__restrict__ acc,
+                                                                       const int *__restrict__ modep,
+                                                                       tgo_summary *out) {
+    const int mode = *modep;
+    if (mode < 0) put_heuristic(out, 0, 0, mode);
+    finalize_block(parts, nparts, n, count, acc, mode, out);
 }
 
 // ------------------------------------------------------------------- launch
@@ -364,15 +432,14 @@ struct ExScratch {
 };
 
 // Device scratch of an enumeration: block partials (64-bit path), the 32-bit
-// path's accumulator, the group's time path, then `extra` bytes of the rule.
+// path's accumulators, the group's time path, then `extra` bytes of the rule.
 struct EnumScratch {
     Partial *parts;
     ExAcc *acc;
     int *mode;
     unsigned char *extra;
 };
-constexpr size_t ENUM_FIXED = 256;  // accumulator and time path, padded
-static_assert(sizeof(ExAcc) + sizeof(int) <= ENUM_FIXED, "fixed scratch");
+constexpr size_t ENUM_FIXED = sizeof(ExAcc) * EX_ACCS + 256;  // accumulators and time path
 
 // Blocks of an enumeration of n_sub subtrees and the scratch it needs.  The
 // grid is sized from the 32-bit kernel (the fast path), capped at one subtree
@@ -401,7 +468,7 @@ inline int enum_grid(const void *k32, size_t shm32, uint32_t n_sub, size_t extra
         if (rc) return rc;
     }
     sc->acc = reinterpret_cast<ExAcc *>(base);
-    sc->mode = reinterpret_cast<int *>(base + sizeof(ExAcc));
+    sc->mode = reinterpret_cast<int *>(base + sizeof(ExAcc) * EX_ACCS);
     sc->extra = base + ENUM_FIXED;
     sc->parts = reinterpret_cast<Partial *>(base + fixed);
     *blocks_out = blocks;
@@ -414,10 +481,11 @@ template <class Rule, int M, bool STORE, int DMA>
 inline int enum_launch(hipStream_t st, const tgo_task *t, int n, const Rates &r, const typename Rule::Args &args,
                        uint32_t n_sub, int64_t *out, uint32_t blocks, const EnumScratch &sc) {
     constexpr bool one = DMA == DMA_ONE;
-    hipLaunchKernelGGL((enum_kernel<Rule, uint32_t, M, STORE, DMA>), dim3(blocks), dim3(EX_THREADS),
+    const uint32_t grid = blocks + (Rule::SIDE ? 1u : 0u);
+    hipLaunchKernelGGL((enum_kernel<Rule, uint32_t, M, STORE, DMA>), dim3(grid), dim3(EX_THREADS),
                        (enum_shm_bytes<Rule, uint32_t>(n, one)), st, t, n, r, args, n_sub, out, sc.parts, sc.acc,
                        sc.mode);
-    hipLaunchKernelGGL((enum_kernel<Rule, uint64_t, M, STORE, DMA>), dim3(blocks), dim3(EX_THREADS),
+    hipLaunchKernelGGL((enum_kernel<Rule, uint64_t, M, STORE, DMA>), dim3(grid), dim3(EX_THREADS),
                        (enum_shm_bytes<Rule, uint64_t>(n, one)), st, t, n, r, args, n_sub, out, sc.parts, sc.acc,
                        sc.mode);
     TGO_HIP(hipGetLastError());

@@ -70,16 +70,39 @@ int launch_evaluate(const Rates &r, const tgo_task *d_tasks, int n, const uint8_
 
 // ---------------------------------------------------------------- heuristic
 
-// One wave per group (heuristic_wave).  Always runs the 64-bit time path.
+// Tables and queue of one wave, in either time width.
+template <typename TT>
+struct HeurLds {
+    Quad<TT> H[MAXN];
+    DRec<TT> D[MAXN];
+    Slot<TT> Q[MAXN];
+};
+
+template <typename TT>
+__device__ __forceinline__ int64_t heuristic_group(const tgo_task *t, int n, const Rates &r, int lane,
+                                                   HeurLds<TT> &l, uint64_t *ord) {
+    if (lane < n) table_entry<TT>(t[lane], r, &l.H[lane], &l.D[lane]);
+    wave_lds_sync();
+    View<TT, 1, 1> v;
+    v.H = l.H;
+    v.D = l.D;
+    v.Q = l.Q;
+    const uint32_t set = (1u << n) - 1u;
+    return r.one_dma ? heuristic_wave<DMA_ONE, Lane<TT>>(set, v, r, ord)
+                     : heuristic_wave<DMA_TWO, CLane<TT>>(set, v, r, ord);
+}
+
+// One wave per group (heuristic_wave), in 32-bit time where the group allows
+// it.  Bound by the latency of one wave's dependent instructions.
 __global__ __launch_bounds__(HEU_WAVES * 64) void heuristic_kernel(const tgo_task *__restrict__ tasks,
                                                                    const int32_t *__restrict__ offs,
                                                                    int n_groups, Rates r,
                                                                    uint8_t *orders, int order_stride,
                                                                    int64_t *ns, int ns_stride) {
-    using TT = uint64_t;
-    __shared__ Quad<TT> Ht[HEU_WAVES][MAXN];
-    __shared__ DRec<TT> Dt[HEU_WAVES][MAXN];
-    __shared__ Slot<TT> Qs[HEU_WAVES][MAXN];
+    __shared__ union {
+        HeurLds<uint32_t> w32;
+        HeurLds<uint64_t> w64;
+    } lds[HEU_WAVES];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const int g = blockIdx.x * HEU_WAVES + w;
@@ -94,21 +117,15 @@ __global__ __launch_bounds__(HEU_WAVES * 64) void heuristic_kernel(const tgo_tas
         return;
     }
     const tgo_task *t = tasks + base;
-    const int cls = classify_group_wave(t, n, r, lane);
+    const int cls = __builtin_amdgcn_readfirstlane(classify_group_wave(t, n, r, lane));
     if (cls < 0) {
         if (lane < 16) orow[lane] = 0xff;
         if (lane == 0) *nsg = cls;
         return;
     }
-    if (lane < n) table_entry<TT>(t[lane], r, &Ht[w][lane], &Dt[w][lane]);
-    wave_lds_sync();
-    View<TT, 1, 1> v;
-    v.H = Ht[w];
-    v.D = Dt[w];
-    v.Q = Qs[w];
     uint64_t ord;
-    const int64_t T = heuristic_wave<DMA_RUNTIME, Lane<TT>>(
-        n, v, r, [&r](const Lane<TT> &s) { return fit_state<TT, 1, 1>(s, r); }, &ord);
+    const int64_t T = cls == 0 ? heuristic_group<uint32_t>(t, n, r, lane, lds[w].w32, &ord)
+                               : heuristic_group<uint64_t>(t, n, r, lane, lds[w].w64, &ord);
     if (lane < 16) orow[lane] = lane < n ? (uint8_t)((ord >> (4 * lane)) & 15u) : (uint8_t)0xff;
     if (lane == 0) *nsg = T;
 }

@@ -15,12 +15,11 @@ namespace tgo {
 
 // The group's time path, decided once before the enumeration: 0 = 32-bit,
 // 1 = 64-bit, or a negative error code (classify_group).
-__global__ void exhaustive_classify(const tgo_task *__restrict__ tasks, int n, Rates r, int *mode,
+__global__ __launch_bounds__(64) void exhaustive_classify(const tgo_task *__restrict__ tasks, int n, Rates r, int *mode,
                                     ExAcc *acc) {
-    if (threadIdx.x == 0) {
-        *mode = classify_group(tasks, n, r);
-        exacc_init(acc);
-    }
+    const int m = classify_group_wave(tasks, n, r, threadIdx.x);
+    if (threadIdx.x == 0) *mode = m;
+    exacc_init(acc, threadIdx.x);
 }
 
 __global__ __launch_bounds__(EX_FIN_THREADS) void exhaustive_finalize(const Partial *__restrict__ parts,

@@ -1,6 +1,6 @@
-// The ordering heuristic of Section 5.1 (Algorithm 1) as a per-lane device
-// function, shared by the per-group heuristic kernel and the proxy of the
-// multi-round evaluator.
+// The ordering heuristic of Section 5.1 (Algorithm 1) as a device function of
+// one wave, shared by the per-group heuristic kernel, the enumerations under a
+// rule and the proxy of the multi-round evaluator.
 //
 // The three selection functions are described in words only; the readings:
 //   select_first: largest K - HtD (short HtD, long kernel); ties to the longer
@@ -18,6 +18,7 @@
 #include "../../include/tgo.h"
 #include "enum_dev.h"
 #include "model_dev.h"
+#include "rule_dev.h"
 
 namespace tgo {
 
@@ -33,98 +34,45 @@ __device__ __forceinline__ int64_t fit(int64_t h, int64_t k, const Fit3 &u) {
     return (a < 0 ? -a : a) + (b < 0 ? -b : b);
 }
 
-template <typename TT, int TS, int QS>
-__device__ __forceinline__ Fit3 fit_state(const Lane<TT> &st, const Rates &r) {
-    Fit3 u;
-    u.th = (int64_t)st.t;
-    u.tk = (int64_t)st.ck;
-    u.td = (int64_t)tail(st, r);
-    return u;
+// Ends of the last HtD, kernel and DtH of the ordered set simulated alone.
+template <int DMA, typename TT>
+__device__ __forceinline__ Fit3 fit_ends(const Lane<TT> &s, const Rates &r) {
+    return Fit3{(int64_t)s.t, (int64_t)s.ck, (int64_t)tail<DMA>(s, r)};
+}
+template <int DMA, typename TT>
+__device__ __forceinline__ Fit3 fit_ends(const CLane<TT> &s, const Rates &r) {
+    return Fit3{(int64_t)s.t, (int64_t)s.ck, (int64_t)tail<DMA>(s, r)};
+}
+template <int DMA, typename TT, int KIND>
+__device__ __forceinline__ Fit3 fit_ends(const RLane<TT, KIND> &s, const Rates &r) {
+    return Fit3{(int64_t)s.t, (int64_t)s.ke, (int64_t)tail<DMA>(s, r)};
+}
+template <int DMA, typename TT, int KIND>
+__device__ __forceinline__ Fit3 fit_ends(const SubChain<TT, KIND> &s, const Rates &r) {
+    return Fit3{(int64_t)s.x, (int64_t)s.kp, (int64_t)tail<DMA>(s, r)};
 }
 
-// Algorithm 1 on n tasks: v holds the lane's tables of tasks 0..n-1 (built
-// by the caller) and its queue; the candidates' durations are read from those
-// LDS tables, not from global memory, since every selection step scans all of
-// them.  Writes the ordering to ord[0..n-1] and returns its total time.
-template <int TS, int QS>
-__device__ int64_t heuristic_order(int n, const View<uint64_t, TS, QS> &v, const Rates &r, uint8_t *ord) {
-    using TT = uint64_t;
-    auto task = [&v](int x) {
-        const Quad<TT> q = v.task((uint32_t)x);
-        tgo_task t;
-        t.htd_ns = (int64_t)q.h;
-        t.kern_ns = (int64_t)q.k;
-        t.dth_ns = (int64_t)q.d;
-        return t;
-    };
-    uint32_t rt = (1u << n) - 1u;
-    int first = -1;
-    int64_t bkh = 0, bd = 0;
-    for (int x = 0; x < n; ++x) {
-        const tgo_task tx = task(x);
-        const int64_t kh = tx.kern_ns - tx.htd_ns, d = tx.dth_ns;
-        if (first < 0 || kh > bkh || (kh == bkh && d > bd)) { first = x; bkh = kh; bd = d; }
-    }
-    ord[0] = (uint8_t)first;
-    rt &= ~(1u << first);
-    Lane<TT> st = lane_init<TT>();
-    window(st, 0, (uint32_t)first, v, r);
-    int pos = 1;
-    while (__popc(rt) > 2) {
-        const Fit3 u = fit_state<TT, TS, QS>(st, r);
-        int best = -1;
-        int64_t bf = 0;
-        for (int c = 0; c < n; ++c) {
-            if (!((rt >> c) & 1u)) continue;
-            const tgo_task tc = task(c);
-            const int64_t f = fit(tc.htd_ns, tc.kern_ns, u);
-            if (best < 0 || f < bf) { best = c; bf = f; }
-        }
-        ord[pos] = (uint8_t)best;
-        rt &= ~(1u << best);
-        window(st, pos, (uint32_t)best, v, r);
-        ++pos;
-    }
-    if (__popc(rt) == 2) {
-        const int a = __ffs(rt) - 1;
-        const int b = 31 - __clz(rt);
-        const Fit3 u = fit_state<TT, TS, QS>(st, r);
-        int bx = -1, by = -1;
-        int64_t bs = 0, bdy = 0;
-        for (int o = 0; o < 2; ++o) {
-            const int x = o == 0 ? a : b, y = o == 0 ? b : a;
-            const tgo_task tx = task(x), ty = task(y);
-            const int64_t s1 = fit(tx.htd_ns, tx.kern_ns, u);
-            Lane<TT> s2 = st;
-            window(s2, pos, (uint32_t)x, v, r);
-            const Fit3 w = fit_state<TT, TS, QS>(s2, r);
-            const int64_t sc = s1 + fit(ty.htd_ns, ty.kern_ns, w) + ty.dth_ns;
-            const int64_t dy = ty.dth_ns;
-            if (bx < 0 || sc < bs || (sc == bs && dy < bdy)) { bx = x; by = y; bs = sc; bdy = dy; }
-        }
-        ord[pos] = (uint8_t)bx;
-        ord[pos + 1] = (uint8_t)by;
-        window(st, pos, (uint32_t)bx, v, r);
-        window(st, pos + 1, (uint32_t)by, v, r);
-        pos += 2;
-    } else if (__popc(rt) == 1) {
-        const int x = __ffs(rt) - 1;
-        ord[pos] = (uint8_t)x;
-        window(st, pos, (uint32_t)x, v, r);
-        ++pos;
-    }
-    return (int64_t)tail(st, r);
+// A 64-bit value rotated right by R lanes within each row of 16 lanes (two
+// DPP moves).
+template <int R>
+__device__ __forceinline__ uint64_t row_ror_u64(uint64_t u) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x120 + R, 0xF, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x120 + R, 0xF, 0xF, false);
+    return ((uint64_t)hi << 32) | lo;
 }
-
-// Wave-wide choice, the same on every lane after the butterfly: the lane
-// with the smallest key (a, b, i) in lexicographic order.
-__device__ __forceinline__ int wave_pick(int64_t a, int64_t b, int i) {
-    for (int m = 32; m >= 1; m >>= 1) {
-        const int64_t a2 = (int64_t)shfl_xor64((uint64_t)a, m), b2 = (int64_t)shfl_xor64((uint64_t)b, m);
-        const int i2 = __shfl_xor(i, m);
-        if (a2 < a || (a2 == a && (b2 < b || (b2 == b && i2 < i)))) { a = a2; b = b2; i = i2; }
-    }
-    return i;
+// The smallest key of lanes 0..15, as a scalar.  Every lane must be active.
+__device__ __forceinline__ uint64_t row0_min(uint64_t k) {
+    uint64_t o = row_ror_u64<8>(k);
+    k = o < k ? o : k;
+    o = row_ror_u64<4>(k);
+    k = o < k ? o : k;
+    o = row_ror_u64<2>(k);
+    k = o < k ? o : k;
+    o = row_ror_u64<1>(k);
+    k = o < k ? o : k;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)k);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(k >> 32));
+    return ((uint64_t)hi << 32) | lo;
 }
 
 // Orders this wave's LDS writes before its later LDS reads.
@@ -134,76 +82,81 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Algorithm 1 on n <= 16 tasks by one wave.  The simulation of the ordered
-// set is the same on every lane (tables and queue shared by the wave, 64-bit
-// time); each selection step scores the remaining tasks on their own lanes
-// and picks with the serial version's tie rules (select_first: largest
-// K - HtD, then longest DtH, then lowest index; select_next: smallest fit,
-// then lowest index).  fit_of(lane) gives the three engine ends of the ordered
-// set.  Returns the total time; *ord_out receives the ordering, one task per
-// nibble.
-template <int DMA, typename LaneT, typename ViewT, typename FitF>
-__device__ __forceinline__ int64_t heuristic_wave(int n, const ViewT &v, const Rates &r, FitF fit_of,
-                                                  uint64_t *ord_out) {
-    using TT = uint64_t;
-    constexpr int64_t BIG = INT64_MAX;
-    constexpr int NONE = 1 << 20;
+// Algorithm 1 by one wave (all 64 lanes active) on the tasks in `set` (bits
+// 0..15, at least one).  The simulation of the ordered set is the same on
+// every lane (each with its own queue column, or one they share); each
+// selection step scores the remaining tasks on their own lanes and takes the
+// smallest key of a row of 16 lanes (DPP moves: a shuffle over the wave per
+// step was half of the time), with the tie rules above.  Every instant stays
+// below 2^56 (16 tasks, work below 2^50 each), so a score and a lane index
+// share one key.  Returns the total time; *ord_out receives the ordering, one task per nibble.
+template <int DMA, typename LaneT, typename ViewT>
+__device__ __forceinline__ int64_t heuristic_wave(uint32_t set, const ViewT &v, const Rates &r, uint64_t *ord_out) {
+    constexpr uint64_t NONE = ~0ull;
     const int lane = threadIdx.x & 63;
-    uint32_t rt = (1u << n) - 1u;
+    uint32_t rt = set;
     uint64_t ord = 0;
     // this lane's task as a candidate
     int64_t ch = 0, ckn = 0, cd = 0;
-    if (lane < n) {
-        const Quad<TT> q = v.task((uint32_t)lane);
+    if (lane < MAXN && ((set >> lane) & 1u)) {
+        const auto q = v.task((uint32_t)lane);
         ch = (int64_t)q.h;
         ckn = (int64_t)q.k;
         cd = (int64_t)q.d;
     }
-    // largest K - HtD, then longest DtH: the smallest (HtD - K, -DtH)
-    const int first = wave_pick(lane < n ? ch - ckn : BIG, lane < n ? -cd : BIG, lane < n ? lane : NONE);
-    ord = (uint64_t)first;
+    auto cand = [&] { return lane < MAXN && ((rt >> lane) & 1u); };
+    // largest K - HtD, then longest DtH, then lowest index
+    const uint64_t kh = (uint64_t)((int64_t(1) << 41) + ch - ckn);
+    const uint64_t lowest = row0_min(cand() ? kh : NONE);
+    const uint64_t longest = row0_min(cand() && kh == lowest
+                                          ? ((uint64_t)((int64_t(1) << 41) - cd) << 4) | (uint64_t)lane : NONE);
+    const uint32_t first = (uint32_t)longest & 15u;
+    ord = first;
     rt &= ~(1u << first);
     LaneT st;
     lane_reset(st);
-    window<DMA>(st, 0, (uint32_t)first, v, r);
+    window<DMA>(st, 0, first, v, r);
     int pos = 1;
     while (__popc(rt) > 2) {
-        const Fit3 u = fit_of(st);
-        const bool cand = lane < n && ((rt >> lane) & 1u);
-        const int best = wave_pick(cand ? fit(ch, ckn, u) : BIG, 0, cand ? lane : NONE);
+        const Fit3 u = fit_ends<DMA>(st, r);
+        const uint64_t key = cand() ? ((uint64_t)fit(ch, ckn, u) << 4) | (uint64_t)lane : NONE;
+        const uint32_t best = (uint32_t)row0_min(key) & 15u;
         ord |= (uint64_t)best << (4 * pos);
         rt &= ~(1u << best);
-        window<DMA>(st, pos, (uint32_t)best, v, r);
+        window<DMA>(st, pos, best, v, r);
         ++pos;
     }
     if (__popc(rt) == 2) {
         // select_last: both orders of the last two, scored on every lane
         const int a = __ffs(rt) - 1;
         const int b = 31 - __clz(rt);
-        const Fit3 u = fit_of(st);
+        const Fit3 u = fit_ends<DMA>(st, r);
         int bx = -1, by = -1;
         int64_t bs = 0, bdy = 0;
+#pragma unroll 1
         for (int o = 0; o < 2; ++o) {
             const int x = o == 0 ? a : b, y = o == 0 ? b : a;
-            const Quad<TT> tx = v.task((uint32_t)x), ty = v.task((uint32_t)y);
+            const auto tx = v.task((uint32_t)x), ty = v.task((uint32_t)y);
             const int64_t s1 = fit((int64_t)tx.h, (int64_t)tx.k, u);
             LaneT s2 = st;
             window<DMA>(s2, pos, (uint32_t)x, v, r);
-            const Fit3 wf = fit_of(s2);
+            const Fit3 wf = fit_ends<DMA>(s2, r);
             const int64_t sc = s1 + fit((int64_t)ty.h, (int64_t)ty.k, wf) + (int64_t)ty.d;
             const int64_t dy = (int64_t)ty.d;
             if (bx < 0 || sc < bs || (sc == bs && dy < bdy)) { bx = x; by = y; bs = sc; bdy = dy; }
         }
+        bx = __builtin_amdgcn_readfirstlane(bx);
+        by = __builtin_amdgcn_readfirstlane(by);
         ord |= ((uint64_t)bx << (4 * pos)) | ((uint64_t)by << (4 * pos + 4));
         window<DMA>(st, pos, (uint32_t)bx, v, r);
-        window<DMA>(st, pos + 1, (uint32_t)by, v, r);
+        window<DMA, false>(st, pos + 1, (uint32_t)by, v, r);
     } else if (__popc(rt) == 1) {
         const int x = __ffs(rt) - 1;
         ord |= (uint64_t)x << (4 * pos);
-        window<DMA>(st, pos, (uint32_t)x, v, r);
+        window<DMA, false>(st, pos, (uint32_t)x, v, r);
     }
     *ord_out = ord;
-    return fit_of(st).td;
+    return fit_ends<DMA>(st, r).td;
 }
 
 }  // namespace tgo

@@ -47,58 +47,20 @@ __device__ __forceinline__ int mem_tables(const tgo_task *__restrict__ tasks, co
     return f < 0 ? f : 0;
 }
 
-// One DMA engine: the closed-form chain of sub-groups (mem_dev.h, Chain) with
-// the open sub-group's buffers as a set of tasks.
-template <typename TT>
-struct MChain {
-    using ST = typename Signed<TT>::type;
-    TT x;          // end of the open sub-group's last HtD (none open: of the last DtH)
-    TT kp;         // end of the last kernel
-    ST emax;       // open sub-group: max of (K_p end - its DtH time before p)
-    TT dsum;       // open sub-group: its DtH time so far
-    uint32_t set;  // open sub-group: its tasks
-};
-template <typename TT>
-__device__ __forceinline__ void lane_reset(MChain<TT> &s) {
-    using ST = typename Signed<TT>::type;
-    s.x = s.kp = s.dsum = 0;
-    s.emax = (ST)(((TT)1) << (8 * sizeof(TT) - 1));  // most negative
-    s.set = 0;
-}
-template <int DMA, typename TT>
-__device__ __forceinline__ TT tail(const MChain<TT> &s, const Rates &) {
-    using ST = typename Signed<TT>::type;
-    const ST e = (ST)s.x > s.emax ? (ST)s.x : s.emax;
-    return (TT)(e + (ST)s.dsum);
-}
-template <int DMA, bool PUT = true, typename TT, typename ViewT>
-__device__ __forceinline__ void window(MChain<TT> &s, int, uint32_t x, const ViewT &v, const Rates &r) {
-    using ST = typename Signed<TT>::type;
-    const Quad<TT> tx = v.task(x);
-    uint32_t set = s.set | (1u << x);
-    // x alone fits, so the first task of a sub-group never closes one
-    const bool close = !((v.fits[set >> 5] >> (set & 31u)) & 1u);
-    s.x = (close ? tail<DMA>(s, r) : s.x) + tx.h;
-    s.set = close ? 1u << x : set;
-    s.kp = tmax(s.x, s.kp) + tx.k;
-    const TT before = close ? TT(0) : s.dsum;
-    const ST e = (ST)s.kp - (ST)before;
-    s.emax = close ? e : (e > s.emax ? e : s.emax);
-    s.dsum = before + tx.d;
-}
-
 // The device-memory limit under the enumeration kernel (enum_kernel.h).  Bound
 // by VALU issue over divergent window loops.  Two engines, n = 12, capacity
 // 40 %: 18.9 ms when every transfer event was stepped (footprints summed in
 // 64 bits at each), 4.2 ms with windows and the set table; one engine 1.2 -> 1.0 ms.
-struct MemRule {
+struct MemRule : SetMajorPrefix {
     struct Args {
         const uint32_t *fits;  // bit s: the tasks of set s fit together
+        tgo_summary *out;      // the heuristic's fields
     };
+    static constexpr bool SIDE = true;
     template <typename TT>
     using View = RView<TT, 1, EX_THREADS, RULE_MEMORY>;
     template <typename TT, int DMA>
-    using Lane = std::conditional_t<DMA == DMA_TWO, RLane<TT, RULE_MEMORY>, MChain<TT>>;
+    using Lane = std::conditional_t<DMA == DMA_TWO, RLane<TT, RULE_MEMORY>, SubChain<TT, RULE_MEMORY>>;
     // 5 waves per SIMD (96 VGPRs): two engines, n = 12, capacity 40 %, three
     // groups: 3.93 / 4.02 / 4.39 ms against 4.18 / 4.17 / 4.52 at 7 waves and
     // 4.70 / 4.77 / 5.09 at 8; one engine 1.01 / 0.96 / 0.94 ms at 5 and 7.
@@ -116,11 +78,18 @@ struct MemRule {
         v.fits = f;
         v.seq = seq;
     }
+    // Algorithm 1 with `update` simulating the ordered set under the limit.
+    template <typename TT, int DMA, typename ViewT>
+    static __device__ __forceinline__ void side(const ViewT &v, int n, const Rates &r, const Args &a) {
+        uint64_t ord;
+        const int64_t T = heuristic_wave<DMA, Lane<TT, DMA>>((1u << n) - 1u, v, r, &ord);
+        put_heuristic(a.out, ord, n, T);
+    }
 };
 static_assert(MemRule::words(TGO_MAX_MEM_N) <= EX_THREADS, "one word of the set table per thread");
 
 // Time path of the group (as classify_group) or TGO_EINVAL (a footprint
-// outside [0, cap]); clears the accumulator and fills the set table (a set
+// outside [0, cap]); clears the accumulators and fills the set table (a set
 // fits if its footprints sum to at most cap; cap <= 2^62, so a partial sum
 // that still fits plus one footprint cannot overflow).
 constexpr int MEM_PREP_THREADS = 1024;
@@ -134,10 +103,8 @@ __global__ __launch_bounds__(MEM_PREP_THREADS) void mem_prepare_kernel(const tgo
         const int c = classify_group_wave(tasks, n, r, lane);
         const int64_t m = lane < n ? mem[lane] : 0;
         const bool bad = __any(m < 0 || (uint64_t)m > cap);
-        if (lane == 0) {
-            *mode = c < 0 ? c : bad ? TGO_EINVAL : c;
-            exacc_init(acc);
-        }
+        if (lane == 0) *mode = c < 0 ? c : bad ? TGO_EINVAL : c;
+        exacc_init(acc, lane);
         // a footprint that fits nowhere is an error (above); the sums stay defined
         if (lane < n) ms[lane] = (m < 0 || (uint64_t)m > cap) ? cap : (uint64_t)m;
     }
@@ -153,72 +120,6 @@ __global__ __launch_bounds__(MEM_PREP_THREADS) void mem_prepare_kernel(const tgo
             }
         const unsigned long long b = __ballot(ok);
         if ((lane & 31) == 0) fits[s >> 5] = (uint32_t)(b >> (lane & 32));
-    }
-}
-
-// Block 0 writes the enumeration's part of the summary, the first wave of
-// block 1 Algorithm 1 with `update` simulating the ordered set under the limit.
-template <int DMA>
-__global__ __launch_bounds__(EX_FIN_THREADS) void mem_finalize_kernel(
-    const Partial *__restrict__ parts, int nparts, int n, uint64_t count, const ExAcc *__restrict__ acc,
-    const int *__restrict__ modep, const tgo_task *__restrict__ tasks, const uint32_t *__restrict__ fits, Rates r,
-    tgo_summary *out) {
-    using TT = uint64_t;
-    const int mode = *modep;
-    if (blockIdx.x == 0) {
-        finalize_block(parts, nparts, n, count, acc, mode, out);
-        return;
-    }
-    if (threadIdx.x >= 64) return;
-    if (mode < 0) {
-        if (threadIdx.x == 0) {
-            put_order(out->heur, 0, 0);
-            out->heur_ns = mode;
-        }
-        return;
-    }
-    __shared__ Quad<TT> Ht[MAXN];
-    __shared__ DRec<TT> Dt[MAXN];
-    __shared__ Slot<TT> Qs[MAXN];
-    if ((int)threadIdx.x < n) table_entry<TT>(tasks[threadIdx.x], r, &Ht[threadIdx.x], &Dt[threadIdx.x]);
-    wave_lds_sync();
-    uint64_t seq = 0;
-    RView<TT, 1, 1, RULE_MEMORY> v;
-    v.H = Ht;
-    v.D = Dt;
-    v.Q = Qs;
-    v.fits = fits;
-    v.seq = &seq;
-    uint64_t ord;
-    int64_t T;
-    if constexpr (DMA == DMA_TWO) {
-        using LaneT = RLane<TT, RULE_MEMORY>;
-        T = heuristic_wave<DMA, LaneT>(
-            n, v, r,
-            [&r](const LaneT &s) {
-                Fit3 u;
-                u.th = (int64_t)s.t;
-                u.tk = (int64_t)s.ke;
-                u.td = (int64_t)tail<DMA>(s, r);
-                return u;
-            },
-            &ord);
-    } else {
-        using LaneT = MChain<TT>;
-        T = heuristic_wave<DMA, LaneT>(
-            n, v, r,
-            [&r](const LaneT &s) {
-                Fit3 u;
-                u.th = (int64_t)s.x;
-                u.tk = (int64_t)s.kp;
-                u.td = (int64_t)tail<DMA>(s, r);
-                return u;
-            },
-            &ord);
-    }
-    if (threadIdx.x == 0) {
-        put_order(out->heur, ord, n);
-        out->heur_ns = T;
     }
 }
 
@@ -285,10 +186,10 @@ static int launch_mem(hipStream_t st, const tgo_task *t, const int64_t *mem, int
     uint32_t *fits = reinterpret_cast<uint32_t *>(sc.extra);
     hipLaunchKernelGGL(mem_prepare_kernel, dim3(1), dim3(MEM_PREP_THREADS), 0, st, t, mem, n, cap, r, sc.mode, sc.acc,
                        fits);
-    rc = enum_launch<MemRule, M, STORE, DMA>(st, t, n, r, MemRule::Args{fits}, n_sub, out, blocks, sc);
+    rc = enum_launch<MemRule, M, STORE, DMA>(st, t, n, r, MemRule::Args{fits, d_out}, n_sub, out, blocks, sc);
     if (rc) return rc;
-    hipLaunchKernelGGL(mem_finalize_kernel<DMA>, dim3(2), dim3(EX_FIN_THREADS), 0, st, sc.parts, (int)blocks, n,
-                       factorial(n), sc.acc, sc.mode, t, fits, r, d_out);
+    hipLaunchKernelGGL(rule_finalize, dim3(1), dim3(EX_FIN_THREADS), 0, st, sc.parts, (int)blocks, n, factorial(n),
+                       sc.acc, sc.mode, d_out);
     TGO_HIP(hipGetLastError());
     return TGO_OK;
 }

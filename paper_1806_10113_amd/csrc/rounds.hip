@@ -15,9 +15,10 @@
 //     to the engine just in time), or at the next arrival if the buffer is
 //     empty then.  One lane per experiment.
 //
-// The window formulation of the single-group kernels assumes an HtD engine
-// busy without gaps; dependencies break that, so this path steps events
-// directly: at each instant every finished command retires, then every ready
+// NoReorder runs the window formulation (rule_dev.h, RULE_ROUNDS): an HtD that
+// depends on a DtH waits at a gate, in launch order like everything else.  The
+// proxy's groups depend on when commands start and end, so the Heuristic setup
+// steps events: at each instant every finished command retires, then every ready
 // queue head starts, then the proxy looks, until nothing changes; time then
 // advances to the earliest completion estimate (remaining transfer work is
 // exact in 1/q solo-ns, estimates rounded up to whole ns, overlapped HtD and
@@ -26,28 +27,18 @@
 // transfer queue holding, per submitted group, its HtDs then its DtHs.
 #include <hip/hip_runtime.h>
 
-#include "enum_dev.h"
+#include "enum_kernel.h"
 #include "heur_dev.h"
+#include "rule_dev.h"
 #include "tables_dev.h"
 #include "tgo_internal.h"
 
 namespace tgo {
 
-constexpr int RD_THREADS = 256;
-constexpr int RD_MAX_BLOCKS = 4096;
-
-__device__ __forceinline__ uint32_t nib(uint64_t v, int i) { return (uint32_t)(v >> (4 * i)) & 15u; }
-__device__ __forceinline__ uint64_t set_nib(uint64_t v, int i, uint32_t x) {
-    return (v & ~(15ull << (4 * i))) | ((uint64_t)x << (4 * i));
-}
-
-struct Dur {
-    int64_t h, k, d;
-};
-
-// Event-stepping state of one simulation.
+// Event-stepping state of one simulation (the proxy's), the same on every lane.
+template <typename TT>
 struct RSim {
-    int64_t t;
+    TT t;
     uint64_t seq;    // nibble j: task at submitted position j
     uint64_t posof;  // nibble x: position of task x (once submitted)
     uint32_t gend;   // bit j: position j closes a submitted group
@@ -61,10 +52,11 @@ struct RSim {
     int xb, xe, xo;
     bool hrun, krun, drun;  // one engine: hrun/drun say which transfer runs
     int hpos, dpos;         // position of the running transfer(s)
-    int64_t uh, ud, kend;   // remaining transfer work (1/q ns), kernel end
+    TT uh, ud, kend;        // remaining transfer work (1/q ns), kernel end
 };
 
-__device__ __forceinline__ void rsim_init(RSim &s) {
+template <typename TT>
+__device__ __forceinline__ void rsim_init(RSim<TT> &s) {
     s.t = 0;
     s.seq = 0;
     s.posof = 0;
@@ -78,36 +70,32 @@ __device__ __forceinline__ void rsim_init(RSim &s) {
     s.uh = s.ud = s.kend = 0;
 }
 
-// Append a group of tasks (in launch order) at the current instant.
-__device__ __forceinline__ void rsim_submit(RSim &s, const uint8_t *order, int g) {
-    for (int i = 0; i < g; ++i) {
-        const int j = s.nsub + i;
-        s.seq = set_nib(s.seq, j, order[i]);
-        s.posof = set_nib(s.posof, order[i], (uint32_t)j);
-    }
+// Append a group of g tasks (in launch order, one nibble each) at the current instant.
+template <typename TT>
+__device__ __forceinline__ void rsim_submit(RSim<TT> &s, uint64_t order, int g) {
+    s.seq |= order << (4 * s.nsub);
+    for (int i = 0; i < g; ++i) s.posof |= (uint64_t)(s.nsub + i) << (4 * nibble(order, i));
     s.nsub += g;
     s.gend |= 1u << (s.nsub - 1);
 }
 
-__device__ __forceinline__ uint64_t ceil_div_u64(uint64_t u, uint64_t p) { return (u + p - 1) / p; }
-
 // The HtD at position j may start once the DtH of the same worker's previous
-// task has ended.
-__device__ __forceinline__ bool dep_ok(const RSim &s, int j, int R) {
-    const uint32_t x = nib(s.seq, j);
-    if (x % (uint32_t)R == 0) return true;
-    return (uint32_t)s.d_done > nib(s.posof, x - 1);
+// task has ended (dep: bit x = task x depends on task x - 1).
+template <typename TT>
+__device__ __forceinline__ bool dep_ok(const RSim<TT> &s, int j, uint32_t dep) {
+    const uint32_t x = nibble(s.seq, j);
+    if (!((dep >> x) & 1u)) return true;
+    return (uint32_t)s.d_done > nibble(s.posof, x - 1);
 }
 
 // One pass at the current instant: retire finished commands, then start every
 // ready head.  Returns whether anything changed; finished DtHs are reported
 // in *arrived (bit x: the worker's next task x became available), the start
 // of the HtD at position trig in *trig_started.
-template <bool ONE>
-__device__ __forceinline__ bool rsim_pass(RSim &s, const Dur *tab, int R, const Rates &r, int trig,
+template <bool ONE, typename TT, typename ViewT>
+__device__ __forceinline__ bool rsim_pass(RSim<TT> &s, const ViewT &v, const Rates &r, int trig,
                                           uint32_t *arrived, bool *trig_started) {
     bool changed = false;
-    const int64_t q = int64_t(1) << r.q_log2;
     // retire
     if (s.hrun && s.uh == 0) { s.hrun = false; ++s.h_done; changed = true; }
     if (s.krun && s.kend == s.t) { s.krun = false; ++s.k_done; changed = true; }
@@ -115,21 +103,20 @@ __device__ __forceinline__ bool rsim_pass(RSim &s, const Dur *tab, int R, const 
         s.drun = false;
         ++s.d_done;
         changed = true;
-        const uint32_t x = nib(s.seq, s.dpos);
-        if (x % (uint32_t)R + 1 < (uint32_t)R) *arrived |= 1u << (x + 1);
+        *arrived |= (2u << nibble(s.seq, s.dpos)) & v.dep;
     }
     // start ready heads
     if constexpr (!ONE) {
-        if (!s.hrun && s.hc < s.nsub && dep_ok(s, s.hc, R)) {
+        if (!s.hrun && s.hc < s.nsub && dep_ok(s, s.hc, v.dep)) {
             s.hpos = s.hc++;
-            s.uh = q * tab[nib(s.seq, s.hpos)].h;
+            s.uh = v.task(nibble(s.seq, s.hpos)).h << r.q_log2;
             s.hrun = true;
             changed = true;
             if (s.hpos == trig) *trig_started = true;
         }
         if (!s.drun && s.dc < s.nsub && s.dc < s.k_done) {
             s.dpos = s.dc++;
-            s.ud = q * tab[nib(s.seq, s.dpos)].d;
+            s.ud = v.task(nibble(s.seq, s.dpos)).d << r.q_log2;
             s.drun = true;
             changed = true;
         }
@@ -145,9 +132,9 @@ __device__ __forceinline__ bool rsim_pass(RSim &s, const Dur *tab, int R, const 
             const int len = s.xe - s.xb;
             if (s.xo < len) {
                 const int j = s.xb + s.xo;
-                if (dep_ok(s, j, R)) {
+                if (dep_ok(s, j, v.dep)) {
                     s.hpos = j;
-                    s.uh = q * tab[nib(s.seq, j)].h;
+                    s.uh = v.task(nibble(s.seq, j)).h << r.q_log2;
                     s.hrun = true;
                     ++s.xo;
                     changed = true;
@@ -157,7 +144,7 @@ __device__ __forceinline__ bool rsim_pass(RSim &s, const Dur *tab, int R, const 
                 const int j = s.xb + s.xo - len;
                 if (s.k_done > j) {
                     s.dpos = j;
-                    s.ud = q * tab[nib(s.seq, j)].d;
+                    s.ud = v.task(nibble(s.seq, j)).d << r.q_log2;
                     s.drun = true;
                     ++s.xo;
                     changed = true;
@@ -167,7 +154,7 @@ __device__ __forceinline__ bool rsim_pass(RSim &s, const Dur *tab, int R, const 
     }
     if (!s.krun && s.kc < s.nsub && s.kc < s.h_done) {
         const int j = s.kc++;
-        s.kend = s.t + tab[nib(s.seq, j)].k;
+        s.kend = s.t + v.task(nibble(s.seq, j)).k;
         s.krun = true;
         changed = true;
     }
@@ -175,252 +162,31 @@ __device__ __forceinline__ bool rsim_pass(RSim &s, const Dur *tab, int R, const 
 }
 
 // Advance to the earliest completion estimate.  Returns false when nothing runs.
-template <bool ONE>
-__device__ __forceinline__ bool rsim_advance(RSim &s, const Rates &r) {
+template <bool ONE, typename TT>
+__device__ __forceinline__ bool rsim_advance(RSim<TT> &s, const Rates &r) {
     if (!s.hrun && !s.krun && !s.drun) return false;
-    const uint64_t q = 1ull << r.q_log2;
     const bool both = !ONE && s.hrun && s.drun;
-    const uint64_t rh = both ? r.p_h : q, rd = both ? r.p_d : q;
-    const int64_t INF = INT64_MAX;
-    const int64_t eh = s.hrun ? (int64_t)ceil_div_u64((uint64_t)s.uh, rh) : INF;
-    const int64_t ed = s.drun ? (int64_t)ceil_div_u64((uint64_t)s.ud, rd) : INF;
-    const int64_t ek = s.krun ? s.kend - s.t : INF;
-    int64_t dt = eh < ed ? eh : ed;
+    const TT q = TT(1) << r.q_log2;
+    constexpr TT INF = ~TT(0);
+    const TT eh = s.hrun ? (both ? (TT)ceil_p(s.uh, r.p_h, r.inv_ph, r.c_ph) : ceil_q(s.uh, r.q_log2)) : INF;
+    const TT ed = s.drun ? (both ? (TT)ceil_p(s.ud, r.p_d, r.inv_pd, r.c_pd) : ceil_q(s.ud, r.q_log2)) : INF;
+    const TT ek = s.krun ? s.kend - s.t : INF;
+    TT dt = eh < ed ? eh : ed;
     dt = ek < dt ? ek : dt;
-    if (s.hrun) s.uh = eh == dt ? 0 : s.uh - (int64_t)rh * dt;
-    if (s.drun) s.ud = ed == dt ? 0 : s.ud - (int64_t)rd * dt;
+    if (s.hrun) s.uh = eh == dt ? TT(0) : s.uh - (both ? TT(r.p_h) : q) * dt;
+    if (s.drun) s.ud = ed == dt ? TT(0) : s.ud - (both ? TT(r.p_d) : q) * dt;
     s.t += dt;
     return true;
 }
 
-// NoReorder: simulate one fully queued launch sequence (groups are rounds).
-template <bool ONE>
-__device__ int64_t rsim_noreorder(RSim &s, const Dur *tab, int R, const Rates &r) {
-    for (;;) {
-        uint32_t arrived = 0;
-        bool trig = false;
-        while (rsim_pass<ONE>(s, tab, R, r, -1, &arrived, &trig)) {}
-        if (!rsim_advance<ONE>(s, r)) break;
-    }
-    return s.t;
-}
-
-__device__ __forceinline__ bool valid_task(const tgo_task &t) {
-    return t.htd_ns >= 0 && t.kern_ns >= 0 && t.dth_ns >= 0 && t.htd_ns < MAX_DURATION &&
-           t.kern_ns < MAX_DURATION && t.dth_ns < MAX_DURATION;
-}
-
-// Per-lane accumulators over the ranks the lane owns (in increasing order).
-struct RAcc {
-    uint64_t min_t, min_r, max_t, max_r, sum_lo, sum_hi, fp;
-};
-
-template <bool ONE, bool STORE>
-__global__ __launch_bounds__(RD_THREADS) void rounds_kernel(const tgo_task *__restrict__ tasks, int T,
-                                                            int R, Rates r, uint32_t count,
-                                                            uint32_t tfact, int64_t *out,
-                                                            Partial *partials) {
-    __shared__ Dur tab[MAXN];
-    __shared__ int bad;
-    const int n = T * R;
-    if (threadIdx.x == 0) bad = 0;
-    __syncthreads();
-    if ((int)threadIdx.x < n) {
-        const tgo_task t = tasks[threadIdx.x];
-        if (!valid_task(t)) atomicOr(&bad, 1);
-        tab[threadIdx.x] = Dur{t.htd_ns, t.kern_ns, t.dth_ns};
-    }
-    __syncthreads();
-    if (bad) {
-        if (threadIdx.x == 0) {
-            Partial p = {};
-            p.status = TGO_ERANGE;
-            partials[blockIdx.x] = p;
-        }
-        return;
-    }
-    RAcc a;
-    a.min_t = ~0ull; a.min_r = ~0ull; a.max_t = 0; a.max_r = ~0ull;
-    a.sum_lo = 0; a.sum_hi = 0; a.fp = 0;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t rk64 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; rk64 < count; rk64 += stride) {
-        const uint32_t rk = (uint32_t)rk64;
-        // rank -> one worker order per round (pi_0 most significant)
-        uint8_t order[MAXN];
-        uint32_t rem = rk;
-        for (int rr = R - 1; rr >= 0; --rr) {
-            uint32_t d = rem % tfact;
-            rem /= tfact;
-            uint64_t list = 0;  // remaining workers, ascending, one per nibble (T <= 12)
-            for (int i = T - 1; i >= 0; --i) list = (list << 4) | (uint64_t)i;
-            uint32_t f = tfact;
-            for (int i = 0; i < T; ++i) {
-                f /= (uint32_t)(T - i);
-                const uint32_t c = d / f;
-                d -= c * f;
-                const uint32_t w = (uint32_t)(list >> (4 * c)) & 15u;
-                const uint64_t lo = list & ((1ull << (4 * c)) - 1ull);
-                const uint64_t hi = (list >> (4 * c + 4)) << (4 * c);
-                list = lo | hi;
-                order[rr * T + i] = (uint8_t)(w * R + rr);
-            }
-        }
-        RSim s;
-        rsim_init(s);
-        for (int rr = 0; rr < R; ++rr) rsim_submit(s, order + rr * T, T);
-        const uint64_t Tt = (uint64_t)rsim_noreorder<ONE>(s, tab, R, r);
-        if constexpr (STORE) out[rk] = (int64_t)Tt;
-        if (Tt < a.min_t) { a.min_t = Tt; a.min_r = rk; }
-        if (Tt + 1 > a.max_t) { a.max_t = Tt + 1; a.max_r = rk; }
-        add128(a.sum_lo, a.sum_hi, Tt, 0);
-        a.fp += (2ull * rk + 1ull) * Tt;
-    }
-    Partial p;
-    p.min_t = a.min_t; p.min_r = a.min_r; p.max_t = a.max_t; p.max_r = a.max_r;
-    p.sum_lo = a.sum_lo; p.sum_hi = a.sum_hi; p.fp = a.fp; p.status = 0; p.pad = 0;
-    for (int m = 32; m >= 1; m >>= 1) {
-        const uint64_t mt = shfl_xor64(p.min_t, m), mr = shfl_xor64(p.min_r, m);
-        const uint64_t xt = shfl_xor64(p.max_t, m), xr = shfl_xor64(p.max_r, m);
-        const uint64_t sl = shfl_xor64(p.sum_lo, m), sh = shfl_xor64(p.sum_hi, m);
-        const uint64_t f = shfl_xor64(p.fp, m);
-        merge_min(p.min_t, p.min_r, mt, mr);
-        merge_max(p.max_t, p.max_r, xt, xr);
-        add128(p.sum_lo, p.sum_hi, sl, sh);
-        p.fp += f;
-    }
-    __shared__ Partial wsum[RD_THREADS / 64];
-    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x / 64] = p;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        Partial o = wsum[0];
-        for (int i = 1; i < RD_THREADS / 64; ++i) {
-            merge_min(o.min_t, o.min_r, wsum[i].min_t, wsum[i].min_r);
-            merge_max(o.max_t, o.max_r, wsum[i].max_t, wsum[i].max_r);
-            add128(o.sum_lo, o.sum_hi, wsum[i].sum_lo, wsum[i].sum_hi);
-            o.fp += wsum[i].fp;
-        }
-        o.status = 0;
-        o.pad = 0;
-        partials[blockIdx.x] = o;
-    }
-}
-
-// Launch sequence (task per position) of NoReorder rank rk.
-__device__ inline void rounds_unrank(int T, int R, uint64_t rk, uint64_t tfact, uint8_t *out) {
-    for (int rr = R - 1; rr >= 0; --rr) {
-        uint64_t d = rk % tfact;
-        rk /= tfact;
-        uint64_t list = 0;
-        for (int i = T - 1; i >= 0; --i) list = (list << 4) | (uint64_t)i;
-        uint64_t f = tfact;
-        for (int i = 0; i < T; ++i) {
-            f /= (uint64_t)(T - i);
-            const uint64_t c = d / f;
-            d -= c * f;
-            const uint64_t w = (list >> (4 * c)) & 15u;
-            const uint64_t lo = list & ((1ull << (4 * c)) - 1ull);
-            const uint64_t hi = (list >> (4 * c + 4)) << (4 * c);
-            list = lo | hi;
-            out[rr * T + i] = (uint8_t)(w * R + rr);
-        }
-    }
-    for (int i = T * R; i < 16; ++i) out[i] = 0xff;
-}
-
-__global__ __launch_bounds__(256) void rounds_finalize(const Partial *__restrict__ parts, int nparts,
-                                                       int T, int R, uint64_t count, uint64_t tfact,
-                                                       tgo_summary *out) {
-    __shared__ Partial red[256];
-    __shared__ int status;
-    if (threadIdx.x == 0) status = 0;
-    __syncthreads();
-    Partial p;
-    p.min_t = ~0ull; p.min_r = ~0ull; p.max_t = 0; p.max_r = ~0ull;
-    p.sum_lo = 0; p.sum_hi = 0; p.fp = 0; p.status = 0; p.pad = 0;
-    for (int i = threadIdx.x; i < nparts; i += blockDim.x) {
-        const Partial q = parts[i];
-        if (q.status != 0) atomicMin(&status, q.status);
-        merge_min(p.min_t, p.min_r, q.min_t, q.min_r);
-        merge_max(p.max_t, p.max_r, q.max_t, q.max_r);
-        add128(p.sum_lo, p.sum_hi, q.sum_lo, q.sum_hi);
-        p.fp += q.fp;
-    }
-    red[threadIdx.x] = p;
-    __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
-            const Partial q = red[threadIdx.x + s];
-            Partial &o = red[threadIdx.x];
-            merge_min(o.min_t, o.min_r, q.min_t, q.min_r);
-            merge_max(o.max_t, o.max_r, q.max_t, q.max_r);
-            add128(o.sum_lo, o.sum_hi, q.sum_lo, q.sum_hi);
-            o.fp += q.fp;
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        const Partial &o = red[0];
-        tgo_summary s;
-        s.n = T * R;
-        s.status = status;
-        s.count = count;
-        for (int i = 0; i < 16; ++i) { s.best[i] = 0xff; s.worst[i] = 0xff; s.heur[i] = 0xff; }
-        s.heur_ns = -1;
-        if (status != 0) {
-            s.min_ns = s.max_ns = 0;
-            s.argmin_rank = s.argmax_rank = 0;
-            s.sum_lo = s.sum_hi = 0;
-            s.fingerprint = 0;
-            s.mean_ns = 0.0;
-        } else {
-            s.min_ns = (int64_t)o.min_t;
-            s.argmin_rank = o.min_r;
-            s.max_ns = (int64_t)(o.max_t - 1);
-            s.argmax_rank = o.max_r;
-            s.sum_lo = o.sum_lo;
-            s.sum_hi = o.sum_hi;
-            s.fingerprint = o.fp;
-            if (o.sum_hi == 0) {
-                const uint64_t qt = o.sum_lo / count, rm = o.sum_lo % count;
-                s.mean_ns = (double)qt + (double)rm / (double)count;
-            } else {
-                s.mean_ns = ((double)o.sum_hi * 18446744073709551616.0 + (double)o.sum_lo) / (double)count;
-            }
-            rounds_unrank(T, R, o.min_r, tfact, s.best);
-            rounds_unrank(T, R, o.max_r, tfact, s.worst);
-        }
-        *out = s;
-    }
-}
-
-// Heuristic setup: one thread drives the proxy and the device model.
-template <bool ONE>
-__global__ __launch_bounds__(64) void rounds_heuristic_kernel(const tgo_task *__restrict__ tasks, int T,
-                                                              int R, Rates r, tgo_summary *out,
-                                                              uint16_t *groups) {
-    __shared__ Dur tab[MAXN];
-    __shared__ Quad<uint64_t> Ht[MAXN];
-    __shared__ DRec<uint64_t> Dt[MAXN];
-    __shared__ Slot<uint64_t> Qs[MAXN];
-    if (threadIdx.x != 0) return;
-    const int n = T * R;
-    for (int x = 0; x < n; ++x) {
-        const tgo_task t = tasks[x];
-        if (!valid_task(t)) {
-            out->heur_ns = TGO_ERANGE;
-            if (groups) *groups = 0;
-            return;
-        }
-        tab[x] = Dur{t.htd_ns, t.kern_ns, t.dth_ns};
-    }
-    View<uint64_t, 1, 1> v;
-    v.H = Ht;
-    v.D = Dt;
-    v.Q = Qs;
-    RSim s;
+// Heuristic setup: one wave drives the proxy and the device model.  v: the
+// tables of all tasks; first: the tasks waiting at t = 0.
+template <bool ONE, typename TT, typename ViewT>
+__device__ __forceinline__ void rounds_proxy(const ViewT &v, uint32_t first, int n, const Rates &r, tgo_summary *out,
+                                             uint16_t *groups) {
+    RSim<TT> s;
     rsim_init(s);
-    uint32_t buffer = 0;
-    for (int w = 0; w < T; ++w) buffer |= 1u << (w * R);
+    uint32_t buffer = first;
     bool armed = true;
     int trig = -1;
     for (;;) {
@@ -428,21 +194,15 @@ __global__ __launch_bounds__(64) void rounds_heuristic_kernel(const tgo_task *__
         while (changed) {
             uint32_t arrived = 0;
             bool started = false;
-            changed = rsim_pass<ONE>(s, tab, R, r, trig, &arrived, &started);
+            changed = rsim_pass<ONE>(s, v, r, trig, &arrived, &started);
             buffer |= arrived;
             armed = armed || started;
             if (armed && buffer) {
-                // the group: waiting tasks in ascending index, ordered by Algorithm 1
-                uint8_t mem[MAXN];
-                int g = 0;
-                for (int x = 0; x < n; ++x)
-                    if ((buffer >> x) & 1u) mem[g++] = (uint8_t)x;
-                for (int i = 0; i < g; ++i) table_entry<uint64_t>(tasks[mem[i]], r, &Ht[i], &Dt[i]);
-                uint8_t ord[MAXN];
-                heuristic_order(g, v, r, ord);
-                uint8_t launch[MAXN];
-                for (int i = 0; i < g; ++i) launch[i] = mem[ord[i]];
-                rsim_submit(s, launch, g);
+                // the group: the waiting tasks, ordered by Algorithm 1
+                uint64_t ord;
+                if constexpr (ONE) heuristic_wave<DMA_ONE, Lane<TT>>(buffer, v, r, &ord);
+                else heuristic_wave<DMA_TWO, CLane<TT>>(buffer, v, r, &ord);
+                rsim_submit(s, ord, __popc(buffer));
                 trig = s.nsub - 1;
                 buffer = 0;
                 armed = false;
@@ -451,58 +211,191 @@ __global__ __launch_bounds__(64) void rounds_heuristic_kernel(const tgo_task *__
         }
         if (!rsim_advance<ONE>(s, r)) break;
     }
-    uint8_t seq[16];
-    for (int j = 0; j < 16; ++j) seq[j] = j < n ? (uint8_t)nib(s.seq, j) : (uint8_t)0xff;
-    for (int j = 0; j < 16; ++j) out->heur[j] = seq[j];
-    out->heur_ns = s.t;
-    if (groups) *groups = (uint16_t)s.gend;
+    put_heuristic(out, s.seq, n, (int64_t)s.t);
+    if (groups && threadIdx.x == 0) *groups = (uint16_t)s.gend;
 }
 
-int launch_summary_finalize(const Partial *d_parts, int nparts, int T, int R, uint64_t count, uint64_t tfact,
-                            tgo_summary *d_out, hipStream_t st) {
-    hipLaunchKernelGGL(rounds_finalize, dim3(1), dim3(256), 0, st, d_parts, nparts, T, R, count, tfact, d_out);
+// Dependent tasks under the enumeration kernel (enum_kernel.h): a subtree
+// holds the orderings that share every earlier round and the last round's
+// first T - M positions; subtrees are taken in rank order.  Bound by the
+// latency of one lane's windows: four workers with four tasks each are 331,776
+// orderings, 55,296 lanes of 28 windows.  Stepping the events of every
+// ordering in 64-bit time took 198 us for them and the Heuristic setup, on one
+// thread after it, 115 us; together, side by side, 313 -> 48 us per call.
+struct RoundsRule {
+    struct Args {
+        int T, R;
+        uint32_t tfact;  // T!
+        tgo_summary *out;  // the Heuristic setup's fields
+        uint16_t *groups;
+    };
+    static constexpr bool SIDE = true;
+    template <typename TT>
+    using View = RView<TT, 1, EX_THREADS, RULE_ROUNDS>;
+    template <typename TT, int DMA>
+    using Lane = std::conditional_t<DMA == DMA_TWO, RLane<TT, RULE_ROUNDS>, SubChain<TT, RULE_ROUNDS>>;
+    template <typename TT, int DMA>
+    static constexpr int min_waves() { return sizeof(TT) == 4 ? 4 : 1; }
+    static constexpr bool queue(bool one_dma) { return !one_dma; }
+    static __host__ __device__ constexpr size_t lds_bytes(int) { return 0; }
+    template <typename ViewT>
+    static __device__ __forceinline__ void load(ViewT &v, unsigned char *, const Args &a, int n, uint64_t *seq) {
+        v.seq = seq;
+        v.pos = 0;
+        v.dep = v.opens = 0;
+        for (int x = 0; x < n; ++x) v.dep |= (x % a.R != 0 ? 1u : 0u) << x;
+        for (int j = a.T; j < n; j += a.T) v.opens |= 1u << j;
+    }
+    template <typename TT, int DMA, typename ViewT>
+    static __device__ __forceinline__ void side(const ViewT &v, int n, const Rates &r, const Args &a) {
+        rounds_proxy<DMA == DMA_ONE, TT>(v, ((1u << n) - 1u) & ~v.dep, n, r, a.out, a.groups);
+    }
+    template <int DMA, typename LaneT, typename ViewT>
+    static __device__ __forceinline__ uint64_t prefix(LaneT &st, uint32_t s, int n, int m, ViewT &v, const Rates &r,
+                                                      const Args &a, uint32_t *lex) {
+        lane_reset(st);
+        *lex = s;
+        uint64_t workers = 0;
+        for (int i = a.T - 1; i >= 0; --i) workers = (workers << 4) | (uint64_t)i;
+        uint32_t mf = 1;
+        for (int i = 2; i <= m; ++i) mf *= (uint32_t)i;
+        // weight of a round's digit, in subtrees; the last round's are its
+        // blocks of m! orderings
+        uint32_t weight = a.tfact / mf;
+        for (int i = 2; i < a.R; ++i) weight *= a.tfact;  // below n_sub < 2^32
+        uint32_t rem = s;
+        uint64_t pos = 0, list = 0;
+        for (int rr = 0; rr < a.R; ++rr) {
+            const bool last = rr == a.R - 1;
+            uint32_t d = rem;
+            if (!last) {
+                d = rem / weight;
+                rem -= d * weight;
+                weight = rr == a.R - 2 ? weight : weight / a.tfact;
+            }
+            list = workers;
+            uint32_t f = last ? a.tfact / mf : a.tfact;
+            const int np = last ? a.T - m : a.T;
+            for (int i = 0; i < np; ++i) {
+                f /= (uint32_t)(a.T - i);
+                const uint32_t c = d / f;
+                d -= c * f;
+                const uint32_t w = (uint32_t)(list >> (4 * c)) & 15u;
+                const uint64_t lo = list & ((1ull << (4 * c)) - 1ull);
+                list = lo | ((list >> (4 * c + 4)) << (4 * c));
+                const uint32_t x = w * (uint32_t)a.R + (uint32_t)rr;
+                const int j = rr * a.T + i;
+                v.pos = pos;
+                window<DMA>(st, j, x, v, r);
+                pos |= (uint64_t)j << (4 * x);
+            }
+        }
+        v.pos = pos;
+        // the workers left in the last round as tasks, ascending
+        uint64_t left = 0;
+        for (int i = 0; i < m; ++i)
+            left |= (uint64_t)(((uint32_t)(list >> (4 * i)) & 15u) * (uint32_t)a.R + (uint32_t)a.R - 1u) << (4 * i);
+        return left;
+    }
+};
+
+// Time path of the group, or TGO_ERANGE; clears the accumulators.
+__global__ __launch_bounds__(64) void rounds_prepare_kernel(const tgo_task *__restrict__ tasks, int n, Rates r,
+                                                            int *mode, ExAcc *acc) {
+    const int m = classify_group_wave(tasks, n, r, threadIdx.x);
+    if (threadIdx.x == 0) *mode = m;
+    exacc_init(acc, threadIdx.x);
+}
+
+// Launch sequence (task per position, one nibble each) of NoReorder rank rk.
+__device__ __forceinline__ uint64_t rounds_unrank(int T, int R, uint64_t rk, uint32_t tfact) {
+    uint32_t rem = (uint32_t)rk;  // (T!)^R < 2^32
+    uint64_t out = 0;
+    for (int rr = R - 1; rr >= 0; --rr) {
+        uint32_t d = rem % tfact;
+        rem /= tfact;
+        uint64_t list = 0;
+        for (int i = T - 1; i >= 0; --i) list = (list << 4) | (uint64_t)i;
+        uint32_t f = tfact;
+        for (int i = 0; i < T; ++i) {
+            f /= (uint32_t)(T - i);
+            const uint32_t c = d / f;
+            d -= c * f;
+            const uint64_t w = (list >> (4 * c)) & 15u;
+            const uint64_t lo = list & ((1ull << (4 * c)) - 1ull);
+            list = lo | ((list >> (4 * c + 4)) << (4 * c));
+            out |= (w * (uint64_t)R + (uint64_t)rr) << (4 * (rr * T + i));
+        }
+    }
+    return out;
+}
+
+__global__ __launch_bounds__(EX_FIN_THREADS) void rounds_finalize_kernel(
+    const Partial *__restrict__ parts, int nparts, int T, int R, uint64_t count, uint32_t tfact,
+    const ExAcc *__restrict__ acc, const int *__restrict__ modep, tgo_summary *out, uint16_t *groups) {
+    const int mode = *modep;
+    if (mode < 0) {
+        put_heuristic(out, 0, 0, mode);
+        if (groups && threadIdx.x == 0) *groups = 0;
+    }
+    finalize_block(parts, nparts, T * R, count, acc, mode,
+                   [=](uint64_t rk) { return rounds_unrank(T, R, rk, tfact); }, out);
+}
+
+template <int M, bool STORE, int DMA>
+static int launch_rounds_m(hipStream_t st, const tgo_task *t, int T, int R, const Rates &r, uint64_t count,
+                           uint32_t tf, int64_t *out, tgo_summary *d_out, uint16_t *d_groups) {
+    const void *k32 = reinterpret_cast<const void *>(&enum_kernel<RoundsRule, uint32_t, M, STORE, DMA>);
+    const uint32_t n_sub = (uint32_t)(count / factorial(M));
+    const int n = T * R;
+    uint32_t blocks = 0;
+    EnumScratch sc;
+    int rc = enum_grid(k32, enum_shm_bytes<RoundsRule, uint32_t>(n, DMA == DMA_ONE), n_sub, 0, ExScratch{}, st,
+                       &blocks, &sc);
+    if (rc) return rc;
+    hipLaunchKernelGGL(rounds_prepare_kernel, dim3(1), dim3(64), 0, st, t, n, r, sc.mode, sc.acc);
+    rc = enum_launch<RoundsRule, M, STORE, DMA>(st, t, n, r, RoundsRule::Args{T, R, tf, d_out, d_groups}, n_sub, out, blocks, sc);
+    if (rc) return rc;
+    hipLaunchKernelGGL(rounds_finalize_kernel, dim3(1), dim3(EX_FIN_THREADS), 0, st, sc.parts, (int)blocks, T, R,
+                       count, tf, sc.acc, sc.mode, d_out, d_groups);
     TGO_HIP(hipGetLastError());
     return TGO_OK;
+}
+
+// Positions of the last round walked depth first per lane (TGO_ROUNDS_M, 1..4,
+// overrides it): the deepest that leaves 32,768 subtrees, as in rule_depth.
+// Four workers with four tasks: 62 / 51 / 48 us per call with 1 / 2 / 3.
+static int choose_rounds_m(int T, uint64_t count) {
+    int top = T < 4 ? T : 4;
+    if (const char *e = std::getenv("TGO_ROUNDS_M")) {
+        const int m = std::atoi(e);
+        if (m >= 1 && m <= top) return m;
+    }
+    while (top > 1 && count / factorial(top) < 32768) --top;
+    return top;
+}
+
+template <bool STORE, int DMA>
+static int launch_rounds_dma(hipStream_t st, const tgo_task *t, int T, int R, const Rates &r, uint64_t count,
+                             uint32_t tf, int64_t *out, tgo_summary *d_out, uint16_t *d_groups) {
+    switch (choose_rounds_m(T, count)) {
+        case 1: return launch_rounds_m<1, STORE, DMA>(st, t, T, R, r, count, tf, out, d_out, d_groups);
+        case 2: return launch_rounds_m<2, STORE, DMA>(st, t, T, R, r, count, tf, out, d_out, d_groups);
+        case 3: return launch_rounds_m<3, STORE, DMA>(st, t, T, R, r, count, tf, out, d_out, d_groups);
+        default: return launch_rounds_m<4, STORE, DMA>(st, t, T, R, r, count, tf, out, d_out, d_groups);
+    }
 }
 
 int launch_rounds(const Rates &r, const tgo_task *d_tasks, int T, int R, int64_t *d_per_order,
                   tgo_summary *d_out, uint16_t *d_groups, hipStream_t st) {
-    const uint64_t tf = factorial(T);
+    const uint32_t tf = (uint32_t)factorial(T);
     uint64_t count = 1;
     for (int i = 0; i < R; ++i) count *= tf;
-    const uint64_t want = (count + RD_THREADS - 1) / RD_THREADS;
-    const uint32_t blocks = (uint32_t)(want < RD_MAX_BLOCKS ? want : RD_MAX_BLOCKS);
-    Partial *parts = nullptr;
-    int rc = workspace(sizeof(Partial) * blocks, (void **)&parts, st);
-    if (rc) return rc;
-    const bool one = r.one_dma != 0;
-    const uint32_t c32 = (uint32_t)count, t32 = (uint32_t)tf;
-    if (one) {
-        if (d_per_order)
-            hipLaunchKernelGGL((rounds_kernel<true, true>), dim3(blocks), dim3(RD_THREADS), 0, st, d_tasks, T,
-                               R, r, c32, t32, d_per_order, parts);
-        else
-            hipLaunchKernelGGL((rounds_kernel<true, false>), dim3(blocks), dim3(RD_THREADS), 0, st, d_tasks, T,
-                               R, r, c32, t32, nullptr, parts);
-    } else {
-        if (d_per_order)
-            hipLaunchKernelGGL((rounds_kernel<false, true>), dim3(blocks), dim3(RD_THREADS), 0, st, d_tasks, T,
-                               R, r, c32, t32, d_per_order, parts);
-        else
-            hipLaunchKernelGGL((rounds_kernel<false, false>), dim3(blocks), dim3(RD_THREADS), 0, st, d_tasks,
-                               T, R, r, c32, t32, nullptr, parts);
-    }
-    TGO_HIP(hipGetLastError());
-    hipLaunchKernelGGL(rounds_finalize, dim3(1), dim3(256), 0, st, parts, (int)blocks, T, R, count, tf, d_out);
-    TGO_HIP(hipGetLastError());
-    if (one)
-        hipLaunchKernelGGL(rounds_heuristic_kernel<true>, dim3(1), dim3(64), 0, st, d_tasks, T, R, r, d_out,
-                           d_groups);
-    else
-        hipLaunchKernelGGL(rounds_heuristic_kernel<false>, dim3(1), dim3(64), 0, st, d_tasks, T, R, r, d_out,
-                           d_groups);
-    TGO_HIP(hipGetLastError());
-    return TGO_OK;
+    if (r.one_dma)
+        return d_per_order ? launch_rounds_dma<true, DMA_ONE>(st, d_tasks, T, R, r, count, tf, d_per_order, d_out, d_groups)
+                           : launch_rounds_dma<false, DMA_ONE>(st, d_tasks, T, R, r, count, tf, nullptr, d_out, d_groups);
+    return d_per_order ? launch_rounds_dma<true, DMA_TWO>(st, d_tasks, T, R, r, count, tf, d_per_order, d_out, d_groups)
+                       : launch_rounds_dma<false, DMA_TWO>(st, d_tasks, T, R, r, count, tf, nullptr, d_out, d_groups);
 }
 
 }  // namespace tgo

@@ -40,8 +40,9 @@ struct RView : View<TT, TS, QS> {
     const int32_t *units;  // CONCURRENT: units per task, and the device's
     int32_t cap;
     const uint32_t *fits;  // MEMORY: bit s = the tasks of set s fit together
-    uint64_t prev;         // ROUNDS: position of each worker's task of the previous round
-    int tasks_per_worker;
+    uint64_t pos;          // ROUNDS: position of each placed task of an earlier round (one nibble each)
+    uint32_t dep;          // ROUNDS: bit x = task x waits for the end of task x - 1
+    uint32_t opens;        // ROUNDS, one engine: bit j = position j opens a round's sub-group
 };
 
 template <typename TT, int KIND>
@@ -86,8 +87,7 @@ __device__ __forceinline__ int gate(RLane<TT, KIND> &s, int j, uint32_t x, const
         s.held = set;
         return s.a;
     } else if constexpr (KIND == RULE_ROUNDS) {
-        const uint32_t w = x / (uint32_t)v.tasks_per_worker;
-        return x % (uint32_t)v.tasks_per_worker == 0 ? 0 : (int)nibble(v.prev, (int)w) + 1;
+        return (v.dep >> x) & 1u ? (int)nibble(v.pos, (int)x - 1) + 1 : 0;
     } else {
         return 0;
     }
@@ -278,6 +278,55 @@ __device__ __forceinline__ TT tail(const RLane<TT, KIND> &s, const Rates &r) {
         }
         return T;
     }
+}
+
+// One DMA engine, the ordering cut into consecutive sub-groups, each launched
+// as its HtDs, then its DtHs, behind the previous one (MEMORY: as long as its
+// buffers fit together; ROUNDS: one per round, whose DtHs all end before the
+// next round's HtDs, so no dependency ever waits).  Transfers never overlap:
+// HtDs back to back, K_i = max(HtD_i end, K_{i-1} end) + k_i, and the
+// sub-group's DtHs end at max(last HtD end, max_p (K_p - sum_{s<p} d_s)) + sum d.
+template <typename TT, int KIND>
+struct SubChain {
+    using ST = typename Signed<TT>::type;
+    TT x;          // end of the open sub-group's last HtD (none open: of the last DtH)
+    TT kp;         // end of the last kernel
+    ST emax;       // open sub-group: max of (K_p end - its DtH time before p)
+    TT dsum;       // open sub-group: its DtH time so far
+    uint32_t set;  // MEMORY: the open sub-group's tasks
+};
+template <typename TT, int KIND>
+__device__ __forceinline__ void lane_reset(SubChain<TT, KIND> &s) {
+    using ST = typename Signed<TT>::type;
+    s.x = s.kp = s.dsum = 0;
+    s.emax = (ST)(((TT)1) << (8 * sizeof(TT) - 1));  // most negative
+    s.set = 0;
+}
+template <int DMA, typename TT, int KIND>
+__device__ __forceinline__ TT tail(const SubChain<TT, KIND> &s, const Rates &) {
+    using ST = typename Signed<TT>::type;
+    const ST e = (ST)s.x > s.emax ? (ST)s.x : s.emax;
+    return (TT)(e + (ST)s.dsum);
+}
+template <int DMA, bool PUT = true, typename TT, int KIND, typename ViewT>
+__device__ __forceinline__ void window(SubChain<TT, KIND> &s, int j, uint32_t x, const ViewT &v, const Rates &r) {
+    using ST = typename Signed<TT>::type;
+    const Quad<TT> tx = v.task(x);
+    bool close;
+    if constexpr (KIND == RULE_MEMORY) {
+        // x alone fits, so the first task of a sub-group never closes one
+        const uint32_t set = s.set | (1u << x);
+        close = !((v.fits[set >> 5] >> (set & 31u)) & 1u);
+        s.set = close ? 1u << x : set;
+    } else {
+        close = (v.opens >> j) & 1u;
+    }
+    s.x = (close ? tail<DMA>(s, r) : s.x) + tx.h;
+    s.kp = tmax(s.x, s.kp) + tx.k;
+    const TT before = close ? TT(0) : s.dsum;
+    const ST e = (ST)s.kp - (ST)before;
+    s.emax = close ? e : (e > s.emax ? e : s.emax);
+    s.dsum = before + tx.d;
 }
 
 }  // namespace tgo
