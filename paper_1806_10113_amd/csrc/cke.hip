@@ -162,7 +162,7 @@ __device__ int64_t cke_sim(uint64_t seq, int n, const CTab &tb, int cap, const R
 // scan of running kernels where a kernel does not fit at once.  As a lane per
 // ordering stepping all of its events in 64-bit time, n = 12 took 123.5 ms
 // (479M orderings); with shared prefixes, windows and 32-bit time 4.6 ms.
-struct CkeRule : SetMajorPrefix {
+struct CkeRule : GroupRule {
     struct Args {
         const int32_t *units;
         int32_t cap;
@@ -180,7 +180,14 @@ struct CkeRule : SetMajorPrefix {
     static constexpr int min_waves() { return sizeof(TT) == 4 ? 6 : 1; }
     static constexpr bool queue(bool) { return true; }
     static __host__ __device__ constexpr size_t lds_bytes(int) { return sizeof(int32_t) * MAXN; }
-    template <typename ViewT>
+    static __device__ __forceinline__ int status(const tgo_task *tasks, int n, const Rates &r, const Args &a,
+                                                 int lane) {
+        const int m = classify_group_wave(tasks, n, r, lane);
+        const int32_t u = lane < n ? a.units[lane] : 1;
+        const bool bad = __any(u < 1 || u > a.cap);
+        return m < 0 ? m : bad ? TGO_EINVAL : m;
+    }
+    template <bool SMALL, typename ViewT>
     static __device__ __forceinline__ void load(ViewT &v, unsigned char *lds, const Args &a, int n, uint64_t *seq) {
         int32_t *u = reinterpret_cast<int32_t *>(lds);
         if ((int)threadIdx.x < n) u[threadIdx.x] = a.units[threadIdx.x];
@@ -200,23 +207,15 @@ struct CkeRule : SetMajorPrefix {
 
 // Time path of the group (as classify_group), or TGO_ERANGE / TGO_EINVAL (a
 // unit count outside 1..cap); clears the accumulators.
-__device__ __forceinline__ int cke_status_wave(const tgo_task *tasks, const int32_t *units, int n, int cap,
-                                               const Rates &r, int lane) {
-    const int m = classify_group_wave(tasks, n, r, lane);
-    const int32_t u = lane < n ? units[lane] : 1;
-    const bool bad = __any(u < 1 || u > cap);
-    return m < 0 ? m : bad ? TGO_EINVAL : m;
-}
-__global__ __launch_bounds__(64) void cke_prepare_kernel(const tgo_task *__restrict__ tasks,
-                                                         const int32_t *__restrict__ units, int n, int cap, Rates r,
-                                                         int *mode, ExAcc *acc) {
-    const int m = cke_status_wave(tasks, units, n, cap, r, threadIdx.x);
+__global__ __launch_bounds__(64) void cke_prepare_kernel(const tgo_task *__restrict__ tasks, CkeRule::Args args, int n,
+                                                         Rates r, int *mode, ExAcc *acc) {
+    const int m = CkeRule::status(tasks, n, r, args, threadIdx.x);
     if (threadIdx.x == 0) *mode = m;
     exacc_init(acc, threadIdx.x);
 }
 
 template <int M, bool STORE, int DMA>
-static int launch_cke(hipStream_t st, const tgo_task *t, const int32_t *units, int n, int cap, const Rates &r,
+static int launch_cke(hipStream_t st, const tgo_task *t, const CkeRule::Args &args, int n, const Rates &r,
                       int64_t *out, tgo_summary *d_out) {
     const void *k32 = reinterpret_cast<const void *>(&enum_kernel<CkeRule, uint32_t, M, STORE, DMA>);
     const uint32_t n_sub = (uint32_t)(factorial(n) / factorial(M));
@@ -225,8 +224,8 @@ static int launch_cke(hipStream_t st, const tgo_task *t, const int32_t *units, i
     int rc = enum_grid(k32, enum_shm_bytes<CkeRule, uint32_t>(n, DMA == DMA_ONE), n_sub, 0, ExScratch{}, st, &blocks,
                        &sc);
     if (rc) return rc;
-    hipLaunchKernelGGL(cke_prepare_kernel, dim3(1), dim3(64), 0, st, t, units, n, cap, r, sc.mode, sc.acc);
-    rc = enum_launch<CkeRule, M, STORE, DMA>(st, t, n, r, CkeRule::Args{units, cap, d_out}, n_sub, out, blocks, sc);
+    hipLaunchKernelGGL(cke_prepare_kernel, dim3(1), dim3(64), 0, st, t, args, n, r, sc.mode, sc.acc);
+    rc = enum_launch<CkeRule, M, STORE, DMA>(st, t, n, r, args, n_sub, out, blocks, sc);
     if (rc) return rc;
     hipLaunchKernelGGL(rule_finalize, dim3(1), dim3(EX_FIN_THREADS), 0, st, sc.parts, (int)blocks, n, factorial(n),
                        sc.acc, sc.mode, d_out);
@@ -247,12 +246,15 @@ static int choose_cke_m(int n) {
 template <bool STORE, int DMA>
 static int launch_cke_m(hipStream_t st, const tgo_task *t, const int32_t *units, int n, int cap, const Rates &r,
                         int64_t *out, tgo_summary *d_out) {
+    const CkeRule::Args a{units, cap, d_out};
+    if (factorial(n) <= SMALL_COUNT && !std::getenv("TGO_CKE_M"))
+        return small_launch<CkeRule, DMA>(st, t, n, r, a, (uint32_t)factorial(n), out, d_out, ExScratch{});
     switch (choose_cke_m(n)) {
-        case 1: return launch_cke<1, STORE, DMA>(st, t, units, n, cap, r, out, d_out);
-        case 2: return launch_cke<2, STORE, DMA>(st, t, units, n, cap, r, out, d_out);
-        case 3: return launch_cke<3, STORE, DMA>(st, t, units, n, cap, r, out, d_out);
-        case 4: return launch_cke<4, STORE, DMA>(st, t, units, n, cap, r, out, d_out);
-        default: return launch_cke<5, STORE, DMA>(st, t, units, n, cap, r, out, d_out);
+        case 1: return launch_cke<1, STORE, DMA>(st, t, a, n, r, out, d_out);
+        case 2: return launch_cke<2, STORE, DMA>(st, t, a, n, r, out, d_out);
+        case 3: return launch_cke<3, STORE, DMA>(st, t, a, n, r, out, d_out);
+        case 4: return launch_cke<4, STORE, DMA>(st, t, a, n, r, out, d_out);
+        default: return launch_cke<5, STORE, DMA>(st, t, a, n, r, out, d_out);
     }
 }
 

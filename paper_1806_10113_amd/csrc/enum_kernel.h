@@ -123,131 +123,6 @@ __device__ __forceinline__ void exacc_init(ExAcc *acc, int lane) {
 }
 static_assert(EX_ACCS == 64, "one wave initialises and merges the accumulators");
 
-// Dynamic LDS of the enumeration kernel: the task tables (n entries each),
-// the rule's own tables, then the per-lane queue, n - 1 slots (the last
-// position's slot is never read; none when the lanes need no queue).  The
-// block reduction reuses the queue's memory at the end.
-template <class Rule, typename TT>
-__host__ __device__ constexpr size_t enum_tables_bytes(int n) {
-    return (size_t)n * (sizeof(Quad<TT>) + sizeof(DRec<TT>)) + Rule::lds_bytes(n);
-}
-template <class Rule, typename TT>
-inline size_t enum_shm_bytes(int n, bool one_dma) {
-    const int slots = Rule::queue(one_dma) ? (n > 1 ? n - 1 : 1) : 0;
-    const size_t q = sizeof(Slot<TT>) * EX_THREADS * (size_t)slots;
-    const size_t red = sizeof(Partial) * (EX_THREADS / 64);
-    return enum_tables_bytes<Rule, TT>(n) + (q > red ? q : red);
-}
-
-// Subtrees of one group in set-major order.
-struct SetMajorPrefix {
-    template <int DMA, typename LaneT, typename ViewT, typename ArgsT>
-    static __device__ __forceinline__ uint64_t prefix(LaneT &st, uint32_t s, int n, int m, ViewT &v, const Rates &r,
-                                                      const ArgsT &, uint32_t *lex) {
-        return prefix_by_set<DMA>(st, s, n, m, v, r, lex);
-    }
-};
-
-// The temporal model alone.  32-bit time path: at most 72 VGPRs so that 7
-// waves fit per SIMD (with the n - 1 slot queue, 7 blocks also fit in LDS at
-// n = 12).
-struct BaseRule : SetMajorPrefix {
-    struct Args {};
-    static constexpr bool SIDE = false;
-    template <typename TT>
-    using View = tgo::View<TT, 1, EX_THREADS>;
-    // two DMA engines: the chain form; one engine: windows without DtH events
-    template <typename TT, int DMA>
-    using Lane = std::conditional_t<DMA == DMA_TWO, CLane<TT>, tgo::Lane<TT>>;
-    template <typename TT, int DMA>
-    static constexpr int min_waves() { return sizeof(TT) == 4 ? 7 : 1; }
-    static constexpr bool queue(bool one_dma) { return !one_dma; }
-    static __host__ __device__ constexpr size_t lds_bytes(int) { return 0; }
-    template <typename ViewT>
-    static __device__ __forceinline__ void load(ViewT &, unsigned char *, const Args &, int, uint64_t *) {}
-};
-
-// Every ordering of one group.  modep: the group's time path, decided by the
-// launch before (0 = 32-bit, 1 = 64-bit, or a negative error code); both
-// widths are launched, and every block of the one that does not match the
-// group's path (or of both, on an error) returns after reading one word.  DMA
-// is the launch scheme (DMA_TWO or DMA_ONE, fixed per instantiation).
-template <class Rule, typename TT, int M, bool STORE, int DMA>
-__global__ __launch_bounds__(EX_THREADS) __attribute__((amdgpu_waves_per_eu(Rule::template min_waves<TT, DMA>())))
-void enum_kernel(const tgo_task *__restrict__ tasks, int n, Rates r, typename Rule::Args args, uint32_t n_sub,
-                 int64_t *out, Partial *partials, ExAcc *acc, const int *__restrict__ modep) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int MODE = sizeof(TT) == 4 ? 0 : 1;
-    if (*modep != MODE) return;
-    Quad<TT> *Ht = reinterpret_cast<Quad<TT> *>(smem);
-    DRec<TT> *Dt = reinterpret_cast<DRec<TT> *>(smem + (size_t)n * sizeof(Quad<TT>));
-    unsigned char *qbase = smem + enum_tables_bytes<Rule, TT>(n);
-    if ((int)threadIdx.x < n) table_entry<TT>(tasks[threadIdx.x], r, &Ht[threadIdx.x], &Dt[threadIdx.x]);
-
-    typename Rule::template View<TT> v;
-    v.H = Ht;
-    v.D = Dt;
-    v.Q = reinterpret_cast<Slot<TT> *>(qbase) + threadIdx.x;
-    uint64_t seq = 0;  // task at each placed position, one per nibble (rules that ask for it)
-    Rule::load(v, smem + (size_t)n * (sizeof(Quad<TT>) + sizeof(DRec<TT>)), args, n, &seq);
-    __syncthreads();
-    // the rule's heuristic runs on one wave of block 0, beside the enumeration
-    // (its latency is that of a small group's whole enumeration)
-    if constexpr (Rule::SIDE) {
-        if (blockIdx.x == 0) {
-            if (threadIdx.x < 64) Rule::template side<TT, DMA>(v, n, r, args);
-            return;
-        }
-    }
-    const uint32_t blocks = gridDim.x - (Rule::SIDE ? 1u : 0u), block = blockIdx.x - (Rule::SIDE ? 1u : 0u);
-    Ctx c;
-    c.n = n;
-    c.r = r;
-    c.out_sub = nullptr;
-
-    Acc<TT> a;
-    acc_init(a);
-    const uint32_t stride = blocks * blockDim.x;
-    using LaneT = typename Rule::template Lane<TT, DMA>;
-    for (uint32_t s = block * blockDim.x + threadIdx.x; s < n_sub; s += stride) {
-        LaneT st;
-        uint32_t lex;
-        const uint64_t list = Rule::template prefix<DMA>(st, s, n, M, v, r, args, &lex);
-        const uint64_t r0 = (uint64_t)lex * factorial(M);
-        if constexpr (STORE) c.out_sub = out + r0;
-        Sub<TT> u;
-        sub_init(u);
-        level<TT, M, STORE, DMA>(c, v, st, (uint32_t)list, 0u, u);
-        fold(a, u, r0);
-    }
-    Partial p;
-    p.min_t = (uint64_t)a.min_t;
-    p.min_r = a.min_r;
-    if constexpr (sizeof(TT) == 4) {
-        p.min_t = a.min_t == inf_time<TT>() ? ~0ull : (uint64_t)a.min_t;
-    }
-    p.max_t = (uint64_t)a.max_t1;
-    p.max_r = a.max_r;
-    p.sum_lo = a.sum_lo;
-    p.sum_hi = a.sum_hi;
-    p.fp = a.fp;
-    p.status = 0;
-    p.pad = 0;
-    const Partial o = block_reduce(p, reinterpret_cast<Partial *>(qbase));
-    if (threadIdx.x == 0) {
-        if constexpr (sizeof(TT) == 4) {
-            // every block owns at least one subtree, so o holds an ordering
-            acc += block % EX_ACCS;
-            atomicMin(&acc->minkey, (unsigned long long)((o.min_t << 33) | o.min_r));
-            atomicMax(&acc->maxkey, (unsigned long long)(((o.max_t - 1) << 33) | (EX_RANK_MASK - o.max_r)));
-            atomicAdd(&acc->sum, (unsigned long long)o.sum_lo);
-            atomicAdd(&acc->fp, (unsigned long long)o.fp);
-        } else {
-            partials[block] = o;
-        }
-    }
-}
-
 // ------------------------------------------------------------------ summary
 
 // Rank -> ordering, one task per nibble.  Only the first digit of n = 13
@@ -325,6 +200,153 @@ __device__ __forceinline__ void write_summary(const Partial &o, int status, int 
         put_order(out->best, status ? 0 : decode(o.min_r), status ? 0 : n);
     } else if (threadIdx.x == 64) {
         put_order(out->worst, status ? 0 : decode(o.max_r), status ? 0 : n);
+    }
+}
+
+// -------------------------------------------------------------- enumeration
+
+// Dynamic LDS of the enumeration kernel: the task tables (n entries each),
+// the rule's own tables, then the per-lane queue, n - 1 slots (the last
+// position's slot is never read; none when the lanes need no queue).  The
+// block reduction reuses the queue's memory at the end.
+template <class Rule, typename TT>
+__host__ __device__ constexpr size_t enum_tables_bytes(int n) {
+    return (size_t)n * (sizeof(Quad<TT>) + sizeof(DRec<TT>)) + Rule::lds_bytes(n);
+}
+template <class Rule, typename TT>
+inline size_t enum_shm_bytes(int n, bool one_dma) {
+    const int slots = Rule::queue(one_dma) ? (n > 1 ? n - 1 : 1) : 0;
+    const size_t q = sizeof(Slot<TT>) * EX_THREADS * (size_t)slots;
+    const size_t red = sizeof(Partial) * (EX_THREADS / 64);
+    return enum_tables_bytes<Rule, TT>(n) + (q > red ? q : red);
+}
+
+// Ranks of one group's orderings: subtrees in set-major order for the large
+// groups, lexicographic order for the small ones.
+struct GroupRule {
+    template <int DMA, typename LaneT, typename ViewT, typename ArgsT>
+    static __device__ __forceinline__ uint64_t prefix(LaneT &st, uint32_t s, int n, int m, ViewT &v, const Rates &r,
+                                                      const ArgsT &, uint32_t *lex) {
+        return prefix_by_set<DMA>(st, s, n, m, v, r, lex);
+    }
+    template <int DMA, typename LaneT, typename ViewT, typename ArgsT>
+    static __device__ __forceinline__ uint64_t small_prefix(LaneT &st, uint32_t rank, int n, ViewT &v, const Rates &r,
+                                                            const ArgsT &) {
+        return tgo::prefix<DMA>(st, rank, n, 1, v, r);
+    }
+    template <typename ArgsT>
+    static __device__ __forceinline__ uint64_t decode(uint64_t rank, int n, const ArgsT &) {
+        return unrank_nibbles(n, rank);
+    }
+    // Other outputs of a group in error.
+    template <typename ArgsT>
+    static __device__ __forceinline__ void on_error(const ArgsT &) {}
+    // Time path or error code of the group, by one wave (lane i: task i).
+    template <typename ArgsT>
+    static __device__ __forceinline__ int status(const tgo_task *tasks, int n, const Rates &r, const ArgsT &,
+                                                 int lane) {
+        return classify_group_wave(tasks, n, r, lane);
+    }
+};
+
+// The temporal model alone.  32-bit time path: at most 72 VGPRs so that 7
+// waves fit per SIMD (with the n - 1 slot queue, 7 blocks also fit in LDS at
+// n = 12).
+struct BaseRule : GroupRule {
+    struct Args {};
+    static constexpr bool SIDE = false;
+    template <typename TT>
+    using View = tgo::View<TT, 1, EX_THREADS>;
+    // two DMA engines: the chain form; one engine: windows without DtH events
+    template <typename TT, int DMA>
+    using Lane = std::conditional_t<DMA == DMA_TWO, CLane<TT>, tgo::Lane<TT>>;
+    template <typename TT, int DMA>
+    static constexpr int min_waves() { return sizeof(TT) == 4 ? 7 : 1; }
+    static constexpr bool queue(bool one_dma) { return !one_dma; }
+    static __host__ __device__ constexpr size_t lds_bytes(int) { return 0; }
+    // SMALL: the rule's tables straight from the call's inputs (small_kernel)
+    template <bool SMALL, typename ViewT>
+    static __device__ __forceinline__ void load(ViewT &, unsigned char *, const Args &, int, uint64_t *) {}
+};
+
+// Every ordering of one group.  modep: the group's time path, decided by the
+// launch before (0 = 32-bit, 1 = 64-bit, or a negative error code); both
+// widths are launched, and every block of the one that does not match the
+// group's path (or of both, on an error) returns after reading one word.  DMA
+// is the launch scheme (DMA_TWO or DMA_ONE, fixed per instantiation).
+template <class Rule, typename TT, int M, bool STORE, int DMA>
+__global__ __launch_bounds__(EX_THREADS) __attribute__((amdgpu_waves_per_eu(Rule::template min_waves<TT, DMA>())))
+void enum_kernel(const tgo_task *__restrict__ tasks, int n, Rates r, typename Rule::Args args, uint32_t n_sub,
+                 int64_t *out, Partial *partials, ExAcc *acc, const int *__restrict__ modep) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int MODE = sizeof(TT) == 4 ? 0 : 1;
+    if (*modep != MODE) return;
+    Quad<TT> *Ht = reinterpret_cast<Quad<TT> *>(smem);
+    DRec<TT> *Dt = reinterpret_cast<DRec<TT> *>(smem + (size_t)n * sizeof(Quad<TT>));
+    unsigned char *qbase = smem + enum_tables_bytes<Rule, TT>(n);
+    if ((int)threadIdx.x < n) table_entry<TT>(tasks[threadIdx.x], r, &Ht[threadIdx.x], &Dt[threadIdx.x]);
+
+    typename Rule::template View<TT> v;
+    v.H = Ht;
+    v.D = Dt;
+    v.Q = reinterpret_cast<Slot<TT> *>(qbase) + threadIdx.x;
+    uint64_t seq = 0;  // task at each placed position, one per nibble (rules that ask for it)
+    Rule::template load<false>(v, smem + (size_t)n * (sizeof(Quad<TT>) + sizeof(DRec<TT>)), args, n, &seq);
+    __syncthreads();
+    // the rule's heuristic runs on one wave of block 0, beside the enumeration
+    // (its latency is that of a small group's whole enumeration)
+    if constexpr (Rule::SIDE) {
+        if (blockIdx.x == 0) {
+            if (threadIdx.x < 64) Rule::template side<TT, DMA>(v, n, r, args);
+            return;
+        }
+    }
+    const uint32_t blocks = gridDim.x - (Rule::SIDE ? 1u : 0u), block = blockIdx.x - (Rule::SIDE ? 1u : 0u);
+    Ctx c;
+    c.n = n;
+    c.r = r;
+    c.out_sub = nullptr;
+
+    Acc<TT> a;
+    acc_init(a);
+    const uint32_t stride = blocks * blockDim.x;
+    using LaneT = typename Rule::template Lane<TT, DMA>;
+    for (uint32_t s = block * blockDim.x + threadIdx.x; s < n_sub; s += stride) {
+        LaneT st;
+        uint32_t lex;
+        const uint64_t list = Rule::template prefix<DMA>(st, s, n, M, v, r, args, &lex);
+        const uint64_t r0 = (uint64_t)lex * factorial(M);
+        if constexpr (STORE) c.out_sub = out + r0;
+        Sub<TT> u;
+        sub_init(u);
+        level<TT, M, STORE, DMA>(c, v, st, (uint32_t)list, 0u, u);
+        fold(a, u, r0);
+    }
+    Partial p;
+    p.min_t = (uint64_t)a.min_t;
+    p.min_r = a.min_r;
+    if constexpr (sizeof(TT) == 4) {
+        p.min_t = a.min_t == inf_time<TT>() ? ~0ull : (uint64_t)a.min_t;
+    }
+    p.max_t = (uint64_t)a.max_t1;
+    p.max_r = a.max_r;
+    p.sum_lo = a.sum_lo;
+    p.sum_hi = a.sum_hi;
+    p.fp = a.fp;
+    p.status = 0;
+    p.pad = 0;
+    const Partial o = block_reduce(p, reinterpret_cast<Partial *>(qbase));
+    if (threadIdx.x == 0) {
+        if constexpr (sizeof(TT) == 4) {
+            // every block owns at least one subtree, so o holds an ordering
+            acc += block % EX_ACCS;
+            atomicMin(&acc->minkey, (unsigned long long)((o.min_t << 33) | o.min_r));
+            atomicMax(&acc->maxkey, (unsigned long long)(((o.max_t - 1) << 33) | (EX_RANK_MASK - o.max_r)));
+            atomicAdd(&acc->sum, (unsigned long long)o.sum_lo);
+            atomicAdd(&acc->fp, (unsigned long long)o.fp);
+        } else {
+            partials[block] = o;
+        }
     }
 }
 
@@ -409,6 +431,157 @@ static __global__ __launch_bounds__(EX_FIN_THREADS) void rule_finalize(const Par
     finalize_block(parts, nparts, n, count, acc, mode, out);
 }
 
+// -------------------------------------------------------------- small groups
+
+// Up to SMALL_COUNT orderings: one lane per ordering, every window of it in a
+// short loop, both time widths in one kernel.  Such a call is launches, cold
+// instruction fetch and latency, not work: the general path's three launches
+// before the finalize (time path, enumeration, its idle twin) and its unrolled
+// walk took 25 of a four-task group's 27 us here.  One block (at most
+// SMALL_ONE orderings) also writes the summary; several leave partials.
+constexpr int SMALL_THREADS = EX_THREADS;  // the views' queue stride
+constexpr uint32_t SMALL_ONE = 1024;
+constexpr uint32_t SMALL_COUNT = 65536;
+
+struct SmallOut {
+    int64_t *times;  // T by rank, or null
+    Partial *parts;
+    tgo_summary *summary;
+};
+
+// The heuristic's fields when no side block writes them.
+template <class Rule>
+__device__ __forceinline__ void no_heuristic(int status, const typename Rule::Args &args, tgo_summary *out) {
+    if (threadIdx.x == 128 && (!Rule::SIDE || status != 0)) {
+        put_order(out->heur, 0, 0);
+        out->heur_ns = Rule::SIDE ? status : -1;
+        if (status != 0) Rule::on_error(args);
+    }
+}
+
+__device__ __forceinline__ uint64_t wave_min_u64(uint64_t x) {
+    for (int m = 32; m >= 1; m >>= 1) {
+        const uint64_t y = shfl_xor64(x, m);
+        x = y < x ? y : x;
+    }
+    return x;
+}
+
+template <class Rule, typename TT, int DMA>
+__device__ __forceinline__ void small_run(const tgo_task *__restrict__ tasks, int n, const Rates &r,
+                                          const typename Rule::Args &args, uint32_t count, int nblocks, bool side,
+                                          unsigned char *smem, const SmallOut &o) {
+    Quad<TT> *Ht = reinterpret_cast<Quad<TT> *>(smem);
+    DRec<TT> *Dt = reinterpret_cast<DRec<TT> *>(smem + (size_t)n * sizeof(Quad<TT>));
+    unsigned char *qbase = smem + enum_tables_bytes<Rule, TT>(n);
+    if ((int)threadIdx.x < n) table_entry<TT>(tasks[threadIdx.x], r, &Ht[threadIdx.x], &Dt[threadIdx.x]);
+    typename Rule::template View<TT> v;
+    v.H = Ht;
+    v.D = Dt;
+    v.Q = reinterpret_cast<Slot<TT> *>(qbase) + threadIdx.x;
+    uint64_t seq = 0;
+    Rule::template load<true>(v, smem + (size_t)n * (sizeof(Quad<TT>) + sizeof(DRec<TT>)), args, n, &seq);
+    __syncthreads();
+    if constexpr (Rule::SIDE) {
+        if (side) {
+            if (threadIdx.x < 64) Rule::template side<TT, DMA>(v, n, r, args);
+            return;
+        }
+    }
+    using LaneT = typename Rule::template Lane<TT, DMA>;
+    Partial p;
+    p.min_t = ~0ull; p.min_r = ~0ull; p.max_t = 0; p.max_r = ~0ull;
+    p.sum_lo = 0; p.sum_hi = 0; p.fp = 0; p.status = 0; p.pad = 0;
+    // a lane meets its ranks in increasing order
+#pragma unroll 1
+    for (uint32_t rk = blockIdx.x * SMALL_THREADS + threadIdx.x; rk < count; rk += (uint32_t)nblocks * SMALL_THREADS) {
+        LaneT st;
+        const uint32_t x = (uint32_t)Rule::template small_prefix<DMA>(st, rk, n, v, r, args);
+        window<DMA, false>(st, n - 1, x, v, r);
+        const uint64_t T = (uint64_t)tail<DMA>(st, r);
+        if (o.times) o.times[rk] = (int64_t)T;
+        if (T < p.min_t) { p.min_t = T; p.min_r = rk; }
+        if (T + 1 > p.max_t) { p.max_t = T + 1; p.max_r = rk; }
+        p.sum_lo += (uint32_t)T;  // halves of the sum: 2^16 terms below 2^32 each
+        p.sum_hi += T >> 32;
+        p.fp += (2ull * rk + 1ull) * T;
+    }
+    // wave: the extreme time, then the lowest rank that has it
+    const uint64_t mn = wave_min_u64(p.min_t), mx = ~wave_min_u64(~p.max_t);
+    const uint64_t mr = wave_min_u64(p.min_t == mn ? p.min_r : ~0ull);
+    const uint64_t xr = wave_min_u64(p.max_t == mx ? p.max_r : ~0ull);
+    for (int m = 32; m >= 1; m >>= 1) {
+        p.sum_lo += shfl_xor64(p.sum_lo, m);
+        p.sum_hi += shfl_xor64(p.sum_hi, m);
+        p.fp += shfl_xor64(p.fp, m);
+    }
+    p.min_t = mn; p.min_r = mr; p.max_t = mx; p.max_r = xr;
+    // whole sum = sum_hi 2^32 + sum_lo
+    const uint64_t lo = p.sum_lo + (p.sum_hi << 32);
+    p.sum_hi = (p.sum_hi >> 32) + (lo < p.sum_lo ? 1ull : 0ull);
+    p.sum_lo = lo;
+    __syncthreads();  // the queue's memory is free
+    Partial *wsum = reinterpret_cast<Partial *>(qbase);
+    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x / 64] = p;
+    __syncthreads();
+    if ((threadIdx.x & 63) != 0 || threadIdx.x > 64) return;
+    Partial t = wsum[0];
+#pragma unroll 1
+    for (int i = 1; i < SMALL_THREADS / 64; ++i) {
+        merge_min(t.min_t, t.min_r, wsum[i].min_t, wsum[i].min_r);
+        merge_max(t.max_t, t.max_r, wsum[i].max_t, wsum[i].max_r);
+        add128(t.sum_lo, t.sum_hi, wsum[i].sum_lo, wsum[i].sum_hi);
+        t.fp += wsum[i].fp;
+    }
+    if (nblocks > 1) {
+        if (threadIdx.x == 0) o.parts[blockIdx.x] = t;
+        return;
+    }
+    write_summary(t, 0, n, count, [&](uint64_t rk) { return Rule::decode(rk, n, args); }, o.summary);
+}
+
+template <class Rule, int DMA>
+__global__ __launch_bounds__(SMALL_THREADS) void small_kernel(const tgo_task *__restrict__ tasks, int n, Rates r,
+                                                              typename Rule::Args args, uint32_t count, int nblocks,
+                                                              SmallOut o) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int cls = __builtin_amdgcn_readfirstlane(Rule::status(tasks, n, r, args, threadIdx.x & 63));
+    const bool side = (int)blockIdx.x == nblocks;
+    if (cls >= 0) {
+        if (!side && nblocks == 1) no_heuristic<Rule>(0, args, o.summary);
+        if (cls == 0) small_run<Rule, uint32_t, DMA>(tasks, n, r, args, count, nblocks, side, smem, o);
+        else small_run<Rule, uint64_t, DMA>(tasks, n, r, args, count, nblocks, side, smem, o);
+        return;
+    }
+    if (side) return;
+    Partial p = {};
+    p.status = cls;
+    if (nblocks > 1) {
+        if (threadIdx.x == 0) o.parts[blockIdx.x] = p;
+        return;
+    }
+    no_heuristic<Rule>(cls, args, o.summary);
+    write_summary(p, cls, n, count, [](uint64_t) { return 0ull; }, o.summary);
+}
+
+template <class Rule>
+__global__ __launch_bounds__(SMALL_THREADS) void small_finalize(const Partial *__restrict__ parts, int nparts, int n,
+                                                                uint32_t count, typename Rule::Args args,
+                                                                tgo_summary *out) {
+    __shared__ Partial red[SMALL_THREADS / 64];
+    const int status = parts[0].status;
+    Partial p;
+    p.min_t = ~0ull; p.min_r = ~0ull; p.max_t = 0; p.max_r = ~0ull;
+    p.sum_lo = 0; p.sum_hi = 0; p.fp = 0; p.status = 0; p.pad = 0;
+    static_assert(SMALL_COUNT <= SMALL_THREADS * SMALL_THREADS, "one partial per thread");
+    if ((int)threadIdx.x < nparts) p = parts[threadIdx.x];
+    p = block_reduce(p, red);
+    if (threadIdx.x == 0) red[0] = p;
+    __syncthreads();
+    no_heuristic<Rule>(status, args, out);
+    write_summary(red[0], status, n, count, [&](uint64_t rk) { return Rule::decode(rk, n, args); }, out);
+}
+
 // ------------------------------------------------------------------- launch
 
 // Blocks per launch, in units of the blocks the 32-bit kernel keeps resident
@@ -489,6 +662,37 @@ inline int enum_launch(hipStream_t st, const tgo_task *t, int n, const Rates &r,
                        (enum_shm_bytes<Rule, uint64_t>(n, one)), st, t, n, r, args, n_sub, out, sc.parts, sc.acc,
                        sc.mode);
     TGO_HIP(hipGetLastError());
+    return TGO_OK;
+}
+
+// A small search (count <= SMALL_COUNT) in one launch, or two.
+template <class Rule, int DMA>
+inline int small_launch(hipStream_t st, const tgo_task *t, int n, const Rates &r, const typename Rule::Args &args,
+                        uint32_t count, int64_t *out, tgo_summary *d_out, ExScratch ws) {
+    SmallOut o;
+    o.times = out;
+    o.summary = d_out;
+    o.parts = nullptr;
+    const int nblocks = count <= SMALL_ONE ? 1 : (int)((count + SMALL_THREADS - 1) / SMALL_THREADS);
+    if (nblocks > 1) {
+        const size_t need = sizeof(Partial) * nblocks;
+        if (!ws.ptr) {
+            int rc = workspace(need, &ws.ptr, st);
+            if (rc) return rc;
+        } else if (ws.bytes < need) {
+            return fail(TGO_ENOMEM, "scratch too small for a small group");
+        }
+        o.parts = reinterpret_cast<Partial *>(ws.ptr);
+    }
+    const dim3 grid((uint32_t)nblocks + (Rule::SIDE ? 1u : 0u));
+    hipLaunchKernelGGL((small_kernel<Rule, DMA>), grid, dim3(SMALL_THREADS),
+                       (enum_shm_bytes<Rule, uint64_t>(n, DMA == DMA_ONE)), st, t, n, r, args, count, nblocks, o);
+    TGO_HIP(hipGetLastError());
+    if (nblocks > 1) {
+        hipLaunchKernelGGL(small_finalize<Rule>, dim3(1), dim3(SMALL_THREADS), 0, st, o.parts, nblocks, n, count, args,
+                           d_out);
+        TGO_HIP(hipGetLastError());
+    }
     return TGO_OK;
 }
 

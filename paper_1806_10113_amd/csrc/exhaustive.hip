@@ -116,6 +116,12 @@ static int launch_m(int m, hipStream_t st, const tgo_task *t, int n,
 static int launch_exhaustive_ws(const Rates &r, const tgo_task *d_tasks, int n, int64_t *d_per_order,
                                 tgo_summary *d_out, hipStream_t st, ExScratch ws) {
     const bool one = r.one_dma != 0;
+    // small groups: unless a tuning override asks for the general path
+    if (factorial(n) <= SMALL_COUNT && !std::getenv("TGO_EXHAUSTIVE_M") && !std::getenv("TGO_EXHAUSTIVE_BLOCKS")) {
+        const uint32_t count = (uint32_t)factorial(n);
+        return one ? small_launch<BaseRule, DMA_ONE>(st, d_tasks, n, r, BaseRule::Args{}, count, d_per_order, d_out, ws)
+                   : small_launch<BaseRule, DMA_TWO>(st, d_tasks, n, r, BaseRule::Args{}, count, d_per_order, d_out, ws);
+    }
     const int m = choose_m(n, one);
     const uint64_t n_sub64 = factorial(n) / factorial(m);
     if (n_sub64 >= (1ull << 32)) return fail(TGO_EINVAL, "group too large to enumerate");

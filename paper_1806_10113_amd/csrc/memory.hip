@@ -51,8 +51,10 @@ __device__ __forceinline__ int mem_tables(const tgo_task *__restrict__ tasks, co
 // by VALU issue over divergent window loops.  Two engines, n = 12, capacity
 // 40 %: 18.9 ms when every transfer event was stepped (footprints summed in
 // 64 bits at each), 4.2 ms with windows and the set table; one engine 1.2 -> 1.0 ms.
-struct MemRule : SetMajorPrefix {
+struct MemRule : GroupRule {
     struct Args {
+        const int64_t *mem;
+        uint64_t cap;
         const uint32_t *fits;  // bit s: the tasks of set s fit together
         tgo_summary *out;      // the heuristic's fields
     };
@@ -71,10 +73,36 @@ struct MemRule : SetMajorPrefix {
     static constexpr bool queue(bool one_dma) { return !one_dma; }
     static __host__ __device__ constexpr int words(int n) { return n <= 5 ? 4 : 1 << (n - 5); }
     static __host__ __device__ constexpr size_t lds_bytes(int n) { return sizeof(uint32_t) * words(n); }
-    template <typename ViewT>
+    static __device__ __forceinline__ int status(const tgo_task *tasks, int n, const Rates &r, const Args &a,
+                                                 int lane) {
+        const int c = classify_group_wave(tasks, n, r, lane);
+        const int64_t m = lane < n ? a.mem[lane] : 0;
+        const bool bad = __any(m < 0 || (uint64_t)m > a.cap);
+        return c < 0 ? c : bad ? TGO_EINVAL : c;
+    }
+    // Whether the tasks of set s fit together (cap <= 2^62: a sum that still
+    // fits plus one footprint cannot overflow).
+    static __device__ __forceinline__ bool set_fits(uint32_t s, const int64_t *mem, int n, uint64_t cap) {
+        uint64_t sum = 0;
+        bool ok = true;
+        for (int i = 0; i < n; ++i)
+            if ((s >> i) & 1u) {
+                sum += ok ? (uint64_t)mem[i] : 0;
+                ok = ok && sum <= cap;
+            }
+        return ok;
+    }
+    template <bool SMALL, typename ViewT>
     static __device__ __forceinline__ void load(ViewT &v, unsigned char *lds, const Args &a, int n, uint64_t *seq) {
         uint32_t *f = reinterpret_cast<uint32_t *>(lds);
-        if ((int)threadIdx.x < words(n)) f[threadIdx.x] = a.fits[threadIdx.x];
+        if constexpr (SMALL) {
+            // n <= 8: one set per thread
+            const unsigned long long b = __ballot(set_fits(threadIdx.x, a.mem, n, a.cap));
+            if ((threadIdx.x & 31) == 0 && (int)(threadIdx.x >> 5) < words(n))
+                f[threadIdx.x >> 5] = (uint32_t)(b >> (threadIdx.x & 32));
+        } else {
+            if ((int)threadIdx.x < words(n)) f[threadIdx.x] = a.fits[threadIdx.x];
+        }
         v.fits = f;
         v.seq = seq;
     }
@@ -87,38 +115,27 @@ struct MemRule : SetMajorPrefix {
     }
 };
 static_assert(MemRule::words(TGO_MAX_MEM_N) <= EX_THREADS, "one word of the set table per thread");
+static_assert(factorial(9) > SMALL_COUNT && (1 << 8) <= SMALL_THREADS, "a small group has at most 256 sets");
 
 // Time path of the group (as classify_group) or TGO_EINVAL (a footprint
-// outside [0, cap]); clears the accumulators and fills the set table (a set
-// fits if its footprints sum to at most cap; cap <= 2^62, so a partial sum
-// that still fits plus one footprint cannot overflow).
+// outside [0, cap]); clears the accumulators and fills the set table (on an
+// error its bits are not read).
 constexpr int MEM_PREP_THREADS = 1024;
 __global__ __launch_bounds__(MEM_PREP_THREADS) void mem_prepare_kernel(const tgo_task *__restrict__ tasks,
-                                                                       const int64_t *__restrict__ mem, int n,
-                                                                       uint64_t cap, Rates r, int *mode, ExAcc *acc,
-                                                                       uint32_t *fits) {
-    __shared__ uint64_t ms[MAXN];
+                                                                       MemRule::Args args, int n, Rates r, int *mode,
+                                                                       ExAcc *acc, uint32_t *fits) {
+    __shared__ int64_t ms[MAXN];
     const int lane = threadIdx.x & 63;
     if (threadIdx.x < 64) {
-        const int c = classify_group_wave(tasks, n, r, lane);
-        const int64_t m = lane < n ? mem[lane] : 0;
-        const bool bad = __any(m < 0 || (uint64_t)m > cap);
-        if (lane == 0) *mode = c < 0 ? c : bad ? TGO_EINVAL : c;
+        const int c = MemRule::status(tasks, n, r, args, lane);
+        if (lane == 0) *mode = c;
         exacc_init(acc, lane);
-        // a footprint that fits nowhere is an error (above); the sums stay defined
-        if (lane < n) ms[lane] = (m < 0 || (uint64_t)m > cap) ? cap : (uint64_t)m;
+        if (lane < n) ms[lane] = args.mem[lane];
     }
     __syncthreads();
     const uint32_t sets = 32u * (uint32_t)MemRule::words(n);
     for (uint32_t s = threadIdx.x; s < sets; s += MEM_PREP_THREADS) {
-        uint64_t sum = 0;
-        bool ok = true;
-        for (int i = 0; i < n; ++i)
-            if ((s >> i) & 1u) {
-                sum += ok ? ms[i] : 0;
-                ok = ok && sum <= cap;
-            }
-        const unsigned long long b = __ballot(ok);
+        const unsigned long long b = __ballot(MemRule::set_fits(s, ms, n, args.cap));
         if ((lane & 31) == 0) fits[s >> 5] = (uint32_t)(b >> (lane & 32));
     }
 }
@@ -174,8 +191,8 @@ __global__ __launch_bounds__(MEM_THREADS) void mem_evaluate_kernel(const tgo_tas
 }
 
 template <int M, bool STORE, int DMA>
-static int launch_mem(hipStream_t st, const tgo_task *t, const int64_t *mem, int n, uint64_t cap, const Rates &r,
-                      int64_t *out, tgo_summary *d_out) {
+static int launch_mem(hipStream_t st, const tgo_task *t, MemRule::Args args, int n, const Rates &r, int64_t *out,
+                      tgo_summary *d_out) {
     const void *k32 = reinterpret_cast<const void *>(&enum_kernel<MemRule, uint32_t, M, STORE, DMA>);
     const uint32_t n_sub = (uint32_t)(factorial(n) / factorial(M));
     uint32_t blocks = 0;
@@ -184,9 +201,9 @@ static int launch_mem(hipStream_t st, const tgo_task *t, const int64_t *mem, int
                        ExScratch{}, st, &blocks, &sc);
     if (rc) return rc;
     uint32_t *fits = reinterpret_cast<uint32_t *>(sc.extra);
-    hipLaunchKernelGGL(mem_prepare_kernel, dim3(1), dim3(MEM_PREP_THREADS), 0, st, t, mem, n, cap, r, sc.mode, sc.acc,
-                       fits);
-    rc = enum_launch<MemRule, M, STORE, DMA>(st, t, n, r, MemRule::Args{fits, d_out}, n_sub, out, blocks, sc);
+    args.fits = fits;
+    hipLaunchKernelGGL(mem_prepare_kernel, dim3(1), dim3(MEM_PREP_THREADS), 0, st, t, args, n, r, sc.mode, sc.acc, fits);
+    rc = enum_launch<MemRule, M, STORE, DMA>(st, t, n, r, args, n_sub, out, blocks, sc);
     if (rc) return rc;
     hipLaunchKernelGGL(rule_finalize, dim3(1), dim3(EX_FIN_THREADS), 0, st, sc.parts, (int)blocks, n, factorial(n),
                        sc.acc, sc.mode, d_out);
@@ -207,12 +224,15 @@ static int choose_mem_m(int n) {
 template <bool STORE, int DMA>
 static int launch_mem_m(hipStream_t st, const tgo_task *t, const int64_t *mem, int n, uint64_t cap, const Rates &r,
                         int64_t *out, tgo_summary *d_out) {
+    const MemRule::Args a{mem, cap, nullptr, d_out};
+    if (factorial(n) <= SMALL_COUNT && !std::getenv("TGO_MEM_M"))
+        return small_launch<MemRule, DMA>(st, t, n, r, a, (uint32_t)factorial(n), out, d_out, ExScratch{});
     switch (choose_mem_m(n)) {
-        case 1: return launch_mem<1, STORE, DMA>(st, t, mem, n, cap, r, out, d_out);
-        case 2: return launch_mem<2, STORE, DMA>(st, t, mem, n, cap, r, out, d_out);
-        case 3: return launch_mem<3, STORE, DMA>(st, t, mem, n, cap, r, out, d_out);
-        case 4: return launch_mem<4, STORE, DMA>(st, t, mem, n, cap, r, out, d_out);
-        default: return launch_mem<5, STORE, DMA>(st, t, mem, n, cap, r, out, d_out);
+        case 1: return launch_mem<1, STORE, DMA>(st, t, a, n, r, out, d_out);
+        case 2: return launch_mem<2, STORE, DMA>(st, t, a, n, r, out, d_out);
+        case 3: return launch_mem<3, STORE, DMA>(st, t, a, n, r, out, d_out);
+        case 4: return launch_mem<4, STORE, DMA>(st, t, a, n, r, out, d_out);
+        default: return launch_mem<5, STORE, DMA>(st, t, a, n, r, out, d_out);
     }
 }
 

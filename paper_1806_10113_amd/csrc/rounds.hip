@@ -215,6 +215,29 @@ __device__ __forceinline__ void rounds_proxy(const ViewT &v, uint32_t first, int
     if (groups && threadIdx.x == 0) *groups = (uint16_t)s.gend;
 }
 
+// Launch sequence (task per position, one nibble each) of NoReorder rank rk.
+__device__ __forceinline__ uint64_t rounds_unrank(int T, int R, uint64_t rk, uint32_t tfact) {
+    uint32_t rem = (uint32_t)rk;  // (T!)^R < 2^32
+    uint64_t out = 0;
+    for (int rr = R - 1; rr >= 0; --rr) {
+        uint32_t d = rem % tfact;
+        rem /= tfact;
+        uint64_t list = 0;
+        for (int i = T - 1; i >= 0; --i) list = (list << 4) | (uint64_t)i;
+        uint32_t f = tfact;
+        for (int i = 0; i < T; ++i) {
+            f /= (uint32_t)(T - i);
+            const uint32_t c = d / f;
+            d -= c * f;
+            const uint64_t w = (list >> (4 * c)) & 15u;
+            const uint64_t lo = list & ((1ull << (4 * c)) - 1ull);
+            list = lo | ((list >> (4 * c + 4)) << (4 * c));
+            out |= (w * (uint64_t)R + (uint64_t)rr) << (4 * (rr * T + i));
+        }
+    }
+    return out;
+}
+
 // Dependent tasks under the enumeration kernel (enum_kernel.h): a subtree
 // holds the orderings that share every earlier round and the last round's
 // first T - M positions; subtrees are taken in rank order.  Bound by the
@@ -238,7 +261,23 @@ struct RoundsRule {
     static constexpr int min_waves() { return sizeof(TT) == 4 ? 4 : 1; }
     static constexpr bool queue(bool one_dma) { return !one_dma; }
     static __host__ __device__ constexpr size_t lds_bytes(int) { return 0; }
-    template <typename ViewT>
+    static __device__ __forceinline__ int status(const tgo_task *tasks, int n, const Rates &r, const Args &,
+                                                 int lane) {
+        return classify_group_wave(tasks, n, r, lane);
+    }
+    static __device__ __forceinline__ void on_error(const Args &a) {
+        if (a.groups) *a.groups = 0;
+    }
+    template <int DMA, typename LaneT, typename ViewT>
+    static __device__ __forceinline__ uint64_t small_prefix(LaneT &st, uint32_t rank, int n, ViewT &v, const Rates &r,
+                                                            const Args &a) {
+        uint32_t lex;
+        return prefix<DMA>(st, rank, n, 1, v, r, a, &lex);
+    }
+    static __device__ __forceinline__ uint64_t decode(uint64_t rk, int, const Args &a) {
+        return rounds_unrank(a.T, a.R, rk, a.tfact);
+    }
+    template <bool SMALL, typename ViewT>
     static __device__ __forceinline__ void load(ViewT &v, unsigned char *, const Args &a, int n, uint64_t *seq) {
         v.seq = seq;
         v.pos = 0;
@@ -307,29 +346,6 @@ __global__ __launch_bounds__(64) void rounds_prepare_kernel(const tgo_task *__re
     exacc_init(acc, threadIdx.x);
 }
 
-// Launch sequence (task per position, one nibble each) of NoReorder rank rk.
-__device__ __forceinline__ uint64_t rounds_unrank(int T, int R, uint64_t rk, uint32_t tfact) {
-    uint32_t rem = (uint32_t)rk;  // (T!)^R < 2^32
-    uint64_t out = 0;
-    for (int rr = R - 1; rr >= 0; --rr) {
-        uint32_t d = rem % tfact;
-        rem /= tfact;
-        uint64_t list = 0;
-        for (int i = T - 1; i >= 0; --i) list = (list << 4) | (uint64_t)i;
-        uint32_t f = tfact;
-        for (int i = 0; i < T; ++i) {
-            f /= (uint32_t)(T - i);
-            const uint32_t c = d / f;
-            d -= c * f;
-            const uint64_t w = (list >> (4 * c)) & 15u;
-            const uint64_t lo = list & ((1ull << (4 * c)) - 1ull);
-            list = lo | ((list >> (4 * c + 4)) << (4 * c));
-            out |= (w * (uint64_t)R + (uint64_t)rr) << (4 * (rr * T + i));
-        }
-    }
-    return out;
-}
-
 __global__ __launch_bounds__(EX_FIN_THREADS) void rounds_finalize_kernel(
     const Partial *__restrict__ parts, int nparts, int T, int R, uint64_t count, uint32_t tfact,
     const ExAcc *__restrict__ acc, const int *__restrict__ modep, tgo_summary *out, uint16_t *groups) {
@@ -391,6 +407,13 @@ int launch_rounds(const Rates &r, const tgo_task *d_tasks, int T, int R, int64_t
     const uint32_t tf = (uint32_t)factorial(T);
     uint64_t count = 1;
     for (int i = 0; i < R; ++i) count *= tf;
+    if (count <= SMALL_COUNT && !std::getenv("TGO_ROUNDS_M")) {
+        const RoundsRule::Args a{T, R, tf, d_out, d_groups};
+        const uint32_t c = (uint32_t)count;
+        return r.one_dma
+                   ? small_launch<RoundsRule, DMA_ONE>(st, d_tasks, T * R, r, a, c, d_per_order, d_out, ExScratch{})
+                   : small_launch<RoundsRule, DMA_TWO>(st, d_tasks, T * R, r, a, c, d_per_order, d_out, ExScratch{});
+    }
     if (r.one_dma)
         return d_per_order ? launch_rounds_dma<true, DMA_ONE>(st, d_tasks, T, R, r, count, tf, d_per_order, d_out, d_groups)
                            : launch_rounds_dma<false, DMA_ONE>(st, d_tasks, T, R, r, count, tf, nullptr, d_out, d_groups);

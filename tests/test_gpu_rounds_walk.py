@@ -25,13 +25,14 @@ def dev():
 
 
 @pytest.mark.parametrize("T,R", [(3, 2), (4, 2), (2, 4), (4, 1)])
-@pytest.mark.parametrize("depth", [1, 2, 3, 4])
+@pytest.mark.parametrize("depth", [None, 1, 2, 3, 4])
 def test_every_depth(dev, monkeypatch, T, R, depth):
     import torch
     from paper_1806_10113_amd import tgo
-    if depth > T:
+    if depth and depth > T:
         pytest.skip("no deeper than a round")
-    monkeypatch.setenv("TGO_ROUNDS_M", str(depth))
+    if depth:
+        monkeypatch.setenv("TGO_ROUNDS_M", str(depth))
     rng = np.random.default_rng(100 * T + R)
     paper = W.rounds_experiment("BK50", T, R, 7)
     for tasks in (paper, rng.integers(0, 4, size=(T * R, 3)).astype(np.int64), paper * 200):

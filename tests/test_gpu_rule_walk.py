@@ -11,7 +11,7 @@ from oracle import model as M
 from paper_1806_10113_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
-N = 8
+N = 8  # 40,320 orderings: also the largest group of the one-lane-per-ordering kernel
 MODELS = [M.DEFAULT, M.Model(16, 9, 13), M.NO_SLOWDOWN, M.Model(4, 3, 3, 1)]
 
 
@@ -56,12 +56,13 @@ def check(summary, po, times):
         assert d["fingerprint"] == sum((2 * r + 1) * int(x) for r, x in enumerate(times)) % (1 << 64)
 
 
-@pytest.mark.parametrize("depth", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("depth", [None, 1, 2, 3, 4, 5])
 @pytest.mark.parametrize("model", MODELS)
 def test_every_depth(dev, monkeypatch, depth, model):
     from paper_1806_10113_amd import tgo
-    monkeypatch.setenv("TGO_MEM_M", str(depth))
-    monkeypatch.setenv("TGO_CKE_M", str(depth))
+    if depth:
+        monkeypatch.setenv("TGO_MEM_M", str(depth))
+        monkeypatch.setenv("TGO_CKE_M", str(depth))
     m = tgo.Model(int(math.log2(model.q)), model.p_htd, model.p_dth, model.dma_engines)
     for tasks, mem, mcap, units, ucap in groups():
         t, md, ud = to_dev(tasks, dev), to_dev(mem, dev), to_dev(units, dev)
@@ -71,6 +72,32 @@ def test_every_depth(dev, monkeypatch, depth, model):
         s, po = tgo.exhaustive_cke(t, ud, ucap, m, per_order=True)
         s2, _ = tgo.exhaustive_cke(t, ud, ucap, m)
         check((s, s2), po, np.asarray(cmodel.cke_times(tasks, units, ucap, model)))
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("model", MODELS)
+def test_small_groups_take_either_path(dev, monkeypatch, n, model):
+    """One lane per ordering (one block up to n = 6, several above) against
+    the general walk: every field of the summary and every time."""
+    from paper_1806_10113_amd import tgo
+    m = tgo.Model(int(math.log2(model.q)), model.p_htd, model.p_dth, model.dma_engines)
+    for tasks, mem, mcap, units, ucap in groups():
+        t, md, ud = to_dev(tasks[:n], dev), to_dev(mem[:n], dev), to_dev(units[:n], dev)
+
+        def runs():
+            out = []
+            for s, po in (tgo.exhaustive(t, m, per_order=True), tgo.exhaustive(t, m),
+                          tgo.exhaustive_mem(t, md, mcap, m, per_order=True),
+                          tgo.exhaustive_cke(t, ud, ucap, m, per_order=True)):
+                out.append((tgo.read_summary(s), None if po is None else po.cpu().tolist()))
+            return out
+
+        small = runs()
+        for k in ("TGO_EXHAUSTIVE_M", "TGO_MEM_M", "TGO_CKE_M"):
+            monkeypatch.setenv(k, "1")
+        assert small == runs()
+        for k in ("TGO_EXHAUSTIVE_M", "TGO_MEM_M", "TGO_CKE_M"):
+            monkeypatch.delenv(k)
 
 
 def test_depths_agree_on_a_large_group(dev, monkeypatch):
