@@ -89,8 +89,10 @@ __device__ __forceinline__ void wave_lds_sync() {
 // smallest key of a row of 16 lanes (DPP moves: a shuffle over the wave per
 // step was half of the time), with the tie rules above.  Every instant stays
 // below 2^56 (16 tasks, work below 2^50 each), so a score and a lane index
-// share one key.  Returns the total time; *ord_out receives the ordering, one task per nibble.
-template <int DMA, typename LaneT, typename ViewT>
+// share one key.  *ord_out receives the ordering, one task per nibble.  Returns
+// the total time (TIME = false: 0, and the windows only the time needs are
+// left out, all of them for one or two tasks).
+template <int DMA, typename LaneT, bool TIME = true, typename ViewT>
 __device__ __forceinline__ int64_t heuristic_wave(uint32_t set, const ViewT &v, const Rates &r, uint64_t *ord_out) {
     constexpr uint64_t NONE = ~0ull;
     const int lane = threadIdx.x & 63;
@@ -113,6 +115,12 @@ __device__ __forceinline__ int64_t heuristic_wave(uint32_t set, const ViewT &v, 
     const uint32_t first = (uint32_t)longest & 15u;
     ord = first;
     rt &= ~(1u << first);
+    if constexpr (!TIME) {
+        if (__popc(rt) < 2) {
+            *ord_out = ord | (rt ? (uint64_t)(__ffs(rt) - 1) << 4 : 0);
+            return 0;
+        }
+    }
     LaneT st;
     lane_reset(st);
     window<DMA>(st, 0, first, v, r);
@@ -148,6 +156,10 @@ __device__ __forceinline__ int64_t heuristic_wave(uint32_t set, const ViewT &v, 
         bx = __builtin_amdgcn_readfirstlane(bx);
         by = __builtin_amdgcn_readfirstlane(by);
         ord |= ((uint64_t)bx << (4 * pos)) | ((uint64_t)by << (4 * pos + 4));
+        if constexpr (!TIME) {
+            *ord_out = ord;
+            return 0;
+        }
         window<DMA>(st, pos, (uint32_t)bx, v, r);
         window<DMA, false>(st, pos + 1, (uint32_t)by, v, r);
     } else if (__popc(rt) == 1) {

@@ -89,20 +89,21 @@ __device__ __forceinline__ bool dep_ok(const RSim<TT> &s, int j, uint32_t dep) {
 }
 
 // One pass at the current instant: retire finished commands, then start every
-// ready head.  Returns whether anything changed; finished DtHs are reported
+// ready head.  Starts depend only on what has finished and been submitted, so
+// another pass is needed only after a command of no length started (returned)
+// or a submission; finished DtHs are reported
 // in *arrived (bit x: the worker's next task x became available), the start
 // of the HtD at position trig in *trig_started.
 template <bool ONE, typename TT, typename ViewT>
 __device__ __forceinline__ bool rsim_pass(RSim<TT> &s, const ViewT &v, const Rates &r, int trig,
                                           uint32_t *arrived, bool *trig_started) {
-    bool changed = false;
+    bool again = false;
     // retire
-    if (s.hrun && s.uh == 0) { s.hrun = false; ++s.h_done; changed = true; }
-    if (s.krun && s.kend == s.t) { s.krun = false; ++s.k_done; changed = true; }
+    if (s.hrun && s.uh == 0) { s.hrun = false; ++s.h_done; }
+    if (s.krun && s.kend == s.t) { s.krun = false; ++s.k_done; }
     if (s.drun && s.ud == 0) {
         s.drun = false;
         ++s.d_done;
-        changed = true;
         *arrived |= (2u << nibble(s.seq, s.dpos)) & v.dep;
     }
     // start ready heads
@@ -111,14 +112,14 @@ __device__ __forceinline__ bool rsim_pass(RSim<TT> &s, const ViewT &v, const Rat
             s.hpos = s.hc++;
             s.uh = v.task(nibble(s.seq, s.hpos)).h << r.q_log2;
             s.hrun = true;
-            changed = true;
+            again = again || s.uh == 0;
             if (s.hpos == trig) *trig_started = true;
         }
         if (!s.drun && s.dc < s.nsub && s.dc < s.k_done) {
             s.dpos = s.dc++;
             s.ud = v.task(nibble(s.seq, s.dpos)).d << r.q_log2;
             s.drun = true;
-            changed = true;
+            again = again || s.ud == 0;
         }
     } else {
         if (!s.hrun && !s.drun) {
@@ -137,7 +138,7 @@ __device__ __forceinline__ bool rsim_pass(RSim<TT> &s, const ViewT &v, const Rat
                     s.uh = v.task(nibble(s.seq, j)).h << r.q_log2;
                     s.hrun = true;
                     ++s.xo;
-                    changed = true;
+                    again = again || s.uh == 0;
                     if (j == trig) *trig_started = true;
                 }
             } else if (s.xo < 2 * len) {
@@ -147,7 +148,7 @@ __device__ __forceinline__ bool rsim_pass(RSim<TT> &s, const ViewT &v, const Rat
                     s.ud = v.task(nibble(s.seq, j)).d << r.q_log2;
                     s.drun = true;
                     ++s.xo;
-                    changed = true;
+                    again = again || s.ud == 0;
                 }
             }
         }
@@ -156,9 +157,9 @@ __device__ __forceinline__ bool rsim_pass(RSim<TT> &s, const ViewT &v, const Rat
         const int j = s.kc++;
         s.kend = s.t + v.task(nibble(s.seq, j)).k;
         s.krun = true;
-        changed = true;
+        again = again || s.kend == s.t;
     }
-    return changed;
+    return again;
 }
 
 // Advance to the earliest completion estimate.  Returns false when nothing runs.
@@ -190,23 +191,23 @@ __device__ __forceinline__ void rounds_proxy(const ViewT &v, uint32_t first, int
     bool armed = true;
     int trig = -1;
     for (;;) {
-        bool changed = true;
-        while (changed) {
+        bool again = true;
+        while (again) {
             uint32_t arrived = 0;
             bool started = false;
-            changed = rsim_pass<ONE>(s, v, r, trig, &arrived, &started);
+            again = rsim_pass<ONE>(s, v, r, trig, &arrived, &started);
             buffer |= arrived;
             armed = armed || started;
             if (armed && buffer) {
                 // the group: the waiting tasks, ordered by Algorithm 1
                 uint64_t ord;
-                if constexpr (ONE) heuristic_wave<DMA_ONE, Lane<TT>>(buffer, v, r, &ord);
-                else heuristic_wave<DMA_TWO, CLane<TT>>(buffer, v, r, &ord);
+                if constexpr (ONE) heuristic_wave<DMA_ONE, Lane<TT>, false>(buffer, v, r, &ord);
+                else heuristic_wave<DMA_TWO, CLane<TT>, false>(buffer, v, r, &ord);
                 rsim_submit(s, ord, __popc(buffer));
                 trig = s.nsub - 1;
                 buffer = 0;
                 armed = false;
-                changed = true;
+                again = true;
             }
         }
         if (!rsim_advance<ONE>(s, r)) break;
