@@ -2,6 +2,8 @@
 // heuristic of Section 5.1 (Algorithm 1, one wave per group).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "enum_dev.h"
 #include "heur_dev.h"
 #include "tables_dev.h"
@@ -10,8 +12,17 @@
 namespace tgo {
 
 constexpr int EV_THREADS = 256;
+// Blocks per launch, in units of the resident ones: 1,000,003 orderings of 16
+// tasks in 91 / 87 / 91 / 92 / 95 us with 1 / 2 / 3 / 4 / 8.
+constexpr uint32_t EV_ROUNDS = 2;
 constexpr int HEU_WAVES = 4;  // groups per block of the heuristic, one wave each
 
+// One lane per given ordering.  Bound by VALU issue over divergent windows.
+// The row is read once, all of its bytes in flight together, checked and kept
+// as nibbles; blocks stride over the rows so that the time path and the tables
+// are set up by few blocks (a block per 256 rows, each with the time path
+// decided by one thread, and as many idle ones of the other width: 1,000,003
+// orderings of 16 tasks in 146 us; now 81).
 template <typename TT>
 __global__ __launch_bounds__(EV_THREADS) void evaluate_kernel(const tgo_task *__restrict__ tasks,
                                                               int n, Rates r,
@@ -21,10 +32,7 @@ __global__ __launch_bounds__(EV_THREADS) void evaluate_kernel(const tgo_task *__
     constexpr int MODE = sizeof(TT) == 4 ? 0 : 1;
     __shared__ Quad<TT> Ht[MAXN];
     __shared__ DRec<TT> Dt[MAXN];
-    __shared__ int mode;
-    if (threadIdx.x == 0) mode = classify_group(tasks, n, r);
-    if ((int)threadIdx.x < n) table_entry<TT>(tasks[threadIdx.x], r, &Ht[threadIdx.x], &Dt[threadIdx.x]);
-    __syncthreads();
+    const int mode = __builtin_amdgcn_readfirstlane(classify_group_wave(tasks, n, r, threadIdx.x & 63));
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     if (mode < 0) {
         if (MODE == 0)
@@ -32,37 +40,51 @@ __global__ __launch_bounds__(EV_THREADS) void evaluate_kernel(const tgo_task *__
         return;
     }
     if (mode != MODE) return;
+    if ((int)threadIdx.x < n) table_entry<TT>(tasks[threadIdx.x], r, &Ht[threadIdx.x], &Dt[threadIdx.x]);
+    __syncthreads();
     View<TT, 1, EV_THREADS> v;
     v.H = Ht;
     v.D = Dt;
     v.Q = reinterpret_cast<Slot<TT> *>(smem) + threadIdx.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) {
         const uint8_t *o = orders + i * n;
-        uint32_t seen = 0;
-        bool ok = true;
-        for (int j = 0; j < n; ++j) {
-            const uint32_t x = o[j];
-            ok = ok && x < (uint32_t)n && !((seen >> x) & 1u);
-            seen |= 1u << (x & 15u);
+        uint32_t b[MAXN];
+#pragma unroll
+        for (int j = 0; j < MAXN; ++j) b[j] = o[j < n ? j : n - 1];
+        uint64_t perm = 0;
+        uint32_t seen = 0, high = 0;
+#pragma unroll
+        for (int j = 0; j < MAXN; ++j) {
+            perm |= (uint64_t)(b[j] & 15u) << (4 * j);
+            seen |= j < n ? 1u << (b[j] & 15u) : 0u;
+            high |= b[j];
         }
-        if (!ok) {
+        // a permutation: no value above 15 and every one of the n below
+        if (high > 15u || seen != (1u << n) - 1u) {
             out[i] = TGO_EINVAL;
             continue;
         }
-        out[i] = (int64_t)simulate_order(n, [o](int j) { return (uint32_t)o[j]; }, v, r);
+        out[i] = (int64_t)simulate_order(
+            n, [perm](int j) { return (uint32_t)(perm >> (4 * j)) & 15u; }, v, r);
     }
 }
 
 int launch_evaluate(const Rates &r, const tgo_task *d_tasks, int n, const uint8_t *d_orders,
                     int64_t m, int64_t *d_out, hipStream_t st) {
     if (m == 0) return TGO_OK;
-    int64_t blocks = (m + EV_THREADS - 1) / EV_THREADS;
-    if (blocks > 8192) blocks = 8192;
-    const size_t shm32 = sizeof(Slot<uint32_t>) * EV_THREADS * n;
-    const size_t shm64 = sizeof(Slot<uint64_t>) * EV_THREADS * n;
-    hipLaunchKernelGGL(evaluate_kernel<uint32_t>, dim3((unsigned)blocks), dim3(EV_THREADS), shm32, st,
+    const int64_t want = (m + EV_THREADS - 1) / EV_THREADS;
+    // the queue holds n - 1 slots (the last position's is never read)
+    const size_t shm32 = sizeof(Slot<uint32_t>) * EV_THREADS * (n > 1 ? n - 1 : 1);
+    const size_t shm64 = sizeof(Slot<uint64_t>) * EV_THREADS * (n > 1 ? n - 1 : 1);
+    auto grid = [want](const void *k, size_t shm, uint32_t rounds) {
+        const uint32_t b = resident_blocks(k, EV_THREADS, shm);
+        return dim3((uint32_t)std::min<int64_t>(want, b ? b * rounds : 8192));
+    };
+    const void *k32 = reinterpret_cast<const void *>(&evaluate_kernel<uint32_t>);
+    const void *k64 = reinterpret_cast<const void *>(&evaluate_kernel<uint64_t>);
+    hipLaunchKernelGGL(evaluate_kernel<uint32_t>, grid(k32, shm32, EV_ROUNDS), dim3(EV_THREADS), shm32, st,
                        d_tasks, n, r, d_orders, m, d_out);
-    hipLaunchKernelGGL(evaluate_kernel<uint64_t>, dim3((unsigned)blocks), dim3(EV_THREADS), shm64, st,
+    hipLaunchKernelGGL(evaluate_kernel<uint64_t>, grid(k64, shm64, EV_ROUNDS), dim3(EV_THREADS), shm64, st,
                        d_tasks, n, r, d_orders, m, d_out);
     TGO_HIP(hipGetLastError());
     return TGO_OK;

@@ -19,7 +19,7 @@ __device__ inline int classify_group(const tgo_task *t, int n, const Rates &r) {
         const uint64_t qh = q * (uint64_t)h, qd = q * (uint64_t)d;
         mx = qh > mx ? qh : mx;
         mx = qd > mx ? qd : mx;
-        sum += (qh + r.p_h - 1) / r.p_h + (uint64_t)k + (qd + r.p_d - 1) / r.p_d;
+        sum += ceil_p(qh, r.p_h, r.inv_ph, r.c_ph) + (uint64_t)k + ceil_p(qd, r.p_d, r.inv_pd, r.c_pd);
     }
     const uint64_t lim32 = 1ull << 31;
     return (mx < lim32 && sum + time_bound_slack(n) < lim32) ? 0 : 1;
@@ -39,7 +39,7 @@ __device__ inline int classify_group_wave(const tgo_task *t, int n, const Rates 
         } else {
             const uint64_t qh = q * (uint64_t)h, qd = q * (uint64_t)d;
             mx = qh > qd ? qh : qd;
-            sum = (qh + r.p_h - 1) / r.p_h + (uint64_t)k + (qd + r.p_d - 1) / r.p_d;
+            sum = ceil_p(qh, r.p_h, r.inv_ph, r.c_ph) + (uint64_t)k + ceil_p(qd, r.p_d, r.inv_pd, r.c_pd);
         }
     }
     for (int m = 32; m >= 1; m >>= 1) {
@@ -61,11 +61,11 @@ __device__ inline void table_entry(const tgo_task &t, const Rates &r, Quad<TT> *
     const uint64_t h = (uint64_t)t.htd_ns, k = (uint64_t)t.kern_ns, d = (uint64_t)t.dth_ns;
     Quad<TT> e;
     e.h = (TT)h;
-    e.hp = (TT)((q * h + r.p_h - 1) / r.p_h);
+    e.hp = (TT)ceil_p(q * h, r.p_h, r.inv_ph, r.c_ph);
     e.k = (TT)k;
     e.d = (TT)d;
     DRec<TT> pd;
-    const uint64_t dp = (q * d + r.p_d - 1) / r.p_d;
+    const uint64_t dp = ceil_p(q * d, r.p_d, r.inv_pd, r.c_pd);
     pd.d = (TT)d;
     pd.dp = (TT)dp;
     pd.slack = (TT)(r.p_d * dp - q * d);
