@@ -13,7 +13,7 @@ namespace tgo {
 
 constexpr int EV_THREADS = 256;
 // Blocks per launch, in units of the resident ones: 1,000,003 orderings of 16
-// tasks in 91 / 87 / 91 / 92 / 95 us with 1 / 2 / 3 / 4 / 8.
+// tasks in 91 / 87 / 91 / 92 / 95 us with 1 / 2 / 3 / 4 / 8 (chain form).
 constexpr uint32_t EV_ROUNDS = 2;
 constexpr int HEU_WAVES = 4;  // groups per block of the heuristic, one wave each
 
@@ -22,7 +22,7 @@ constexpr int HEU_WAVES = 4;  // groups per block of the heuristic, one wave eac
 // as nibbles; blocks stride over the rows so that the time path and the tables
 // are set up by few blocks (a block per 256 rows, each with the time path
 // decided by one thread, and as many idle ones of the other width: 1,000,003
-// orderings of 16 tasks in 146 us; now 81).
+// orderings of 16 tasks in 146 us; now 81, and 62 in the potential form).
 template <typename TT>
 __global__ __launch_bounds__(EV_THREADS) void evaluate_kernel(const tgo_task *__restrict__ tasks,
                                                               int n, Rates r,
@@ -30,8 +30,7 @@ __global__ __launch_bounds__(EV_THREADS) void evaluate_kernel(const tgo_task *__
                                                               int64_t m, int64_t *out) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int MODE = sizeof(TT) == 4 ? 0 : 1;
-    __shared__ Quad<TT> Ht[MAXN];
-    __shared__ DRec<TT> Dt[MAXN];
+    __shared__ OrderTables<TT> ot;
     const int mode = __builtin_amdgcn_readfirstlane(classify_group_wave(tasks, n, r, threadIdx.x & 63));
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     if (mode < 0) {
@@ -40,12 +39,9 @@ __global__ __launch_bounds__(EV_THREADS) void evaluate_kernel(const tgo_task *__
         return;
     }
     if (mode != MODE) return;
-    if ((int)threadIdx.x < n) table_entry<TT>(tasks[threadIdx.x], r, &Ht[threadIdx.x], &Dt[threadIdx.x]);
+    const bool potential = order_tables(ot, tasks, n, r);  // every wave writes the same
     __syncthreads();
-    View<TT, 1, EV_THREADS> v;
-    v.H = Ht;
-    v.D = Dt;
-    v.Q = reinterpret_cast<Slot<TT> *>(smem) + threadIdx.x;
+    const auto v = ot.template view<EV_THREADS>(reinterpret_cast<TT *>(smem) + threadIdx.x);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) {
         const uint8_t *o = orders + i * n;
         uint32_t b[MAXN];
@@ -64,8 +60,7 @@ __global__ __launch_bounds__(EV_THREADS) void evaluate_kernel(const tgo_task *__
             out[i] = TGO_EINVAL;
             continue;
         }
-        out[i] = (int64_t)simulate_order(
-            n, [perm](int j) { return (uint32_t)(perm >> (4 * j)) & 15u; }, v, r);
+        out[i] = (int64_t)simulate_order(n, perm, v, r, potential);
     }
 }
 
@@ -73,9 +68,8 @@ int launch_evaluate(const Rates &r, const tgo_task *d_tasks, int n, const uint8_
                     int64_t m, int64_t *d_out, hipStream_t st) {
     if (m == 0) return TGO_OK;
     const int64_t want = (m + EV_THREADS - 1) / EV_THREADS;
-    // the queue holds n - 1 slots (the last position's is never read)
-    const size_t shm32 = sizeof(Slot<uint32_t>) * EV_THREADS * (n > 1 ? n - 1 : 1);
-    const size_t shm64 = sizeof(Slot<uint64_t>) * EV_THREADS * (n > 1 ? n - 1 : 1);
+    const size_t shm32 = order_queue_bytes<uint32_t>(n, EV_THREADS);
+    const size_t shm64 = order_queue_bytes<uint64_t>(n, EV_THREADS);
     auto grid = [want](const void *k, size_t shm, uint32_t rounds) {
         const uint32_t b = resident_blocks(k, EV_THREADS, shm);
         return dim3((uint32_t)std::min<int64_t>(want, b ? b * rounds : 8192));

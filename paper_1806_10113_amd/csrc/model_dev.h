@@ -174,8 +174,8 @@ __device__ __forceinline__ void lane_reset(Lane<TT> &s) { s = lane_init<TT>(); }
 // at solo speed (two transfers never move data at the same time), kernels
 // follow K_j = max(HtD_j end, K_{j-1} end) + k, and every DtH waits for the
 // last HtD.  A window is the HtD alone; the DtHs are left to the tail.
-template <typename TT, int TS, int QS>
-__device__ __forceinline__ void window_one(Lane<TT> &s, uint32_t x, const View<TT, TS, QS> &v) {
+template <typename TT, typename ViewT>
+__device__ __forceinline__ void window_one(Lane<TT> &s, uint32_t x, const ViewT &v) {
     using ST = typename Signed<TT>::type;
     const Quad<TT> tx = v.task(x);
     s.t += tx.h;
@@ -417,21 +417,231 @@ __device__ __forceinline__ TT tail(const CLane<TT> &s, const Rates &r) {
     return T;
 }
 
-// T of one whole ordering o[0..n) (o(j) gives the task at position j): the
-// chain form with two DMA engines, the event form's windows with one.  The
-// queue needs n - 1 slots.
-template <typename TT, int TS, int QS, typename Order>
-__device__ __forceinline__ TT simulate_order(int n, Order o, const View<TT, TS, QS> &v, const Rates &r) {
+// ------------------------------------------------------- whole orderings
+// Potential form: how far the HtD engine has come.  Let W(t) be the work it
+// has done by t, in 1/q solo-ns, if it is never idle: W grows by q per ns while
+// the DtH engine is idle and by p_htd while it runs, and the DtH of position i
+// ends at E_i with W(E_i) = G_i.  Both follow when the position is placed:
+// S = max(E_{i-1}, K_i), E_i = S + dp_i, G_i = G_{i-1} + q (S - E_{i-1}) + p_htd dp_i.
+// An HtD of h ns that starts at t ends at the first instant with
+// W >= X = W(t) + q h.  So a window only has to find the first DtH with
+// G_i >= X: between E_{i-1} and E_i, W is the smaller of the line of slope q
+// through (E_{i-1}, G_{i-1}) and the line of slope p_htd through (E_i, G_i)
+// (q >= p_htd), so the HtD ends at the later of the two lines' crossings of X,
+// rounded up -- the event windows' roundings, since every rate change falls on
+// a whole ns.  No branch but the search, whose step is one LDS read and one
+// comparison, where the chain form's loop divides at every gap: on random
+// orderings the lanes of a wave disagree about nearly every branch (35 % of
+// them active in the chain form, 196 VALU instructions per window).
+//
+// The potentials are below q T: the 32-bit form needs q times the group's time
+// bound below 2^31, the 64-bit one below 2^51 (its quotients are taken in
+// double); other groups take the chain form.
+
+// Task x of the potential form: q h, k, d, dp, and p_htd dp beside it.
+template <typename TT>
+struct alignas(4 * sizeof(TT)) PRec {
+    TT qh, k, d, dp;
+};
+
+// Tables of a lane that evaluates whole orderings, one after another, and its
+// queue: G of n positions (the last only ever a sentinel) and E of n - 1 in the
+// potential form; the kernel ends alone in the chain form.
+template <typename TT, int QS>
+struct OrderView {
+    const Quad<TT> *H;
+    const DRec<TT> *D;
+    const PRec<TT> *P;
+    const TT *gain;
+    TT *Q;
+    __device__ __forceinline__ Quad<TT> task(uint32_t x) const { return H[x]; }
+};
+template <typename TT>
+__host__ __device__ constexpr size_t order_queue_bytes(int n, int threads) {
+    return sizeof(TT) * (size_t)threads * (size_t)(2 * n - 1);
+}
+
+// The tables of up to MAXN tasks in LDS: a group takes one of the two forms.
+template <typename TT>
+struct OrderTables {
+    union {
+        struct {
+            Quad<TT> H[MAXN];
+            DRec<TT> D[MAXN];
+        };
+        struct {
+            PRec<TT> P[MAXN];
+            TT gain[MAXN];
+        };
+    };
+    template <int QS>
+    __device__ __forceinline__ OrderView<TT, QS> view(TT *q) const {
+        return OrderView<TT, QS>{H, D, P, gain, q};
+    }
+};
+
+// Whether a group with this time bound may take the potential form.
+template <typename TT>
+__device__ __forceinline__ bool potential_fits(uint64_t bound, const Rates &r) {
+    return bound < (1ull << ((sizeof(TT) == 4 ? 31 : 51) - r.q_log2));
+}
+
+// floor(u / p): u < 2^32 as trunc(fma(u, 1/p, 1/(2p))) (as ceil_p); u < 2^51 by
+// the exact remainder.
+__device__ __forceinline__ uint32_t floor_p(uint32_t u, uint32_t, double inv) {
+    return (uint32_t)__builtin_fma((double)u, inv, 0.5 * inv);
+}
+__device__ __forceinline__ uint64_t floor_p(uint64_t u, uint32_t p, double inv) {
+    const uint64_t est = (uint64_t)((double)u * inv);
+    const int64_t rem = (int64_t)(u - est * p);
+    return est + (rem >= (int64_t)p ? 1u : 0u) - (rem < 0 ? 1u : 0u);
+}
+
+template <typename TT, int QS>
+__device__ __forceinline__ TT simulate_potential(int n, uint64_t perm, const OrderView<TT, QS> &v, const Rates &r) {
+    using ST = typename Signed<TT>::type;
+    constexpr TT INF = ~TT(0) >> 1;  // above every potential
+    const TT q1 = (TT(1) << r.q_log2) - 1;
+    TT t = 0, w = 0, ck = 0, dpre = 0;
+    ST emax = (ST)(((TT)1) << (8 * sizeof(TT) - 1));  // most negative
+    TT gl = 0, el = 0;            // the last DtH placed
+    TT gp = 0, ep = 0;            // the DtH before the cursor (none: the start)
+    TT gc = INF, ec = 0;          // DtH i, the first that ends at t or later (INF: none placed)
+    int i = 0;
+    TT *const G = v.Q, *const E = v.Q + n * QS;
+    uint64_t seq = perm;
+    for (int j = 0; j < n; ++j, seq >>= 4) {
+        const uint32_t x = (uint32_t)seq & 15u;
+        const PRec<TT> tx = v.P[x];
+        const TT X = w + tx.qh;
+        while (gc < X) {
+            gp = gc;
+            ep = ec;
+            ++i;
+            gc = G[i * QS];  // slot j holds INF
+            ec = E[(i < j ? i : j - 1) * QS];
+        }
+        const TT eq = ep + ((X - gp + q1) >> r.q_log2);
+        const TT ek = ec - (TT)floor_p((TT)(gc - X), r.p_h, r.inv_ph);
+        const bool live = gc != INF;
+        t = live && (ST)ek > (ST)eq ? ek : eq;
+        w = gp + ((t - ep) << r.q_log2);
+        const TT wp = gc - TT(r.p_h) * (ec - t);
+        w = live && wp < w ? wp : w;
+        ck = tmax(t, ck) + tx.k;
+        const ST e = (ST)ck - (ST)dpre;
+        emax = e > emax ? e : emax;
+        dpre += tx.d;
+        if (j + 1 < n) {
+            const TT S = tmax(el, ck);
+            gl += ((S - el) << r.q_log2) + v.gain[x];
+            el = S + tx.dp;
+            G[j * QS] = gl;
+            E[j * QS] = el;
+            G[(j + 1) * QS] = INF;
+            gc = live ? gc : gl;  // every earlier DtH has ended: DtH j is the cursor's
+            ec = live ? ec : el;
+        }
+    }
+    TT T = (TT)(emax + (ST)dpre);
+    if (gc != INF) {
+        // DtH i may run at t: its solo time less what it has moved, then the
+        // solo times of the DtHs after it
+        uint64_t cur = perm >> (4 * i);
+        const TT S = ec - v.P[(uint32_t)cur & 15u].dp;
+        if (S < t) {
+            TT rest = 0;
+            for (int s = i; s < n; ++s, cur >>= 4) rest += v.P[(uint32_t)cur & 15u].d;
+            T = tmax(T, t + rest - ((TT(r.p_d) * (t - S)) >> r.q_log2));
+        }
+    }
+    return T;
+}
+
+// T of one whole ordering (perm: the task at position j in nibble j): with one
+// DMA engine the event form's windows; with two the potential form, or
+// (potential false: the group's potentials do not fit) the chain form's windows
+// (CLane), the chain entries computed when the cursor reaches them.
+template <typename TT, int QS>
+__device__ __forceinline__ TT simulate_order(int n, uint64_t perm, const OrderView<TT, QS> &v, const Rates &r,
+                                             bool potential) {
+    using ST = typename Signed<TT>::type;
+    if (potential) return simulate_potential(n, perm, v, r);
     if (is_one_dma<DMA_RUNTIME>(r)) {
         Lane<TT> st = lane_init<TT>();
-        for (int j = 0; j < n; ++j) window<DMA_ONE>(st, j, o(j), v, r);
+        for (int j = 0; j < n; ++j) window_one(st, (uint32_t)(perm >> (4 * j)) & 15u, v);
         return tail<DMA_ONE>(st, r);
     }
-    CLane<TT> st;
-    lane_reset(st);
-    for (int j = 0; j + 1 < n; ++j) window<DMA_TWO, true>(st, j, o(j), v, r);
-    if (n > 0) window<DMA_TWO, false>(st, n - 1, o(n - 1), v, r);
-    return tail<DMA_TWO>(st, r);
+    TT t = 0, ck = 0, dpre = 0, dcross = 0;
+    ST emax = (ST)(((TT)1) << (8 * sizeof(TT) - 1));  // most negative
+    // the cursor: DtH i of solo time dc, from S to E while the HtD engine is busy
+    int i = 0;
+    TT S = 0, E = 0, dc = 0;
+    bool run = false;
+    uint64_t seq = perm;
+    for (int j = 0; j < n; ++j, seq >>= 4) {
+        const uint32_t x = (uint32_t)seq & 15u;
+        const Quad<TT> tx = v.task(x);
+        TT rc = t;
+        TT u = tx.h << r.q_log2;
+        TT eb, ecmp = E;
+        if (!(i < j)) {
+            eb = t + tx.h;
+            ecmp = inf_time<TT>();
+        } else if (S < t) {
+            eb = t + tx.hp;
+        } else {
+            const TT ei = t + tx.h;
+            if (S < ei) {
+                u -= (S - t) << r.q_log2;
+                rc = S;
+                eb = S + (TT)ceil_p(u, r.p_h, r.inv_ph, r.c_ph);
+            } else {
+                eb = ei;
+                ecmp = inf_time<TT>();
+            }
+        }
+        while (ecmp < eb) {
+            dcross += dc;
+            const TT ep = E;
+            ++i;
+            const DRec<TT> y = v.D[(uint32_t)(perm >> (4 * i)) & 15u];
+            S = tmax(ep, v.Q[(i < j ? i : j - 1) * QS]);  // slot j - 1 exists: i >= 1
+            E = S + y.dp;
+            dc = y.d;
+            ecmp = E;
+            if (!(i < j) || S != ep) {
+                u -= TT(r.p_h) * (ep - rc);
+                rc = ep;
+                const TT ei = rc + ceil_q(u, r.q_log2);
+                const bool start = i < j && S < ei;
+                const TT us = u - ((S - rc) << r.q_log2);
+                const TT ebs = S + (TT)ceil_p(us, r.p_h, r.inv_ph, r.c_ph);
+                u = start ? us : u;
+                rc = start ? S : rc;
+                eb = start ? ebs : ei;
+                ecmp = start ? ecmp : inf_time<TT>();
+            }
+        }
+        run = ecmp != inf_time<TT>();
+        t = eb;
+        ck = tmax(eb, ck) + tx.k;
+        const ST e = (ST)ck - (ST)dpre;
+        emax = e > emax ? e : emax;
+        dpre += tx.d;
+        if (j + 1 < n) v.Q[j * QS] = ck;
+        if (i == j) {  // every earlier DtH has ended: DtH j starts when its kernel ends
+            S = ck;
+            E = ck + v.D[x].dp;
+            dc = tx.d;
+        }
+    }
+    TT T = (TT)(emax + (ST)dpre);
+    if (run) {
+        const TT dend = t + (dpre - dcross) - ((TT(r.p_d) * (t - S)) >> r.q_log2);
+        T = tmax(T, dend);
+    }
+    return T;
 }
 
 // Host-side validity bound for the 32-bit time path (checked on the device

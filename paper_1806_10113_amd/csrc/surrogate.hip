@@ -41,35 +41,30 @@ constexpr int GK = 32;  // K per MFMA instruction (16 x 16 x 32 bf16)
 // otherwise (mode 1); every kernel below exists in both widths and takes the
 // groups of its own mode.
 
+// The group's tables for this wave; whether it takes the potential form.
 template <typename TT>
-struct WaveTables {
-    Quad<TT> H[4][MAXN];
-    DRec<TT> D[4][MAXN];
-};
-
-template <typename TT, int NT>
-__device__ __forceinline__ TT eval_perm(uint64_t perm, int n, const View<TT, 1, NT> &v, const Rates &r) {
-    return simulate_order(n, [perm](int j) { return (uint32_t)((perm >> (4 * j)) & 15u); }, v, r);
-}
-
-template <typename TT>
-__device__ __forceinline__ void load_group(WaveTables<TT> &wt, int w, int lane, const tgo_task *t, int n,
-                                           const Rates &r) {
-    if (lane < n) table_entry<TT>(t[lane], r, &wt.H[w][lane], &wt.D[w][lane]);
+__device__ __forceinline__ bool load_group(OrderTables<TT> &wt, const tgo_task *t, int n, const Rates &r) {
+    const bool potential = order_tables(wt, t, n, r);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    return potential;
 }
 
 template <typename TT>
 constexpr int mode_of() { return sizeof(TT) == 4 ? 0 : 1; }
 
-// dynamic LDS of the exact-lane kernels: the per-lane kernel queue
-// (the 64-bit kernels run blocks of 128 lanes: their queue stays at 32 KB)
+// Lanes per block of the exact-lane kernels, and their dynamic LDS: the
+// per-lane queue.  One wave per block: waves work alone, and LDS (8.3 KB a wave
+// at 16 positions in 32-bit time) is what limits how many are resident, so
+// small blocks waste least of it: the plain search below took 751 / 764 / 786 /
+// 783 us with 64 / 128 / 192 / 256 lanes.
 template <typename TT>
-constexpr int lane_threads() { return sizeof(TT) == 4 ? SG_THREADS : SG_THREADS / 2; }
+constexpr int lane_threads() { return 64; }
 template <typename TT>
-constexpr size_t lane_queue_bytes() { return sizeof(Slot<TT>) * lane_threads<TT>() * SG_POS; }
+constexpr int lane_waves() { return lane_threads<TT>() / 64; }
+template <typename TT>
+constexpr size_t lane_queue_bytes() { return order_queue_bytes<TT>(SG_POS, lane_threads<TT>()); }
 
 // per group: 0 (32-bit path), 1 (64-bit path) or a TGO_E* code (size out of
 // range, a duration outside [0, 2^40))
@@ -93,12 +88,9 @@ __global__ __launch_bounds__(NT) void pairs_kernel(const tgo_task *__restrict__ 
                                                            const int32_t *__restrict__ mode,
                                                            uint8_t *orders, int32_t *gid, int64_t *T) {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ WaveTables<TT> wt;
+    __shared__ OrderTables<TT> wt[NT / 64];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    View<TT, 1, NT> v;
-    v.H = wt.H[w];
-    v.D = wt.D[w];
-    v.Q = reinterpret_cast<Slot<TT> *>(smem) + threadIdx.x;
+    const auto v = wt[w].template view<NT>(reinterpret_cast<TT *>(smem) + threadIdx.x);
     const int64_t tiles_per_group = per / 64;
     const int64_t total = tiles_per_group * G;
     const int64_t wstride = (int64_t)gridDim.x * (NT / 64);
@@ -119,9 +111,9 @@ __global__ __launch_bounds__(NT) void pairs_kernel(const tgo_task *__restrict__ 
             continue;
         }
         gid[row] = g;
-        load_group(wt, w, lane, tasks + offs[g], n, r);
+        const bool potential = load_group(wt[w], tasks + offs[g], n, r);
         const uint64_t perm = sample_ordering(n, (uint32_t)g, (uint64_t)s, seed);
-        T[row] = (int64_t)eval_perm<TT, NT>(perm, n, v, r);
+        T[row] = (int64_t)simulate_order(n, perm, v, r, potential);
         for (int p = 0; p < SG_POS; ++p) o[p] = p < n ? (uint8_t)((perm >> (4 * p)) & 15u) : 0xff;
         __builtin_amdgcn_wave_barrier();
     }
@@ -139,6 +131,10 @@ __device__ __forceinline__ void pair_min(uint64_t &t, uint64_t &s, uint64_t t2, 
 }
 
 // Plain exact search: `per` sampled orderings per group (a multiple of 64).
+// Bound by the latency of dependent instructions and LDS reads at the 4-5
+// waves per SIMD that LDS leaves.  1,024 groups of 16 tasks x 16,384 samples:
+// 1,240 us in the chain form (3,145 VALU instructions per ordering and wave,
+// 35 % of the lanes active), 751 us in the potential form (1,627).
 // Each wave takes chunks of `chunk` consecutive 64-sample tiles of one group,
 // so the group's table is loaded and the wave's minimum published once per
 // chunk; wave-uniform values are kept in scalar registers.  32-bit path: the
@@ -155,12 +151,9 @@ __global__ __launch_bounds__(NT) void random_search_kernel(const tgo_task *__res
                                                                    const int32_t *__restrict__ mode,
                                                                    unsigned long long *best, BestPair *wpart) {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ WaveTables<TT> wt;
+    __shared__ OrderTables<TT> wt[NT / 64];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    View<TT, 1, NT> v;
-    v.H = wt.H[w];
-    v.D = wt.D[w];
-    v.Q = reinterpret_cast<Slot<TT> *>(smem) + threadIdx.x;
+    const auto v = wt[w].template view<NT>(reinterpret_cast<TT *>(smem) + threadIdx.x);
     const int64_t tiles_per_group = per / 64;
     const int64_t chunks_per_group = (tiles_per_group + chunk_tiles - 1) / chunk_tiles;
     const int64_t total = chunks_per_group * G;
@@ -169,14 +162,14 @@ __global__ __launch_bounds__(NT) void random_search_kernel(const tgo_task *__res
         const int g = (int)(chunk / chunks_per_group);
         if (mode[g] != mode_of<TT>()) continue;
         const int n = offs[g + 1] - offs[g];
-        load_group(wt, w, lane, tasks + offs[g], n, r);
+        const bool potential = load_group(wt[w], tasks + offs[g], n, r);
         const int64_t t0 = (chunk % chunks_per_group) * chunk_tiles;
         const int64_t t1 = t0 + chunk_tiles < tiles_per_group ? t0 + chunk_tiles : tiles_per_group;
         uint64_t bt = ~0ull, bs = ~0ull;
         for (int64_t tile = t0; tile < t1; ++tile) {
             const int64_t s = tile * 64 + lane;
             const uint64_t perm = sample_ordering(n, (uint32_t)g, (uint64_t)s, seed);
-            pair_min(bt, bs, (uint64_t)eval_perm<TT, NT>(perm, n, v, r), (uint64_t)s);
+            pair_min(bt, bs, (uint64_t)simulate_order(n, perm, v, r, potential), (uint64_t)s);
         }
         for (int m = 32; m >= 1; m >>= 1) {
             const uint64_t t2 = shfl_xor64(bt, m), s2 = shfl_xor64(bs, m);
@@ -208,12 +201,9 @@ __global__ __launch_bounds__(NT) void rescore_kernel(const tgo_task *__restrict_
                                                              const unsigned long long *__restrict__ keys,
                                                              int key_stride, BestPair *out) {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ WaveTables<TT> wt;
+    __shared__ OrderTables<TT> wt[NT / 64];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    View<TT, 1, NT> v;
-    v.H = wt.H[w];
-    v.D = wt.D[w];
-    v.Q = reinterpret_cast<Slot<TT> *>(smem) + threadIdx.x;
+    const auto v = wt[w].template view<NT>(reinterpret_cast<TT *>(smem) + threadIdx.x);
     for (int g = blockIdx.x * (NT / 64) + w; g < G; g += gridDim.x * (NT / 64)) {
         const int md = mode[g];
         if (md >= 0 && md != mode_of<TT>()) continue;
@@ -222,13 +212,13 @@ __global__ __launch_bounds__(NT) void rescore_kernel(const tgo_task *__restrict_
             continue;
         }
         const int n = offs[g + 1] - offs[g];
-        load_group(wt, w, lane, tasks + offs[g], n, r);
+        const bool potential = load_group(wt[w], tasks + offs[g], n, r);
         uint64_t bt = ~0ull, bs = ~0ull;
         const unsigned long long kk = lane < k ? keys[(int64_t)g * key_stride + lane] : ~0ull;
         if (kk != ~0ull) {
             const uint64_t s = kk & 0xffffffffull;
             const uint64_t perm = sample_ordering(n, gkeys ? gkeys[g] : (uint32_t)g, s, seed);
-            bt = (uint64_t)eval_perm<TT, NT>(perm, n, v, r);
+            bt = (uint64_t)simulate_order(n, perm, v, r, potential);
             bs = s;
         }
         for (int m = 32; m >= 1; m >>= 1) {
@@ -1673,11 +1663,11 @@ int tgo_surrogate_pairs(const tgo_model *model, const tgo_task *d_tasks, const i
     hipLaunchKernelGGL(group_status_kernel, dim3((G + 255) / 256), dim3(256), 0, st, d_tasks, d_offs, G, r, mode,
                        d_status);
     const int64_t tiles = per_group / 64 * G;
-    const int blocks = (int)std::min<int64_t>((tiles + 3) / 4, 8192);
-    hipLaunchKernelGGL(pairs_kernel<uint32_t>, dim3(blocks), dim3(SG_THREADS), lane_queue_bytes<uint32_t>(), st,
+    const auto grid = [tiles](int waves) { return dim3((uint32_t)std::min<int64_t>((tiles + waves - 1) / waves, 32768 / waves)); };
+    hipLaunchKernelGGL(pairs_kernel<uint32_t>, grid(lane_waves<uint32_t>()), dim3(lane_threads<uint32_t>()), lane_queue_bytes<uint32_t>(), st,
                        d_tasks, d_offs, G, r, per_group, seed, mode, d_orders, d_gid, d_T);
     // groups on the 64-bit time path (the blocks skip every other group)
-    hipLaunchKernelGGL(pairs_kernel<uint64_t>, dim3(2 * blocks), dim3(lane_threads<uint64_t>()), lane_queue_bytes<uint64_t>(), st,
+    hipLaunchKernelGGL(pairs_kernel<uint64_t>, grid(lane_waves<uint64_t>()), dim3(lane_threads<uint64_t>()), lane_queue_bytes<uint64_t>(), st,
                        d_tasks, d_offs, G, r, per_group, seed, mode, d_orders, d_gid, d_T);
     TGO_HIP(hipGetLastError());
     return TGO_OK;
@@ -1906,9 +1896,9 @@ int tgo_surrogate_search(tgo_surrogate *s, const tgo_model *model, const tgo_tas
     if (rc) return rc;
     rc = launch_heuristic(r, d_tasks, d_offs, G, s->horders, 16, s->hns, 1, st);
     if (rc) return rc;
-    hipLaunchKernelGGL(rescore_kernel<uint32_t>, dim3((G + 3) / 4), dim3(SG_THREADS), lane_queue_bytes<uint32_t>(), st,
+    hipLaunchKernelGGL(rescore_kernel<uint32_t>, dim3((G + lane_waves<uint32_t>() - 1) / lane_waves<uint32_t>()), dim3(lane_threads<uint32_t>()), lane_queue_bytes<uint32_t>(), st,
                        d_tasks, d_offs, G, r, topk, seed, s->status, d_keys, s->cand[cur], (int)len, s->best);
-    hipLaunchKernelGGL(rescore_kernel<uint64_t>, dim3((G + 1) / 2), dim3(lane_threads<uint64_t>()), lane_queue_bytes<uint64_t>(), st,
+    hipLaunchKernelGGL(rescore_kernel<uint64_t>, dim3((G + lane_waves<uint64_t>() - 1) / lane_waves<uint64_t>()), dim3(lane_threads<uint64_t>()), lane_queue_bytes<uint64_t>(), st,
                        d_tasks, d_offs, G, r, topk, seed, s->status, d_keys, s->cand[cur], (int)len, s->best);
     hipLaunchKernelGGL(search_finish_kernel, dim3((G + 255) / 256), dim3(256), 0, st, d_offs, G, seed, d_keys,
                        s->status, s->best, (const unsigned long long *)nullptr, (const BestPair *)nullptr, 0,
@@ -1968,8 +1958,9 @@ int tgo_random_search(const tgo_model *model, const tgo_task *d_tasks, const int
         const int64_t tiles = tpg * G;
         const int64_t chunk_tiles = std::max<int64_t>(1, std::min<int64_t>(64, tiles >> 16));
         const int64_t chunks = (tpg + chunk_tiles - 1) / chunk_tiles * G;
-        const int blocks = (int)std::min<int64_t>((chunks + 3) / 4, 16384);
-        hipLaunchKernelGGL(random_search_kernel<uint32_t>, dim3(blocks), dim3(SG_THREADS),
+        constexpr int lw = lane_waves<uint32_t>();
+        const int blocks = (int)std::min<int64_t>((chunks + lw - 1) / lw, 65536 / lw);
+        hipLaunchKernelGGL(random_search_kernel<uint32_t>, dim3(blocks), dim3(lane_threads<uint32_t>()),
                            lane_queue_bytes<uint32_t>(), st, d_tasks, d_offs, G, r, per, seed, chunk_tiles, mode,
                            best, wpart);
         // groups on the 64-bit time path: at most RS_WIDE_CHUNKS chunks each

@@ -69,11 +69,11 @@ __device__ __forceinline__ uint64_t sample_ordering(int n, uint32_t g, uint64_t 
         if (k == 8) x = u.z;
         if (k == 12) x = u.w;
         const uint64_t p = (uint64_t)x * (uint64_t)(i + 1);
-        const uint32_t j = (uint32_t)(p >> 32);
+        const uint32_t sj = 4u * (uint32_t)(p >> 32);
         x = (uint32_t)p;
-        const uint64_t vi = (perm >> (4 * i)) & 15u, vj = (perm >> (4 * j)) & 15u;
-        perm &= ~((15ull << (4 * i)) | (15ull << (4 * j)));
-        perm |= (vi << (4 * j)) | (vj << (4 * i));
+        // swap nibbles i and j: flip the bits in which they differ, in both (none if i = j)
+        const uint64_t diff = ((perm >> (4 * i)) ^ (perm >> sj)) & 15u;
+        perm ^= (diff << (4 * i)) ^ (diff << sj);
     }
     return perm;
 }

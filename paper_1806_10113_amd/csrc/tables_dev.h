@@ -74,4 +74,31 @@ __device__ inline void table_entry(const tgo_task &t, const Rates &r, Quad<TT> *
     *D = pd;
 }
 
+// Entry `lane` of a wave's or block's tables (every lane of the wave active):
+// the tasks' and, where the group takes the potential form, that form's.
+// Returns whether it does, as a scalar: two DMA engines, and the time bound
+// that classify_group tests is small enough.
+template <typename TT>
+__device__ __forceinline__ bool order_tables(OrderTables<TT> &o, const tgo_task *t, int n, const Rates &r) {
+    const int lane = threadIdx.x & 63;
+    Quad<TT> h = {};
+    DRec<TT> d = {};
+    if (lane < n) table_entry<TT>(t[lane], r, &h, &d);
+    uint64_t sum = (uint64_t)h.hp + (uint64_t)h.k + (uint64_t)d.dp;
+    for (int m = 8; m >= 1; m >>= 1) sum += shfl_xor64(sum, m);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)sum);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(sum >> 32));
+    const bool potential = !r.one_dma && potential_fits<TT>((((uint64_t)hi << 32) | lo) + time_bound_slack(n), r);
+    if (lane < n) {
+        if (potential) {
+            o.P[lane] = PRec<TT>{(TT)(h.h << r.q_log2), h.k, h.d, d.dp};
+            o.gain[lane] = TT(r.p_h) * d.dp;
+        } else {
+            o.H[lane] = h;
+            o.D[lane] = d;
+        }
+    }
+    return potential;
+}
+
 }  // namespace tgo
