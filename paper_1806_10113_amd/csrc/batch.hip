@@ -22,7 +22,7 @@
 #include <string>
 #include <vector>
 
-#include "enum_dev.h"
+#include "enum_kernel.h"
 #include "tables_dev.h"
 #include "tgo_internal.h"
 
@@ -67,34 +67,45 @@ __device__ __forceinline__ uint32_t subtrees_of(int n, int m) {
     return (uint32_t)(fact_c(n) / fact_c(m));
 }
 
-// One block: per-group status and tile counts, exclusive scan into tile_off,
-// accumulators reset, tile counter reset.
 __device__ __forceinline__ uint32_t wide_tiles_of(int n, int wide_tiles) {
     const uint32_t S = subtrees_of(n, n < BT_WIDE_M ? n : BT_WIDE_M);
     return S < (uint32_t)wide_tiles ? S : (uint32_t)wide_tiles;
 }
 
-// Inclusive block scan of v (1024 threads) in sc; returns the exclusive prefix.
-__device__ __forceinline__ uint32_t block_exscan(uint32_t v, uint32_t *sc) {
-    sc[threadIdx.x] = v;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        const uint32_t x = threadIdx.x >= (unsigned)off ? sc[threadIdx.x - off] : 0u;
-        __syncthreads();
-        sc[threadIdx.x] += x;
-        __syncthreads();
+// Exclusive scans of v and w over a block of 1024 threads, and their totals.
+__device__ __forceinline__ void block_exscan2(uint32_t v, uint32_t w, uint2 *wave_sum, uint2 *ex, uint2 *total) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    uint32_t a = v, b = w;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t x = __shfl_up(a, off), y = __shfl_up(b, off);
+        a += lane >= off ? x : 0u;
+        b += lane >= off ? y : 0u;
     }
-    return sc[threadIdx.x] - v;
+    if (lane == 63) wave_sum[wid] = make_uint2(a, b);
+    __syncthreads();
+    uint2 before = make_uint2(0, 0), all = make_uint2(0, 0);
+    for (int i = 0; i < 16; ++i) {
+        const uint2 t = wave_sum[i];
+        before.x += i < wid ? t.x : 0u;
+        before.y += i < wid ? t.y : 0u;
+        all.x += t.x;
+        all.y += t.y;
+    }
+    __syncthreads();
+    *ex = make_uint2(before.x + a - v, before.y + b - w);
+    *total = all;
 }
 
+// One block: per-group status and tile counts, exclusive scan into tile_off,
+// accumulators reset, tile counters reset.  waves: the batch kernel's, which take the first `waves` tiles by their own
+// number; the counter hands out the rest.
 __global__ __launch_bounds__(1024) void batch_prepare(const tgo_task *__restrict__ tasks,
                                                       const int32_t *__restrict__ offs, int G,
                                                       Rates r, BatchCfg cfg, int wide_tiles, int max_n, GroupAcc *acc,
-                                                      uint32_t *tile_off, uint32_t *wtile_off, BatchHdr *hdr) {
-    __shared__ uint32_t sc[1024];
-    __shared__ uint32_t carry, wcarry;
-    if (threadIdx.x == 0) carry = wcarry = 0;
-    __syncthreads();
+                                                      uint32_t *tile_off, uint32_t *wtile_off, BatchHdr *hdr,
+                                                      uint32_t waves, uint32_t wide_waves) {
+    __shared__ uint2 wave_sum[16];
+    uint2 carry = make_uint2(0, 0);
     const uint32_t per_tile = 64u * (uint32_t)cfg.lane_mult;
     for (int base = 0; base < G; base += 1024) {
         const int g = base + threadIdx.x;
@@ -122,28 +133,34 @@ __global__ __launch_bounds__(1024) void batch_prepare(const tgo_task *__restrict
             if (st == 0 && !wide) tiles = (subtrees_of(n, cfg.m[n]) + per_tile - 1) / per_tile;
             if (st == 0 && wide) wtiles = wide_tiles_of(n, wide_tiles);
         }
-        const uint32_t ex = block_exscan(tiles, sc);
-        if (g < G) tile_off[g] = carry + ex;
-        const uint32_t last = sc[1023];
-        __syncthreads();
-        const uint32_t wex = block_exscan(wtiles, sc);
-        if (g < G) wtile_off[g] = wcarry + wex;
-        const uint32_t wlast = sc[1023];
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            carry += last;
-            wcarry += wlast;
+        uint2 ex, total;
+        block_exscan2(tiles, wtiles, wave_sum, &ex, &total);
+        if (g < G) {
+            tile_off[g] = carry.x + ex.x;
+            wtile_off[g] = carry.y + ex.y;
         }
-        __syncthreads();
+        carry.x += total.x;
+        carry.y += total.y;
     }
     if (threadIdx.x == 0) {
-        tile_off[G] = carry;
-        wtile_off[G] = wcarry;
-        hdr->next_tile = 0;
-        hdr->total_tiles = carry;
-        hdr->next_wide = 0;
-        hdr->total_wide = wcarry;
+        tile_off[G] = carry.x;
+        wtile_off[G] = carry.y;
+        hdr->next_tile = waves;
+        hdr->total_tiles = carry.x;
+        hdr->next_wide = wide_waves;
+        hdr->total_wide = carry.y;
     }
+}
+
+// The wave's next tile after `tile` (first: its own number), wave-uniform.
+// Same-address atomics are served one after another (about 15 ns each here): a
+// launch of 8,192 waves that each asked once took 100 us to find a small
+// batch empty.
+__device__ __forceinline__ uint32_t next_tile(unsigned int *counter, uint32_t total, uint32_t waves, int lane) {
+    if (total <= waves) return total;  // one tile per wave covers the batch
+    uint32_t tile = 0;
+    if (lane == 0) tile = atomicAdd(counter, 1u);
+    return __builtin_amdgcn_readfirstlane(tile);
 }
 
 // Simulation state of a lane: the chain form with two DMA engines, the
@@ -182,7 +199,10 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long x) {
 // Two DMA engines: at most 80 VGPRs, so 6 waves fit per SIMD (the 26 KB of
 // LDS per block allows 6 per CU); the walk of 5 levels then spills a few
 // registers that are read once per tile or subtree, not in the event loop
-// (12.1 -> 11.3 ms on the 4,096-group batch).
+// (12.1 -> 11.3 ms on the 4,096-group batch).  Subtrees in set-major order, as
+// in the single-group kernel: the lanes of a wave walk the same remaining tasks
+// (4,096 groups of 4 to 10 tasks, one label per task: 13.3 ms in rank order,
+// 10.1 in set-major order).
 template <int DMA, int MMAX>
 __global__ __launch_bounds__(BT_THREADS) __attribute__((amdgpu_waves_per_eu(DMA == DMA_TWO ? 6 : 1))) void batch_kernel(const tgo_task *__restrict__ tasks,
                                                            const int32_t *__restrict__ offs, int G,
@@ -198,13 +218,9 @@ __global__ __launch_bounds__(BT_THREADS) __attribute__((amdgpu_waves_per_eu(DMA 
     v.H = Ht[w];
     v.D = Dt[w];
     v.Q = reinterpret_cast<Slot<uint32_t> *>(smem) + threadIdx.x;
-    const uint32_t total = hdr->total_tiles;
+    const uint32_t total = hdr->total_tiles, waves = gridDim.x * BT_WAVES;
     const uint32_t per_tile = 64u * (uint32_t)cfg.lane_mult;
-    for (;;) {
-        uint32_t tile = 0;
-        if (lane == 0) tile = atomicAdd(&hdr->next_tile, 1u);
-        tile = __builtin_amdgcn_readfirstlane(__shfl(tile, 0));  // wave-uniform: keep it scalar
-        if (tile >= total) break;
+    for (uint32_t tile = blockIdx.x * BT_WAVES + w; tile < total; tile = next_tile(&hdr->next_tile, total, waves, lane)) {
         // group of this tile: largest g with tile_off[g] <= tile
         int lo = 0, hi = G;  // tile_off[lo] <= tile < tile_off[hi]
         while (hi - lo > 1) {
@@ -230,7 +246,8 @@ __global__ __launch_bounds__(BT_THREADS) __attribute__((amdgpu_waves_per_eu(DMA 
             const uint32_t s = s0 + (uint32_t)k * 64u + (uint32_t)lane;
             if (s < S) {
                 BatchLane<uint32_t, DMA> st;
-                const uint32_t list = (uint32_t)prefix<DMA>(st, s, n, m, v, r);
+                uint32_t lex;
+                const uint32_t list = (uint32_t)prefix_by_set<DMA>(st, s, n, m, v, r, &lex);
                 Sub<uint32_t> u;
                 sub_init(u);
                 switch (m) {
@@ -244,7 +261,7 @@ __global__ __launch_bounds__(BT_THREADS) __attribute__((amdgpu_waves_per_eu(DMA 
                         if constexpr (MMAX >= 5) run_subtree<5, DMA>(c, v, st, list, u);
                         break;
                 }
-                const uint64_t r0 = (uint64_t)s * fact_c(m);
+                const uint64_t r0 = (uint64_t)lex * fact_c(m);
                 const unsigned long long a = ((unsigned long long)u.min_t << 32) | (r0 + u.min_l);
                 const unsigned long long b =
                     ((unsigned long long)(u.max_t1 - 1u) << 32) | (0xffffffffull - (r0 + u.max_l));
@@ -286,12 +303,8 @@ __global__ __launch_bounds__(BT_THREADS) void batch_wide_kernel(const tgo_task *
     v.H = Ht[w];
     v.D = Dt[w];
     v.Q = reinterpret_cast<Slot<TT> *>(smem) + threadIdx.x;
-    const uint32_t total = hdr->total_wide;
-    for (;;) {
-        uint32_t tile = 0;
-        if (lane == 0) tile = atomicAdd(&hdr->next_wide, 1u);
-        tile = __builtin_amdgcn_readfirstlane(__shfl(tile, 0));
-        if (tile >= total) break;
+    const uint32_t total = hdr->total_wide, waves = gridDim.x * BT_WAVES;
+    for (uint32_t tile = blockIdx.x * BT_WAVES + w; tile < total; tile = next_tile(&hdr->next_wide, total, waves, lane)) {
         int lo = 0, hi = G;  // wtile_off[lo] <= tile < wtile_off[hi]
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
@@ -348,29 +361,16 @@ __global__ __launch_bounds__(BT_THREADS) void batch_wide_kernel(const tgo_task *
     }
 }
 
-__device__ inline void unrank16(int n, uint64_t r, uint8_t *out) {
-    uint64_t list = 0;
-    for (int i = n - 1; i >= 0; --i) list = (list << 4) | (uint64_t)i;
-    for (int i = 0; i < n; ++i) {
-        const uint64_t f = fact_c(n - 1 - i);
-        const uint64_t cd = r / f;
-        r -= cd * f;
-        out[i] = (uint8_t)((list >> (4 * cd)) & 15u);
-        const uint64_t lo = list & ((1ull << (4 * cd)) - 1ull);
-        const uint64_t hi = (list >> (4 * cd + 4)) << (4 * cd);
-        list = lo | hi;
-    }
-    for (int i = n; i < 16; ++i) out[i] = 0xff;
-}
-
+// One thread per group: its summary, written field by field.
 __global__ __launch_bounds__(256) void batch_finalize(const GroupAcc *__restrict__ acc, int G,
                                                       const uint32_t *__restrict__ wtile_off,
                                                       const Partial *__restrict__ parts, tgo_summary *out) {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= G) return;
     const GroupAcc a = acc[g];
+    Partial p = {};
     if (a.status == 0 && a.wide) {
-        Partial p = parts[wtile_off[g]];
+        p = parts[wtile_off[g]];
         for (uint32_t i = wtile_off[g] + 1; i < wtile_off[g + 1]; ++i) {
             const Partial q = parts[i];
             merge_min(p.min_t, p.min_r, q.min_t, q.min_r);
@@ -378,59 +378,32 @@ __global__ __launch_bounds__(256) void batch_finalize(const GroupAcc *__restrict
             add128(p.sum_lo, p.sum_hi, q.sum_lo, q.sum_hi);
             p.fp += q.fp;
         }
-        tgo_summary s;
-        const uint64_t count = fact_c(a.n);
-        s.n = a.n;
-        s.status = 0;
-        for (int i = 0; i < 16; ++i) { s.best[i] = 0xff; s.worst[i] = 0xff; s.heur[i] = 0xff; }
-        s.heur_ns = -1;
-        s.min_ns = (int64_t)p.min_t;
-        s.argmin_rank = p.min_r;
-        s.max_ns = (int64_t)(p.max_t - 1);
-        s.argmax_rank = p.max_r;
-        s.sum_lo = p.sum_lo;
-        s.sum_hi = p.sum_hi;
-        s.count = count;
-        s.fingerprint = p.fp;
-        if (p.sum_hi == 0) {
-            const uint64_t qt = p.sum_lo / count, rm = p.sum_lo % count;
-            s.mean_ns = (double)qt + (double)rm / (double)count;
-        } else {
-            s.mean_ns = ((double)p.sum_hi * 18446744073709551616.0 + (double)p.sum_lo) / (double)count;
-        }
-        unrank16(a.n, s.argmin_rank, s.best);
-        unrank16(a.n, s.argmax_rank, s.worst);
-        out[g] = s;
-        return;
+    } else if (a.status == 0) {
+        p.min_t = a.minkey >> 32;
+        p.min_r = a.minkey & 0xffffffffull;
+        p.max_t = (a.maxkey >> 32) + 1;
+        p.max_r = 0xffffffffull - (a.maxkey & 0xffffffffull);
+        p.sum_lo = a.sum;
+        p.fp = a.fp;
     }
-    tgo_summary s;
-    s.n = a.n;
-    s.status = a.status;
-    for (int i = 0; i < 16; ++i) { s.best[i] = 0xff; s.worst[i] = 0xff; s.heur[i] = 0xff; }
-    s.heur_ns = -1;
-    if (a.status != 0) {
-        s.min_ns = s.max_ns = 0;
-        s.argmin_rank = s.argmax_rank = 0;
-        s.sum_lo = s.sum_hi = 0;
-        s.count = 0;
-        s.fingerprint = 0;
-        s.mean_ns = 0.0;
-    } else {
-        const uint64_t count = fact_c(a.n);
-        s.min_ns = (int64_t)(a.minkey >> 32);
-        s.argmin_rank = a.minkey & 0xffffffffull;
-        s.max_ns = (int64_t)(a.maxkey >> 32);
-        s.argmax_rank = 0xffffffffull - (a.maxkey & 0xffffffffull);
-        s.sum_lo = a.sum;
-        s.sum_hi = 0;
-        s.count = count;
-        s.fingerprint = a.fp;
-        const uint64_t qt = a.sum / count, rm = a.sum % count;
-        s.mean_ns = (double)qt + (double)rm / (double)count;
-        unrank16(a.n, s.argmin_rank, s.best);
-        unrank16(a.n, s.argmax_rank, s.worst);
-    }
-    out[g] = s;
+    const bool ok = a.status == 0;
+    const uint64_t count = ok ? fact_c(a.n) : 0;
+    tgo_summary *s = out + g;
+    s->n = a.n;
+    s->status = a.status;
+    s->count = count;
+    s->min_ns = ok ? (int64_t)p.min_t : 0;
+    s->max_ns = ok ? (int64_t)(p.max_t - 1) : 0;
+    s->argmin_rank = ok ? p.min_r : 0;
+    s->argmax_rank = ok ? p.max_r : 0;
+    s->sum_lo = p.sum_lo;
+    s->sum_hi = p.sum_hi;
+    s->fingerprint = p.fp;
+    s->mean_ns = ok ? mean_of(p.sum_lo, p.sum_hi, count) : 0.0;
+    put_order(s->best, ok ? unrank_nibbles(a.n, p.min_r) : 0, ok ? a.n : 0);
+    put_order(s->worst, ok ? unrank_nibbles(a.n, p.max_r) : 0, ok ? a.n : 0);
+    put_order(s->heur, 0, 0);
+    s->heur_ns = -1;
 }
 
 // ------------------------------------------------------------------- host side
@@ -484,8 +457,10 @@ namespace tgo {
 
 static int enqueue_batch(tgo_plan *p, const BatchCfg &cfg, const tgo_task *d_tasks,
                          const int32_t *d_offs, int G, tgo_summary *d_out, hipStream_t st) {
+    const dim3 wgrid(p->cus * 2);
     hipLaunchKernelGGL(batch_prepare, dim3(1), dim3(1024), 0, st, d_tasks, d_offs, G, p->r, cfg, p->wide_tiles,
-                       p->max_n, p->acc, p->tile_off, p->wtile_off, p->hdr);
+                       p->max_n, p->acc, p->tile_off, p->wtile_off, p->hdr, (uint32_t)cfg.blocks * BT_WAVES,
+                       wgrid.x * BT_WAVES);
     int mmax = 1;
     for (int n = 1; n <= BT_MAX_N; ++n) mmax = std::max(mmax, (int)cfg.m[n]);
     // no kernel-completion queue with one DMA engine
@@ -514,7 +489,6 @@ static int enqueue_batch(tgo_plan *p, const BatchCfg &cfg, const tgo_task *d_tas
     }
     // the 64-bit path (its blocks return at once when no group needs it)
     const size_t wshm = sizeof(Slot<uint64_t>) * BT_THREADS * BT_MAX_N;
-    const dim3 wgrid(p->cus * 2);
     if (p->r.one_dma)
         hipLaunchKernelGGL(batch_wide_kernel<DMA_ONE>, wgrid, block, 0, st, d_tasks, d_offs, G, p->r, p->wide_tiles,
                            p->wtile_off, p->hdr, p->wparts);

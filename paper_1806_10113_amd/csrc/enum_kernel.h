@@ -170,6 +170,15 @@ static_assert(offsetof(tgo_summary, best) % 8 == 0 && offsetof(tgo_summary, wors
                   offsetof(tgo_summary, heur) % 8 == 0,
               "orderings are written as 8-byte words");
 
+// sum / count: whole part exactly, then the fraction
+__device__ __forceinline__ double mean_of(uint64_t sum_lo, uint64_t sum_hi, uint64_t count) {
+    if (sum_hi == 0) {
+        const uint64_t qt = sum_lo / count, rm = sum_lo % count;
+        return (double)qt + (double)rm / (double)count;
+    }
+    return ((double)sum_hi * 18446744073709551616.0 + (double)sum_lo) / (double)count;
+}
+
 // The fields of *out that the enumeration fills, from its reduced result
 // (thread 0 the numbers and the best ordering, thread 64 the worst).
 template <typename Decode>
@@ -186,17 +195,7 @@ __device__ __forceinline__ void write_summary(const Partial &o, int status, int 
         out->sum_lo = status ? 0 : o.sum_lo;
         out->sum_hi = status ? 0 : o.sum_hi;
         out->fingerprint = status ? 0 : o.fp;
-        // mean = sum / count: whole part exactly, then the fraction
-        double mean = 0.0;
-        if (status == 0) {
-            if (o.sum_hi == 0) {
-                const uint64_t qt = o.sum_lo / count, rm = o.sum_lo % count;
-                mean = (double)qt + (double)rm / (double)count;
-            } else {
-                mean = ((double)o.sum_hi * 18446744073709551616.0 + (double)o.sum_lo) / (double)count;
-            }
-        }
-        out->mean_ns = mean;
+        out->mean_ns = status ? 0.0 : mean_of(o.sum_lo, o.sum_hi, count);
         put_order(out->best, status ? 0 : decode(o.min_r), status ? 0 : n);
     } else if (threadIdx.x == 64) {
         put_order(out->worst, status ? 0 : decode(o.max_r), status ? 0 : n);
