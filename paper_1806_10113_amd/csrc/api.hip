@@ -38,6 +38,14 @@ int make_rates(const tgo_model *m, Rates *r) {
     r->c_ph = ((double)m->p_htd - 0.5) * r->inv_ph;
     r->inv_pd = 1.0 / (double)m->p_dth;
     r->c_pd = ((double)m->p_dth - 0.5) * r->inv_pd;
+    uint32_t odd = (uint32_t)(q - m->p_htd);
+    r->dsh = 0;
+    r->dinv = 0;
+    if (odd) {
+        for (; !(odd & 1u); odd >>= 1) ++r->dsh;
+        r->dinv = odd;  // Newton: each step doubles the correct low bits (3 at first)
+        for (int i = 0; i < 4; ++i) r->dinv *= 2u - odd * r->dinv;
+    }
     return TGO_OK;
 }
 

@@ -214,8 +214,7 @@ __host__ __device__ constexpr size_t enum_tables_bytes(int n) {
 }
 template <class Rule, typename TT>
 inline size_t enum_shm_bytes(int n, bool one_dma) {
-    const int slots = Rule::queue(one_dma) ? (n > 1 ? n - 1 : 1) : 0;
-    const size_t q = sizeof(Slot<TT>) * EX_THREADS * (size_t)slots;
+    const size_t q = Rule::queue(one_dma) ? EX_THREADS * Rule::template lane_bytes<TT>(n) : 0;
     const size_t red = sizeof(Partial) * (EX_THREADS / 64);
     return enum_tables_bytes<Rule, TT>(n) + (q > red ? q : red);
 }
@@ -223,6 +222,22 @@ inline size_t enum_shm_bytes(int n, bool one_dma) {
 // Ranks of one group's orderings: subtrees in set-major order for the large
 // groups, lexicographic order for the small ones.
 struct GroupRule {
+    // Mode word for which a kernel of this width runs.
+    template <typename TT>
+    static constexpr int mode() { return sizeof(TT) == 4 ? 0 : 1; }
+    // Queue of one lane, and the view's pointers into the block's.
+    template <typename TT>
+    static __host__ __device__ constexpr size_t lane_bytes(int n) {
+        return sizeof(Slot<TT>) * (size_t)(n > 1 ? n - 1 : 1);
+    }
+    template <typename TT, typename ViewT>
+    static __device__ __forceinline__ void bind(ViewT &v, unsigned char *queue, int) {
+        v.Q = reinterpret_cast<Slot<TT> *>(queue) + threadIdx.x;
+    }
+    template <typename TT>
+    static __device__ __forceinline__ void entry(const tgo_task &t, const Rates &r, Quad<TT> *H, DRec<TT> *D) {
+        table_entry<TT>(t, r, H, D);
+    }
     template <int DMA, typename LaneT, typename ViewT, typename ArgsT>
     static __device__ __forceinline__ uint64_t prefix(LaneT &st, uint32_t s, int n, int m, ViewT &v, const Rates &r,
                                                       const ArgsT &, uint32_t *lex) {
@@ -278,17 +293,17 @@ __global__ __launch_bounds__(EX_THREADS) __attribute__((amdgpu_waves_per_eu(Rule
 void enum_kernel(const tgo_task *__restrict__ tasks, int n, Rates r, typename Rule::Args args, uint32_t n_sub,
                  int64_t *out, Partial *partials, ExAcc *acc, const int *__restrict__ modep) {
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int MODE = sizeof(TT) == 4 ? 0 : 1;
-    if (*modep != MODE) return;
+    if (*modep != Rule::template mode<TT>()) return;
     Quad<TT> *Ht = reinterpret_cast<Quad<TT> *>(smem);
     DRec<TT> *Dt = reinterpret_cast<DRec<TT> *>(smem + (size_t)n * sizeof(Quad<TT>));
     unsigned char *qbase = smem + enum_tables_bytes<Rule, TT>(n);
-    if ((int)threadIdx.x < n) table_entry<TT>(tasks[threadIdx.x], r, &Ht[threadIdx.x], &Dt[threadIdx.x]);
+    if ((int)threadIdx.x < n)
+        Rule::template entry<TT>(tasks[threadIdx.x], r, &Ht[threadIdx.x], &Dt[threadIdx.x]);
 
     typename Rule::template View<TT> v;
     v.H = Ht;
     v.D = Dt;
-    v.Q = reinterpret_cast<Slot<TT> *>(qbase) + threadIdx.x;
+    Rule::template bind<TT>(v, qbase, n);
     uint64_t seq = 0;  // task at each placed position, one per nibble (rules that ask for it)
     Rule::template load<false>(v, smem + (size_t)n * (sizeof(Quad<TT>) + sizeof(DRec<TT>)), args, n, &seq);
     __syncthreads();
@@ -383,7 +398,7 @@ __device__ __forceinline__ void finalize_block(const Partial *__restrict__ parts
         if (threadIdx.x == 0) red[0] = p;
         __syncthreads();
         p = red[0];
-    } else if (mode == 0) {
+    } else if (mode >= 0) {
         // every wave merges the accumulators (waves 0 and 1 use the result)
         if (threadIdx.x >= 128) return;
         const ExAcc mine = acc[threadIdx.x & 63];
@@ -647,19 +662,22 @@ inline int enum_grid(const void *k32, size_t shm32, uint32_t n_sub, size_t extra
     return TGO_OK;
 }
 
+// Launch one instantiation.
+template <class Rule, typename TT, int M, bool STORE, int DMA>
+inline void enum_launch_one(hipStream_t st, const tgo_task *t, int n, const Rates &r, const typename Rule::Args &args,
+                            uint32_t n_sub, int64_t *out, uint32_t blocks, const EnumScratch &sc) {
+    hipLaunchKernelGGL((enum_kernel<Rule, TT, M, STORE, DMA>), dim3(blocks + (Rule::SIDE ? 1u : 0u)), dim3(EX_THREADS),
+                       (enum_shm_bytes<Rule, TT>(n, DMA == DMA_ONE)), st, t, n, r, args, n_sub, out, sc.parts, sc.acc,
+                       sc.mode);
+}
+
 // Launch the 32-bit and 64-bit instantiations (the one that does not match
 // the group's time path returns at once).
 template <class Rule, int M, bool STORE, int DMA>
 inline int enum_launch(hipStream_t st, const tgo_task *t, int n, const Rates &r, const typename Rule::Args &args,
                        uint32_t n_sub, int64_t *out, uint32_t blocks, const EnumScratch &sc) {
-    constexpr bool one = DMA == DMA_ONE;
-    const uint32_t grid = blocks + (Rule::SIDE ? 1u : 0u);
-    hipLaunchKernelGGL((enum_kernel<Rule, uint32_t, M, STORE, DMA>), dim3(grid), dim3(EX_THREADS),
-                       (enum_shm_bytes<Rule, uint32_t>(n, one)), st, t, n, r, args, n_sub, out, sc.parts, sc.acc,
-                       sc.mode);
-    hipLaunchKernelGGL((enum_kernel<Rule, uint64_t, M, STORE, DMA>), dim3(grid), dim3(EX_THREADS),
-                       (enum_shm_bytes<Rule, uint64_t>(n, one)), st, t, n, r, args, n_sub, out, sc.parts, sc.acc,
-                       sc.mode);
+    enum_launch_one<Rule, uint32_t, M, STORE, DMA>(st, t, n, r, args, n_sub, out, blocks, sc);
+    enum_launch_one<Rule, uint64_t, M, STORE, DMA>(st, t, n, r, args, n_sub, out, blocks, sc);
     TGO_HIP(hipGetLastError());
     return TGO_OK;
 }

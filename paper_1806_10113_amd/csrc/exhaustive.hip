@@ -10,15 +10,18 @@
 #include <mutex>
 
 #include "enum_kernel.h"
+#include "potential_dev.h"
 
 namespace tgo {
 
 // The group's time path, decided once before the enumeration: 0 = 32-bit,
-// 1 = 64-bit, or a negative error code (classify_group).
-__global__ __launch_bounds__(64) void exhaustive_classify(const tgo_task *__restrict__ tasks, int n, Rates r, int *mode,
-                                    ExAcc *acc) {
-    const int m = classify_group_wave(tasks, n, r, threadIdx.x);
-    if (threadIdx.x == 0) *mode = m;
+// 1 = 64-bit, 2 = 32-bit in the potential form (if `potential` and the group's
+// potentials fit), or a negative error code (classify_group).
+__global__ __launch_bounds__(64) void exhaustive_classify(const tgo_task *__restrict__ tasks, int n, Rates r,
+                                                          bool potential, int *mode, ExAcc *acc) {
+    uint64_t bound;
+    const int m = classify_group_wave(tasks, n, r, threadIdx.x, &bound);
+    if (threadIdx.x == 0) *mode = potential && m == 0 && potential_fits<uint32_t>(bound, r) ? 2 : m;
     exacc_init(acc, threadIdx.x);
 }
 
@@ -79,6 +82,12 @@ uint32_t resident_blocks(const void *kern, int threads, size_t shm) {
     return b;
 }
 
+// The walk that also has the potential form (PotRule): the deepest, which the
+// groups of 11 and more take.  There the form wins 10 to 40% of 0.2 to 25 ms; at
+// depth 4 it does not (a group of 12: 2259 / 2208 / 2251 us, chain form 2165 /
+// 2011 / 2551), and the groups below 11, which are done in less than 50 us, would
+// pay the launch that finds nothing to do, 4.5 us, when theirs does not fit.
+constexpr int POT_M = 5;
 template <int M, bool STORE, int DMA>
 static int launch_pair(hipStream_t st, const tgo_task *t, int n, const Rates &r, uint32_t n_sub, int64_t *out,
                        tgo_summary *d_out, ExScratch ws) {
@@ -87,7 +96,15 @@ static int launch_pair(hipStream_t st, const tgo_task *t, int n, const Rates &r,
     EnumScratch sc;
     int rc = enum_grid(k32, enum_shm_bytes<BaseRule, uint32_t>(n, DMA == DMA_ONE), n_sub, 0, ws, st, &blocks, &sc);
     if (rc) return rc;
-    hipLaunchKernelGGL(exhaustive_classify, dim3(1), dim3(64), 0, st, t, n, r, sc.mode, sc.acc);
+    constexpr bool two = DMA == DMA_TWO;
+    const bool potential = two && M == POT_M && pot_rates(r, n);
+    hipLaunchKernelGGL(exhaustive_classify, dim3(1), dim3(64), 0, st, t, n, r, potential, sc.mode, sc.acc);
+    if constexpr (two && M == POT_M) {
+        if (potential) {
+            enum_launch_one<PotRule, uint32_t, M, STORE, DMA>(st, t, n, r, PotRule::Args{}, n_sub, out, blocks, sc);
+            TGO_HIP(hipGetLastError());
+        }
+    }
     rc = enum_launch<BaseRule, M, STORE, DMA>(st, t, n, r, BaseRule::Args{}, n_sub, out, blocks, sc);
     if (rc) return rc;
     hipLaunchKernelGGL(exhaustive_finalize, dim3(1), dim3(EX_FIN_THREADS), 0, st, sc.parts, (int)blocks, n,

@@ -51,6 +51,9 @@ struct Rates {
     // so for p <= 1024 the truncation is exact.
     double inv_ph, c_ph;
     double inv_pd, c_pd;
+    // exact quotients by q - p_h (p_h < q): it is odd << dsh, odd * dinv = 1 mod 2^32
+    uint32_t dinv;
+    int32_t dsh;
 };
 
 template <typename TT>

@@ -246,7 +246,7 @@ __device__ __forceinline__ uint64_t rounds_unrank(int T, int R, uint64_t rk, uin
 // orderings, 55,296 lanes of 28 windows.  Stepping the events of every
 // ordering in 64-bit time took 198 us for them and the Heuristic setup, on one
 // thread after it, 115 us; together, side by side, 313 -> 48 us per call.
-struct RoundsRule {
+struct RoundsRule : GroupRule {
     struct Args {
         int T, R;
         uint32_t tfact;  // T!

@@ -27,7 +27,8 @@ __device__ inline int classify_group(const tgo_task *t, int n, const Rates &r) {
 
 // The group's status as classify_group computes it, with one lane per task
 // (the per-task terms are combined by wave reductions; same result).
-__device__ inline int classify_group_wave(const tgo_task *t, int n, const Rates &r, int lane) {
+__device__ inline int classify_group_wave(const tgo_task *t, int n, const Rates &r, int lane,
+                                          uint64_t *bound = nullptr) {
     const uint64_t q = 1ull << r.q_log2;
     int bad = 0;
     uint64_t mx = 0, sum = 0;
@@ -48,6 +49,7 @@ __device__ inline int classify_group_wave(const tgo_task *t, int n, const Rates 
         mx = mx2 > mx ? mx2 : mx;
         sum += shfl_xor64(sum, m);
     }
+    if (bound) *bound = sum + time_bound_slack(n);
     if (bad) return TGO_ERANGE;
     const uint64_t lim32 = 1ull << 31;
     return (mx < lim32 && sum + time_bound_slack(n) < lim32) ? 0 : 1;
