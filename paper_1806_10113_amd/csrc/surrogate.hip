@@ -319,6 +319,15 @@ __device__ __forceinline__ unsigned long long wave_merge_low64(unsigned long lon
     return v;
 }
 
+// Block barrier that waits only for this wave's LDS accesses: __syncthreads()
+// also waits for every outstanding global load and store, which would drain
+// the next layer's weight loads and the activation stores at each layer.  The
+// kernel below never reads global memory that it writes, so only LDS needs
+// ordering here.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // One block scores FM_ROWS rows end to end: it builds their first-layer
 // inputs in LDS, runs the three hidden layers on MFMA with the activations
 // kept in LDS (rounded to bf16, as the layer-by-layer path stores them) and
@@ -330,9 +339,16 @@ __device__ __forceinline__ unsigned long long wave_merge_low64(unsigned long lon
 // (weights as the A operand, activations as B), so a lane's accumulator holds
 // four consecutive output columns of one row: a layer's outputs leave in
 // 8-byte LDS stores and the head reduces over four lanes per row.
+// What bounds it: the matrix cores (0.31 TFLOP per million rows) once the LDS
+// keeps up: with every wave reading all rows, both need the same 64 cycles per
+// K step when a 16-byte read takes 8 cycles, as it does at any padded pitch.
+// Swizzled rows (4 cycles), accumulators that start from the first product
+// instead of registers set to zero, pairs rounded at once and barriers that
+// leave the weight loads in flight: 361 -> 305 us per million rows, 1020 of the
+// 1160 TFLOP/s that a large matrix product reaches.  Registers stay below 129
+// (two blocks per CU: one loses 30%).
 constexpr int FM_ROWS = 128;
 constexpr int FM_RT = FM_ROWS / 16;    // row tiles per block
-constexpr int FM_LD = SG_H + 8;        // LDS row pitch in bf16
 constexpr int FM_WAVES = 8;            // wave w owns output columns FM_CT * 16 * w ..
 constexpr int FM_CT = SG_H / 16 / FM_WAVES;  // column tiles per wave
 constexpr int FM_THREADS = 64 * FM_WAVES;
@@ -342,44 +358,71 @@ static_assert(FM_TPR * FM_ROWS == FM_THREADS && FM_PPT * FM_TPR == SG_POS && FM_
                   (SG_K0 / 2 - 3 * SG_POS / 2) % FM_TPR == 0 && FM_ROWS % 64 == 0,
               "input build: whole positions and padding words per thread, whole waves of rows");
 
+// An LDS activation row of SG_H bf16 is 32 chunks of 16 bytes; chunk c of row r
+// sits at slot c ^ (r % 16).  A fragment read (lane l: chunk 4 ks + l/16 of row
+// l%16) then covers all 64 banks in each of the groups of 16 lanes that the
+// hardware serves at a time, which no padded pitch does: rows 264 bf16 apart
+// cost 8 cycles per 16-byte read, half of them conflicts.
+__device__ __forceinline__ int swz(int row, int chunk) { return (chunk ^ (row & 15)) << 3; }
+
+// Two floats rounded to bf16 (as f2bf does), the first in the low half.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t f2bf_pair(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+}
+
+// Weight fragments of K step ks.  W is in fragment order (pack_frag_kernel):
+// fragment (column tile FM_CT w + t, K step ks) of lane l at
+// ((FM_CT w + t) K/GK + ks) 512 + 8 l.
 template <int K>
-__device__ __forceinline__ void fm_layer(const uint16_t (*Hs)[FM_LD], const uint16_t *__restrict__ W, int w, int l,
-                                         f32x4 (&acc)[FM_RT][FM_CT]) {
+__device__ __forceinline__ void fm_weights(bf16x8 (&f)[FM_CT], const uint16_t *__restrict__ W, int w, int l, int ks) {
+    const uint16_t *wf = W + ((int64_t)FM_CT * w * (K / GK) * 64 + l) * 8;
+#pragma unroll
+    for (int t = 0; t < FM_CT; ++t) f[t] = *reinterpret_cast<const bf16x8 *>(wf + ((int64_t)t * (K / GK) + ks) * 512);
+}
+
+// One layer; fb[0] holds the weights of K step 0.
+template <int K>
+__device__ __forceinline__ void fm_layer(const uint16_t (*Hs)[SG_H], const uint16_t *__restrict__ W, int w, int l,
+                                         bf16x8 (&fb)[2][FM_CT], f32x4 (&acc)[FM_RT][FM_CT]) {
+    constexpr int KS = K / GK;
+    const uint16_t *row = &Hs[l & 15][0];
+    auto rows = [&](bf16x8 (&f)[FM_RT], int ks) {
+        const uint16_t *at = row + swz(l & 15, 4 * ks + (l >> 4));
+#pragma unroll
+        for (int t = 0; t < FM_RT; ++t) f[t] = *reinterpret_cast<const bf16x8 *>(at + 16 * t * SG_H);
+    };
+    bf16x8 fa[FM_RT];
+    fm_weights<K>(fb[1], W, w, l, 1);
+    rows(fa, 0);
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int a = 0; a < FM_RT; ++a)
 #pragma unroll
-        for (int b = 0; b < FM_CT; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // W in fragment order (pack_frag_kernel): fragment (column tile
-    // FM_CT w + t, K step ks) of this lane at wf + (t KS + ks) 512
-    constexpr int KS = K / GK;
-    const uint16_t *wf = W + ((int64_t)FM_CT * w * KS * 64 + l) * 8;
-    bf16x8 fb[FM_CT], nb[FM_CT];
-#pragma unroll
-    for (int t = 0; t < FM_CT; ++t) fb[t] = *reinterpret_cast<const bf16x8 *>(wf + (int64_t)t * KS * 512);
-#pragma unroll 1
-    for (int k0 = 0; k0 < K; k0 += GK) {
-        if (k0 + GK < K) {
-#pragma unroll
-            for (int t = 0; t < FM_CT; ++t)
-                nb[t] = *reinterpret_cast<const bf16x8 *>(wf + ((int64_t)t * KS + (k0 + GK) / GK) * 512);
-        }
-        bf16x8 fa[FM_RT];
-#pragma unroll
-        for (int t = 0; t < FM_RT; ++t)
-            fa[t] = *reinterpret_cast<const bf16x8 *>(&Hs[16 * t + (l & 15)][k0 + (l >> 4) * 8]);
+        for (int b = 0; b < FM_CT; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[0][b], fa[a], zero, 0, 0, 0);
+    // two K steps at a time, the weights of each a step ahead
+    auto step = [&](const bf16x8 (&f)[FM_CT], int ks) {
+        rows(fa, ks);
 #pragma unroll
         for (int a = 0; a < FM_RT; ++a)
 #pragma unroll
             for (int b = 0; b < FM_CT; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[b], fa[a], acc[a][b], 0, 0, 0);
-#pragma unroll
-        for (int t = 0; t < FM_CT; ++t) fb[t] = nb[t];
+                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[b], fa[a], acc[a][b], 0, 0, 0);
+    };
+#pragma unroll 1
+    for (int ks = 1; ks + 2 < KS; ks += 2) {
+        fm_weights<K>(fb[0], W, w, l, ks + 1);
+        step(fb[1], ks);
+        fm_weights<K>(fb[1], W, w, l, ks + 2);
+        step(fb[0], ks + 1);
     }
+    step(fb[1], KS - 1);
 }
 
 // relu(acc + bias) as bf16 into Hs (lane l holds columns
 // 16 (FM_CT w + b) + 4(l/16) + i of row 16a + l%16)
-__device__ __forceinline__ void fm_store(uint16_t (*Hs)[FM_LD], const float *__restrict__ bias, int w, int l,
+__device__ __forceinline__ void fm_store(uint16_t (*Hs)[SG_H], const float *__restrict__ bias, int w, int l,
                                          const f32x4 (&acc)[FM_RT][FM_CT]) {
 #pragma unroll
     for (int b = 0; b < FM_CT; ++b) {
@@ -387,15 +430,13 @@ __device__ __forceinline__ void fm_store(uint16_t (*Hs)[FM_LD], const float *__r
         float bb[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) bb[i] = bias[c0 + i];
+        uint16_t *at = &Hs[l & 15][swz(l & 15, c0 >> 3) + (c0 & 7)];
 #pragma unroll
         for (int a = 0; a < FM_RT; ++a) {
-            uint32_t h[4];
+            float v[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float v = acc[a][b][i] + bb[i];
-                h[i] = f2bf(v > 0.f ? v : 0.f);
-            }
-            *reinterpret_cast<uint2 *>(&Hs[16 * a + (l & 15)][c0]) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+            for (int i = 0; i < 4; ++i) v[i] = fmaxf(acc[a][b][i] + bb[i], 0.f);
+            *reinterpret_cast<uint2 *>(at + 16 * a * SG_H) = make_uint2(f2bf_pair(v[0], v[1]), f2bf_pair(v[2], v[3]));
         }
     }
 }
@@ -430,7 +471,7 @@ __global__ void pack_frag_kernel(const uint16_t *__restrict__ W1, const uint16_t
 // Rows are chosen as in features_kernel.  Output: score[i] (keys == null) or
 // the top-k key of row i (keys != null: orderable score bits << 32 | sample
 // index, ~0 for padding rows).
-__global__ __launch_bounds__(FM_THREADS) void mlp_fused_kernel(const float *__restrict__ F,
+__global__ __launch_bounds__(FM_THREADS) __attribute__((amdgpu_waves_per_eu(4))) void mlp_fused_kernel(const float *__restrict__ F,
                                                                const int32_t *__restrict__ offs,
                                                                const uint32_t *__restrict__ gkeys,
                                                                const uint8_t *__restrict__ orders,
@@ -441,7 +482,7 @@ __global__ __launch_bounds__(FM_THREADS) void mlp_fused_kernel(const float *__re
                                                                const uint16_t *__restrict__ W3,
                                                                const float *__restrict__ p, float *score,
                                                                unsigned long long *keys) {
-    __shared__ __align__(16) uint16_t Hs[FM_ROWS][FM_LD];
+    __shared__ __align__(16) uint16_t Hs[FM_ROWS][SG_H];
     __shared__ float part[FM_WAVES][FM_ROWS];
     __shared__ uint8_t okrow[FM_ROWS];
     __shared__ unsigned long long sperm[FM_ROWS];
@@ -460,7 +501,9 @@ __global__ __launch_bounds__(FM_THREADS) void mlp_fused_kernel(const float *__re
         sperm[tid] = perm;
         sgn[tid] = ok ? (g << 5) | n : -1;
     }
-    __syncthreads();
+    bf16x8 fb[2][FM_CT];
+    fm_weights<SG_K0>(fb[0], W1, w, l, 0);
+    lds_barrier();
     {
         const int r = tid % FM_ROWS, q = tid / FM_ROWS;
         const int gn = sgn[r];
@@ -484,24 +527,28 @@ __global__ __launch_bounds__(FM_THREADS) void mlp_fused_kernel(const float *__re
         }
         // features 3 FM_PPT q .. are words 3 FM_PPT q / 2 .. of the row; the
         // words after the 48 features are padding (a 64-wide first layer)
-        uint32_t *row = reinterpret_cast<uint32_t *>(&Hs[r][0]);
+        auto word = [&](int wd, uint32_t v) { *reinterpret_cast<uint32_t *>(&Hs[r][swz(r, wd >> 2) + 2 * (wd & 3)]) = v; };
 #pragma unroll
-        for (int c = 0; c < 3 * FM_PPT / 2; ++c) row[3 * FM_PPT / 2 * q + c] = f[2 * c] | (f[2 * c + 1] << 16);
+        for (int c = 0; c < 3 * FM_PPT / 2; ++c) word(3 * FM_PPT / 2 * q + c, f[2 * c] | (f[2 * c + 1] << 16));
         constexpr int PAD = (SG_K0 / 2 - 3 * SG_POS / 2) / FM_TPR;
 #pragma unroll
-        for (int c = 0; c < PAD; ++c) row[3 * SG_POS / 2 + PAD * q + c] = 0u;
+        for (int c = 0; c < PAD; ++c) word(3 * SG_POS / 2 + PAD * q + c, 0u);
     }
-    __syncthreads();
+    lds_barrier();
+    // a layer's first weights are loaded before the previous one's outputs are
+    // stored, so that their latency passes behind the barriers
     f32x4 acc[FM_RT][FM_CT];
-    fm_layer<SG_K0>(Hs, W1, w, l, acc);
-    __syncthreads();
+    fm_layer<SG_K0>(Hs, W1, w, l, fb, acc);
+    fm_weights<SG_H>(fb[0], W2, w, l, 0);
+    lds_barrier();
     fm_store(Hs, p + SG_OFF_B1, w, l, acc);
-    __syncthreads();
-    fm_layer<SG_H>(Hs, W2, w, l, acc);
-    __syncthreads();
+    lds_barrier();
+    fm_layer<SG_H>(Hs, W2, w, l, fb, acc);
+    fm_weights<SG_H>(fb[0], W3, w, l, 0);
+    lds_barrier();
     fm_store(Hs, p + SG_OFF_B2, w, l, acc);
-    __syncthreads();
-    fm_layer<SG_H>(Hs, W3, w, l, acc);
+    lds_barrier();
+    fm_layer<SG_H>(Hs, W3, w, l, fb, acc);
     // head on the bf16-rounded third layer: per-row partial sums over this
     // wave's columns, reduced across the 4 lanes that share a row
     float sum[FM_RT];
@@ -519,9 +566,10 @@ __global__ __launch_bounds__(FM_THREADS) void mlp_fused_kernel(const float *__re
 #pragma unroll
         for (int a = 0; a < FM_RT; ++a)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float v = acc[a][b][i] + bb[i];
-                sum[a] += bf2f(f2bf(v > 0.f ? v : 0.f)) * w4[i];
+            for (int i = 0; i < 4; i += 2) {
+                const uint32_t h = f2bf_pair(fmaxf(acc[a][b][i] + bb[i], 0.f), fmaxf(acc[a][b][i + 1] + bb[i + 1], 0.f));
+                sum[a] += __uint_as_float(h << 16) * w4[i];
+                sum[a] += __uint_as_float(h & 0xffff0000u) * w4[i + 1];
             }
     }
 #pragma unroll
@@ -531,7 +579,7 @@ __global__ __launch_bounds__(FM_THREADS) void mlp_fused_kernel(const float *__re
         v += __shfl_xor(v, 32);
         if (l < 16) part[w][16 * a + l] = v;
     }
-    __syncthreads();
+    lds_barrier();
     if (tid < FM_ROWS) {  // one row per lane
         const int64_t i = base + tid;
         float sc = p[SG_OFF_B4];
@@ -596,15 +644,6 @@ constexpr int WG_KS_MAX = 64;               // K chunks (partials) at most
 constexpr int WG_KC = 1024;                 // rows per K chunk (more for larger batches)
 static_assert(TR_ROWS * SG_POS % TR_THREADS == 0, "features: whole passes of one thread per (row, position)");
 static_assert(2 * TR_HALF * 2 * 4 == 64, "a lane's ReLU mask bits fill one 64-bit word");
-
-// Block barrier that waits only for this wave's LDS accesses: __syncthreads()
-// also waits for every outstanding global load and store, which would drain
-// the next layer's weight loads and the activation stores at each layer.  The
-// kernel below never reads global memory that it writes, so only LDS needs
-// ordering here.
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
 
 // Read for the tasks of an empty group (then masked), so that the feature
 // loads need no branch.
