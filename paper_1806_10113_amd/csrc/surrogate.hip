@@ -18,6 +18,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "enum_dev.h"
@@ -333,13 +334,12 @@ __device__ __forceinline__ void lds_barrier() {
 // kept in LDS (rounded to bf16, as the layer-by-layer path stores them) and
 // applies the head, so only the scores (or top-k keys) leave the block.  Each
 // of the 8 waves computes 32 output columns of each layer for all rows as
-// FM_RT x FM_CT MFMA tiles; weights (bf16, in the fragment order that
-// pack_frag_kernel writes) come from global memory, where every block reads
-// the same 282 KB.  The tiles are computed transposed
+// FM_RT x FM_CT MFMA tiles; weights (bf16, in fragment order, frag_at) come
+// from global memory, where every block reads the same 282 KB.  The tiles are computed transposed
 // (weights as the A operand, activations as B), so a lane's accumulator holds
 // four consecutive output columns of one row: a layer's outputs leave in
 // 8-byte LDS stores and the head reduces over four lanes per row.
-// What bounds it: the matrix cores (0.31 TFLOP per million rows) once the LDS
+// What bounds it: the matrix cores (0.31 TFLOP per million rows), once the LDS
 // keeps up: with every wave reading all rows, both need the same 64 cycles per
 // K step when a 16-byte read takes 8 cycles, as it does at any padded pitch.
 // Swizzled rows (4 cycles), accumulators that start from the first product
@@ -358,6 +358,16 @@ static_assert(FM_TPR * FM_ROWS == FM_THREADS && FM_PPT * FM_TPR == SG_POS && FM_
                   (SG_K0 / 2 - 3 * SG_POS / 2) % FM_TPR == 0 && FM_ROWS % 64 == 0,
               "input build: whole positions and padding words per thread, whole waves of rows");
 
+// The bf16 weights ([out][in], W1 padded to SG_K0 inputs) lie in the order in
+// which the matrix instructions take them: the fragment of column tile ct and K
+// step ks (16 outputs x GK inputs) is 64 lanes x 8 bf16 at ((ct K/GK + ks) 64 +
+// lane) 8, lane l holding W[16 ct + l%16][GK ks + 8 (l/16) ..], so a wave's load
+// reads 1 KB from end to end (row by row it would touch 16 half lines).
+// Position of W[o][c] of a layer of K inputs:
+__host__ __device__ constexpr int frag_at(int K, int o, int c) {
+    return ((o / 16 * (K / GK) + c / GK) * 64 + c % GK / 8 * 16 + o % 16) * 8 + c % 8;
+}
+
 // An LDS activation row of SG_H bf16 is 32 chunks of 16 bytes; chunk c of row r
 // sits at slot c ^ (r % 16).  A fragment read (lane l: chunk 4 ks + l/16 of row
 // l%16) then covers all 64 banks in each of the groups of 16 lanes that the
@@ -372,9 +382,7 @@ __device__ __forceinline__ uint32_t f2bf_pair(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
 }
 
-// Weight fragments of K step ks.  W is in fragment order (pack_frag_kernel):
-// fragment (column tile FM_CT w + t, K step ks) of lane l at
-// ((FM_CT w + t) K/GK + ks) 512 + 8 l.
+// Weight fragments of K step ks.
 template <int K>
 __device__ __forceinline__ void fm_weights(bf16x8 (&f)[FM_CT], const uint16_t *__restrict__ W, int w, int l, int ks) {
     const uint16_t *wf = W + ((int64_t)FM_CT * w * (K / GK) * 64 + l) * 8;
@@ -439,33 +447,6 @@ __device__ __forceinline__ void fm_store(uint16_t (*Hs)[SG_H], const float *__re
             *reinterpret_cast<uint2 *>(at + 16 * a * SG_H) = make_uint2(f2bf_pair(v[0], v[1]), f2bf_pair(v[2], v[3]));
         }
     }
-}
-
-// The three layers' bf16 weights ([out][in], W1 padded to SG_K0 inputs) in
-// the fragment order mlp_fused_kernel reads: the B fragment of column tile ct
-// and K step ks (16 output columns x GK inputs) is 64 lanes x 8 bf16 at
-// ((ct K/GK + ks) 64 + lane) 8, lane l holding W[16 ct + l%16][GK ks +
-// 8 (l/16) ..], so each of a wave's fragment loads reads 1 KB contiguously.
-// Layers at 0, FM_WF1 and FM_WF1 + SG_H^2 of Wf.
-constexpr int FM_WF1 = SG_H * SG_K0;
-constexpr int FM_WF = FM_WF1 + 2 * SG_H * SG_H;
-__global__ void pack_frag_kernel(const uint16_t *__restrict__ W1, const uint16_t *__restrict__ W2,
-                                 const uint16_t *__restrict__ W3, uint16_t *__restrict__ Wf) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= FM_WF) return;
-    const uint16_t *W = W3;
-    int K = SG_H, q = e - FM_WF1 - SG_H * SG_H;
-    if (e < FM_WF1) {
-        W = W1;
-        K = SG_K0;
-        q = e;
-    } else if (e < FM_WF1 + SG_H * SG_H) {
-        W = W2;
-        q = e - FM_WF1;
-    }
-    const int j = q & 7, lane = (q >> 3) & 63, frag = q >> 9;
-    const int ks = frag % (K / GK), ct = frag / (K / GK);
-    Wf[e] = W[(16 * ct + (lane & 15)) * K + GK * ks + 8 * (lane >> 4) + j];
 }
 
 // Rows are chosen as in features_kernel.  Output: score[i] (keys == null) or
@@ -606,7 +587,8 @@ __global__ __launch_bounds__(FM_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
 //                         LDS, the loss gradient, and back-propagation through
 //                         layers 3 and 2, all without leaving the block.  It
 //                         stores the bf16 activations and activation gradients
-//                         transposed ([feature][row]) for the weight gradients,
+//                         transposed ([feature][position], row_position) for
+//                         the weight gradients,
 //                         and per-block sums for the bias, head and loss terms.
 //   train_wgrad_kernel    weight gradients G^T A of the three layers as one
 //                         split-K launch (128 x 128 output tiles staged
@@ -616,21 +598,35 @@ __global__ __launch_bounds__(FM_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
 //   train_update_kernel   sums the K-chunk partials into the gradient and
 //                         (optionally) applies Adam and refreshes the bf16
 //                         weight copies.
-// Every wave keeps the B operands of its 32 output columns of a whole layer
-// in registers (64 VGPRs for K = 256), the next layer's loaded while the
-// current one runs, so the MFMA loop reads only LDS.  Every weight a CU
-// fetches serves the block's 128 rows (the weights are the kernel's largest
-// memory stream).  Two LDS activation buffers of 128 rows suffice: the ReLU
-// masks of layers 1 and 2, needed again by the backward pass, stay in
-// registers as bits, because a lane owns the same (row, column) elements in
-// every layer.
+// Every wave keeps the weights of its 32 output columns of a whole layer in
+// registers (64 VGPRs for K = 256), the next layer's loaded while the current
+// one runs, so the MFMA loop reads only LDS.  Every weight a CU fetches serves
+// the block's 128 rows (the weights are the kernel's largest memory stream).
+// Two LDS activation buffers of 128 rows suffice: the ReLU masks of layers 1
+// and 2, needed again by the backward pass, stay in registers as bits, because a
+// lane owns the same (row, column) elements in every layer.
+// The tiles are computed transposed (weights as the A operand), so a lane ends
+// with four columns of one row of each of four row tiles: 8 bytes per row for
+// the LDS, 8 bytes per column for the transposed arrays (row_position), a head
+// sum over two lane exchanges, and a loss gradient per row tile instead of one
+// per row.
+// What bounds it: one block fits a CU, and its eight waves meet at a barrier
+// after every layer, so no unit is busy for long: of 73 us for 65,536 rows the
+// matrix cores take 15, the vector units 18, the LDS 15, the weights' way from
+// the L2 9 and the loads of the features 8.  With a column's rows in a lane
+// instead (four 2-byte LDS stores per four values, 32-byte pieces of the
+// transposed lines, a 64-bit mask shifted per element, bank conflicts) it took
+// 123 us; with the weights row by row instead of in fragment order 85.
+// Weight gradients: 46 -> 37 us for the same rows once 48 chunks of ten tiles
+// fill the 512 places (two blocks per CU) in one go; 64 chunks need a second
+// one for the last quarter, 96 are 43 us and sum longer afterwards.  Smaller
+// batches take chunks of 256 rows: 60 -> 49 us for a whole gradient of 1,024
+// rows, 65 -> 55 at 4,096, 66 -> 64 at 16,384 against chunks of 1,024.
 constexpr int TR_WAVES = 8;
 constexpr int TR_THREADS = 64 * TR_WAVES;   // wave w owns output columns 32w .. 32w+31
 constexpr int TR_RT = 8;                    // row tiles of 16
 constexpr int TR_ROWS = 16 * TR_RT;         // rows per block
 constexpr int TR_HALF = TR_RT / 2;          // row tiles per MFMA pass (two passes per layer)
-constexpr int TR_LD = SG_H + 8;             // LDS pitch (bf16) of a 256-wide activation
-constexpr int TR_LD0 = SG_K0 + 8;           // LDS pitch of the 64-wide input
 // per-block vector: sums over the block's rows of the bias gradients of
 // layers 1..3, the head weight and bias gradients, and the loss
 constexpr int TR_V_B1 = 0, TR_V_B2 = 256, TR_V_B3 = 512, TR_V_W4 = 768, TR_V_B4 = 1024, TR_V_LOSS = 1025;
@@ -638,12 +634,11 @@ constexpr int TR_VLEN = 1026, TR_VSTRIDE = 1028;
 constexpr int WG_BT = 128;                  // weight-gradient output tile: 128 x 128 (layer 1: 128 x 64)
 constexpr int WG_TILES = 10;                // 4 (layer 3) + 4 (layer 2) + 2 (layer 1)
 constexpr int WG_BK = 64;                   // rows (K) per LDS stage
-constexpr int WG_LDK = WG_BK + 8;           // LDS pitch (bf16) of a staged operand row
 constexpr int WG_VEC_BLOCKS = (TR_VLEN + 255) / 256;
-constexpr int WG_KS_MAX = 64;               // K chunks (partials) at most
-constexpr int WG_KC = 1024;                 // rows per K chunk (more for larger batches)
+constexpr int WG_KS_MAX = 48;               // K chunks (partials) at most
+constexpr int WG_KC = 256;                  // rows per K chunk (more for larger batches)
 static_assert(TR_ROWS * SG_POS % TR_THREADS == 0, "features: whole passes of one thread per (row, position)");
-static_assert(2 * TR_HALF * 2 * 4 == 64, "a lane's ReLU mask bits fill one 64-bit word");
+static_assert(TR_HALF == 4, "a pass packs four rows of a column into 8 bytes; its ReLU mask bits fill one word");
 
 // Read for the tasks of an empty group (then masked), so that the feature
 // loads need no branch.
@@ -654,8 +649,8 @@ __device__ const tgo_task ZERO_TASK = {0, 0, 0};
 template <int R>
 __device__ __forceinline__ int64_t row_ror64(int64_t v) {
     const uint64_t u = (uint64_t)v;
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x120 + R, 0xF, 0xF, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x120 + R, 0xF, 0xF, false);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x120 + R, 0xF, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x120 + R, 0xF, 0xF, true);
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 // Sum / minimum over the 16 lanes of a row, left in every lane of the row.
@@ -686,80 +681,112 @@ struct WRegs {
     bf16x8 v[K / GK][2];
 };
 
-// W: bf16 [256][K] output-major.  Wave w takes the B operands of output
-// columns 32w + 16b + (l % 16), b = 0, 1, for every K step.
+// Wave w takes the fragments of column tiles 2w and 2w + 1, every K step.
 template <int K>
 __device__ __forceinline__ void wload(WRegs<K> &t, const uint16_t *__restrict__ W, int w, int l) {
-    const uint16_t *base = W + (int64_t)(32 * w + (l & 15)) * K + (l >> 4) * 8;
+    const uint16_t *base = W + ((int64_t)2 * w * (K / GK) * 64 + l) * 8;
 #pragma unroll
     for (int s = 0; s < K / GK; ++s)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) t.v[s][b] = *reinterpret_cast<const bf16x8 *>(base + (int64_t)16 * b * K + GK * s);
+        for (int b = 0; b < 2; ++b) t.v[s][b] = *reinterpret_cast<const bf16x8 *>(base + (b * (K / GK) + s) * 512);
 }
 
-// acc[a][b] = A[16(a0 + a) .. +15][0..K) x W[cols of tile b][0..K)^T; lane l
-// ends with rows 16(a0 + a) + 4(l/16) + i, column 32w + 16b + l%16.
-template <int K, int LD, int RA>
-__device__ __forceinline__ void wmma_rows(const uint16_t (*A)[LD], int a0, const WRegs<K> &t, int l,
-                                          f32x4 (&acc)[RA][2]) {
-#pragma unroll
-    for (int a = 0; a < RA; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+// acc[a][b] = W[cols of tile b][0..K) x A[16(a0 + a) .. +15][0..K)^T, A an LDS
+// block of swizzled rows (swz); lane l ends with row 16(a0 + a) + l%16, columns
+// 32w + 16b + 4(l/16) + i.
+template <int K>
+__device__ __forceinline__ void wmma_rows(const uint16_t (*A)[SG_H], int a0, const WRegs<K> &t, int l,
+                                          f32x4 (&acc)[TR_HALF][2]) {
+    const uint16_t *row = &A[16 * a0 + (l & 15)][0];
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < K / GK; ++s) {
-        bf16x8 fa[RA];
+        bf16x8 fa[TR_HALF];
 #pragma unroll
-        for (int a = 0; a < RA; ++a)
-            fa[a] = *reinterpret_cast<const bf16x8 *>(&A[16 * (a0 + a) + (l & 15)][GK * s + (l >> 4) * 8]);
+        for (int a = 0; a < TR_HALF; ++a)
+            fa[a] = *reinterpret_cast<const bf16x8 *>(row + 16 * a * SG_H + swz(l & 15, 4 * s + (l >> 4)));
 #pragma unroll
-        for (int a = 0; a < RA; ++a)
+        for (int a = 0; a < TR_HALF; ++a)
 #pragma unroll
             for (int b = 0; b < 2; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[a], t.v[s][b], acc[a][b], 0, 0, 0);
+                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t.v[s][b], fa[a], s ? acc[a][b] : zero, 0, 0, 0);
     }
 }
 
-// Transposed store of an LDS activation block: dst[c][r0 + r] = S[r][c] for
-// c < WIDTH, r < TR_ROWS (8 rows = 16 bytes per store).  The transposed
-// arrays hold ld >= every row a block writes (see TR_LD_PAD), so no store
-// needs a bounds test; stores without branches and with a fixed count let
-// the compiler wait for exactly the loads it needs later, instead of for
+// The transposed arrays [feature][position] keep a block's rows in the order
+// the accumulators hold them: of each 64 rows, row 16a + r stands at position
+// 4r + a, so that a lane's four rows of a column are 8 bytes and 16 lanes fill
+// a 128-byte line.  The weight gradients sum over the rows, in any order that
+// is the same in all arrays.
+__host__ __device__ constexpr int64_t row_position(int64_t row) {
+    return (row & ~int64_t(63)) + 4 * (row & 15) + ((row >> 4) & 3);
+}
+
+// Transposed store of the input features (8 positions = 16 bytes per store).
+// The transposed arrays hold ld >= every row a block writes (see TR_LD_PAD), so
+// no store needs a bounds test; stores without branches and with a fixed count
+// let the compiler wait for exactly the loads it needs later, instead of for
 // every outstanding memory operation.
-template <int WIDTH, int LD>
-__device__ __forceinline__ void store_t(const uint16_t (*S)[LD], uint16_t *dst, int64_t ld, int r0, int tid) {
-    constexpr int chunks = WIDTH * (TR_ROWS / 8);
+__device__ __forceinline__ void store_x(const uint16_t (*X)[SG_H], uint16_t *dst, int64_t ld, int r0, int tid) {
+    constexpr int chunks = SG_K0 * (TR_ROWS / 8);
     static_assert(chunks % TR_THREADS == 0, "whole passes");
 #pragma unroll
     for (int qq = 0; qq < chunks / TR_THREADS; ++qq) {
         const int q = tid + qq * TR_THREADS;
-        const int c = q / (TR_ROWS / 8), r = (q % (TR_ROWS / 8)) * 8;
-        uint4 v;
-        v.x = S[r][c] | ((uint32_t)S[r + 1][c] << 16);
-        v.y = S[r + 2][c] | ((uint32_t)S[r + 3][c] << 16);
-        v.z = S[r + 4][c] | ((uint32_t)S[r + 5][c] << 16);
-        v.w = S[r + 6][c] | ((uint32_t)S[r + 7][c] << 16);
-        *reinterpret_cast<uint4 *>(dst + (int64_t)c * ld + r0 + r) = v;
+        const int c = q / (TR_ROWS / 8), pos = (q % (TR_ROWS / 8)) * 8;
+        const int row = (pos & 64) + ((pos & 63) >> 2);  // rows row + 16a, then row + 1 + 16a
+        uint32_t v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int r = row + (e >> 2) + 16 * (e & 3);
+            v[e] = X[r][swz(r, c >> 3) + (c & 7)];
+        }
+        *reinterpret_cast<uint4 *>(dst + (int64_t)c * ld + r0 + pos) =
+            make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
     }
 }
 
-// The four values a lane holds for (row tile a, column col) are rows
-// 16a + 4(l/16) + 0..3 of that column: one 8-byte store into the transposed
-// layout dst[col][row] (every row a block writes lies below ld).
-__device__ __forceinline__ void store4_t(uint16_t *dst, int64_t ld, int col, int row0, const uint16_t (&v)[4]) {
-    uint2 q;
-    q.x = v[0] | ((uint32_t)v[1] << 16);
-    q.y = v[2] | ((uint32_t)v[3] << 16);
-    *reinterpret_cast<uint2 *>(dst + (int64_t)col * ld + row0) = q;
+// One column tile of a pass leaves the registers: value (a, i) of the lane is
+// row 16(a0 + a) + l%16, column c0 + i.  Into the LDS block S (if PUT; 8 bytes
+// per row) and into the transposed array at `out`, the address of column c0 and
+// this lane's position (8 bytes per column).
+template <bool PUT>
+__device__ __forceinline__ void put_tile(const f32x4 (&v)[TR_HALF], uint16_t *S, uint16_t *out, int64_t ld) {
+    if constexpr (PUT) {
+#pragma unroll
+        for (int a = 0; a < TR_HALF; ++a)
+            *reinterpret_cast<uint2 *>(S + 16 * a * SG_H) =
+                make_uint2(f2bf_pair(v[a][0], v[a][1]), f2bf_pair(v[a][2], v[a][3]));
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<uint2 *>(out + (int64_t)i * ld) =
+            make_uint2(f2bf_pair(v[0][i], v[1][i]), f2bf_pair(v[2][i], v[3][i]));
 }
 
-// Sum over the rows a lane holds (4 per row tile) and over the lanes that
-// share its column (l, l ^ 16, l ^ 32, l ^ 48); lanes l < 16 end with the
-// column total.
-__device__ __forceinline__ float col_total(float v) {
-    v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
-    return v;
+// Sum over the 16 lanes that share a lane's columns, in every lane.
+template <int R>
+__device__ __forceinline__ float row_ror_add(float v) {
+    return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + R, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float row16_total(float v) {
+    return row_ror_add<1>(row_ror_add<2>(row_ror_add<4>(row_ror_add<8>(v))));
+}
+// Column sums of a wave's 32 columns: the four columns of tile b that a lane
+// holds start at dst[16 b].
+__device__ __forceinline__ void put_totals(const float (&v)[2][4], float *dst, int l) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        f32x4 t;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) t[i] = row16_total(v[b][i]);
+        if ((l & 15) == 0) *reinterpret_cast<f32x4 *>(dst + 16 * b) = t;
+    }
+}
+
+// A float's bits where bit k of m is set, else zero.
+__device__ __forceinline__ float keep_bit(float v, uint32_t m, int k) {
+    return __uint_as_float(__float_as_uint(v) & (uint32_t)((int32_t)(m << (31 - k)) >> 31));
 }
 
 // Forward and backward of the rows [128 blockIdx.x, +128).  Rows >= `rows`
@@ -773,28 +800,30 @@ __global__ __launch_bounds__(TR_THREADS) void train_fwd_bwd_kernel(
     const uint16_t *__restrict__ W2t, const uint16_t *__restrict__ W3t, const float *__restrict__ p, int64_t ld,
     uint16_t *Xt, uint16_t *H1t, uint16_t *H2t, uint16_t *G3t, uint16_t *G2t, uint16_t *G1t, float *vec,
     uint16_t *H3keep, float *score_keep) {
-    __shared__ __align__(16) uint16_t bufA[TR_ROWS][TR_LD];
-    __shared__ __align__(16) uint16_t bufB[TR_ROWS][TR_LD];
+    __shared__ __align__(16) uint16_t bufA[TR_ROWS][SG_H];
+    __shared__ __align__(16) uint16_t bufB[TR_ROWS][SG_H];
     __shared__ float part[TR_WAVES][TR_ROWS];
     __shared__ float ys[TR_ROWS], dss[TR_ROWS];
-    uint16_t (*Xs)[TR_LD0] = reinterpret_cast<uint16_t (*)[TR_LD0]>(&bufB[0][0]);
+    __shared__ __align__(16) float vecs[4][SG_H];  // biases of layers 1 to 3, head weights
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
     const int r0 = blockIdx.x * TR_ROWS;
     float *vb = vec + (int64_t)blockIdx.x * TR_VSTRIDE;
-    // the row a lane's element (pass h, row tile a, value i) belongs to, and
-    // the bit of that element in the lane's ReLU masks
-#define TR_ROW(h, a, i) (16 * ((h) * TR_HALF + (a)) + 4 * (l >> 4) + (i))
-#define TR_BIT(h, a, b, i) ((((h) * TR_HALF + (a)) * 2 + (b)) * 4 + (i))
+    // this lane's four columns of the wave's first column tile (the second: +16)
+    // and its row of each row tile
+    const int c0 = 32 * w + 4 * (l >> 4), rl = l & 15;
+    const int64_t at = (int64_t)c0 * ld + r0 + 4 * rl;  // column c0, this lane's position, of a transposed array
+    // address of column c0 + 16 b, row 64 h + rl, of an LDS block
+    auto cell = [&](uint16_t (*S)[SG_H], int h, int b) {
+        const int c = c0 + 16 * b;
+        return &S[64 * h + rl][swz(rl, c >> 3) + (c & 7)];
+    };
+    auto columns = [&](int k, int b) { return *reinterpret_cast<const f32x4 *>(&vecs[k][c0 + 16 * b]); };
 
-    // biases and head weights of this lane's two columns
-    float bias1[2], bias2[2], bias3[2], w4c[2];
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-        const int col = 32 * w + 16 * b + (l & 15);
-        bias1[b] = p[SG_OFF_B1 + col];
-        bias2[b] = p[SG_OFF_B2 + col];
-        bias3[b] = p[SG_OFF_B3 + col];
-        w4c[b] = p[SG_OFF_W4 + col];
+    for (int k = 0; k < 4 * SG_H / TR_THREADS; ++k) {
+        const int e = tid + k * TR_THREADS, col = e % SG_H;
+        vecs[e / SG_H][col] =
+            p[(e < SG_H ? SG_OFF_B1 : e < 2 * SG_H ? SG_OFF_B2 : e < 3 * SG_H ? SG_OFF_B3 : SG_OFF_W4) + col];
     }
     const float bias4 = p[SG_OFF_B4];
 
@@ -861,10 +890,11 @@ __global__ __launch_bounds__(TR_THREADS) void train_fwd_bwd_kernel(
             lb = lb < 1 ? 1 : lb;
             ys[rr] = live ? (float)((double)Tv[it] / (double)lb - 1.0) : 0.f;
         }
-        Xs[rr][3 * pos] = f0;
-        Xs[rr][3 * pos + 1] = f1;
-        Xs[rr][3 * pos + 2] = f2;
-        Xs[rr][SG_FEAT + pos] = 0;
+        auto input = [&](int c, uint16_t f) { bufB[rr][swz(rr, c >> 3) + (c & 7)] = f; };
+        input(3 * pos, f0);
+        input(3 * pos + 1, f1);
+        input(3 * pos + 2, f2);
+        input(SG_FEAT + pos, 0);
     }
     // the first two layers' weights are loaded once the features are built
     // (vector memory returns in order: loads issued before the features'
@@ -875,30 +905,38 @@ __global__ __launch_bounds__(TR_THREADS) void train_fwd_bwd_kernel(
     WRegs<SG_H> w2r;
     wload(w2r, W2, w, l);
     lds_barrier();
-    store_t<SG_K0>(Xs, Xt, ld, r0, tid);
+    store_x(bufB, Xt, ld, r0, tid);
 
-    uint64_t m1 = 0, m2 = 0;  // ReLU masks of layers 1 and 2 (bit TR_BIT: h > 0)
-    // layer 1: Xs -> bufA
+    // ReLU masks of layers 1 and 2, a word per pass (bit 16b + 4a + i: the
+    // stored value is not zero, i.e. above half the smallest bf16)
+    uint32_t m1a = 0, m1b = 0, m2a = 0, m2b = 0;
+    constexpr float NONZERO = 0x1p-134f;
+    // one pass of a hidden layer: relu(S W + bias), its mask, and its way out
+    auto hidden = [&](const f32x4 (&acc)[TR_HALF][2], int k, int h, uint16_t (*dst)[SG_H], uint16_t *out) {
+        uint32_t m = 0;
+#pragma unroll
+        for (int b = 1; b >= 0; --b) {
+            const f32x4 bias = columns(k, b);
+            f32x4 v[TR_HALF];
+#pragma unroll
+            for (int a = TR_HALF - 1; a >= 0; --a)
+#pragma unroll
+                for (int i = 3; i >= 0; --i) {
+                    v[a][i] = fmaxf(acc[a][b][i] + bias[i], 0.f);
+                    m = m + m + (v[a][i] > NONZERO ? 1u : 0u);
+                }
+            put_tile<true>(v, cell(dst, h, b), out + at + (int64_t)16 * b * ld + 64 * h, ld);
+        }
+        return m;
+    };
+    // layer 1: bufB -> bufA
 #pragma unroll 1
     for (int h = 0; h < 2; ++h) {
         f32x4 acc[TR_HALF][2];
-        wmma_rows<SG_K0, TR_LD0, TR_HALF>(Xs, h * TR_HALF, w1r, l, acc);
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int col = 32 * w + 16 * b + (l & 15);
-#pragma unroll
-            for (int a = 0; a < TR_HALF; ++a) {
-                uint16_t hv[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float v = acc[a][b][i] + bias1[b];
-                    hv[i] = f2bf(v > 0.f ? v : 0.f);
-                    bufA[TR_ROW(h, a, i)][col] = hv[i];
-                    m1 |= (uint64_t)(hv[i] != 0) << TR_BIT(h, a, b, i);
-                }
-                store4_t(H1t, ld, col, r0 + TR_ROW(h, a, 0), hv);
-            }
-        }
+        wmma_rows<SG_K0>(bufB, h * TR_HALF, w1r, l, acc);
+        const uint32_t m = hidden(acc, 0, h, bufA, H1t);
+        m1a = h ? m1a : m;
+        m1b = m;
     }
     compiler_fence();  // the next layer's weights load only once this layer is done
     WRegs<SG_H> w3r;
@@ -908,23 +946,10 @@ __global__ __launch_bounds__(TR_THREADS) void train_fwd_bwd_kernel(
 #pragma unroll 1
     for (int h = 0; h < 2; ++h) {
         f32x4 acc[TR_HALF][2];
-        wmma_rows<SG_H, TR_LD, TR_HALF>(bufA, h * TR_HALF, w2r, l, acc);
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int col = 32 * w + 16 * b + (l & 15);
-#pragma unroll
-            for (int a = 0; a < TR_HALF; ++a) {
-                uint16_t hv[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float v = acc[a][b][i] + bias2[b];
-                    hv[i] = f2bf(v > 0.f ? v : 0.f);
-                    bufB[TR_ROW(h, a, i)][col] = hv[i];
-                    m2 |= (uint64_t)(hv[i] != 0) << TR_BIT(h, a, b, i);
-                }
-                store4_t(H2t, ld, col, r0 + TR_ROW(h, a, 0), hv);
-            }
-        }
+        wmma_rows<SG_H>(bufA, h * TR_HALF, w2r, l, acc);
+        const uint32_t m = hidden(acc, 1, h, bufB, H2t);
+        m2a = h ? m2a : m;
+        m2b = m;
     }
     compiler_fence();  // the next layer's weights load only once this layer is done
     WRegs<SG_H> w3tr;
@@ -935,31 +960,34 @@ __global__ __launch_bounds__(TR_THREADS) void train_fwd_bwd_kernel(
 #pragma unroll 1
     for (int h = 0; h < 2; ++h) {
         f32x4 acc[TR_HALF][2];
-        wmma_rows<SG_H, TR_LD, TR_HALF>(bufB, h * TR_HALF, w3r, l, acc);
+        wmma_rows<SG_H>(bufB, h * TR_HALF, w3r, l, acc);
+        float sum[TR_HALF] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int a = 0; a < TR_HALF; ++a) {
-            float sum[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < 2; ++b) {
+            const f32x4 bias = columns(2, b), w4 = columns(3, b);
+            uint16_t *S = cell(bufA, h, b);
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const int col = 32 * w + 16 * b + (l & 15);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float v = acc[a][b][i] + bias3[b];
-                    const uint16_t hq = f2bf(v > 0.f ? v : 0.f);
-                    bufA[TR_ROW(h, a, i)][col] = hq;
-                    sum[i] += bf2f(hq) * w4c[b];
-                    if (H3keep) {
-                        const int row = r0 + TR_ROW(h, a, i);
-                        if (row < rows) H3keep[(int64_t)row * SG_H + col] = hq;
-                    }
+            for (int a = 0; a < TR_HALF; ++a) {
+                uint2 q;
+                q.x = f2bf_pair(fmaxf(acc[a][b][0] + bias[0], 0.f), fmaxf(acc[a][b][1] + bias[1], 0.f));
+                q.y = f2bf_pair(fmaxf(acc[a][b][2] + bias[2], 0.f), fmaxf(acc[a][b][3] + bias[3], 0.f));
+                *reinterpret_cast<uint2 *>(S + 16 * a * SG_H) = q;
+                sum[a] += __uint_as_float(q.x << 16) * w4[0];
+                sum[a] += __uint_as_float(q.x & 0xffff0000u) * w4[1];
+                sum[a] += __uint_as_float(q.y << 16) * w4[2];
+                sum[a] += __uint_as_float(q.y & 0xffff0000u) * w4[3];
+                if (H3keep) {
+                    const int row = r0 + 64 * h + 16 * a + rl;
+                    if (row < rows) *reinterpret_cast<uint2 *>(H3keep + (int64_t)row * SG_H + c0 + 16 * b) = q;
                 }
             }
+        }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float v = sum[i];
-                for (int m = 1; m < 16; m <<= 1) v += __shfl_xor(v, m);
-                if ((l & 15) == 0) part[w][TR_ROW(h, a, i)] = v;
-            }
+        for (int a = 0; a < TR_HALF; ++a) {
+            float v = sum[a];
+            v += __shfl_xor(v, 16);
+            v += __shfl_xor(v, 32);
+            if (l < 16) part[w][64 * h + 16 * a + l] = v;
         }
     }
     compiler_fence();  // the next layer's weights load only once this layer is done
@@ -996,113 +1024,95 @@ __global__ __launch_bounds__(TR_THREADS) void train_fwd_bwd_kernel(
     }
     lds_barrier();
     // dL/dz3 = ds w4 where h3 > 0, in place of h3 in bufA; head and layer-3 bias sums
+    {
+        float gw4[2][4], gb3[2][4];
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-        const int col = 32 * w + 16 * b + (l & 15);
-        float gw4 = 0.f, gb3 = 0.f;
+        for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+            for (int i = 0; i < 4; ++i) gw4[b][i] = gb3[b][i] = 0.f;
+#pragma unroll 1
+        for (int h = 0; h < 2; ++h) {
+            float ds[TR_HALF];
 #pragma unroll
-            for (int a = 0; a < TR_HALF; ++a) {
-                uint16_t gv[4];
+            for (int a = 0; a < TR_HALF; ++a) ds[a] = dss[64 * h + 16 * a + rl];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int row = TR_ROW(h, a, i);
-                    const float ds = dss[row];
-                    const float hf = bf2f(bufA[row][col]);
-                    const uint16_t g = hf > 0.f ? f2bf(ds * w4c[b]) : (uint16_t)0;
-                    gv[i] = g;
-                    bufA[row][col] = g;
-                    gw4 += ds * hf;
-                    gb3 += bf2f(g);
+            for (int b = 0; b < 2; ++b) {
+                const f32x4 w4 = columns(3, b);
+                uint16_t *S = cell(bufA, h, b);
+                f32x4 v[TR_HALF];
+#pragma unroll
+                for (int a = 0; a < TR_HALF; ++a) {
+                    const uint2 q = *reinterpret_cast<const uint2 *>(S + 16 * a * SG_H);
+                    const float hf[4] = {__uint_as_float(q.x << 16), __uint_as_float(q.x & 0xffff0000u),
+                                         __uint_as_float(q.y << 16), __uint_as_float(q.y & 0xffff0000u)};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        v[a][i] = hf[i] > 0.f ? bf2f(f2bf(ds[a] * w4[i])) : 0.f;
+                        gw4[b][i] += ds[a] * hf[i];
+                        gb3[b][i] += v[a][i];
+                    }
                 }
-                store4_t(G3t, ld, col, r0 + TR_ROW(h, a, 0), gv);
+                put_tile<true>(v, S, G3t + at + (int64_t)16 * b * ld + 64 * h, ld);
             }
-        gw4 = col_total(gw4);
-        gb3 = col_total(gb3);
-        if (l < 16) {
-            vb[TR_V_W4 + col] = gw4;
-            vb[TR_V_B3 + col] = gb3;
         }
+        put_totals(gw4, vb + TR_V_W4 + c0, l);
+        put_totals(gb3, vb + TR_V_B3 + c0, l);
     }
     lds_barrier();
+    // one pass of a back-propagated gradient: acc where the mask is set, its
+    // column sums (of the rounded values) and its way out
+    auto back = [&](const f32x4 (&acc)[TR_HALF][2], uint32_t m, int h, auto put, uint16_t *out, float (&gb)[2][4]) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            f32x4 v[TR_HALF];
+#pragma unroll
+            for (int a = 0; a < TR_HALF; ++a)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    v[a][i] = bf2f(f2bf(keep_bit(acc[a][b][i], m, 16 * b + 4 * a + i)));
+                    gb[b][i] += v[a][i];
+                }
+            put_tile<decltype(put)::value>(v, cell(bufB, h, b), out + at + (int64_t)16 * b * ld + 64 * h, ld);
+        }
+    };
     // dL/dz2 = (dL/dz3 W3) where h2 > 0: bufA -> bufB (h2 is no longer read)
     {
-        float gb[2] = {0.f, 0.f};
+        float gb[2][4] = {};
 #pragma unroll 1
         for (int h = 0; h < 2; ++h) {
             f32x4 acc[TR_HALF][2];
-            wmma_rows<SG_H, TR_LD, TR_HALF>(bufA, h * TR_HALF, w3tr, l, acc);
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const int col = 32 * w + 16 * b + (l & 15);
-#pragma unroll
-                for (int a = 0; a < TR_HALF; ++a) {
-                    uint16_t gv[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const uint16_t g = (m2 >> TR_BIT(h, a, b, i)) & 1 ? f2bf(acc[a][b][i]) : (uint16_t)0;
-                        gv[i] = g;
-                        bufB[TR_ROW(h, a, i)][col] = g;
-                        gb[b] += bf2f(g);
-                    }
-                    store4_t(G2t, ld, col, r0 + TR_ROW(h, a, 0), gv);
-                }
-            }
+            wmma_rows<SG_H>(bufA, h * TR_HALF, w3tr, l, acc);
+            back(acc, h ? m2b : m2a, h, std::true_type{}, G2t, gb);
         }
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const float t = col_total(gb[b]);
-            if (l < 16) vb[TR_V_B2 + 32 * w + 16 * b + l] = t;
-        }
+        put_totals(gb, vb + TR_V_B2 + c0, l);
     }
     lds_barrier();
     // dL/dz1 = (dL/dz2 W2) where h1 > 0, from bufB; stored only
     {
-        float gb[2] = {0.f, 0.f};
+        float gb[2][4] = {};
 #pragma unroll 1
         for (int h = 0; h < 2; ++h) {
             f32x4 acc[TR_HALF][2];
-            wmma_rows<SG_H, TR_LD, TR_HALF>(bufB, h * TR_HALF, w2tr, l, acc);
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const int col = 32 * w + 16 * b + (l & 15);
-#pragma unroll
-                for (int a = 0; a < TR_HALF; ++a) {
-                    uint16_t gv[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const uint16_t g = (m1 >> TR_BIT(h, a, b, i)) & 1 ? f2bf(acc[a][b][i]) : (uint16_t)0;
-                        gv[i] = g;
-                        gb[b] += bf2f(g);
-                    }
-                    store4_t(G1t, ld, col, r0 + TR_ROW(h, a, 0), gv);
-                }
-            }
+            wmma_rows<SG_H>(bufB, h * TR_HALF, w2tr, l, acc);
+            back(acc, h ? m1b : m1a, h, std::false_type{}, G1t, gb);
         }
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const float t = col_total(gb[b]);
-            if (l < 16) vb[TR_V_B1 + 32 * w + 16 * b + l] = t;
-        }
+        put_totals(gb, vb + TR_V_B1 + c0, l);
     }
-#undef TR_ROW
-#undef TR_BIT
 }
 
 // src[0] + src[stride] + ... + src[(ks - 1) stride], added in that order, with
-// the loads issued eight at a time.
+// the loads issued sixteen at a time (ks is the same in all lanes).
 __device__ __forceinline__ float chunk_sum(const float *__restrict__ src, int64_t stride, int ks) {
+    constexpr int B = 16;
     float s = 0.f;
-    int c = 0;
-    for (; c + 8 <= ks; c += 8) {
-        float v[8];
+    for (int c = 0; c < ks; c += B) {
+        float v[B];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = src[(int64_t)(c + u) * stride];
+        for (int u = 0; u < B; ++u) v[u] = src[(int64_t)(c + u < ks ? c + u : ks - 1) * stride];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) s += v[u];
+        for (int u = 0; u < B; ++u)
+            if (c + u < ks) s += v[u];
     }
-    for (; c < ks; ++c) s += src[(int64_t)c * stride];
     return s;
 }
 
@@ -1119,26 +1129,32 @@ __device__ __forceinline__ void wg_fetch(u32x4 (&rg)[4], u32x4 (&ra)[4], const u
         ra[q] = 32 * q + cr < na ? *reinterpret_cast<const u32x4 *>(asrc + (int64_t)32 * q * ld + k) : u32x4{0, 0, 0, 0};
     }
 }
-__device__ __forceinline__ void wg_stash(const u32x4 (&rg)[4], const u32x4 (&ra)[4], uint16_t (*sg)[WG_LDK],
-                                         uint16_t (*sa)[WG_LDK], int cr, int ck) {
+// A staged row is 128 bytes, eight chunks of 16; chunk c of row r sits at slot
+// c ^ (r / 2 % 8), so that both the copies in (eight lanes per row) and the
+// fragment reads (16 rows, a chunk each) use every bank once per group of lanes.
+__device__ __forceinline__ int wg_swz(int row, int chunk) { return (chunk ^ ((row >> 1) & 7)) << 3; }
+__device__ __forceinline__ void wg_stash(const u32x4 (&rg)[4], const u32x4 (&ra)[4], uint16_t (*sg)[WG_BK],
+                                         uint16_t (*sa)[WG_BK], int cr, int ck) {
+    const int at = wg_swz(cr, ck >> 3);  // rows 32 apart share it
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        *reinterpret_cast<u32x4 *>(&sg[32 * q + cr][ck]) = rg[q];
-        *reinterpret_cast<u32x4 *>(&sa[32 * q + cr][ck]) = ra[q];
+        *reinterpret_cast<u32x4 *>(&sg[32 * q + cr][at]) = rg[q];
+        *reinterpret_cast<u32x4 *>(&sa[32 * q + cr][at]) = ra[q];
     }
 }
 
 // The MFMAs of one LDS stage: this wave's 64 x 64 quarter (rows 64 wo.., columns
 // 64 wi..) over the stage's 64 K values.
-__device__ __forceinline__ void wg_mma(f32x4 (&acc)[4][4], const uint16_t (*sg)[WG_LDK], const uint16_t (*sa)[WG_LDK],
+__device__ __forceinline__ void wg_mma(f32x4 (&acc)[4][4], const uint16_t (*sg)[WG_BK], const uint16_t (*sa)[WG_BK],
                                        int wo, int wi, int l) {
 #pragma unroll
     for (int kk = 0; kk < WG_BK / GK; ++kk) {
         bf16x8 fg[4], fa[4];
+        const int at = wg_swz(l & 15, (GK / 8) * kk + (l >> 4));
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
-            fg[x] = *reinterpret_cast<const bf16x8 *>(&sg[64 * wo + 16 * x + (l & 15)][GK * kk + (l >> 4) * 8]);
-            fa[x] = *reinterpret_cast<const bf16x8 *>(&sa[64 * wi + 16 * x + (l & 15)][GK * kk + (l >> 4) * 8]);
+            fg[x] = *reinterpret_cast<const bf16x8 *>(&sg[64 * wo + 16 * x + (l & 15)][at]);
+            fa[x] = *reinterpret_cast<const bf16x8 *>(&sa[64 * wi + 16 * x + (l & 15)][at]);
         }
 #pragma unroll
         for (int x = 0; x < 4; ++x)
@@ -1159,7 +1175,7 @@ __device__ __forceinline__ void wg_mma(f32x4 (&acc)[4][4], const uint16_t (*sg)[
 // to the 8 XCDs in turn (block b to XCD b % 8), and XCD x takes the chunks
 // x, x + 8, ...; the chunk's rows of the six activation arrays are then
 // fetched into that XCD's L2 once.
-// Both operands are K-contiguous in HBM ([feature][row]); a stage of 64 rows
+// Both operands are K-contiguous in HBM ([feature][position]); a stage of 64 rows
 // of both is copied into LDS with whole 128-byte lines per feature (double
 // buffered, with the loads two stages ahead in flight), and each of the four
 // waves computes a 64 x 64 quarter of the tile from LDS.
@@ -1189,8 +1205,8 @@ __global__ __launch_bounds__(256) void train_wgrad_kernel(
         }
         return;
     }
-    __shared__ __align__(16) uint16_t sG[2][WG_BT][WG_LDK];
-    __shared__ __align__(16) uint16_t sA[2][WG_BT][WG_LDK];
+    __shared__ __align__(16) uint16_t sG[2][WG_BT][WG_BK];
+    __shared__ __align__(16) uint16_t sA[2][WG_BT][WG_BK];
     const uint16_t *G, *A;
     int tm, tn, na;  // output rows 128 tm.., columns 128 tn.., na columns in the tile
     if (tile < 4) {
@@ -1260,7 +1276,7 @@ struct AdamArgs {
     float lr, beta1, beta2, eps, c1, c2, omb1, omb2;
 };
 
-// mode 0: gradient only (sum the chunk partials into g);
+// mode 0: gradient only (sum the chunk partials into g, if it is wanted);
 // mode 1: that, then Adam and the bf16 copies; mode 2: Adam on the given
 // gradient gin.  Block 0 also writes the loss (modes 0, 1).
 __global__ void train_update_kernel(int mode, const float *__restrict__ wpart, const float *__restrict__ vpart,
@@ -1275,7 +1291,7 @@ __global__ void train_update_kernel(int mode, const float *__restrict__ wpart, c
         gi = gin[i];
     } else {
         gi = chunk_sum(wpart + i, SG_NPARAM, ks);
-        g[i] = gi;
+        if (g) g[i] = gi;
     }
     if (mode == 0) return;
     const float mi = a.beta1 * m[i] + a.omb1 * gi;
@@ -1286,15 +1302,15 @@ __global__ void train_update_kernel(int mode, const float *__restrict__ wpart, c
     p[i] = pi;
     const uint16_t bb = f2bf(pi);
     if (i < SG_OFF_B1) {
-        W1[(i / SG_FEAT) * SG_K0 + i % SG_FEAT] = bb;
+        W1[frag_at(SG_K0, i / SG_FEAT, i % SG_FEAT)] = bb;
     } else if (i >= SG_OFF_W2 && i < SG_OFF_B2) {
         const int j = i - SG_OFF_W2;
-        W2[j] = bb;
-        W2t[(j % SG_H) * SG_H + j / SG_H] = bb;
+        W2[frag_at(SG_H, j / SG_H, j % SG_H)] = bb;
+        W2t[frag_at(SG_H, j % SG_H, j / SG_H)] = bb;
     } else if (i >= SG_OFF_W3 && i < SG_OFF_B3) {
         const int j = i - SG_OFF_W3;
-        W3[j] = bb;
-        W3t[(j % SG_H) * SG_H + j / SG_H] = bb;
+        W3[frag_at(SG_H, j / SG_H, j % SG_H)] = bb;
+        W3t[frag_at(SG_H, j % SG_H, j / SG_H)] = bb;
     }
 }
 
@@ -1303,16 +1319,16 @@ __global__ void refresh_bf16_kernel(const float *__restrict__ p, uint16_t *W1, u
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < SG_H * SG_K0) {
         const int o = i / SG_K0, c = i % SG_K0;
-        W1[o * SG_K0 + c] = c < SG_FEAT ? f2bf(p[SG_OFF_W1 + o * SG_FEAT + c]) : (uint16_t)0;
+        W1[frag_at(SG_K0, o, c)] = c < SG_FEAT ? f2bf(p[SG_OFF_W1 + o * SG_FEAT + c]) : (uint16_t)0;
     }
     if (i < SG_H * SG_H) {
         const int o = i / SG_H, c = i % SG_H;
         const uint16_t b2 = f2bf(p[SG_OFF_W2 + i]);
         const uint16_t b3 = f2bf(p[SG_OFF_W3 + i]);
-        W2[i] = b2;
-        W2t[c * SG_H + o] = b2;
-        W3[i] = b3;
-        W3t[c * SG_H + o] = b3;
+        W2[frag_at(SG_H, o, c)] = b2;
+        W2t[frag_at(SG_H, c, o)] = b2;
+        W3[frag_at(SG_H, o, c)] = b3;
+        W3t[frag_at(SG_H, c, o)] = b3;
     }
 }
 
@@ -1462,11 +1478,11 @@ struct tgo_surrogate {
     int64_t ldt = 0;  // max_rows + TR_LD_PAD
     int64_t step = 0;
     void *mem = nullptr;
-    // parameters: float32 masters, gradient, Adam moments; bf16 working copies
-    // W [out][in] (W1 padded to 64 inputs) and, for back-propagation, W^T
-    float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
+    // parameters: float32 masters, Adam moments; bf16 working copies
+    // W [out][in] (W1 padded to 64 inputs) and, for back-propagation, W^T, all in
+    // fragment order (frag_at)
+    float *p = nullptr, *m = nullptr, *v = nullptr;
     uint16_t *W1 = nullptr, *W2 = nullptr, *W2t = nullptr, *W3 = nullptr, *W3t = nullptr;
-    uint16_t *Wf = nullptr;  // W1, W2, W3 in the fused inference kernel's fragment order
     // training batch, transposed [feature][row] with row pitch max_rows
     uint16_t *Xt = nullptr, *H1t = nullptr, *H2t = nullptr, *G1t = nullptr, *G2t = nullptr, *G3t = nullptr;
     // kept by tgo_surrogate_grad for inspection: h3 [row][256] and scores
@@ -1533,10 +1549,10 @@ static AdamArgs adam_args(int64_t step, float lr) {
     return a;
 }
 
-static void launch_update(tgo_surrogate *s, int mode, int ks, const float *gin, const AdamArgs &a, float *loss,
+static void launch_update(tgo_surrogate *s, int mode, int ks, const float *gin, float *g, const AdamArgs &a, float *loss,
                           hipStream_t st) {
     hipLaunchKernelGGL(train_update_kernel, dim3((SG_NPARAM + 255) / 256), dim3(256), 0, st, mode, s->wpart,
-                       s->vpart, ks, gin, s->p, s->g, s->m, s->v, a, loss, s->W1, s->W2, s->W2t, s->W3, s->W3t);
+                       s->vpart, ks, gin, s->p, g, s->m, s->v, a, loss, s->W1, s->W2, s->W2t, s->W3, s->W3t);
 }
 
 }  // namespace tgo
@@ -1564,10 +1580,10 @@ int tgo_surrogate_create(int64_t max_rows, int max_groups, tgo_surrogate **out) 
     const size_t R = (size_t)max_rows, LT = (size_t)s->ldt;
     const size_t blocks = (R + TR_ROWS - 1) / TR_ROWS;
     std::vector<std::pair<void **, size_t>> parts = {
-        {(void **)&s->p, 4 * SG_NPARAM}, {(void **)&s->g, 4 * SG_NPARAM}, {(void **)&s->m, 4 * SG_NPARAM},
+        {(void **)&s->p, 4 * SG_NPARAM}, {(void **)&s->m, 4 * SG_NPARAM},
         {(void **)&s->v, 4 * SG_NPARAM},
         {(void **)&s->W1, 2 * SG_H * SG_K0}, {(void **)&s->W2, 2 * SG_H * SG_H}, {(void **)&s->W2t, 2 * SG_H * SG_H},
-        {(void **)&s->W3, 2 * SG_H * SG_H}, {(void **)&s->W3t, 2 * SG_H * SG_H}, {(void **)&s->Wf, 2 * (size_t)FM_WF},
+        {(void **)&s->W3, 2 * SG_H * SG_H}, {(void **)&s->W3t, 2 * SG_H * SG_H},
         {(void **)&s->Xt, 2 * LT * SG_K0}, {(void **)&s->H1t, 2 * LT * SG_H}, {(void **)&s->H2t, 2 * LT * SG_H},
         {(void **)&s->G1t, 2 * LT * SG_H}, {(void **)&s->G2t, 2 * LT * SG_H}, {(void **)&s->G3t, 2 * LT * SG_H},
         {(void **)&s->H3, 2 * R * SG_H}, {(void **)&s->score, 4 * R},
@@ -1723,10 +1739,9 @@ int tgo_surrogate_score(tgo_surrogate *s, const tgo_task *d_tasks, const int32_t
     hipStream_t st = (hipStream_t)stream;
     hipLaunchKernelGGL(group_features_kernel, dim3((G * SG_POS + 255) / 256), dim3(256), 0, st, d_tasks, d_offs,
                        G, s->F);
-    hipLaunchKernelGGL(pack_frag_kernel, dim3((FM_WF + 255) / 256), dim3(256), 0, st, s->W1, s->W2, s->W3, s->Wf);
     hipLaunchKernelGGL(mlp_fused_kernel, dim3((unsigned)((rows + FM_ROWS - 1) / FM_ROWS)), dim3(FM_THREADS), 0, st, s->F,
                        d_offs, (const uint32_t *)nullptr, d_orders, d_gid, (int64_t)0, rows, (int64_t)1, (int64_t)1,
-                       (uint64_t)0, s->Wf, s->Wf + FM_WF1, s->Wf + FM_WF1 + SG_H * SG_H, s->p, d_scores,
+                       (uint64_t)0, s->W1, s->W2, s->W3, s->p, d_scores,
                        (unsigned long long *)nullptr);
     TGO_HIP(hipGetLastError());
     return TGO_OK;
@@ -1745,9 +1760,8 @@ int tgo_surrogate_grad(tgo_surrogate *s, const tgo_task *d_tasks, const int32_t 
     rc = train_pass(s, d_tasks, d_offs, d_orders, d_gid, d_T, rows, true, &ks, st);
     if (rc) return rc;
     s->kept_rows = rows;
-    launch_update(s, 0, ks, nullptr, adam_args(1, 0.f), d_loss, st);
+    launch_update(s, 0, ks, nullptr, d_grad, adam_args(1, 0.f), d_loss, st);
     TGO_HIP(hipGetLastError());
-    if (d_grad) TGO_HIP(hipMemcpyAsync(d_grad, s->g, 4 * SG_NPARAM, hipMemcpyDeviceToDevice, st));
     return TGO_OK;
 }
 
@@ -1765,7 +1779,7 @@ int tgo_surrogate_train_step(tgo_surrogate *s, const tgo_task *d_tasks, const in
     rc = train_pass(s, d_tasks, d_offs, d_orders, d_gid, d_T, rows, false, &ks, st);
     if (rc) return rc;
     s->step += 1;
-    launch_update(s, 1, ks, nullptr, adam_args(s->step, lr), d_loss, st);
+    launch_update(s, 1, ks, nullptr, nullptr, adam_args(s->step, lr), d_loss, st);
     TGO_HIP(hipGetLastError());
     return TGO_OK;
 }
@@ -1774,7 +1788,7 @@ int tgo_surrogate_adam_step(tgo_surrogate *s, const float *d_grad, float lr, tgo
     if (!s || !d_grad) return fail(TGO_EINVAL, "NULL argument");
     if (!(lr > 0.f)) return fail(TGO_EINVAL, "lr must be > 0");
     s->step += 1;
-    launch_update(s, 2, 0, d_grad, adam_args(s->step, lr), nullptr, (hipStream_t)stream);
+    launch_update(s, 2, 0, d_grad, nullptr, adam_args(s->step, lr), nullptr, (hipStream_t)stream);
     TGO_HIP(hipGetLastError());
     return TGO_OK;
 }
@@ -1803,13 +1817,14 @@ int tgo_surrogate_get_batch(tgo_surrogate *s, int what, int64_t rows, void *h_ou
     const uint16_t *src = what == 0 ? s->Xt : what == 1 ? s->H1t : what == 2 ? s->H2t
                         : what == 5 ? s->G3t : what == 6 ? s->G2t : s->G1t;
     const int width = what == 0 ? SG_K0 : SG_H, keep = what == 0 ? SG_FEAT : SG_H;
-    std::vector<uint16_t> t((size_t)width * rows);
-    TGO_HIP(hipMemcpy2DAsync(t.data(), 2 * (size_t)rows, src, 2 * (size_t)s->ldt, 2 * (size_t)rows, width,
+    const int64_t span = (rows + 63) & ~int64_t(63);  // whole units of row_position
+    std::vector<uint16_t> t((size_t)width * span);
+    TGO_HIP(hipMemcpy2DAsync(t.data(), 2 * (size_t)span, src, 2 * (size_t)s->ldt, 2 * (size_t)span, width,
                              hipMemcpyDeviceToHost, st));
     TGO_HIP(hipStreamSynchronize(st));
     uint16_t *o = (uint16_t *)h_out;
     for (int64_t r = 0; r < rows; ++r)
-        for (int c = 0; c < keep; ++c) o[r * keep + c] = t[(size_t)c * rows + r];
+        for (int c = 0; c < keep; ++c) o[r * keep + c] = t[(size_t)c * span + row_position(r)];
     return TGO_OK;
 }
 
@@ -1872,14 +1887,13 @@ static int search_candidates(tgo_surrogate *s, const Rates &r, const tgo_task *d
                        s->status, (int32_t *)nullptr);
     hipLaunchKernelGGL(group_features_kernel, dim3((G * SG_POS + 255) / 256), dim3(256), 0, st, d_tasks, d_offs,
                        G, s->F);
-    hipLaunchKernelGGL(pack_frag_kernel, dim3((FM_WF + 255) / 256), dim3(256), 0, st, s->W1, s->W2, s->W3, s->Wf);
     const int64_t total = (int64_t)G * spad;
     for (int64_t row0 = 0; row0 < total; row0 += chunk) {
         const int64_t rows = std::min(chunk, total - row0);
         // rows is a multiple of TK_RUN, hence of FM_ROWS
         hipLaunchKernelGGL(mlp_fused_kernel, dim3((unsigned)(rows / FM_ROWS)), dim3(FM_THREADS), 0, st, s->F, d_offs, d_keys,
-                           (const uint8_t *)nullptr, (const int32_t *)nullptr, row0, rows, spad, samples, seed, s->Wf,
-                           s->Wf + FM_WF1, s->Wf + FM_WF1 + SG_H * SG_H, s->p, (float *)nullptr, s->keys);
+                           (const uint8_t *)nullptr, (const int32_t *)nullptr, row0, rows, spad, samples, seed, s->W1,
+                           s->W2, s->W3, s->p, (float *)nullptr, s->keys);
         const int nrun = (int)(rows / TK_RUN);
         hipLaunchKernelGGL(topk_pass_kernel, dim3(nrun, 1), dim3(TK_THREADS), 0, st, s->keys, (int64_t)0, rows, nrun,
                            s->cand[0] + (row0 / TK_RUN) * TK_KEEP, (int64_t)0);
