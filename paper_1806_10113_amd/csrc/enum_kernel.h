@@ -123,6 +123,21 @@ __device__ __forceinline__ void exacc_init(ExAcc *acc, int lane) {
 }
 static_assert(EX_ACCS == 64, "one wave initialises and merges the accumulators");
 
+// A block's result (one lane): into an accumulator (32-bit time) or as a partial.
+template <typename TT>
+__device__ __forceinline__ void block_out(const Partial &o, uint32_t block, Partial *partials, ExAcc *acc) {
+    if constexpr (sizeof(TT) == 4) {
+        // every block owns at least one subtree, so o holds an ordering
+        acc += block % EX_ACCS;
+        atomicMin(&acc->minkey, (unsigned long long)((o.min_t << 33) | o.min_r));
+        atomicMax(&acc->maxkey, (unsigned long long)(((o.max_t - 1) << 33) | (EX_RANK_MASK - o.max_r)));
+        atomicAdd(&acc->sum, (unsigned long long)o.sum_lo);
+        atomicAdd(&acc->fp, (unsigned long long)o.fp);
+    } else {
+        partials[block] = o;
+    }
+}
+
 // ------------------------------------------------------------------ summary
 
 // Rank -> ordering, one task per nibble.  Only the first digit of n = 13
@@ -350,18 +365,7 @@ void enum_kernel(const tgo_task *__restrict__ tasks, int n, Rates r, typename Ru
     p.status = 0;
     p.pad = 0;
     const Partial o = block_reduce(p, reinterpret_cast<Partial *>(qbase));
-    if (threadIdx.x == 0) {
-        if constexpr (sizeof(TT) == 4) {
-            // every block owns at least one subtree, so o holds an ordering
-            acc += block % EX_ACCS;
-            atomicMin(&acc->minkey, (unsigned long long)((o.min_t << 33) | o.min_r));
-            atomicMax(&acc->maxkey, (unsigned long long)(((o.max_t - 1) << 33) | (EX_RANK_MASK - o.max_r)));
-            atomicAdd(&acc->sum, (unsigned long long)o.sum_lo);
-            atomicAdd(&acc->fp, (unsigned long long)o.fp);
-        } else {
-            partials[block] = o;
-        }
-    }
+    if (threadIdx.x == 0) block_out<TT>(o, block, partials, acc);
 }
 
 constexpr int EX_FIN_THREADS = 1024;

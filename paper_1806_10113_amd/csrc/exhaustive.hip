@@ -10,6 +10,7 @@
 #include <mutex>
 
 #include "enum_kernel.h"
+#include "one_dev.h"
 #include "potential_dev.h"
 
 namespace tgo {
@@ -37,22 +38,24 @@ __global__ __launch_bounds__(EX_FIN_THREADS) void exhaustive_finalize(const Part
     }
 }
 
-// Positions enumerated depth-first per lane: enough subtrees to fill the GPU.
-// TGO_EXHAUSTIVE_M overrides the choice for tuning experiments (1..5, or
-// 1..6 with one DMA engine).
+// Last positions that one lane enumerates (two engines, a walk) or whose orders
+// a block's prefixes share (one engine).  TGO_EXHAUSTIVE_M overrides the choice
+// for tuning experiments (1..5, or 1..6 with one DMA engine).
 static int choose_m(int n, bool one_dma) {
-    const int cap = one_dma ? 6 : 5;
+    const int cap = one_dma ? ONE_MAX_M : 5;
     if (const char *e = std::getenv("TGO_EXHAUSTIVE_M")) {
         const int m = std::atoi(e);
         if (m >= 1 && m <= cap && m <= n) return m;
     }
-    // two engines: with the three innermost levels unrolled, 5 levels beat 4
-    // at n = 12 on MI355X (1.81 vs 1.99 ms: fewer windows per ordering, 2.77
-    // vs 3.0).  One engine: a window is a handful of operations, so the
-    // per-subtree prefix decode is worth amortising over 6 levels.
-    const int top = one_dma ? 6 : 5;
+    // one engine: 720 prefixes per set, two tiles that fill their lanes.  Groups of
+    // 9 / 10 / 11 in us, with 3 to 6 positions shared: 28 28 36 79 / 43 32 37 81 /
+    // 249 85 50 84 (fewer: the block computes (B, C) for nothing; more: idle lanes)
+    if (one_dma) return n < 7 ? 1 : (n - 6 < cap ? n - 6 : cap);
+    // enough subtrees to fill the GPU.  With the three innermost levels
+    // unrolled, 5 levels beat 4 at n = 12 on MI355X (1.81 vs 1.99 ms: fewer
+    // windows per ordering, 2.77 vs 3.0).
     int m = 1;
-    for (int c = top; c >= 1; --c) {
+    for (int c = cap; c >= 1; --c) {
         if (c > n) continue;
         const uint64_t sub = factorial(n) / factorial(c);
         if (sub >= 32768 || c == 1) { m = c; break; }
@@ -88,24 +91,23 @@ uint32_t resident_blocks(const void *kern, int threads, size_t shm) {
 // 2011 / 2551), and the groups below 11, which are done in less than 50 us, would
 // pay the launch that finds nothing to do, 4.5 us, when theirs does not fit.
 constexpr int POT_M = 5;
-template <int M, bool STORE, int DMA>
-static int launch_pair(hipStream_t st, const tgo_task *t, int n, const Rates &r, uint32_t n_sub, int64_t *out,
-                       tgo_summary *d_out, ExScratch ws) {
-    const void *k32 = reinterpret_cast<const void *>(&enum_kernel<BaseRule, uint32_t, M, STORE, DMA>);
+template <int M, bool STORE>
+static int launch_two(hipStream_t st, const tgo_task *t, int n, const Rates &r, uint32_t n_sub, int64_t *out,
+                      tgo_summary *d_out, ExScratch ws) {
+    const void *k32 = reinterpret_cast<const void *>(&enum_kernel<BaseRule, uint32_t, M, STORE, DMA_TWO>);
     uint32_t blocks = 0;
     EnumScratch sc;
-    int rc = enum_grid(k32, enum_shm_bytes<BaseRule, uint32_t>(n, DMA == DMA_ONE), n_sub, 0, ws, st, &blocks, &sc);
+    int rc = enum_grid(k32, enum_shm_bytes<BaseRule, uint32_t>(n, false), n_sub, 0, ws, st, &blocks, &sc);
     if (rc) return rc;
-    constexpr bool two = DMA == DMA_TWO;
-    const bool potential = two && M == POT_M && pot_rates(r, n);
+    const bool potential = M == POT_M && pot_rates(r, n);
     hipLaunchKernelGGL(exhaustive_classify, dim3(1), dim3(64), 0, st, t, n, r, potential, sc.mode, sc.acc);
-    if constexpr (two && M == POT_M) {
+    if constexpr (M == POT_M) {
         if (potential) {
-            enum_launch_one<PotRule, uint32_t, M, STORE, DMA>(st, t, n, r, PotRule::Args{}, n_sub, out, blocks, sc);
+            enum_launch_one<PotRule, uint32_t, M, STORE, DMA_TWO>(st, t, n, r, PotRule::Args{}, n_sub, out, blocks, sc);
             TGO_HIP(hipGetLastError());
         }
     }
-    rc = enum_launch<BaseRule, M, STORE, DMA>(st, t, n, r, BaseRule::Args{}, n_sub, out, blocks, sc);
+    rc = enum_launch<BaseRule, M, STORE, DMA_TWO>(st, t, n, r, BaseRule::Args{}, n_sub, out, blocks, sc);
     if (rc) return rc;
     hipLaunchKernelGGL(exhaustive_finalize, dim3(1), dim3(EX_FIN_THREADS), 0, st, sc.parts, (int)blocks, n,
                        factorial(n), sc.acc, sc.mode, d_out);
@@ -113,21 +115,35 @@ static int launch_pair(hipStream_t st, const tgo_task *t, int n, const Rates &r,
     return TGO_OK;
 }
 
-template <bool STORE, int DMA>
-static int launch_m(int m, hipStream_t st, const tgo_task *t, int n,
-                    const Rates &r, uint32_t n_sub, int64_t *out, tgo_summary *d_out, ExScratch ws) {
+template <bool STORE>
+static int launch_two_m(int m, hipStream_t st, const tgo_task *t, int n,
+                        const Rates &r, uint32_t n_sub, int64_t *out, tgo_summary *d_out, ExScratch ws) {
     switch (m) {
-        case 1: return launch_pair<1, STORE, DMA>(st, t, n, r, n_sub, out, d_out, ws);
-        case 2: return launch_pair<2, STORE, DMA>(st, t, n, r, n_sub, out, d_out, ws);
-        case 3: return launch_pair<3, STORE, DMA>(st, t, n, r, n_sub, out, d_out, ws);
-        case 4: return launch_pair<4, STORE, DMA>(st, t, n, r, n_sub, out, d_out, ws);
-        case 5: return launch_pair<5, STORE, DMA>(st, t, n, r, n_sub, out, d_out, ws);
-        default:
-            if constexpr (DMA == DMA_ONE)
-                return launch_pair<6, STORE, DMA>(st, t, n, r, n_sub, out, d_out, ws);
-            else
-                return launch_pair<5, STORE, DMA>(st, t, n, r, n_sub, out, d_out, ws);
+        case 1: return launch_two<1, STORE>(st, t, n, r, n_sub, out, d_out, ws);
+        case 2: return launch_two<2, STORE>(st, t, n, r, n_sub, out, d_out, ws);
+        case 3: return launch_two<3, STORE>(st, t, n, r, n_sub, out, d_out, ws);
+        case 4: return launch_two<4, STORE>(st, t, n, r, n_sub, out, d_out, ws);
+        default: return launch_two<5, STORE>(st, t, n, r, n_sub, out, d_out, ws);
     }
+}
+
+template <bool STORE>
+static int launch_one(int m, hipStream_t st, const tgo_task *t, int n, const Rates &r, int64_t *out,
+                      tgo_summary *d_out, ExScratch ws) {
+    const OneShape sh = one_shape(n, m);
+    const size_t lds = one_lds<uint64_t, STORE>(n, sh.orders);
+    uint32_t blocks = 0;
+    EnumScratch sc;
+    int rc = enum_grid(reinterpret_cast<const void *>(&one_kernel<STORE>), lds, sh.tiles * EX_THREADS, 0, ws, st,
+                       &blocks, &sc);
+    if (rc) return rc;
+    hipLaunchKernelGGL(exhaustive_classify, dim3(1), dim3(64), 0, st, t, n, r, false, sc.mode, sc.acc);
+    hipLaunchKernelGGL(one_kernel<STORE>, dim3(blocks), dim3(EX_THREADS), lds, st, t, n, m, r, sh, out, sc.parts,
+                       sc.acc, sc.mode);
+    hipLaunchKernelGGL(exhaustive_finalize, dim3(1), dim3(EX_FIN_THREADS), 0, st, sc.parts, (int)blocks, n,
+                       factorial(n), sc.acc, sc.mode, d_out);
+    TGO_HIP(hipGetLastError());
+    return TGO_OK;
 }
 
 static int launch_exhaustive_ws(const Rates &r, const tgo_task *d_tasks, int n, int64_t *d_per_order,
@@ -143,14 +159,11 @@ static int launch_exhaustive_ws(const Rates &r, const tgo_task *d_tasks, int n, 
     const uint64_t n_sub64 = factorial(n) / factorial(m);
     if (n_sub64 >= (1ull << 32)) return fail(TGO_EINVAL, "group too large to enumerate");
     const uint32_t n_sub = (uint32_t)n_sub64;
-    if (one) {
-        return d_per_order
-                   ? launch_m<true, DMA_ONE>(m, st, d_tasks, n, r, n_sub, d_per_order, d_out, ws)
-                   : launch_m<false, DMA_ONE>(m, st, d_tasks, n, r, n_sub, nullptr, d_out, ws);
-    }
-    return d_per_order
-               ? launch_m<true, DMA_TWO>(m, st, d_tasks, n, r, n_sub, d_per_order, d_out, ws)
-               : launch_m<false, DMA_TWO>(m, st, d_tasks, n, r, n_sub, nullptr, d_out, ws);
+    if (one)
+        return d_per_order ? launch_one<true>(m, st, d_tasks, n, r, d_per_order, d_out, ws)
+                           : launch_one<false>(m, st, d_tasks, n, r, nullptr, d_out, ws);
+    return d_per_order ? launch_two_m<true>(m, st, d_tasks, n, r, n_sub, d_per_order, d_out, ws)
+                       : launch_two_m<false>(m, st, d_tasks, n, r, n_sub, nullptr, d_out, ws);
 }
 
 int launch_exhaustive(const Rates &r, const tgo_task *d_tasks, int n, int64_t *d_per_order,

@@ -108,6 +108,8 @@ __device__ __forceinline__ uint64_t ceil_p(uint64_t u, uint32_t p, double inv, d
 
 template <typename TT>
 __device__ __forceinline__ TT tmax(TT a, TT b) { return a > b ? a : b; }
+template <typename TT>
+__device__ __forceinline__ TT tmin(TT a, TT b) { return a < b ? a : b; }
 
 template <typename TT>
 __device__ __forceinline__ TT inf_time() { return ~TT(0); }
