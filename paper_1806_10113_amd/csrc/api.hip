@@ -46,6 +46,12 @@ int make_rates(const tgo_model *m, Rates *r) {
         r->dinv = odd;  // Newton: each step doubles the correct low bits (3 at first)
         for (int i = 0; i < 4; ++i) r->dinv *= 2u - odd * r->dinv;
     }
+    // with 2^l >= p_h: m = floor(2^(31+l) / p_h) + 1 is off by e / p_h with
+    // 0 < e <= p_h, so x m / 2^(31+l) exceeds x / p_h by less than 1 / p_h
+    int l = 0;
+    while ((1ll << l) < m->p_htd) ++l;
+    r->phm = l ? (uint32_t)((1ull << (31 + l)) / (uint64_t)m->p_htd + 1) : 0;
+    r->phs = l ? l - 1 : 0;
     return TGO_OK;
 }
 

@@ -86,10 +86,10 @@ uint32_t resident_blocks(const void *kern, int threads, size_t shm) {
 }
 
 // The walk that also has the potential form (PotRule): the deepest, which the
-// groups of 11 and more take.  There the form wins 10 to 40% of 0.2 to 25 ms; at
-// depth 4 it does not (a group of 12: 2259 / 2208 / 2251 us, chain form 2165 /
-// 2011 / 2551), and the groups below 11, which are done in less than 50 us, would
-// pay the launch that finds nothing to do, 4.5 us, when theirs does not fit.
+// groups of 11 and more take.  There the form takes 1782 / 1712 / 1744 us where the
+// chain form takes 2165 / 2011 / 2551 (three groups of 12); at depth 4 it gained
+// nothing, and the groups below 11, done in 60 us and less, would pay the launch
+// that finds nothing to do, 4.5 us, when theirs does not fit.
 constexpr int POT_M = 5;
 template <int M, bool STORE>
 static int launch_two(hipStream_t st, const tgo_task *t, int n, const Rates &r, uint32_t n_sub, int64_t *out,

@@ -54,6 +54,9 @@ struct Rates {
     // exact quotients by q - p_h (p_h < q): it is odd << dsh, odd * dinv = 1 mod 2^32
     uint32_t dinv;
     int32_t dsh;
+    // floor(x / p_h) = umulhi(x, phm) >> phs for x < 2^31 (p_h > 1)
+    uint32_t phm;
+    int32_t phs;
 };
 
 template <typename TT>

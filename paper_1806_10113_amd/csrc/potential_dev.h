@@ -2,8 +2,8 @@
 // kernel: the windows of a walk, 32-bit time.
 //
 // A lane's queue holds, per placed position, G_i and E_i of its DtH and, in a
-// byte, the rounding slack of the DtHs before it.  What a window needs of them
-// it reads after the search, so the state saved at each level of the walk is
+// byte, the rounding slack of the DtHs before it.  What a window needs of the DtH
+// before its cursor it reads after the search, so the state saved at each level of the walk is
 // seven words (the chain form's is ten) and the search itself is one LDS read
 // and one comparison per DtH.
 //
@@ -19,12 +19,14 @@
 // the group's time bound below 2^31.
 //
 // What bounds it: instruction issue and the chain of LDS reads of the search,
-// about evenly (171 vector instructions and 33 LDS accesses per ordering; the
-// vector units issue in 59% of the cycles).  Three groups of 12 (479 M orderings
-// each), five tasks left at the root of a walk: chain form 2165 / 2011 / 2551 us
-// (a group's time follows the length of its searches and, there, how often the
-// lanes of a wave part), potential form 1855 / 1823 / 1842 us at 6 waves per
-// SIMD, 1959 / 1933 / 1959 at 5, 1914 / 1864 / 1887 at 7 (spills).
+// about evenly.  Three groups of 12 (479 M orderings each), five tasks left at the
+// root of a walk: chain form 2165 / 2011 / 2551 us (a group's time follows the
+// length of its searches and, there, how often the lanes of a wave part), potential
+// form 1782 / 1712 / 1744 us.  Slots of 8 bytes hold five waves per SIMD at 12
+// tasks; potentials and ends in arrays of their own, without the last end, hold six
+// but read twice as often and select the origin: 1855 / 1823 / 1842.  The slack
+// bytes in the last slot's spare word hold six, too, and spill: 1960 / 1826 / 1845.
+// The DtH before taken along in the search: 1845 / 1777 / 1817 (it spills).
 #pragma once
 
 #include "enum_kernel.h"
@@ -33,12 +35,18 @@ namespace tgo {
 
 constexpr uint32_t POT_INF = 0x7fffffffu;  // above every potential
 
+// A placed DtH: its potential and its end, one 8-byte LDS access.
+struct PotSlot {
+    uint32_t g, e;
+};
+
 template <int QS>
 struct PotView {
     const Quad<uint32_t> *H;  // (q h, k, d, dp) of a task
     const DRec<uint32_t> *D;  // (p_htd dp, slack)
-    uint32_t *G, *E;          // slot i at [i * QS]
-    uint8_t *S;
+    PotSlot *Q;               // slot i at [i * QS]
+    const PotSlot *zero;      // the slot before the first: the origin (one for the block)
+    uint8_t *S;               // at [i * QS]
 };
 
 struct PotLane {
@@ -48,7 +56,7 @@ struct PotLane {
     int32_t emax;   // max over placed positions p of (K_p end - sum_{s<p} d_s)
     uint32_t dpre;  // sum of solo DtH durations of the positions placed so far
     uint32_t sig;   // sum of their slacks
-    int i;          // cursor: the first DtH that ends at t or later
+    int i;          // cursor times QS: the first DtH that ends at t or later
     // the last position's window: DtH i (g = POT_INF: none), its slack byte
     uint32_t g, e, s;
 };
@@ -68,20 +76,15 @@ __device__ __forceinline__ void window(PotLane &s, int j, uint32_t x, const PotV
     int i = s.i;
     // the search stops at slot j: what a sibling of this position left there is
     // cleared (the last position's slot never holds anything else)
-    if constexpr (PUT) v.G[j * QS] = POT_INF;
-    uint32_t gc = v.G[i * QS];
-    while (gc < X) gc = v.G[++i * QS];
+    if constexpr (PUT) v.Q[j * QS].g = POT_INF;
+    PotSlot c = v.Q[i];
+    while (c.g < X) c = v.Q[i += QS];
     // the lines of slope q through the DtH before and of slope p_htd through
     // DtH i; the origin before the first one
-    const bool live = gc != POT_INF;
-    const int b = i > 0 ? i - 1 : 0;
-    uint32_t gp = v.G[b * QS], ep = v.E[b * QS];
-    const int ci = live ? i : b;
-    const uint32_t ec = v.E[ci * QS];
-    gp = i > 0 ? gp : 0;
-    ep = i > 0 ? ep : 0;
-    const uint32_t eq = ep + ((X - gp + ((1u << r.q_log2) - 1u)) >> r.q_log2);
-    const uint32_t ek = ec - floor_p(gc - X, r.p_h, r.inv_ph);
+    const PotSlot p = *(i > 0 ? v.Q + (i - QS) : v.zero);
+    const uint32_t eq = p.e + ((X + ((1u << r.q_log2) - 1u) - p.g) >> r.q_log2);
+    const uint32_t ek = c.e - (__umulhi(c.g - X, r.phm) >> r.phs);
+    const bool live = c.g != POT_INF;
     const uint32_t t = live && (int32_t)ek > (int32_t)eq ? ek : eq;
     s.ck = tmax(t, s.ck) + tx.hp;
     const int32_t e = (int32_t)s.ck - (int32_t)s.dpre;
@@ -89,20 +92,22 @@ __device__ __forceinline__ void window(PotLane &s, int j, uint32_t x, const PotV
     s.dpre += tx.k;
     s.t = t;
     if constexpr (PUT) {
-        const uint32_t wq = gp + ((t - ep) << r.q_log2), wp = gc - r.p_h * (ec - t);
+        const uint32_t wq = p.g + ((t - p.e) << r.q_log2), wp = c.g - r.p_h * (c.e - t);
         s.w = live && wp < wq ? wp : wq;
         s.i = i;
         const DRec<uint32_t> dx = v.D[x];
-        const uint32_t gl = j > 0 ? v.G[(j - 1) * QS] : 0u, el = j > 0 ? v.E[(j - 1) * QS] : 0u;
-        const uint32_t S = tmax(el, s.ck);
-        v.G[j * QS] = gl + ((S - el) << r.q_log2) + dx.d;
-        v.E[j * QS] = S + tx.d;
+        const PotSlot l = *(j > 0 ? v.Q + (j - 1) * QS : v.zero);
+        const uint32_t S = tmax(l.e, s.ck);
+        PotSlot o;
+        o.g = l.g + ((S - l.e) << r.q_log2) + dx.d;
+        o.e = S + tx.d;
+        v.Q[j * QS] = o;
         v.S[j * QS] = (uint8_t)s.sig;
         s.sig += dx.dp;
     } else {
-        s.g = gc;
-        s.e = ec;
-        s.s = v.S[ci * QS];
+        s.g = c.g;
+        s.e = c.e;
+        s.s = v.S[live ? i : 0];
     }
 }
 
@@ -125,22 +130,23 @@ struct PotRule : GroupRule {
     template <typename TT, int DMA>
     using Lane = PotLane;
     template <typename TT, int DMA>
-    static constexpr int min_waves() { return 6; }
+    static constexpr int min_waves() { return 5; }
     template <typename TT>
     static constexpr int mode() { return 2; }
     static constexpr bool queue(bool) { return true; }
-    static __host__ __device__ constexpr size_t lds_bytes(int) { return 0; }
+    static __host__ __device__ constexpr size_t lds_bytes(int) { return sizeof(Quad<uint32_t>); }  // the origin
     template <typename TT>
     static __host__ __device__ constexpr size_t lane_bytes(int n) {
-        return (size_t)(4 * n + 5 * (n > 1 ? n - 1 : 1));
+        return sizeof(PotSlot) * n + (size_t)(n > 1 ? n - 1 : 1);
     }
     template <typename TT>
     static __device__ __forceinline__ void bind(PotView<EX_THREADS> &v, unsigned char *queue, int n) {
-        const int m = n > 1 ? n - 1 : 1;
-        v.G = reinterpret_cast<uint32_t *>(queue) + threadIdx.x;
-        v.E = v.G + n * EX_THREADS;
-        v.S = queue + (size_t)4 * EX_THREADS * (n + m) + threadIdx.x;
-        v.G[(n - 1) * EX_THREADS] = POT_INF;
+        PotSlot *q = reinterpret_cast<PotSlot *>(queue), *zero = reinterpret_cast<PotSlot *>(queue - sizeof(Quad<TT>));
+        v.Q = q + threadIdx.x;
+        v.S = queue + sizeof(PotSlot) * EX_THREADS * n + threadIdx.x;
+        v.Q[(n - 1) * EX_THREADS].g = POT_INF;
+        v.zero = zero;
+        if (threadIdx.x == 0) zero->g = zero->e = 0;
     }
     template <typename TT>
     static __device__ __forceinline__ void entry(const tgo_task &t, const Rates &r, Quad<TT> *H, DRec<TT> *D) {
@@ -161,7 +167,7 @@ struct PotRule : GroupRule {
 
 // Whether the rates allow the form for groups of n tasks.
 inline bool pot_rates(const Rates &r, int n) {
-    return !r.one_dma && r.p_h < (1u << r.q_log2) && (uint64_t)(n > 2 ? n - 2 : 0) * (r.p_d - 1) < 256;
+    return !r.one_dma && r.p_h > 1 && r.p_h < (1u << r.q_log2) && (uint64_t)(n > 2 ? n - 2 : 0) * (r.p_d - 1) < 256;
 }
 
 }  // namespace tgo
