@@ -23,6 +23,7 @@
 #include <vector>
 
 #include "enum_kernel.h"
+#include "potential_dev.h"
 #include "tables_dev.h"
 #include "tgo_internal.h"
 
@@ -39,13 +40,19 @@ struct BatchCfg {
     int32_t blocks;          // persistent grid size
 };
 
+// Largest group whose potential form fits the queue of the chain form: 8 bytes and,
+// but for the last slot, a slack byte per slot.
+constexpr int BT_POT_N = 10;
+static_assert(8 * BT_POT_N + BT_POT_N - 1 <= (int)sizeof(Slot<uint32_t>) * BT_MAX_N, "the lane's queue");
+
 struct GroupAcc {
     unsigned long long minkey;  // (T << 32) | rank, smallest
     unsigned long long maxkey;  // (T << 32) | (2^32 - 1 - rank), largest
     unsigned long long sum;     // sum of T (n <= 12 and T < 2^31: no overflow)
     unsigned long long fp;      // sum of (2 rank + 1) T mod 2^64
     int32_t status, n;
-    int32_t wide, pad;          // 1: the group runs the 64-bit path (per-tile partials)
+    int32_t wide;               // 1: the group runs the 64-bit path (per-tile partials)
+    int32_t potential;          // 1: its walk takes the potential form
 };
 
 struct BatchHdr {
@@ -112,13 +119,15 @@ __global__ __launch_bounds__(1024) void batch_prepare(const tgo_task *__restrict
         uint32_t tiles = 0, wtiles = 0;
         if (g < G) {
             const int n = offs[g + 1] - offs[g];
-            int st = 0, wide = 0;
+            int st = 0, wide = 0, potential = 0;
             if (n < 1 || n > max_n) {
                 st = TGO_EINVAL;
             } else {
-                const int c = classify_group(tasks + offs[g], n, r);
+                uint64_t bound;
+                const int c = classify_group(tasks + offs[g], n, r, &bound);
                 st = c < 0 ? c : 0;
                 wide = c == 1;
+                potential = c == 0 && n <= BT_POT_N && pot_rates(r, n) && potential_fits<uint32_t>(bound, r);
             }
             GroupAcc a;
             a.minkey = ~0ull;
@@ -128,7 +137,7 @@ __global__ __launch_bounds__(1024) void batch_prepare(const tgo_task *__restrict
             a.status = st;
             a.n = n;
             a.wide = wide;
-            a.pad = 0;
+            a.potential = potential;
             acc[g] = a;
             if (st == 0 && !wide) tiles = (subtrees_of(n, cfg.m[n]) + per_tile - 1) / per_tile;
             if (st == 0 && wide) wtiles = wide_tiles_of(n, wide_tiles);
@@ -168,13 +177,6 @@ __device__ __forceinline__ uint32_t next_tile(unsigned int *counter, uint32_t to
 template <typename TT, int DMA>
 using BatchLane = std::conditional_t<DMA == DMA_TWO, CLane<TT>, Lane<TT>>;
 
-template <int M, int DMA>
-__device__ __forceinline__ void run_subtree(const Ctx &c, const View<uint32_t, 1, BT_THREADS> &v,
-                                            const BatchLane<uint32_t, DMA> &st, uint32_t list,
-                                            Sub<uint32_t> &u) {
-    level<uint32_t, M, false, DMA>(c, v, st, list, 0u, u);
-}
-
 __device__ __forceinline__ unsigned long long wave_min(unsigned long long x) {
     for (int m = 32; m >= 1; m >>= 1) {
         const unsigned long long y = shfl_xor64(x, m);
@@ -194,15 +196,48 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long x) {
     return x;
 }
 
+struct TileKeys {
+    unsigned long long min, max, sum, fp;
+};
+
+// One lane's subtree s of a group of n (m positions walked) into the tile's keys.
+template <int MMAX, int DMA, typename LaneT, typename ViewT>
+__device__ __forceinline__ void walk_subtree(const Ctx &c, const ViewT &v, uint32_t s, int m, TileKeys &k) {
+    LaneT st;
+    uint32_t lex;
+    const uint32_t list = (uint32_t)prefix_by_set<DMA>(st, s, c.n, m, v, c.r, &lex);
+    Sub<uint32_t> u;
+    sub_init(u);
+    switch (m) {
+        case 1: level<uint32_t, 1, false, DMA>(c, v, st, list, 0u, u); break;
+        case 2: level<uint32_t, 2, false, DMA>(c, v, st, list, 0u, u); break;
+        case 3: level<uint32_t, 3, false, DMA>(c, v, st, list, 0u, u); break;
+        case 4:
+            if constexpr (MMAX >= 4) level<uint32_t, 4, false, DMA>(c, v, st, list, 0u, u);
+            break;
+        default:
+            if constexpr (MMAX >= 5) level<uint32_t, 5, false, DMA>(c, v, st, list, 0u, u);
+            break;
+    }
+    const uint64_t r0 = (uint64_t)lex * fact_c(m);
+    const unsigned long long a = ((unsigned long long)u.min_t << 32) | (r0 + u.min_l);
+    const unsigned long long b = ((unsigned long long)(u.max_t1 - 1u) << 32) | (0xffffffffull - (r0 + u.max_l));
+    k.min = a < k.min ? a : k.min;
+    k.max = b > k.max ? b : k.max;
+    k.sum += u.sum;
+    k.fp += 2ull * (r0 * u.sum + u.s2) + u.sum;
+}
+
 // MMAX: deepest per-lane walk compiled in (the plan's largest m); a smaller
 // bound lets the compiler keep fewer level snapshots live, so more waves fit.
 // Two DMA engines: at most 80 VGPRs, so 6 waves fit per SIMD (the 26 KB of
-// LDS per block allows 6 per CU); the walk of 5 levels then spills a few
-// registers that are read once per tile or subtree, not in the event loop
-// (12.1 -> 11.3 ms on the 4,096-group batch).  Subtrees in set-major order, as
-// in the single-group kernel: the lanes of a wave walk the same remaining tasks
-// (4,096 groups of 4 to 10 tasks, one label per task: 13.3 ms in rank order,
-// 10.1 in set-major order).
+// LDS per block allows 6 per CU); the walk of 5 levels then spills registers that
+// are mostly read once per tile or subtree (5 waves: the same within 0.5%).
+// Subtrees in set-major order, as in the single-group kernel: the lanes of a wave
+// walk the same remaining tasks.  Groups that allow it take the potential form, a
+// tile at a time, so that one launch serves all.  4,096 groups of 4 to 10 tasks,
+// one label per task: 13.3 ms in rank order, 10.1 in set-major order, 7.7 in the
+// potential form.
 template <int DMA, int MMAX>
 __global__ __launch_bounds__(BT_THREADS) __attribute__((amdgpu_waves_per_eu(DMA == DMA_TWO ? 6 : 1))) void batch_kernel(const tgo_task *__restrict__ tasks,
                                                            const int32_t *__restrict__ offs, int G,
@@ -218,6 +253,17 @@ __global__ __launch_bounds__(BT_THREADS) __attribute__((amdgpu_waves_per_eu(DMA 
     v.H = Ht[w];
     v.D = Dt[w];
     v.Q = reinterpret_cast<Slot<uint32_t> *>(smem) + threadIdx.x;
+    __shared__ PotSlot origin;
+    PotView<BT_THREADS> pv;
+    pv.H = Ht[w];
+    pv.D = Dt[w];
+    pv.Q = reinterpret_cast<PotSlot *>(smem) + threadIdx.x;
+    pv.S = smem + sizeof(PotSlot) * BT_THREADS * BT_POT_N + threadIdx.x;
+    pv.zero = &origin;
+    if constexpr (DMA == DMA_TWO) {
+        if (threadIdx.x == 0) origin.g = origin.e = 0;
+        __syncthreads();
+    }
     const uint32_t total = hdr->total_tiles, waves = gridDim.x * BT_WAVES;
     const uint32_t per_tile = 64u * (uint32_t)cfg.lane_mult;
     for (uint32_t tile = blockIdx.x * BT_WAVES + w; tile < total; tile = next_tile(&hdr->next_tile, total, waves, lane)) {
@@ -231,7 +277,12 @@ __global__ __launch_bounds__(BT_THREADS) __attribute__((amdgpu_waves_per_eu(DMA 
         const int base = offs[g];
         const int n = offs[g + 1] - base;
         const int m = cfg.m[n];
-        if (lane < n) table_entry<uint32_t>(tasks[base + lane], r, &Ht[w][lane], &Dt[w][lane]);
+        const bool potential = DMA == DMA_TWO && acc[g].potential;
+        if (lane < n) {
+            if (potential) PotRule::entry<uint32_t>(tasks[base + lane], r, &Ht[w][lane], &Dt[w][lane]);
+            else table_entry<uint32_t>(tasks[base + lane], r, &Ht[w][lane], &Dt[w][lane]);
+        }
+        if (potential) pv.Q[(n - 1) * BT_THREADS].g = POT_INF;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -241,40 +292,21 @@ __global__ __launch_bounds__(BT_THREADS) __attribute__((amdgpu_waves_per_eu(DMA 
         c.n = n;
         c.r = r;
         c.out_sub = nullptr;
-        unsigned long long kmin = ~0ull, kmax = 0, ksum = 0, kfp = 0;
+        TileKeys key = {~0ull, 0, 0, 0};
         for (int k = 0; k < cfg.lane_mult; ++k) {
             const uint32_t s = s0 + (uint32_t)k * 64u + (uint32_t)lane;
             if (s < S) {
-                BatchLane<uint32_t, DMA> st;
-                uint32_t lex;
-                const uint32_t list = (uint32_t)prefix_by_set<DMA>(st, s, n, m, v, r, &lex);
-                Sub<uint32_t> u;
-                sub_init(u);
-                switch (m) {
-                    case 1: run_subtree<1, DMA>(c, v, st, list, u); break;
-                    case 2: run_subtree<2, DMA>(c, v, st, list, u); break;
-                    case 3: run_subtree<3, DMA>(c, v, st, list, u); break;
-                    case 4:
-                        if constexpr (MMAX >= 4) run_subtree<4, DMA>(c, v, st, list, u);
-                        break;
-                    default:
-                        if constexpr (MMAX >= 5) run_subtree<5, DMA>(c, v, st, list, u);
-                        break;
+                if constexpr (DMA == DMA_TWO) {
+                    if (potential) {
+                        walk_subtree<MMAX, DMA, PotLane>(c, pv, s, m, key);
+                        continue;
+                    }
                 }
-                const uint64_t r0 = (uint64_t)lex * fact_c(m);
-                const unsigned long long a = ((unsigned long long)u.min_t << 32) | (r0 + u.min_l);
-                const unsigned long long b =
-                    ((unsigned long long)(u.max_t1 - 1u) << 32) | (0xffffffffull - (r0 + u.max_l));
-                kmin = a < kmin ? a : kmin;
-                kmax = b > kmax ? b : kmax;
-                ksum += u.sum;
-                kfp += 2ull * (r0 * u.sum + u.s2) + u.sum;
+                walk_subtree<MMAX, DMA, BatchLane<uint32_t, DMA>>(c, v, s, m, key);
             }
         }
-        kmin = wave_min(kmin);
-        kmax = wave_max(kmax);
-        ksum = wave_sum(ksum);
-        kfp = wave_sum(kfp);
+        const unsigned long long kmin = wave_min(key.min), kmax = wave_max(key.max);
+        const unsigned long long ksum = wave_sum(key.sum), kfp = wave_sum(key.fp);
         if (lane == 0) {
             atomicMin(&acc[g].minkey, kmin);
             atomicMax(&acc[g].maxkey, kmax);

@@ -166,7 +166,7 @@ struct PotRule : GroupRule {
 };
 
 // Whether the rates allow the form for groups of n tasks.
-inline bool pot_rates(const Rates &r, int n) {
+__host__ __device__ inline bool pot_rates(const Rates &r, int n) {
     return !r.one_dma && r.p_h > 1 && r.p_h < (1u << r.q_log2) && (uint64_t)(n > 2 ? n - 2 : 0) * (r.p_d - 1) < 256;
 }
 

@@ -9,7 +9,7 @@ namespace tgo {
 
 // 0 = every instant and work amount fits the 32-bit path, 1 = 64-bit path,
 // TGO_ERANGE = a duration is negative or >= 2^40 ns.
-__device__ inline int classify_group(const tgo_task *t, int n, const Rates &r) {
+__device__ inline int classify_group(const tgo_task *t, int n, const Rates &r, uint64_t *bound = nullptr) {
     const uint64_t q = 1ull << r.q_log2;
     uint64_t mx = 0, sum = 0;
     for (int i = 0; i < n; ++i) {
@@ -21,6 +21,7 @@ __device__ inline int classify_group(const tgo_task *t, int n, const Rates &r) {
         mx = qd > mx ? qd : mx;
         sum += ceil_p(qh, r.p_h, r.inv_ph, r.c_ph) + (uint64_t)k + ceil_p(qd, r.p_d, r.inv_pd, r.c_pd);
     }
+    if (bound) *bound = sum + time_bound_slack(n);
     const uint64_t lim32 = 1ull << 31;
     return (mx < lim32 && sum + time_bound_slack(n) < lim32) ? 0 : 1;
 }
