@@ -961,7 +961,12 @@ __global__ __launch_bounds__(TR_THREADS) void train_fwd_bwd_kernel(
     for (int h = 0; h < 2; ++h) {
         f32x4 acc[TR_HALF][2];
         wmma_rows<SG_H>(bufB, h * TR_HALF, w3r, l, acc);
-        float sum[TR_HALF] = {0.f, 0.f, 0.f, 0.f};
+        // head: columns c and 16 + c together, then pairs of columns 1, 2, 4 and 8
+        // apart, whichever lanes hold them (the order of a sum decides how it rounds,
+        // and a score's last bit how the loss gradients round to bf16)
+        f32x4 sum[TR_HALF];
+#pragma unroll
+        for (int a = 0; a < TR_HALF; ++a) sum[a] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
             const f32x4 bias = columns(2, b), w4 = columns(3, b);
@@ -972,10 +977,10 @@ __global__ __launch_bounds__(TR_THREADS) void train_fwd_bwd_kernel(
                 q.x = f2bf_pair(fmaxf(acc[a][b][0] + bias[0], 0.f), fmaxf(acc[a][b][1] + bias[1], 0.f));
                 q.y = f2bf_pair(fmaxf(acc[a][b][2] + bias[2], 0.f), fmaxf(acc[a][b][3] + bias[3], 0.f));
                 *reinterpret_cast<uint2 *>(S + 16 * a * SG_H) = q;
-                sum[a] += __uint_as_float(q.x << 16) * w4[0];
-                sum[a] += __uint_as_float(q.x & 0xffff0000u) * w4[1];
-                sum[a] += __uint_as_float(q.y << 16) * w4[2];
-                sum[a] += __uint_as_float(q.y & 0xffff0000u) * w4[3];
+                sum[a][0] += __uint_as_float(q.x << 16) * w4[0];
+                sum[a][1] += __uint_as_float(q.x & 0xffff0000u) * w4[1];
+                sum[a][2] += __uint_as_float(q.y << 16) * w4[2];
+                sum[a][3] += __uint_as_float(q.y & 0xffff0000u) * w4[3];
                 if (H3keep) {
                     const int row = r0 + 64 * h + 16 * a + rl;
                     if (row < rows) *reinterpret_cast<uint2 *>(H3keep + (int64_t)row * SG_H + c0 + 16 * b) = q;
@@ -984,7 +989,7 @@ __global__ __launch_bounds__(TR_THREADS) void train_fwd_bwd_kernel(
         }
 #pragma unroll
         for (int a = 0; a < TR_HALF; ++a) {
-            float v = sum[a];
+            float v = (sum[a][0] + sum[a][1]) + (sum[a][2] + sum[a][3]);
             v += __shfl_xor(v, 16);
             v += __shfl_xor(v, 32);
             if (l < 16) part[w][64 * h + 16 * a + l] = v;
