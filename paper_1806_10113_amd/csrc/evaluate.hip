@@ -24,21 +24,11 @@ constexpr int HEU_WAVES = 4;  // groups per block of the heuristic, one wave eac
 // decided by one thread, and as many idle ones of the other width: 1,000,003
 // orderings of 16 tasks in 146 us; now 81, and 62 in the potential form).
 template <typename TT>
-__global__ __launch_bounds__(EV_THREADS) void evaluate_kernel(const tgo_task *__restrict__ tasks,
-                                                              int n, Rates r,
-                                                              const uint8_t *__restrict__ orders,
-                                                              int64_t m, int64_t *out) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int MODE = sizeof(TT) == 4 ? 0 : 1;
+__device__ __forceinline__ void evaluate_rows(const tgo_task *__restrict__ tasks, int n, const Rates &r,
+                                              const uint8_t *__restrict__ orders, int64_t m, int64_t *out,
+                                              unsigned char *smem) {
     __shared__ OrderTables<TT> ot;
-    const int mode = __builtin_amdgcn_readfirstlane(classify_group_wave(tasks, n, r, threadIdx.x & 63));
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    if (mode < 0) {
-        if (MODE == 0)
-            for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) out[i] = mode;
-        return;
-    }
-    if (mode != MODE) return;
     const bool potential = order_tables(ot, tasks, n, r);  // every wave writes the same
     __syncthreads();
     const auto v = ot.template view<EV_THREADS>(reinterpret_cast<TT *>(smem) + threadIdx.x);
@@ -64,6 +54,34 @@ __global__ __launch_bounds__(EV_THREADS) void evaluate_kernel(const tgo_task *__
     }
 }
 
+// ONLY: the time width it runs for (0: 32 bits, 1: 64; errors go with 0), or -1: both.
+template <int ONLY>
+__global__ __launch_bounds__(EV_THREADS) void evaluate_kernel(const tgo_task *__restrict__ tasks,
+                                                              int n, Rates r,
+                                                              const uint8_t *__restrict__ orders,
+                                                              int64_t m, int64_t *out) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int mode = __builtin_amdgcn_readfirstlane(classify_group_wave(tasks, n, r, threadIdx.x & 63));
+    if (mode < 0) {
+        if (ONLY != 1)
+            for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m;
+                 i += (int64_t)gridDim.x * blockDim.x)
+                out[i] = mode;
+        return;
+    }
+    if constexpr (ONLY != 1)
+        if (mode == 0) evaluate_rows<uint32_t>(tasks, n, r, orders, m, out, smem);
+    if constexpr (ONLY != 0)
+        if (mode == 1) evaluate_rows<uint64_t>(tasks, n, r, orders, m, out, smem);
+}
+
+// Rows up to which both widths share a launch: the second width's idle launch
+// costs 3 us, its code a part of the resident blocks, which two blocks per CU do
+// not miss.  One launch against two in us, 16 tasks: 500 rows 13.4 / 14.8, 65,536
+// 13.9 / 15.7, 131,072 14.8 / 17.0, 262,144 27.6 / 21.5 (64-bit time, 131,072:
+// 17.5 / 19.6, 262,144: 32.8 / 35.0); 5 tasks, 3 rows: 10.7 / 13.4.
+constexpr int64_t EV_BOTH = 131072;
+
 int launch_evaluate(const Rates &r, const tgo_task *d_tasks, int n, const uint8_t *d_orders,
                     int64_t m, int64_t *d_out, hipStream_t st) {
     if (m == 0) return TGO_OK;
@@ -74,12 +92,16 @@ int launch_evaluate(const Rates &r, const tgo_task *d_tasks, int n, const uint8_
         const uint32_t b = resident_blocks(k, EV_THREADS, shm);
         return dim3((uint32_t)std::min<int64_t>(want, b ? b * rounds : 8192));
     };
-    const void *k32 = reinterpret_cast<const void *>(&evaluate_kernel<uint32_t>);
-    const void *k64 = reinterpret_cast<const void *>(&evaluate_kernel<uint64_t>);
-    hipLaunchKernelGGL(evaluate_kernel<uint32_t>, grid(k32, shm32, EV_ROUNDS), dim3(EV_THREADS), shm32, st,
-                       d_tasks, n, r, d_orders, m, d_out);
-    hipLaunchKernelGGL(evaluate_kernel<uint64_t>, grid(k64, shm64, EV_ROUNDS), dim3(EV_THREADS), shm64, st,
-                       d_tasks, n, r, d_orders, m, d_out);
+    auto launch = [&](auto *kernel, size_t shm) {
+        hipLaunchKernelGGL(kernel, grid(reinterpret_cast<const void *>(kernel), shm, EV_ROUNDS), dim3(EV_THREADS), shm,
+                           st, d_tasks, n, r, d_orders, m, d_out);
+    };
+    if (m <= EV_BOTH) {
+        launch(&evaluate_kernel<-1>, shm64);
+    } else {
+        launch(&evaluate_kernel<0>, shm32);
+        launch(&evaluate_kernel<1>, shm64);
+    }
     TGO_HIP(hipGetLastError());
     return TGO_OK;
 }

@@ -44,3 +44,19 @@ def test_evaluate_rows_at_any_alignment(dev, n):
     reps = 4000  # 1.2 million rows: every lane takes several
     got = tgo.evaluate(t, torch.as_tensor(rows).to(dev).repeat(reps, 1)).cpu().numpy()
     assert np.array_equal(got, np.tile(np.array(want[:len(rows)]), reps))
+
+
+@pytest.mark.parametrize("rows", [1, 256, 257, 131072, 131073])
+@pytest.mark.parametrize("scale", [1, 300, -1])
+def test_one_launch_or_two(dev, rows, scale):
+    """Row counts around a block and around the last that both time widths share
+    a launch for: 32-bit time, 64-bit time (tasks of seconds) and a group in error."""
+    import torch
+    from paper_1806_10113_amd import tgo
+    rng = np.random.default_rng(rows)
+    tasks = W.batch_groups(1, 9, 9, 7, per_task_label=True).tasks * scale
+    few = np.array([rng.permutation(9) for _ in range(min(rows, 97))], dtype=np.uint8)
+    orders = np.resize(few, (rows, 9))
+    got = tgo.evaluate(torch.as_tensor(tasks).to(dev), torch.as_tensor(orders).to(dev)).cpu().numpy()
+    want = [M.simulate(tasks, o, M.DEFAULT) if scale > 0 else tgo.TGO_ERANGE for o in few]
+    assert np.array_equal(got, np.resize(np.array(want), rows))
