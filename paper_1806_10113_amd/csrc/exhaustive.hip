@@ -15,14 +15,41 @@
 
 namespace tgo {
 
+// Whether a group that fits the potential form also gains by it (32-bit time, one
+// wave, lane i: task i).  The chain form's cost is the DtHs that end before the
+// last HtD.  From 12 tasks on (five waves of the potential form per SIMD, seven of
+// the chain form) it is the faster one where the DtHs together take much longer
+// than the HtDs.  120 groups of 12, ratio of the two sums (overlapped rates) and
+// time of the chain form over that of the potential form: up to 0.95 1.25 to 1.28
+// (at least 1.00), 1.0 to 1.2 1.15 (1.00), 1.2 to 1.65 1.04 (0.91), 1.7 to 2.1 1.01
+// (0.86), above 0.95 (0.85).  The line lies at 5/4.  Groups of 11: 1.18 to 1.4 over
+// the same rates, whatever the ratio.
+__device__ __forceinline__ bool potential_gains(const tgo_task *__restrict__ tasks, int n, const Rates &r, int lane) {
+    if (n < 12) return true;
+    uint32_t h = 0, d = 0;
+    if (lane < n) {
+        Quad<uint32_t> H;
+        DRec<uint32_t> D;
+        table_entry<uint32_t>(tasks[lane], r, &H, &D);
+        h = H.hp;
+        d = D.dp;
+    }
+    for (int m = 8; m >= 1; m >>= 1) {  // lanes 0 to 15 hold the tasks
+        h += __shfl_xor(h, m);
+        d += __shfl_xor(d, m);
+    }
+    return 4ull * d <= 5ull * h;
+}
+
 // The group's time path, decided once before the enumeration: 0 = 32-bit,
-// 1 = 64-bit, 2 = 32-bit in the potential form (if `potential` and the group's
+// 1 = 64-bit, 2 = 32-bit in the potential form (if `potential`, and the group's
 // potentials fit), or a negative error code (classify_group).
 __global__ __launch_bounds__(64) void exhaustive_classify(const tgo_task *__restrict__ tasks, int n, Rates r,
                                                           bool potential, int *mode, ExAcc *acc) {
     uint64_t bound;
-    const int m = classify_group_wave(tasks, n, r, threadIdx.x, &bound);
-    if (threadIdx.x == 0) *mode = potential && m == 0 && potential_fits<uint32_t>(bound, r) ? 2 : m;
+    int m = classify_group_wave(tasks, n, r, threadIdx.x, &bound);
+    if (potential && m == 0 && potential_fits<uint32_t>(bound, r) && potential_gains(tasks, n, r, threadIdx.x)) m = 2;
+    if (threadIdx.x == 0) *mode = m;
     exacc_init(acc, threadIdx.x);
 }
 
@@ -86,9 +113,9 @@ uint32_t resident_blocks(const void *kern, int threads, size_t shm) {
 }
 
 // The walk that also has the potential form (PotRule): the deepest, which the
-// groups of 11 and more take.  There the form takes 1782 / 1712 / 1744 us where the
-// chain form takes 2165 / 2011 / 2551 (three groups of 12); at depth 4 it gained
-// nothing, and the groups below 11, done in 60 us and less, would pay the launch
+// groups of 11 and more take, where it gains (potential_gains): 1782 / 1712 / 1744
+// us where the chain form takes 2165 / 2011 / 2551 (three groups of 12).  At depth
+// 4 it gained nothing, and the groups below 11, done in 60 us and less, would pay the launch
 // that finds nothing to do, 4.5 us, when theirs does not fit.
 constexpr int POT_M = 5;
 template <int M, bool STORE>

@@ -77,3 +77,29 @@ def test_first_group_that_takes_it(dev):
     rng = np.random.default_rng(11)
     for tasks in tasks_of(11, (2, 3, 3), rng)[1:3]:
         check(dev, tasks, tgo.Model(), M.DEFAULT, per_order=False)
+
+
+@pytest.mark.parametrize("swap", [False, True])
+def test_twelve_tasks_either_way(dev, monkeypatch, swap):
+    """From 12 tasks on the form depends on the DtHs' share of the transfers: the
+    same group with HtDs and DtHs exchanged takes one form and then the other."""
+    import torch
+    from paper_1806_10113_amd import tgo
+    tasks = W.single_group_mixed(12, 5)
+    tasks[:, 0] *= 2
+    if swap:
+        tasks = np.ascontiguousarray(tasks[:, ::-1])
+    s, _ = tgo.exhaustive(torch.as_tensor(tasks).to(dev), tgo.Model())
+    d = tgo.read_summary(s)
+    model = M.DEFAULT
+    assert d["status"] == 0 and d["count"] == math.factorial(12)
+    # a sample of ranks bounds the extremes, and the reported orderings attain them
+    lo = cmodel.exhaustive(tasks, model, stride=7919)
+    assert d["min_ns"] <= lo["min_ns"] and d["max_ns"] >= lo["max_ns"]
+    for key, rank in (("min_ns", "argmin_rank"), ("max_ns", "argmax_rank")):
+        one = cmodel.exhaustive(tasks, model, lo=int(d[rank]), hi=int(d[rank]) + 1)
+        assert one["min_ns"] == d[key]
+    # exchanging the walk's depth exchanges the kernel, not the answer
+    monkeypatch.setenv("TGO_EXHAUSTIVE_M", "4")
+    s4, _ = tgo.exhaustive(torch.as_tensor(tasks).to(dev), tgo.Model())
+    assert tgo.read_summary(s4) == d
