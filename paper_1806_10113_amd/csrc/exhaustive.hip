@@ -18,27 +18,27 @@ namespace tgo {
 // Whether a group that fits the potential form also gains by it (32-bit time, one
 // wave, lane i: task i).  The chain form's cost is the DtHs that end before the
 // last HtD.  From 12 tasks on (five waves of the potential form per SIMD, seven of
-// the chain form) it is the faster one where the DtHs together take much longer
-// than the HtDs.  120 groups of 12, ratio of the two sums (overlapped rates) and
-// time of the chain form over that of the potential form: up to 0.95 1.25 to 1.28
-// (at least 1.00), 1.0 to 1.2 1.15 (1.00), 1.2 to 1.65 1.04 (0.91), 1.7 to 2.1 1.01
-// (0.86), above 0.95 (0.85).  The line lies at 5/4.  Groups of 11: 1.18 to 1.4 over
-// the same rates, whatever the ratio.
+// the chain form) it is the faster one where the DtHs (at the overlapped rate) take
+// longer together than the HtDs and the kernels, which precede them.  113 groups of
+// 12 at six pairs of rates, D / (H + K) and time of the chain form over that of the
+// potential form, mean and least: up to 0.6 1.35 (1.20), 0.8 1.16 (1.01), 0.9 1.06
+// (1.00), 1.0 1.03 (0.94); above, 1.1 0.99 (0.92), 1.3 0.96 (0.88), more 0.92
+// (0.85).  Groups of 11: 1.18 to 1.4 on average over the same rates, always on.
 __device__ __forceinline__ bool potential_gains(const tgo_task *__restrict__ tasks, int n, const Rates &r, int lane) {
     if (n < 12) return true;
-    uint32_t h = 0, d = 0;
+    uint32_t lead = 0, d = 0;
     if (lane < n) {
         Quad<uint32_t> H;
         DRec<uint32_t> D;
         table_entry<uint32_t>(tasks[lane], r, &H, &D);
-        h = H.hp;
+        lead = H.hp + H.k;
         d = D.dp;
     }
-    for (int m = 8; m >= 1; m >>= 1) {  // lanes 0 to 15 hold the tasks
-        h += __shfl_xor(h, m);
+    for (int m = 8; m >= 1; m >>= 1) {  // lanes 0 to 15 hold the tasks; both sums are below 2^31
+        lead += __shfl_xor(lead, m);
         d += __shfl_xor(d, m);
     }
-    return 4ull * d <= 5ull * h;
+    return d <= lead;
 }
 
 // The group's time path, decided once before the enumeration: 0 = 32-bit,
