@@ -104,8 +104,8 @@ __device__ __forceinline__ void block_exscan2(uint32_t v, uint32_t w, uint2 *wav
 }
 
 // One block: per-group status and tile counts, exclusive scan into tile_off,
-// accumulators reset, tile counters reset.  waves: the batch kernel's, which take the first `waves` tiles by their own
-// number; the counter hands out the rest.
+// accumulators reset, tile counters reset.  waves: the batch kernel's, which take
+// the first `waves` tiles by their own number; the counter hands out the rest.
 __global__ __launch_bounds__(1024) void batch_prepare(const tgo_task *__restrict__ tasks,
                                                       const int32_t *__restrict__ offs, int G,
                                                       Rates r, BatchCfg cfg, int wide_tiles, int max_n, GroupAcc *acc,

@@ -370,8 +370,9 @@ void enum_kernel(const tgo_task *__restrict__ tasks, int n, Rates r, typename Ru
 
 constexpr int EX_FIN_THREADS = 1024;
 
-// One block: the group's result from the accumulators (32-bit path) or from the block partials (64-bit path).  decode(rank) gives an
-// ordering, one task per nibble.
+// One block: the group's result from the accumulators (32-bit path) or from the
+// block partials (64-bit path).  decode(rank) gives an ordering, one task per
+// nibble.
 template <typename Decode>
 __device__ __forceinline__ void finalize_block(const Partial *__restrict__ parts, int nparts, int n, uint64_t count,
                                                const ExAcc *__restrict__ acc, int mode, Decode decode,

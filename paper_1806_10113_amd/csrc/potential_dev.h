@@ -3,9 +3,9 @@
 //
 // A lane's queue holds, per placed position, G_i and E_i of its DtH and, in a
 // byte, the rounding slack of the DtHs before it.  What a window needs of the DtH
-// before its cursor it reads after the search, so the state saved at each level of the walk is
-// seven words (the chain form's is ten) and the search itself is one LDS read
-// and one comparison per DtH.
+// before its cursor it reads after the search, so the state saved at each level of
+// the walk is seven words (the chain form's is ten) and the search itself is one
+// LDS read and one comparison per DtH.
 //
 // A DtH that runs when the last HtD ends at t has moved p_dth (t - S_i) of its
 // work.  With P_i = sum_{s<=i} dp_s, the time the DtH engine has stood idle

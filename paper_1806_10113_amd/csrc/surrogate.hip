@@ -1488,7 +1488,7 @@ struct tgo_surrogate {
     // fragment order (frag_at)
     float *p = nullptr, *m = nullptr, *v = nullptr;
     uint16_t *W1 = nullptr, *W2 = nullptr, *W2t = nullptr, *W3 = nullptr, *W3t = nullptr;
-    // training batch, transposed [feature][row] with row pitch max_rows
+    // training batch, transposed [feature][position] (row_position), pitch ldt
     uint16_t *Xt = nullptr, *H1t = nullptr, *H2t = nullptr, *G1t = nullptr, *G2t = nullptr, *G3t = nullptr;
     // kept by tgo_surrogate_grad for inspection: h3 [row][256] and scores
     uint16_t *H3 = nullptr;
