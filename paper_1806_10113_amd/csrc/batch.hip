@@ -43,7 +43,12 @@ struct BatchCfg {
 // Largest group whose potential form fits the queue of the chain form: 8 bytes and,
 // but for the last slot, a slack byte per slot.
 constexpr int BT_POT_N = 10;
-static_assert(8 * BT_POT_N + BT_POT_N - 1 <= (int)sizeof(Slot<uint32_t>) * BT_MAX_N, "the lane's queue");
+// The queues of a wave's lanes are a region of their own, slots and slack bytes in
+// columns of 64: the waves of a block are on different groups, each in its group's
+// form, so what one form keeps in a wave's region is nothing in the other's place.
+constexpr int BT_LANES = 64;
+constexpr size_t BT_WAVE_QUEUE = sizeof(Slot<uint32_t>) * BT_LANES * BT_MAX_N;
+static_assert(PotRule::lane_bytes<uint32_t>(BT_POT_N) * BT_LANES <= BT_WAVE_QUEUE, "slots, then slack bytes");
 
 struct GroupAcc {
     unsigned long long minkey;  // (T << 32) | rank, smallest
@@ -249,16 +254,17 @@ __global__ __launch_bounds__(BT_THREADS) __attribute__((amdgpu_waves_per_eu(DMA 
     __shared__ DRec<uint32_t> Dt[BT_WAVES][MAXN];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    View<uint32_t, 1, BT_THREADS> v;
+    unsigned char *const region = smem + BT_WAVE_QUEUE * w;
+    View<uint32_t, 1, BT_LANES> v;
     v.H = Ht[w];
     v.D = Dt[w];
-    v.Q = reinterpret_cast<Slot<uint32_t> *>(smem) + threadIdx.x;
+    v.Q = reinterpret_cast<Slot<uint32_t> *>(region) + lane;
     __shared__ PotSlot origin;
-    PotView<BT_THREADS> pv;
+    PotView<BT_LANES> pv;
     pv.H = Ht[w];
     pv.D = Dt[w];
-    pv.Q = reinterpret_cast<PotSlot *>(smem) + threadIdx.x;
-    pv.S = smem + sizeof(PotSlot) * BT_THREADS * BT_POT_N + threadIdx.x;
+    pv.Q = reinterpret_cast<PotSlot *>(region) + lane;
+    pv.S = region + sizeof(PotSlot) * BT_LANES * BT_POT_N + lane;
     pv.zero = &origin;
     if constexpr (DMA == DMA_TWO) {
         if (threadIdx.x == 0) origin.g = origin.e = 0;
@@ -282,10 +288,10 @@ __global__ __launch_bounds__(BT_THREADS) __attribute__((amdgpu_waves_per_eu(DMA 
             if (potential) PotRule::entry<uint32_t>(tasks[base + lane], r, &Ht[w][lane], &Dt[w][lane]);
             else table_entry<uint32_t>(tasks[base + lane], r, &Ht[w][lane], &Dt[w][lane]);
         }
-        if (potential) pv.Q[(n - 1) * BT_THREADS].g = POT_INF;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (potential) pv.Q[(n - 1) * BT_LANES].g = POT_INF;
         const uint32_t S = subtrees_of(n, m);
         const uint32_t s0 = (tile - tile_off[g]) * per_tile;
         Ctx c;
@@ -496,7 +502,7 @@ static int enqueue_batch(tgo_plan *p, const BatchCfg &cfg, const tgo_task *d_tas
     int mmax = 1;
     for (int n = 1; n <= BT_MAX_N; ++n) mmax = std::max(mmax, (int)cfg.m[n]);
     // no kernel-completion queue with one DMA engine
-    const size_t shm = p->r.one_dma ? 0 : sizeof(Slot<uint32_t>) * BT_THREADS * BT_MAX_N;
+    const size_t shm = p->r.one_dma ? 0 : BT_WAVE_QUEUE * BT_WAVES;
     const dim3 grid(cfg.blocks), block(BT_THREADS);
     if (p->r.one_dma) {
         if (mmax <= 3)
