@@ -57,7 +57,7 @@ struct GroupAcc {
     unsigned long long fp;      // sum of (2 rank + 1) T mod 2^64
     int32_t status, n;
     int32_t wide;               // 1: the group runs the 64-bit path (per-tile partials)
-    int32_t potential;          // 1: its walk takes the potential form
+    int32_t pad;
 };
 
 struct BatchHdr {
@@ -74,6 +74,16 @@ struct BatchHdr {
 constexpr int BT_WIDE_M = 3;              // positions enumerated per lane (64-bit path)
 constexpr size_t BT_WIDE_BUDGET = 64u << 20;  // bytes of partials per plan
 constexpr int BT_WIDE_TILES_MAX = 256;
+
+// The wide tile offsets carry in their top bit whether the group's walk takes the
+// potential form.  (The accumulators would be the natural place, but a load from the
+// line that every tile's atomics go to makes them twice as slow: two groups of 12,
+// 124,740 tiles, 12.1 ms where 5.3 suffice.)
+constexpr uint32_t BT_POTENTIAL = 1u << 31;
+static_assert(BT_WIDE_BUDGET / sizeof(Partial) < BT_POTENTIAL, "wide tiles of a plan");
+__device__ __forceinline__ uint32_t wide_off(const uint32_t *__restrict__ wtile_off, int g) {
+    return wtile_off[g] & ~BT_POTENTIAL;
+}
 
 __device__ __forceinline__ uint32_t subtrees_of(int n, int m) {
     return (uint32_t)(fact_c(n) / fact_c(m));
@@ -121,10 +131,10 @@ __global__ __launch_bounds__(1024) void batch_prepare(const tgo_task *__restrict
     const uint32_t per_tile = 64u * (uint32_t)cfg.lane_mult;
     for (int base = 0; base < G; base += 1024) {
         const int g = base + threadIdx.x;
-        uint32_t tiles = 0, wtiles = 0;
+        uint32_t tiles = 0, wtiles = 0, potential = 0;
         if (g < G) {
             const int n = offs[g + 1] - offs[g];
-            int st = 0, wide = 0, potential = 0;
+            int st = 0, wide = 0;
             if (n < 1 || n > max_n) {
                 st = TGO_EINVAL;
             } else {
@@ -132,7 +142,8 @@ __global__ __launch_bounds__(1024) void batch_prepare(const tgo_task *__restrict
                 const int c = classify_group(tasks + offs[g], n, r, &bound);
                 st = c < 0 ? c : 0;
                 wide = c == 1;
-                potential = c == 0 && n <= BT_POT_N && pot_rates(r, n) && potential_fits<uint32_t>(bound, r);
+                if (c == 0 && n <= BT_POT_N && pot_rates(r, n) && potential_fits<uint32_t>(bound, r))
+                    potential = BT_POTENTIAL;
             }
             GroupAcc a;
             a.minkey = ~0ull;
@@ -142,7 +153,7 @@ __global__ __launch_bounds__(1024) void batch_prepare(const tgo_task *__restrict
             a.status = st;
             a.n = n;
             a.wide = wide;
-            a.potential = potential;
+            a.pad = 0;
             acc[g] = a;
             if (st == 0 && !wide) tiles = (subtrees_of(n, cfg.m[n]) + per_tile - 1) / per_tile;
             if (st == 0 && wide) wtiles = wide_tiles_of(n, wide_tiles);
@@ -151,7 +162,7 @@ __global__ __launch_bounds__(1024) void batch_prepare(const tgo_task *__restrict
         block_exscan2(tiles, wtiles, wave_sum, &ex, &total);
         if (g < G) {
             tile_off[g] = carry.x + ex.x;
-            wtile_off[g] = carry.y + ex.y;
+            wtile_off[g] = (carry.y + ex.y) | potential;
         }
         carry.x += total.x;
         carry.y += total.y;
@@ -248,7 +259,7 @@ __global__ __launch_bounds__(BT_THREADS) __attribute__((amdgpu_waves_per_eu(DMA 
                                                            const int32_t *__restrict__ offs, int G,
                                                            Rates r, BatchCfg cfg, GroupAcc *acc,
                                                            const uint32_t *__restrict__ tile_off,
-                                                           BatchHdr *hdr) {
+                                                           const uint32_t *__restrict__ wtile_off, BatchHdr *hdr) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ Quad<uint32_t> Ht[BT_WAVES][MAXN];
     __shared__ DRec<uint32_t> Dt[BT_WAVES][MAXN];
@@ -283,7 +294,7 @@ __global__ __launch_bounds__(BT_THREADS) __attribute__((amdgpu_waves_per_eu(DMA 
         const int base = offs[g];
         const int n = offs[g + 1] - base;
         const int m = cfg.m[n];
-        const bool potential = DMA == DMA_TWO && acc[g].potential;
+        const bool potential = DMA == DMA_TWO && (wtile_off[g] & BT_POTENTIAL) != 0;
         if (lane < n) {
             if (potential) PotRule::entry<uint32_t>(tasks[base + lane], r, &Ht[w][lane], &Dt[w][lane]);
             else table_entry<uint32_t>(tasks[base + lane], r, &Ht[w][lane], &Dt[w][lane]);
@@ -343,10 +354,10 @@ __global__ __launch_bounds__(BT_THREADS) void batch_wide_kernel(const tgo_task *
     v.Q = reinterpret_cast<Slot<TT> *>(smem) + threadIdx.x;
     const uint32_t total = hdr->total_wide, waves = gridDim.x * BT_WAVES;
     for (uint32_t tile = blockIdx.x * BT_WAVES + w; tile < total; tile = next_tile(&hdr->next_wide, total, waves, lane)) {
-        int lo = 0, hi = G;  // wtile_off[lo] <= tile < wtile_off[hi]
+        int lo = 0, hi = G;  // wide_off(lo) <= tile < wide_off(hi)
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
-            if (wtile_off[mid] <= tile) lo = mid; else hi = mid;
+            if (wide_off(wtile_off, mid) <= tile) lo = mid; else hi = mid;
         }
         const int g = lo;
         const int base = offs[g];
@@ -358,7 +369,7 @@ __global__ __launch_bounds__(BT_THREADS) void batch_wide_kernel(const tgo_task *
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         const uint32_t S = subtrees_of(n, m);
         const uint32_t W = wide_tiles_of(n, wide_tiles);
-        const uint32_t t = tile - wtile_off[g];
+        const uint32_t t = tile - wide_off(wtile_off, g);
         const uint32_t s0 = (uint32_t)((uint64_t)S * t / W), s1 = (uint32_t)((uint64_t)S * (t + 1) / W);
         Ctx c;
         c.n = n;
@@ -408,8 +419,10 @@ __global__ __launch_bounds__(256) void batch_finalize(const GroupAcc *__restrict
     const GroupAcc a = acc[g];
     Partial p = {};
     if (a.status == 0 && a.wide) {
-        p = parts[wtile_off[g]];
-        for (uint32_t i = wtile_off[g] + 1; i < wtile_off[g + 1]; ++i) {
+        const uint32_t end = wide_off(wtile_off, g + 1);
+        uint32_t i = wide_off(wtile_off, g);
+        p = parts[i];
+        for (++i; i < end; ++i) {
             const Partial q = parts[i];
             merge_min(p.min_t, p.min_r, q.min_t, q.min_r);
             merge_max(p.max_t, p.max_r, q.max_t, q.max_r);
@@ -507,23 +520,23 @@ static int enqueue_batch(tgo_plan *p, const BatchCfg &cfg, const tgo_task *d_tas
     if (p->r.one_dma) {
         if (mmax <= 3)
             hipLaunchKernelGGL((batch_kernel<DMA_ONE, 3>), grid, block, shm, st, d_tasks, d_offs, G, p->r, cfg,
-                               p->acc, p->tile_off, p->hdr);
+                               p->acc, p->tile_off, p->wtile_off, p->hdr);
         else if (mmax == 4)
             hipLaunchKernelGGL((batch_kernel<DMA_ONE, 4>), grid, block, shm, st, d_tasks, d_offs, G, p->r, cfg,
-                               p->acc, p->tile_off, p->hdr);
+                               p->acc, p->tile_off, p->wtile_off, p->hdr);
         else
             hipLaunchKernelGGL((batch_kernel<DMA_ONE, 5>), grid, block, shm, st, d_tasks, d_offs, G, p->r, cfg,
-                               p->acc, p->tile_off, p->hdr);
+                               p->acc, p->tile_off, p->wtile_off, p->hdr);
     } else {
         if (mmax <= 3)
             hipLaunchKernelGGL((batch_kernel<DMA_TWO, 3>), grid, block, shm, st, d_tasks, d_offs, G, p->r, cfg,
-                               p->acc, p->tile_off, p->hdr);
+                               p->acc, p->tile_off, p->wtile_off, p->hdr);
         else if (mmax == 4)
             hipLaunchKernelGGL((batch_kernel<DMA_TWO, 4>), grid, block, shm, st, d_tasks, d_offs, G, p->r, cfg,
-                               p->acc, p->tile_off, p->hdr);
+                               p->acc, p->tile_off, p->wtile_off, p->hdr);
         else
             hipLaunchKernelGGL((batch_kernel<DMA_TWO, 5>), grid, block, shm, st, d_tasks, d_offs, G, p->r, cfg,
-                               p->acc, p->tile_off, p->hdr);
+                               p->acc, p->tile_off, p->wtile_off, p->hdr);
     }
     // the 64-bit path (its blocks return at once when no group needs it)
     const size_t wshm = sizeof(Slot<uint64_t>) * BT_THREADS * BT_MAX_N;
