@@ -12,18 +12,41 @@
 namespace tgo {
 
 constexpr int EV_THREADS = 256;
-// Blocks per launch, in units of the resident ones: 1,000,003 orderings of 16
-// tasks in 91 / 87 / 91 / 92 / 95 us with 1 / 2 / 3 / 4 / 8 (chain form).
+// Blocks per launch, in units of the resident ones.  A block's tables cost what some
+// rows do: groups of up to EV_FEW tasks take one round of blocks with the same number
+// of rows each, larger ones two rounds, whose blocks finish at different times.
+// 1,000,003 / 2,000,000 rows in us, one even round, one round, two rounds: 3 tasks
+// 16.4 / 24.9, 17.6 / 23.7, 22.3 / 28.0; 5 tasks 20.9 / 34.4, 22.0 / 32.0, 26.1 / 35.0;
+// 12 tasks 39 / 70, 33 / 61, 38 / 61; 16 tasks 50 / 127, 61 / 114, 54 / 98 (a kernel per
+// width, NARROW).
 constexpr uint32_t EV_ROUNDS = 2;
+constexpr int EV_FEW = 5;
 constexpr int HEU_WAVES = 4;  // groups per block of the heuristic, one wave each
+
+// A row of n <= N bytes, as nibbles: N loads (past the row its last byte again), in
+// flight together.  seen: bit of every value, high: all of their bits.
+template <int N>
+__device__ __forceinline__ void read_row(const uint8_t *o, int n, uint64_t *perm, uint32_t *seen, uint32_t *high) {
+    uint32_t b[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) b[j] = o[j < n ? j : n - 1];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        *perm |= (uint64_t)(b[j] & 15u) << (4 * j);
+        *seen |= j < n ? 1u << (b[j] & 15u) : 0u;
+        *high |= b[j];
+    }
+}
 
 // One lane per given ordering.  Bound by VALU issue over divergent windows.
 // The row is read once, all of its bytes in flight together, checked and kept
 // as nibbles; blocks stride over the rows so that the time path and the tables
 // are set up by few blocks (a block per 256 rows, each with the time path
 // decided by one thread, and as many idle ones of the other width: 1,000,003
-// orderings of 16 tasks in 146 us; now 81, and 62 in the potential form).
-template <typename TT>
+// orderings of 16 tasks in 146 us; now 81, and 57 in the potential form).  NARROW: short
+// rows are read by fewer loads (3 tasks, 1,000,003 rows: 25.9 us with 16 loads and two
+// rounds of blocks in two launches, 13.7 as now).
+template <typename TT, bool NARROW>
 __device__ __forceinline__ void evaluate_rows(const tgo_task *__restrict__ tasks, int n, const Rates &r,
                                               const uint8_t *__restrict__ orders, int64_t m, int64_t *out,
                                               unsigned char *smem) {
@@ -34,16 +57,22 @@ __device__ __forceinline__ void evaluate_rows(const tgo_task *__restrict__ tasks
     const auto v = ot.template view<EV_THREADS>(reinterpret_cast<TT *>(smem) + threadIdx.x);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) {
         const uint8_t *o = orders + i * n;
-        uint32_t b[MAXN];
-#pragma unroll
-        for (int j = 0; j < MAXN; ++j) b[j] = o[j < n ? j : n - 1];
         uint64_t perm = 0;
         uint32_t seen = 0, high = 0;
+        if constexpr (NARROW) {
+            if (n <= 4) read_row<4>(o, n, &perm, &seen, &high);
+            else if (n <= 8) read_row<8>(o, n, &perm, &seen, &high);
+            else read_row<MAXN>(o, n, &perm, &seen, &high);
+        } else {  // read_row<MAXN>, written out: called, 64-bit time took 2 % more
+            uint32_t b[MAXN];
 #pragma unroll
-        for (int j = 0; j < MAXN; ++j) {
-            perm |= (uint64_t)(b[j] & 15u) << (4 * j);
-            seen |= j < n ? 1u << (b[j] & 15u) : 0u;
-            high |= b[j];
+            for (int j = 0; j < MAXN; ++j) b[j] = o[j < n ? j : n - 1];
+#pragma unroll
+            for (int j = 0; j < MAXN; ++j) {
+                perm |= (uint64_t)(b[j] & 15u) << (4 * j);
+                seen |= j < n ? 1u << (b[j] & 15u) : 0u;
+                high |= b[j];
+            }
         }
         // a permutation: no value above 15 and every one of the n below
         if (high > 15u || seen != (1u << n) - 1u) {
@@ -70,16 +99,18 @@ __global__ __launch_bounds__(EV_THREADS) void evaluate_kernel(const tgo_task *__
         return;
     }
     if constexpr (ONLY != 1)
-        if (mode == 0) evaluate_rows<uint32_t>(tasks, n, r, orders, m, out, smem);
+        if (mode == 0) evaluate_rows<uint32_t, ONLY == -1>(tasks, n, r, orders, m, out, smem);
     if constexpr (ONLY != 0)
-        if (mode == 1) evaluate_rows<uint64_t>(tasks, n, r, orders, m, out, smem);
+        if (mode == 1) evaluate_rows<uint64_t, ONLY == -1>(tasks, n, r, orders, m, out, smem);
 }
 
 // Rows up to which both widths share a launch: the second width's idle launch
 // costs 3 us, its code a part of the resident blocks, which two blocks per CU do
 // not miss.  One launch against two in us, 16 tasks: 500 rows 13.4 / 14.8, 65,536
 // 13.9 / 15.7, 131,072 14.8 / 17.0, 262,144 27.6 / 21.5 (64-bit time, 131,072:
-// 17.5 / 19.6, 262,144: 32.8 / 35.0); 5 tasks, 3 rows: 10.7 / 13.4.
+// 17.5 / 19.6, 262,144: 32.8 / 35.0); 5 tasks, 3 rows: 10.7 / 13.4.  Groups of up to
+// EV_FEW tasks, whose queues leave seven blocks per CU in either width, share it
+// whatever the rows.
 constexpr int64_t EV_BOTH = 131072;
 
 int launch_evaluate(const Rates &r, const tgo_task *d_tasks, int n, const uint8_t *d_orders,
@@ -88,15 +119,18 @@ int launch_evaluate(const Rates &r, const tgo_task *d_tasks, int n, const uint8_
     const int64_t want = (m + EV_THREADS - 1) / EV_THREADS;
     const size_t shm32 = order_queue_bytes<uint32_t>(n, EV_THREADS);
     const size_t shm64 = order_queue_bytes<uint64_t>(n, EV_THREADS);
-    auto grid = [want](const void *k, size_t shm, uint32_t rounds) {
-        const uint32_t b = resident_blocks(k, EV_THREADS, shm);
-        return dim3((uint32_t)std::min<int64_t>(want, b ? b * rounds : 8192));
+    auto grid = [want, n](const void *k, size_t shm) {
+        const int64_t b = resident_blocks(k, EV_THREADS, shm);
+        if (b == 0) return dim3((uint32_t)std::min<int64_t>(want, 8192));
+        if (n > EV_FEW) return dim3((uint32_t)std::min<int64_t>(want, b * EV_ROUNDS));
+        const int64_t rows = (want + b - 1) / b;  // per thread
+        return dim3((uint32_t)((want + rows - 1) / rows));
     };
     auto launch = [&](auto *kernel, size_t shm) {
-        hipLaunchKernelGGL(kernel, grid(reinterpret_cast<const void *>(kernel), shm, EV_ROUNDS), dim3(EV_THREADS), shm,
-                           st, d_tasks, n, r, d_orders, m, d_out);
+        hipLaunchKernelGGL(kernel, grid(reinterpret_cast<const void *>(kernel), shm), dim3(EV_THREADS), shm, st,
+                           d_tasks, n, r, d_orders, m, d_out);
     };
-    if (m <= EV_BOTH) {
+    if (m <= EV_BOTH || n <= EV_FEW) {
         launch(&evaluate_kernel<-1>, shm64);
     } else {
         launch(&evaluate_kernel<0>, shm32);
