@@ -225,10 +225,19 @@ __device__ __forceinline__ void write_summary(const Partial &o, int status, int 
 // block reduction reuses the queue's memory at the end.
 template <class Rule, typename TT>
 __host__ __device__ constexpr size_t enum_tables_bytes(int n) {
-    return (size_t)n * (sizeof(Quad<TT>) + sizeof(DRec<TT>)) + Rule::lds_bytes(n);
+    return ((size_t)n * (sizeof(Quad<TT>) + sizeof(DRec<TT>)) + Rule::lds_bytes(n) + 15) & ~size_t(15);
+}
+// The queue's slots and the reduction's partials lie at their alignment for every n.
+template <class Rule, typename TT>
+constexpr bool enum_queue_aligned() {
+    for (int n = 1; n <= MAXN; ++n)
+        if (enum_tables_bytes<Rule, TT>(n) % alignof(Slot<TT>) || enum_tables_bytes<Rule, TT>(n) % alignof(Partial))
+            return false;
+    return true;
 }
 template <class Rule, typename TT>
 inline size_t enum_shm_bytes(int n, bool one_dma) {
+    static_assert(enum_queue_aligned<Rule, TT>(), "queue alignment");
     const size_t q = Rule::queue(one_dma) ? EX_THREADS * Rule::template lane_bytes<TT>(n) : 0;
     const size_t red = sizeof(Partial) * (EX_THREADS / 64);
     return enum_tables_bytes<Rule, TT>(n) + (q > red ? q : red);
