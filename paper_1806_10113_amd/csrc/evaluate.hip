@@ -113,6 +113,12 @@ __global__ __launch_bounds__(EV_THREADS) void evaluate_kernel(const tgo_task *__
 // whatever the rows.
 constexpr int64_t EV_BOTH = 131072;
 
+// What a block may take without asking for more: both widths' tables and the 64-bit
+// queue of the largest group.
+static_assert(sizeof(OrderTables<uint32_t>) + sizeof(OrderTables<uint64_t>) +
+                      order_queue_bytes<uint64_t>(MAXN, EV_THREADS) <= 64 * 1024,
+              "LDS of a block");
+
 int launch_evaluate(const Rates &r, const tgo_task *d_tasks, int n, const uint8_t *d_orders,
                     int64_t m, int64_t *d_out, hipStream_t st) {
     if (m == 0) return TGO_OK;
