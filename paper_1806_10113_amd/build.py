@@ -10,6 +10,8 @@ import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
 
+from paper_1806_10113_amd import codecheck
+
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
@@ -62,6 +64,9 @@ def build(verbose: bool = True) -> str:
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
+    kernels, bad = codecheck.scan(tmp)
+    if bad or not kernels:
+        raise RuntimeError(f"{kernels} kernels; 64-bit shifts by the last register: {bad}")
     os.replace(tmp, LIB)
     # the calibration library (not part of the product ABI)
     tmp = PROBE_LIB + ".tmp"
