@@ -102,9 +102,10 @@ __device__ __forceinline__ uint32_t ceil_p(uint32_t u, uint32_t, double inv, dou
 // 64-bit: u < 2^51 is exact as a double, and u / p there is off by less than
 // 1/2, so the truncated quotient is off by at most one; the exact remainder
 // says which way.  (A 64-bit integer division is a sequence of over a hundred
-// instructions.)
+// instructions.)  Taken as signed: windows also pass work left at an instant that
+// they then do not choose, above -2^61, for which the conversion has to be defined.
 __device__ __forceinline__ uint64_t ceil_p(uint64_t u, uint32_t p, double inv, double) {
-    const uint64_t est = (uint64_t)((double)u * inv);
+    const uint64_t est = (uint64_t)(int64_t)((double)(int64_t)u * inv);
     const int64_t rem = (int64_t)(u - est * p);
     return est + (rem > 0 ? 1u : 0u) + (rem > (int64_t)p ? 1u : 0u);
 }
