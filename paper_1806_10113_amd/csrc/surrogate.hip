@@ -622,6 +622,11 @@ __global__ __launch_bounds__(FM_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
 // one for the last quarter, 96 are 43 us and sum longer afterwards.  Smaller
 // batches take chunks of 256 rows: 60 -> 49 us for a whole gradient of 1,024
 // rows, 65 -> 55 at 4,096, 66 -> 64 at 16,384 against chunks of 1,024.
+// The rms error of the weight gradients against 64-bit sums of the same activations
+// is 1.08e-7 at 65,536 rows and 1.19e-7 at 262,144 (64 chunks of rows in their own
+// order: 1.20e-7 and 1.24e-7).  Beyond, longer chunks are less exact than those were
+// (1,048,576 rows: 1.57e-7, 1.47e-7), so such batches take 64: 1.47e-7, and a training
+// step 1.95 ms (48 chunks: 1.74; before all of this 2.67).
 constexpr int TR_WAVES = 8;
 constexpr int TR_THREADS = 64 * TR_WAVES;   // wave w owns output columns 32w .. 32w+31
 constexpr int TR_RT = 8;                    // row tiles of 16
@@ -636,6 +641,8 @@ constexpr int WG_TILES = 10;                // 4 (layer 3) + 4 (layer 2) + 2 (la
 constexpr int WG_BK = 64;                   // rows (K) per LDS stage
 constexpr int WG_VEC_BLOCKS = (TR_VLEN + 255) / 256;
 constexpr int WG_KS_MAX = 48;               // K chunks (partials) at most
+constexpr int WG_LONG_ROWS = 1 << 18;       // batches with more rows take up to WG_KS_LONG:
+constexpr int WG_KS_LONG = 64;              // a chunk's float32 sums grow less exact with its rows
 constexpr int WG_KC = 256;                  // rows per K chunk (more for larger batches)
 static_assert(TR_ROWS * SG_POS % TR_THREADS == 0, "features: whole passes of one thread per (row, position)");
 static_assert(TR_HALF == 4, "a pass packs four rows of a column into 8 bytes; its ReLU mask bits fill one word");
@@ -1512,11 +1519,12 @@ namespace tgo {
 
 static size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
-// K chunks of the weight-gradient launch: at most WG_KS_MAX, each a whole
-// number of row blocks.
+// K chunks of the weight-gradient launch: at most WG_KS_MAX (WG_KS_LONG for a long
+// batch), each a whole number of row blocks.
 static void wgrad_chunks(int rows, int *ks, int *kc) {
     int k = (rows + WG_KC - 1) / WG_KC;
-    k = k < 1 ? 1 : (k > WG_KS_MAX ? WG_KS_MAX : k);
+    const int most = rows > WG_LONG_ROWS ? WG_KS_LONG : WG_KS_MAX;
+    k = k < 1 ? 1 : (k > most ? most : k);
     int c = ((rows + k - 1) / k + TR_ROWS - 1) / TR_ROWS * TR_ROWS;
     *kc = c;
     *ks = (rows + c - 1) / c;
@@ -1584,6 +1592,7 @@ int tgo_surrogate_create(int64_t max_rows, int max_groups, tgo_surrogate **out) 
     (void)hipGetDevice(&s->device);
     const size_t R = (size_t)max_rows, LT = (size_t)s->ldt;
     const size_t blocks = (R + TR_ROWS - 1) / TR_ROWS;
+    const size_t chunks = max_rows > WG_LONG_ROWS ? WG_KS_LONG : WG_KS_MAX;  // of wgrad_chunks, at most
     std::vector<std::pair<void **, size_t>> parts = {
         {(void **)&s->p, 4 * SG_NPARAM}, {(void **)&s->m, 4 * SG_NPARAM},
         {(void **)&s->v, 4 * SG_NPARAM},
@@ -1593,8 +1602,8 @@ int tgo_surrogate_create(int64_t max_rows, int max_groups, tgo_surrogate **out) 
         {(void **)&s->G1t, 2 * LT * SG_H}, {(void **)&s->G2t, 2 * LT * SG_H}, {(void **)&s->G3t, 2 * LT * SG_H},
         {(void **)&s->H3, 2 * R * SG_H}, {(void **)&s->score, 4 * R},
         {(void **)&s->vec, 4 * blocks * TR_VSTRIDE},
-        {(void **)&s->wpart, 4 * (size_t)WG_KS_MAX * SG_NPARAM},
-        {(void **)&s->vpart, 4 * (size_t)WG_KS_MAX},
+        {(void **)&s->wpart, 4 * chunks * SG_NPARAM},
+        {(void **)&s->vpart, 4 * chunks},
         {(void **)&s->F, 4 * (size_t)max_groups * SG_POS * 3},
         {(void **)&s->status, 4 * (size_t)max_groups}, {(void **)&s->horders, 16 * (size_t)max_groups},
         {(void **)&s->hns, 8 * (size_t)max_groups}, {(void **)&s->best, sizeof(BestPair) * (size_t)max_groups},
