@@ -188,8 +188,8 @@ __device__ __forceinline__ uint32_t next_tile(unsigned int *counter, uint32_t to
     return __builtin_amdgcn_readfirstlane(tile);
 }
 
-// Simulation state of a lane: the chain form with two DMA engines, the
-// event form (windows without DtH events) with one.
+// Simulation state of a lane: the chain form with two DMA engines, windows
+// without DtHs with one.
 template <typename TT, int DMA>
 using BatchLane = std::conditional_t<DMA == DMA_TWO, CLane<TT>, Lane<TT>>;
 

@@ -53,7 +53,7 @@ struct Ctx {
 
 // Level with L positions left (position n - L is being chosen).  list holds
 // the remaining tasks in increasing order, one per nibble.  LaneT is the
-// simulation state (Lane: event form, CLane: chain form, or a lane under a
+// simulation state (Lane: one DMA engine, CLane: chain form, or a lane under a
 // start rule) and ViewT its tables and queue.
 template <typename TT, int L, bool STORE, int DMA, typename LaneT, typename ViewT>
 __device__ __forceinline__ void level(const Ctx &c, const ViewT &v, const LaneT &s, uint32_t list, uint32_t l,

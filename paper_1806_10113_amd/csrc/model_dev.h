@@ -16,13 +16,19 @@
 //     running transfer carries its absolute end time, and the remaining work is
 //     recomputed (one multiply) only when its rate changes.
 //   * The kernel engine needs no events of its own: K_j = max(HtD_j end,
-//     K_{j-1} end) + k.  A kernel completion matters only to the DtH engine,
-//     which reads it from a per-lane queue in LDS (slot j = K_j end and the
-//     overlapped duration of DtH j, so one read serves each DtH event).
+//     K_{j-1} end) + k.
 //   * The simulation is cut into "windows": window j runs from the start to
-//     the end of HtD at position j and processes the DtH events inside it.
+//     the end of HtD at position j and processes the DtHs inside it.
 //     The state at the start of window j depends only on positions < j, which
 //     lets an enumeration share the windows of a common prefix.
+//   * After the last HtD every DtH runs at full speed, so the rest is the
+//     two-machine recurrence D = max(D, K_p end) + d_p over the remaining
+//     positions, whose value is
+//       max(end of the running DtH + sum of the solo DtH left after it,
+//           max_p (K_p end + sum_{s >= p} d_s)).
+//     Terms of positions whose DtH already started are lower bounds of the total
+//     (every DtH takes at least its solo time after its kernel), so the second
+//     max may run over every placed position: it is emax + dpre, kept per window.
 //   * Chain form (CLane below): since every DtH that starts before the last
 //     HtD ends runs at the overlapped rate, its start and end follow from the
 //     previous DtH's end and its own kernel's end alone:
@@ -118,16 +124,8 @@ __device__ __forceinline__ TT tmin(TT a, TT b) { return a < b ? a : b; }
 template <typename TT>
 __device__ __forceinline__ TT inf_time() { return ~TT(0); }
 
-// Launch scheme a function is compiled for: read from Rates at run time, or
-// fixed at compile time (kernels specialised for one scheme).
-enum DmaMode : int { DMA_RUNTIME = 0, DMA_ONE = 1, DMA_TWO = 2 };
-
-template <int DMA>
-__device__ __forceinline__ bool is_one_dma(const Rates &r) {
-    if constexpr (DMA == DMA_ONE) return true;
-    else if constexpr (DMA == DMA_TWO) return false;
-    else return r.one_dma != 0;
-}
+// Launch scheme a function is compiled for.
+enum DmaMode : int { DMA_ONE = 1, DMA_TWO = 2 };
 
 // Task tables and the per-lane kernel-completion queue.  Entry x of a table
 // is at [x * TS], slot j of the queue at [j * QS] (compile-time strides);
@@ -147,44 +145,30 @@ struct View {
     __device__ __forceinline__ void put_span(int j, Span<TT> e) const { reinterpret_cast<Span<TT> *>(Q)[j * QS] = e; }
 };
 
-// Simulation state at the start of a window (an HtD about to start).
-template <typename TT>
-struct Lane {
-    using ST = typename Signed<TT>::type;
-    TT t;        // now: end of the previous HtD (0 before the first)
-    TT ck;       // end of the previous kernel
-    TT dev;      // next DtH event: end of the running DtH, or (idle) end of
-                 // the kernel it waits for; inf while that is not known yet
-    TT slack;    // running DtH: p_dth dp - q d of its task; with end estimate
-                 // dev its work left at time t <= dev is p_dth (dev - t) - slack
-    TT dpre;     // sum of solo DtH durations of the positions placed so far
-    TT dthru;    // sum of solo DtH durations up to the cursor (running included)
-    ST emax;     // max over placed positions p of (K_p end - sum_{s<p} d_s)
-    int i;       // DtH cursor (position of the running or next DtH)
-    bool drun;   // DtH engine busy
-};
-
-template <typename TT>
-__device__ __forceinline__ Lane<TT> lane_init() {
-    using ST = typename Signed<TT>::type;
-    Lane<TT> s;
-    s.t = 0; s.ck = 0; s.dev = inf_time<TT>(); s.slack = 0;
-    s.dpre = 0; s.dthru = 0;
-    s.emax = (ST)(((TT)1) << (8 * sizeof(TT) - 1));  // most negative
-    s.i = 0; s.drun = false;
-    return s;
-}
-
-template <typename TT>
-__device__ __forceinline__ void lane_reset(Lane<TT> &s) { s = lane_init<TT>(); }
-
 // One DMA engine (Section 3.2, scheme for such devices): every HtD is queued
 // on the one transfer engine before every DtH, so the HtDs run back to back
 // at solo speed (two transfers never move data at the same time), kernels
 // follow K_j = max(HtD_j end, K_{j-1} end) + k, and every DtH waits for the
 // last HtD.  A window is the HtD alone; the DtHs are left to the tail.
-template <typename TT, typename ViewT>
-__device__ __forceinline__ void window_one(Lane<TT> &s, uint32_t x, const ViewT &v) {
+template <typename TT>
+struct Lane {
+    using ST = typename Signed<TT>::type;
+    TT t;     // end of the previous HtD (0 before the first)
+    TT ck;    // end of the previous kernel
+    TT dpre;  // sum of solo DtH durations of the positions placed so far
+    ST emax;  // max over placed positions p of (K_p end - sum_{s<p} d_s)
+};
+
+template <typename TT>
+__device__ __forceinline__ void lane_reset(Lane<TT> &s) {
+    using ST = typename Signed<TT>::type;
+    s.t = 0; s.ck = 0; s.dpre = 0;
+    s.emax = (ST)(((TT)1) << (8 * sizeof(TT) - 1));  // most negative
+}
+
+template <int DMA = DMA_ONE, bool PUT = true, typename TT, typename ViewT>
+__device__ __forceinline__ void window(Lane<TT> &s, int, uint32_t x, const ViewT &v, const Rates &) {
+    static_assert(DMA == DMA_ONE, "a lane of the one-engine scheme");
     using ST = typename Signed<TT>::type;
     const Quad<TT> tx = v.task(x);
     s.t += tx.h;
@@ -194,104 +178,15 @@ __device__ __forceinline__ void window_one(Lane<TT> &s, uint32_t x, const ViewT 
     s.dpre += tx.d;
 }
 
-// Window j: HtD of task x starts at s.t; process DtH events until it ends,
-// then derive the kernel of position j and record it in the queue.
-//
-// A DtH event is either a completion (engine busy) or a start from idle.  A
-// completion followed at once by the next DtH leaves both rates unchanged, so
-// the HtD end estimate stays valid; only a change of the DtH engine between
-// busy and idle changes the HtD rate and forces a new estimate from the exact
-// remaining work.
-// PUT = false skips writing the position's queue slot (the last position of
-// an ordering: no later window reads it).
-template <int DMA = DMA_RUNTIME, bool PUT = true, typename TT, int TS, int QS>
-__device__ __forceinline__ void window(Lane<TT> &s, int j, uint32_t x, const View<TT, TS, QS> &v,
-                                       const Rates &r) {
-    using ST = typename Signed<TT>::type;
-    if (is_one_dma<DMA>(r)) {
-        window_one(s, x, v);
-        return;
-    }
-    const TT q = TT(1) << r.q_log2;
-    const Quad<TT> tx = v.task(x);
-    // an idle DtH waiting for the previous position's kernel now knows its time
-    if (!s.drun && s.i == j - 1) s.dev = s.ck;
-    const int jlast = j > 0 ? j - 1 : 0;
-    TT uh = tx.h << r.q_log2;  // remaining HtD work at th0
-    TT th0 = s.t;
-    TT eh = s.t + (s.drun ? tx.hp : tx.h);
-    for (;;) {
-        const TT ev = s.dev;
-        if (!(ev < eh)) break;
-        const int inew = s.i + (s.drun ? 1 : 0);
-        // slot inew is only used if inew < j.  The last position's window
-        // (PUT = false) reads slot min(inew, j - 1) so that a queue of n - 1
-        // slots suffices; other windows read slots <= j < n - 1
-        const Slot<TT> nx = v.q(PUT ? inew : (inew < jlast ? inew : jlast));
-        const bool start = inew < j && nx.ck <= ev;
-        if (start != s.drun) {
-            // the HtD rate changes at ev: exact remaining work, new estimate
-            // (both roundings computed and selected: no nested branch)
-            uh -= (s.drun ? TT(r.p_h) : q) * (ev - th0);
-            th0 = ev;
-            const TT cp = (TT)ceil_p(uh, r.p_h, r.inv_ph, r.c_ph);
-            const TT cq = ceil_q(uh, r.q_log2);
-            eh = ev + (start ? cp : cq);
-        }
-        // the DtH that starts (or not): computed on every lane and selected,
-        // which measured faster than a second divergent branch.  Its solo time
-        // and rounding slack come from w = p_dth dp = q d + slack (no further
-        // LDS read on the loop's path)
-        const TT w = TT(r.p_d) * nx.dp;
-        s.dthru += start ? (w >> r.q_log2) : TT(0);
-        s.slack = start ? (w & (q - 1)) : s.slack;
-        s.dev = start ? ev + nx.dp : (inew < j ? nx.ck : inf_time<TT>());
-        s.drun = start;
-        s.i = inew;
-    }
-    s.t = eh;
-    s.ck = tmax(eh, s.ck) + tx.k;
-    const ST e = (ST)s.ck - (ST)s.dpre;
-    s.emax = e > s.emax ? e : s.emax;
-    s.dpre += tx.d;
-    if constexpr (PUT) {
-        Slot<TT> sl;
-        sl.ck = s.ck;
-        sl.dp = v.d(x).dp;
-        v.put(j, sl);
-    }
-}
-
-// Total time once the last placed HtD has ended at s.t (used for the whole
-// group, and for a prefix simulated on its own).  After that instant every
-// DtH runs at full speed, so the rest is the two-machine recurrence
-// D = max(D, K_p end) + d_p over the remaining positions, whose value is
-//   max(end of the running DtH + sum of the solo DtH left after it,
-//       max_p (K_p end + sum_{s >= p} d_s)).
-// Terms of positions whose DtH already started are lower bounds of the total
-// (every DtH takes at least its solo time after its kernel), so the second max
-// may run over every placed position: it is emax + dpre, kept per window.
-//
-// With one DMA engine the DtH recurrence starts when the last HtD ends (the
-// engine is busy with HtDs until s.t), so the total is
+// Total time: the DtHs start when the last HtD ends (the engine is busy with
+// HtDs until s.t), so it is
 // max(s.t + sum d, max_p (K_p end + sum_{s >= p} d_s)) = max(s.t, emax) + dpre.
-template <int DMA = DMA_RUNTIME, typename TT>
-__device__ __forceinline__ TT tail(const Lane<TT> &s, const Rates &r) {
+template <int DMA = DMA_ONE, typename TT>
+__device__ __forceinline__ TT tail(const Lane<TT> &s, const Rates &) {
+    static_assert(DMA == DMA_ONE, "a lane of the one-engine scheme");
     using ST = typename Signed<TT>::type;
-    if (is_one_dma<DMA>(r)) {
-        const ST e = (ST)s.t > s.emax ? (ST)s.t : s.emax;
-        return (TT)(e + (ST)s.dpre);
-    }
-    TT T = (TT)(s.emax + (ST)s.dpre);
-    if (s.drun) {
-        // work left on the running DtH (it ran at p_dth since its start;
-        // s.dev >= s.t): q d - p_dth (t - start) = p_dth (dev - t) - slack
-        const TT pw = TT(r.p_d) * (s.dev - s.t);
-        const TT ud = pw > s.slack ? pw - s.slack : TT(0);
-        const TT dend = s.t + ceil_q(ud, r.q_log2) + (s.dpre - s.dthru);
-        T = tmax(T, dend);
-    }
-    return T;
+    const ST e = (ST)s.t > s.emax ? (ST)s.t : s.emax;
+    return (TT)(e + (ST)s.dpre);
 }
 
 // ------------------------------------------------------------ chain form
@@ -326,7 +221,7 @@ __device__ __forceinline__ void lane_reset(CLane<TT> &s) {
 // the HtD end estimate stays valid while DtHs follow each other without a gap;
 // at a gap the exact remaining work gives the idle estimate, and a DtH that
 // starts before it gives a new busy estimate.  Event order and roundings are
-// those of the event-by-event window (an event at ev is processed when ev is
+// those of stepping every event (an event at ev is processed when ev is
 // before the current estimate).  PUT = false skips appending DtH j (the last
 // position: no later window reads it).
 template <int DMA = DMA_TWO, bool PUT = true, typename TT, int TS, int QS>
@@ -409,8 +304,7 @@ __device__ __forceinline__ void window(CLane<TT> &s, int j, uint32_t x, const Vi
     }
 }
 
-// Total time of the chain form once the last HtD has ended at s.t: the
-// two-machine recurrence of the event form's tail.  A DtH running at s.t has
+// Total time of the chain form once the last HtD has ended at s.t.  A DtH running at s.t has
 // moved p_dth (s.t - start) of its q d work, so it needs
 // d - floor(p_dth (s.t - start) / q) more ns at full speed, followed by the
 // solo times of the DtHs after it.
@@ -568,7 +462,7 @@ __device__ __forceinline__ TT simulate_potential(int n, uint64_t perm, const Ord
 }
 
 // T of one whole ordering (perm: the task at position j in nibble j): with one
-// DMA engine the event form's windows; with two the potential form, or
+// DMA engine its windows; with two the potential form, or
 // (potential false: the group's potentials do not fit) the chain form's windows
 // (CLane), the chain entries computed when the cursor reaches them.
 template <typename TT, int QS>
@@ -576,10 +470,11 @@ __device__ __forceinline__ TT simulate_order(int n, uint64_t perm, const OrderVi
                                              bool potential) {
     using ST = typename Signed<TT>::type;
     if (potential) return simulate_potential(n, perm, v, r);
-    if (is_one_dma<DMA_RUNTIME>(r)) {
-        Lane<TT> st = lane_init<TT>();
-        for (int j = 0; j < n; ++j) window_one(st, (uint32_t)(perm >> (4 * j)) & 15u, v);
-        return tail<DMA_ONE>(st, r);
+    if (r.one_dma) {
+        Lane<TT> st;
+        lane_reset(st);
+        for (int j = 0; j < n; ++j) window(st, j, (uint32_t)(perm >> (4 * j)) & 15u, v, r);
+        return tail(st, r);
     }
     TT t = 0, ck = 0, dpre = 0, dcross = 0;
     ST emax = (ST)(((TT)1) << (8 * sizeof(TT) - 1));  // most negative
