@@ -186,6 +186,17 @@ __device__ __forceinline__ T shfl_xor64(T v, int m) {
     return (T)(((uint64_t)hi << 32) | lo);
 }
 
+// A 64-bit value rotated right by R lanes within each row of 16 lanes (two
+// DPP moves; every lane active).  BC sets the moves' bound control: the same value,
+// without a move that clears the destination first.  (The walks of concurrent kernels
+// take other registers with it: 4.32 -> 4.33 ms at 12 tasks.)
+template <int R, bool BC = false>
+__device__ __forceinline__ uint64_t row_ror_u64(uint64_t u) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x120 + R, 0xF, 0xF, BC);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x120 + R, 0xF, 0xF, BC);
+    return ((uint64_t)hi << 32) | lo;
+}
+
 // (t, r) pairs: smaller t wins, ties to smaller r.
 __device__ __forceinline__ void merge_min(uint64_t &t, uint64_t &r, uint64_t t2, uint64_t r2) {
     if (t2 < t || (t2 == t && r2 < r)) { t = t2; r = r2; }

@@ -52,14 +52,6 @@ __device__ __forceinline__ Fit3 fit_ends(const SubChain<TT, KIND> &s, const Rate
     return Fit3{(int64_t)s.x, (int64_t)s.kp, (int64_t)tail<DMA>(s, r)};
 }
 
-// A 64-bit value rotated right by R lanes within each row of 16 lanes (two
-// DPP moves).
-template <int R>
-__device__ __forceinline__ uint64_t row_ror_u64(uint64_t u) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x120 + R, 0xF, 0xF, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x120 + R, 0xF, 0xF, false);
-    return ((uint64_t)hi << 32) | lo;
-}
 // The smallest key of lanes 0..15, as a scalar.  Every lane must be active.
 __device__ __forceinline__ uint64_t row0_min(uint64_t k) {
     uint64_t o = row_ror_u64<8>(k);

@@ -651,16 +651,9 @@ static_assert(TR_HALF == 4, "a pass packs four rows of a column into 8 bytes; it
 // loads need no branch.
 __device__ const tgo_task ZERO_TASK = {0, 0, 0};
 
-// A 64-bit value rotated right by R lanes within each row of 16 lanes (two
-// DPP moves).
-template <int R>
-__device__ __forceinline__ int64_t row_ror64(int64_t v) {
-    const uint64_t u = (uint64_t)v;
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x120 + R, 0xF, 0xF, true);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x120 + R, 0xF, 0xF, true);
-    return (int64_t)(((uint64_t)hi << 32) | lo);
-}
 // Sum / minimum over the 16 lanes of a row, left in every lane of the row.
+template <int R>
+__device__ __forceinline__ int64_t row_ror64(int64_t v) { return (int64_t)row_ror_u64<R, true>((uint64_t)v); }
 __device__ __forceinline__ void row16_sum(int64_t &v) {
     v += row_ror64<8>(v);
     v += row_ror64<4>(v);
