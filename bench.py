@@ -44,12 +44,13 @@ VALU_LANE_OPS_PER_ORDERING = 144.45
 # this share are the lane-ops that did work for some ordering; lanes masked off
 # in a divergent step do none.
 VALU_LANE_UTILISATION = 0.9223
-# Integer operations the method needs per ordering of that workload, counted
-# for the chain form (which the potential form, with the same windows, replaced
-# here) by `python opcount.py` (a transcription of the chain form of the windows and
-# the walk over the last five positions, each statement priced at its 32-bit
-# ALU operations, lanes counted on their own: 2.77 windows, 1.32 DtHs crossed
-# and 0.23 gaps of the DtH engine per ordering, the set-major prefix decode).
+# Integer operations the method needs per ordering of that workload, counted by
+# `python opcount.py` (transcriptions of the windows of both forms of the model and
+# of the walk over the last five positions, each statement priced at its 32-bit ALU
+# operations, lanes counted on their own: 2.77 windows and 1.32 DtHs crossed per
+# ordering, the set-major prefix decode).  The chain form needs 110.6, the potential
+# form, which the kernel runs, 141.7 in fewer steps that depend on each other; the
+# figure here is the lesser, so the share of the peak that it gives is the lower one.
 ALG_OPS_PER_ORDERING = 110.6
 # HBM bytes per launch: FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000, each scaled by
 # what the counter reads for a 256 MiB device copy (same profile file).
@@ -695,7 +696,8 @@ def main():
                                          / VALU_PEAK_TOPS,
                      "frac_note": "frac = issued VALU lane-ops (counter run) / peak; frac_alg counts "
                                   "only the lanes active in each issued instruction; frac_alg_opcount = "
-                                  "the method's counted integer ops per ordering (opcount.py) / peak"})
+                                  "the counted integer ops per ordering (opcount.py) of the chain form, "
+                                  "fewer than the potential form's that runs, / peak"})
     else:
         roof.update({"achieved": None, "frac": None})
     roof["traffic"] = TRAFFIC_BYTES_PER_LAUNCH

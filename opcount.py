@@ -1,13 +1,15 @@
 """Algorithmic operation count of the exhaustive enumeration (measurement aid).
 
-Counts, on the CPU, the integer operations that the chain form of the model
-(Section 4.1 simulator, overlap rates of Section 4.2.1: every DtH that starts
-before the last HtD ends runs at the overlapped rate, so its start and end are
-appended to a chain once its kernel's end is known) and the prefix-sharing
-walk over the last M positions need per ordering: windows, DtHs crossed
-inside a window, gaps of the DtH engine, starts from idle, chain appends,
-tails and the per-ordering bookkeeping, each priced at the 32-bit ALU
-operations its statement needs (listed in COSTS).  Lanes are counted on their
+Counts, on the CPU, the integer operations that a form of the model (Section
+4.1 simulator, overlap rates of Section 4.2.1) and the prefix-sharing walk over
+the last M positions need per ordering.  Potential form (the headline kernel's):
+the search for the first DtH whose potential reaches the HtD's, the crossings of
+two lines, the DtH's potential and end.  Chain form (every DtH that starts before
+the last HtD ends runs at the overlapped rate, so its start and end are appended
+to a chain once its kernel's end is known): windows, DtHs crossed inside a
+window, gaps of the DtH engine, starts from idle, chain appends.  Both: tails and
+the per-ordering bookkeeping.  Each statement is priced at the 32-bit ALU
+operations it needs (listed in COSTS).  Lanes are counted on their
 own: the lockstep of a wave (a wave runs as many loop iterations as its
 busiest lane) is reported separately, as the ratio of wave-lockstep to lane
 iterations.
@@ -44,6 +46,13 @@ COSTS = {
     "append": 6,           # chain entry (max, add), slot address, cursor refresh (compare, two selects)
     "tail": 2,             # emax + dpre when no DtH runs at the last HtD end
     "tail_running": 7,     # work moved by the running DtH (sub, mul, shift), solo times left (sub, add), max
+    # potential form
+    "pot_window": 2,       # the potential to reach (add), queue address of the cursor
+    "pot_step": 2,         # potential reached?, next address
+    "pot_cross": 13,       # origin or the DtH before (select), two crossings (4 and 4), live?, the later (select)
+    "pot_end": 5,          # kernel end (max, add), its lateness (sub, max), DtH prefix
+    "pot_append": 15,      # HtD potential (3, 3, select), the DtH's start (max), potential (4), end, slack sum
+    "pot_tail": 14,        # idle time before the DtH (shift, sub, shift, mul), work moved (5), end (2), max
     "leaf": 12,            # min / max with rank, 64-bit sum, 64-bit rank-weighted sum
     "child": 9,            # next task from the nibble list (2), leaf index (2), remaining list (5)
     "prefix_position": 13,  # factorial digit (div, mul, sub), nibble extract and list splice,
@@ -83,8 +92,8 @@ class Lane:
         self.E = [0] * n
 
     def copy(self):
-        c = Lane.__new__(Lane)
-        for f in Lane.__slots__:
+        c = type(self).__new__(type(self))
+        for f in self.__slots__:
             setattr(c, f, getattr(self, f))
         return c
 
@@ -174,15 +183,83 @@ def tail(s, r, cnt):
     return T
 
 
-def walk_subtree(tasks, sub, M, r, cnt, trace=None):
+class PotLane:
+    """State at the start of a window of the potential form; G, E is the queue
+    (shared by copies): potential and end of the DtH of each placed position."""
+    __slots__ = ("t", "w", "ck", "emax", "dpre", "i", "g", "e", "p", "G", "E", "P")
+
+    def __init__(self, n):
+        self.t = self.w = self.ck = self.dpre = self.i = self.e = self.p = 0
+        self.emax, self.g = -INF, INF
+        self.G, self.E, self.P = [INF] * n, [0] * n, [0] * n
+
+    copy = Lane.copy
+
+
+def pot_window(s, j, x, H, D, r, put, cnt, iters_out=None):
+    """Window j of the potential form."""
+    q = 1 << r.q_log2
+    h, _, k, d = H[x]
+    cnt.add("pot_window")
+    cnt.windows += 1
+    X, i, it = s.w + q * h, s.i, 0
+    s.G[j] = INF
+    cnt.add("pot_step")
+    while s.G[i] < X:
+        i, it = i + 1, it + 1
+        cnt.add("pot_step")
+        cnt.events += 1
+    cnt.add("pot_cross")
+    g, e = s.G[i], s.E[i]
+    pg, pe = (s.G[i - 1], s.E[i - 1]) if i else (0, 0)
+    live = g != INF
+    t = pe + -(-(X - pg) // q)
+    if live:
+        t = max(t, e - (g - X) // r.p_h)
+    cnt.add("pot_end")
+    s.t = t
+    s.ck = max(t, s.ck) + k
+    s.emax = max(s.emax, s.ck - s.dpre)
+    s.dpre += d
+    if put:
+        cnt.add("pot_append")
+        s.w = pg + q * (t - pe)
+        if live:
+            s.w = min(s.w, g - r.p_h * (e - t))
+        s.i = i
+        lg, le = (s.G[j - 1], s.E[j - 1]) if j else (0, 0)
+        start = max(le, s.ck)
+        s.G[j], s.E[j] = lg + q * (start - le) + r.p_h * D[x], start + D[x]
+        s.P[j] = (s.P[j - 1] if j else 0) + r.p_d * D[x] - q * d
+    else:  # DtH i, and the rounding slack of the DtHs before it
+        s.g, s.e, s.p = g, e, s.P[i - 1] if i else 0
+    if iters_out is not None:
+        iters_out.append(it)
+
+
+def pot_tail(s, r, cnt):
+    cnt.add("pot_tail")
+    T = s.emax + s.dpre
+    if s.g != INF:
+        q = 1 << r.q_log2
+        busy = (q * s.e - s.g) // (q - r.p_h)
+        T = max(T, s.t + s.dpre - (r.p_d * (s.t - s.e + busy) - s.p) // q)
+    return T
+
+
+FORMS = {"chain": (Lane, window, tail), "potential": (PotLane, pot_window, pot_tail)}
+
+
+def walk_subtree(tasks, sub, M, r, cnt, trace=None, form="chain"):
     """The orderings of subtree `sub` (ranks sub*M! ..), as one lane walks
     them; returns their times in rank order.  trace (optional) receives the
     loop iterations (DtHs crossed) of every window in walk order."""
+    lane, window, tail = FORMS[form]
     n = len(tasks)
     H, D = tables(tasks, r)
     cnt.add("subtree")
     rest = list(range(n))
-    s = Lane(n)
+    s = lane(n)
     plen = n - M
     blk = math.factorial(n - 1) // math.factorial(M)
     rem = sub
@@ -246,35 +323,36 @@ def main():
     n, M = 12, 5
     r = Rates()
     nsub = math.factorial(n) // math.factorial(M)
-    rng = np.random.default_rng(0)
-    cnt = Counter()
-    subs = rng.choice(nsub, size=args.subtrees, replace=False)
-    for sidx in subs:
-        walk_subtree(tasks, int(sidx), M, r, cnt)
-    orderings = args.subtrees * math.factorial(M)
-    # lockstep of waves: 64 lanes take 64 consecutive set-major subtrees
-    lane_iters, wave_iters = 0, 0
-    starts = rng.choice(nsub // 64, size=args.waves, replace=False)
-    for w0 in starts:
-        traces = []
-        for lane in range(64):
-            tr = []
-            walk_subtree(tasks, set_major_subtree(64 * int(w0) + lane, n, M), M, r, Counter(), tr)
-            traces.append(tr)
-        arr = np.array(traces)  # every lane walks the same tree shape
-        lane_iters += arr.sum()
-        wave_iters += 64 * arr.max(axis=0).sum()
-    res = {
-        "group": "mixed N=12, seed 1, overlap 3/4, two DMA engines",
-        "M": M, "subtrees": args.subtrees, "orderings": orderings,
-        "alg_ops_per_ordering": cnt.ops / orderings,
-        "windows_per_ordering": cnt.windows / orderings,
-        "dth_crossings_per_ordering": cnt.events / orderings,
-        "gaps_per_ordering": cnt.rate_changes / orderings,
-        "lockstep_iterations_ratio": float(wave_iters / lane_iters),
-        "costs": COSTS,
-    }
-    print(json.dumps(res, indent=1))
+    for form in FORMS:
+        rng = np.random.default_rng(0)
+        cnt = Counter()
+        subs = rng.choice(nsub, size=args.subtrees, replace=False)
+        for sidx in subs:
+            walk_subtree(tasks, int(sidx), M, r, cnt, form=form)
+        orderings = args.subtrees * math.factorial(M)
+        # lockstep of waves: 64 lanes take 64 consecutive set-major subtrees
+        lane_iters, wave_iters = 0, 0
+        starts = rng.choice(nsub // 64, size=args.waves, replace=False)
+        for w0 in starts:
+            traces = []
+            for lane in range(64):
+                tr = []
+                walk_subtree(tasks, set_major_subtree(64 * int(w0) + lane, n, M), M, r, Counter(), tr, form)
+                traces.append(tr)
+            arr = np.array(traces)  # every lane walks the same tree shape
+            lane_iters += arr.sum()
+            wave_iters += 64 * arr.max(axis=0).sum()
+        res = {
+            "group": "mixed N=12, seed 1, overlap 3/4, two DMA engines",
+            "form": form, "M": M, "subtrees": args.subtrees, "orderings": orderings,
+            "alg_ops_per_ordering": cnt.ops / orderings,
+            "windows_per_ordering": cnt.windows / orderings,
+            "dth_crossings_per_ordering": cnt.events / orderings,
+            "gaps_per_ordering": cnt.rate_changes / orderings,
+            "lockstep_iterations_ratio": float(wave_iters / lane_iters),
+        }
+        print(json.dumps(res, indent=1))
+    print(json.dumps({"costs": COSTS}, indent=1))
 
 
 if __name__ == "__main__":
