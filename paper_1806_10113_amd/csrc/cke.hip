@@ -173,8 +173,8 @@ struct CkeRule : GroupRule {
     using View = RView<TT, 1, EX_THREADS, RULE_CONCURRENT>;
     template <typename TT, int DMA>
     using Lane = RLane<TT, RULE_CONCURRENT>;
-    // 6 waves per SIMD (80 VGPRs; some saved walk state spills): 4.15 / 4.22 /
-    // 4.49 ms on three n = 12 groups, against 4.32 / 4.53 / 4.77 at 5 waves,
+    // 6 waves per SIMD (80 VGPRs; 160 B of saved walk state per lane spill): 4.15 /
+    // 4.22 / 4.49 ms on three n = 12 groups, against 4.32 / 4.53 / 4.77 at 5 waves,
     // 4.24 / 4.12 / 4.43 at 7 and 4.89 / 4.87 / 5.09 at 8
     template <typename TT, int DMA>
     static constexpr int min_waves() { return sizeof(TT) == 4 ? 6 : 1; }

@@ -19,11 +19,18 @@ namespace tgo {
 // wave, lane i: task i).  The chain form's cost is the DtHs that end before the
 // last HtD.  From 12 tasks on (five waves of the potential form per SIMD, seven of
 // the chain form) it is the faster one where the DtHs (at the overlapped rate) take
-// longer together than the HtDs and the kernels, which precede them.  113 groups of
-// 12 at six pairs of rates, D / (H + K) and time of the chain form over that of the
-// potential form, mean and least: up to 0.6 1.35 (1.20), 0.8 1.16 (1.01), 0.9 1.06
-// (1.00), 1.0 1.03 (0.94); above, 1.1 0.99 (0.92), 1.3 0.96 (0.88), more 0.92
-// (0.85).  Groups of 11: 1.18 to 1.4 on average over the same rates, always on.
+// longer together than the HtDs and the kernels, which precede them.  960 groups of
+// 12 timed in both forms (eight pairs of rates, durations of three spreads): the
+// line at 1.0 to 1.07 gives the least mean, 0.8995 of the chain form's time.  384
+// groups of 12, D / (H + K) and the time without the potential form over that with
+// it, mean and least: up to 0.4 1.28 (1.00), 0.6 1.16 (0.95), 0.8 1.09 (0.96), 0.85
+// 1.04 (0.94), 0.9 1.03 (1.00), 0.95 1.01 (1.00), 1.0 1.02 (0.91); above (chain
+// form) 1.00 (1.00).  So 9 of 384 lose, 8 of them more than 2%: the chain
+// form's time also follows how often the lanes of a wave part, which no sum over the
+// tasks that was tried shows.  D <= 1.24 H as well would leave 3 of 960 that lose
+// more than 2%, for a mean of 0.908.
+// Groups of 11, always on: 1.08 and more on average in each of those ranges, least
+// 0.99; of 13: 1.08 to 1.29, least 0.995.
 __device__ __forceinline__ bool potential_gains(const tgo_task *__restrict__ tasks, int n, const Rates &r, int lane) {
     if (n < 12) return true;
     uint32_t lead = 0, d = 0;
@@ -116,7 +123,10 @@ uint32_t resident_blocks(const void *kern, int threads, size_t shm) {
 // groups of 11 and more take, where it gains (potential_gains): 1782 / 1712 / 1744
 // us where the chain form takes 2165 / 2011 / 2551 (three groups of 12).  At depth
 // 4 it gained nothing, and the groups below 11, done in 60 us and less, would pay the launch
-// that finds nothing to do, 4.5 us, when theirs does not fit.
+// that finds nothing to do, 4.5 us, when theirs does not fit.  Both forms take one
+// grid, 12 rounds of the chain form's resident blocks (EX_ROUNDS, seven waves per
+// SIMD): 16.8 rounds of the potential form's, with five; twice the grid was slower
+// (1803 us against 1684).
 constexpr int POT_M = 5;
 template <int M, bool STORE>
 static int launch_two(hipStream_t st, const tgo_task *t, int n, const Rates &r, uint32_t n_sub, int64_t *out,

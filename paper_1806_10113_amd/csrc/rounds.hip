@@ -245,7 +245,8 @@ __device__ __forceinline__ uint64_t rounds_unrank(int T, int R, uint64_t rk, uin
 // latency of one lane's windows: four workers with four tasks each are 331,776
 // orderings, 55,296 lanes of 28 windows.  Stepping the events of every
 // ordering in 64-bit time took 198 us for them and the Heuristic setup, on one
-// thread after it, 115 us; together, side by side, 313 -> 48 us per call.
+// thread after it, 115 us; together, side by side, 313 -> 48 us per call, 40 with
+// the proxies' single pass per instant.
 struct RoundsRule : GroupRule {
     struct Args {
         int T, R;
@@ -381,7 +382,8 @@ static int launch_rounds_m(hipStream_t st, const tgo_task *t, int T, int R, cons
 
 // Positions of the last round walked depth first per lane (TGO_ROUNDS_M, 1..4,
 // overrides it): the deepest that leaves 32,768 subtrees, as in rule_depth.
-// Four workers with four tasks: 62 / 51 / 48 us per call with 1 / 2 / 3.
+// Four workers with four tasks: 62 / 51 / 48 us per call with 1 / 2 / 3 (before the
+// proxies took one pass per instant: 40 with 3).
 static int choose_rounds_m(int T, uint64_t count) {
     int top = T < 4 ? T : 4;
     if (const char *e = std::getenv("TGO_ROUNDS_M")) {
